@@ -16,8 +16,7 @@ void set_hip_error(hipError_t e, const char* what) {
 }
 
 static const char* const kKernelNames[KID_COUNT] = {
-    "sample_hist0", "sample_hist1", "sample_hist2", "sample_count",
-    "sample_write",  "sample_remap", "normalize_x",  "gather_normalize_w", "gemm_rowmax",
+    "sample_scan", "sample_write", "normalize_x",  "gather_normalize_w", "gemm_rowmax",
     "row_ref", "gemm_logits",
     "row_combine",   "gemm_dweight", "dweight_reduce", "dweight_label", "dweight_label_combine",
     "gemm_dfeatures", "dfeatures_final", "update", "gemm_dweight_update"};
@@ -65,7 +64,7 @@ static int dev_alloc(void** p, size_t bytes) {
 int pfc_destroy(pfc_ctx* c) {
   if (!c) return PFC_EINVAL;
   (void)hipStreamSynchronize(c->stream);
-  void* bufs[] = {c->pos_bits, c->hist, c->sel, c->blk_cnt, c->err_flag, c->Xn,
+  void* bufs[] = {c->samp_mem, c->err_flag, c->Xn,
                   c->Xs, c->rnormX, c->Wn, c->rnormW, c->head, c->E, c->rowpart, c->rowmaxpart, c->rowmax,
                   c->rowref,
                   c->clabel, c->rowscale, c->dlabel, c->lossrow, c->dXpart, c->dlab, c->dWtmp,
@@ -122,14 +121,11 @@ int pfc_create(pfc_ctx** out, int64_t N, int32_t D, int32_t B_max, double r_max,
   const size_t es = c->esize;
   const size_t Bp = (size_t)c->Bp_cap, kp = (size_t)c->kp_cap, Dz = (size_t)D;
   const size_t Dpz = (size_t)round_up(D, 256);   // row length of the GEMM operands
-  c->nblk_cap = (int32_t)((N + 2047) / 2048);
+  const size_t samp_bytes = sample_layout(N, B_max, nullptr, &c->samp);
   int rc = PFC_OK;
 #define ALLOC(field, bytes)                                  \
   if (rc == PFC_OK) rc = dev_alloc((void**)&c->field, (bytes))
-  ALLOC(pos_bits, ((size_t)(N + 31) / 32 + 64) * 4);
-  ALLOC(hist, 3 * 4096 * 4);
-  ALLOC(sel, sizeof(SelState));
-  ALLOC(blk_cnt, (size_t)c->nblk_cap * 2 * 4);
+  ALLOC(samp_mem, samp_bytes);
   ALLOC(err_flag, 16);
   ALLOC(Xn, Bp * Dpz * es);
   ALLOC(Xs, Bp * Dpz * es);
@@ -164,11 +160,10 @@ int pfc_create(pfc_ctx** out, int64_t N, int32_t D, int32_t B_max, double r_max,
       rc = PFC_ENOMEM;
     }
   }
-  // the sampler keeps its scratch all zero between calls (every last reader clears its piece)
+  // the sampler starts from zeroed scratch; afterwards every call clears what the next one needs
   if (rc == PFC_OK) {
-    hipError_t e = hipMemsetAsync(c->pos_bits, 0, ((size_t)(N + 31) / 32 + 64) * 4, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->hist, 0, 3 * 4096 * 4, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->sel, 0, sizeof(SelState), c->stream);
+    sample_layout(N, B_max, (char*)c->samp_mem, &c->samp);
+    hipError_t e = hipMemsetAsync(c->samp_mem, 0, samp_bytes, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->spare, 0, 2 * Dz * 4, c->stream);
     if (e != hipSuccess) {
       set_hip_error(e, "hipMemsetAsync(sampler scratch)");

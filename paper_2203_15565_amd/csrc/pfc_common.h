@@ -22,12 +22,8 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
 // Kernel ids for the optional per-kernel timing.
 enum KernelId {
-  KID_SAMPLE_HIST0 = 0,
-  KID_SAMPLE_HIST1,
-  KID_SAMPLE_HIST2,
-  KID_SAMPLE_COUNT,
+  KID_SAMPLE_SCAN = 0,
   KID_SAMPLE_WRITE,
-  KID_SAMPLE_REMAP,
   KID_NORM_X,
   KID_GATHER_W,
   KID_GEMM_ROWMAX,
@@ -45,15 +41,32 @@ enum KernelId {
   KID_COUNT
 };
 
-// State of the radix select, kept in device memory between the sampler's kernels.
-struct SelState {
-  uint32_t U;          // number of distinct labels (positives); cleared again once consumed
-  uint32_t k;          // |S| = max(U, ceil(r*N))
-  uint32_t none;       // 1: no negative is taken at all (k == U)
-  uint32_t total;      // number of ids written (must equal k)
-  uint32_t need[3];    // after radix pass P: negatives still to be taken inside the chosen bin
-  uint32_t prefix[3];  // after radix pass P: threshold bits fixed so far (in place, low bits zero)
-  uint32_t pad[2];
+// Device state of the sampler (pfc_sample.hip).  Counts of one call; there are two of them, used in
+// turn.
+struct SampleHdr {
+  uint32_t U;           // number of distinct labels (batch classes)
+  uint32_t pos_above;   // of these, the ones whose score lies above the window
+  uint32_t npos;        // and the ones inside it (entries of pos_list)
+  uint32_t overflow;    // a workgroup had more classes in the window than it can list
+  uint32_t nblk, nwords;   // workgroups and bitmap words of the call (what is to be cleared)
+  uint32_t listed;      // entries of list
+  uint32_t pad[9];
+};
+struct SampleState {
+  uint32_t next, cur;   // set of the next call / of the call at hand
+  uint32_t k;           // |S| = max(U, ceil(r*N))
+  uint32_t spare[13];
+  SampleHdr hdr[2];
+};
+struct SampleScratch {
+  SampleState* st;
+  uint32_t* pos_bits[2];   // bit j set <=> class j is in the batch
+  uint32_t* blk_pos[2];    // per workgroup: batch classes not above | above the window << 16
+  uint64_t* pos_list[2];   // keys of the batch classes inside the window
+  uint32_t* above_bits;    // bit j set <=> the score of class j lies above the window
+  uint32_t* above_cnt;     // their number, per workgroup
+  uint64_t* list;          // keys of all classes inside the window
+  uint32_t list_cap, pos_cap;
 };
 
 }  // namespace pfc
@@ -72,11 +85,8 @@ struct pfc_ctx {
   size_t esize;     // bytes per GEMM operand element (4 or 2)
 
   // sampler scratch
-  uint32_t* pos_bits;     // ceil(N/32) words (+ slack): bit j set <=> class j is in the batch
-  uint32_t* hist;         // 3 x 4096 bins (radix passes of 8, 12 and 12 bits)
-  pfc::SelState* sel;
-  uint32_t* blk_cnt;      // 2 x nblk: per block (#sure, #equal-to-threshold)
-  int32_t nblk_cap;
+  pfc::SampleScratch samp;
+  void* samp_mem;         // the one allocation behind it
   int32_t* err_flag;      // device: nonzero once a bad label / index was seen
   uint32_t* host_pin;     // pinned host words for read-backs
 
@@ -157,6 +167,9 @@ struct UpdateArgs {
 };
 
 // entry points implemented per translation unit (called by the extern "C" layer)
+// Places the sampler's scratch for up to N classes and B samples at `base` (256-byte aligned; may
+// be null) and returns its size; all of it has to be zero before the first call.
+size_t sample_layout(int64_t N, int64_t B, char* base, SampleScratch* out);
 int sample_impl(pfc_ctx* ctx, const int64_t* labels, int32_t B, double r, uint64_t seed,
                 uint64_t step, uint32_t score_mask, int32_t* idx_out, int32_t* yl_out,
                 int64_t* k_out);

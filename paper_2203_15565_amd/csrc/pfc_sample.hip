@@ -1,11 +1,30 @@
 // pfc_sample: the sampled class set S of one iteration (arXiv 2203.15565, Sec. 3.2 / Fig. 4:
 // the classes present in the batch go in first, random negatives fill the buffer up to r*N).
 //
-// Integer work only.  Every class gets a 32-bit Philox4x32-10 score (Salmon et al., SC'11),
-// recomputed wherever it is needed (about 60 integer operations per four classes; nothing is
-// stored per class except one "is in the batch" bit).  The k - U negatives with the largest
-// scores are found by a three-pass radix select (8 + 12 + 12 bits), equal scores going to the
-// smaller class id; an index-ordered compaction then writes S in ascending class id.
+// Integer work only.  Every class gets a 32-bit Philox4x32-10 score (Salmon et al., SC'11); the
+// k - U negatives with the largest scores are taken, equal scores going to the smaller class id,
+// and S is written in ascending class id.
+//
+// The scores are independent and uniform, so the score at which the selection ends is known
+// beforehand up to a few standard deviations: the number of classes at or above a score is
+// binomial.  The host hands the kernels a window of scores that holds it (about 6.5 standard
+// deviations and the batch size wide, select_window), and two launches do the rest:
+//
+//   sample_scan   every score once: one bit per class that lies above the window, and a list of
+//                 the classes inside it (a few thousand of millions); marks the batch classes
+//   sample_write  every workgroup finds the exact end of the selection in the list, its own output
+//                 offset from the counts of the workgroups in front, and writes its part of S and
+//                 the positions of the labels that fall into it
+//
+// A window that misses (about once in 10^10 calls; always if a score mask makes the scores far
+// from uniform) is seen by sample_write from the counts, and its workgroups then run a full radix
+// select each for themselves: the same result, slowly.
+//
+// What bounds it: latency (a launch takes 5 us whatever it does; sample_write is a chain of four
+// dependent reads) and, for many classes, the one Philox block per four of them (13 us of integer
+// work at 10 million).  Measured with rocprofv3, sum of the sampler's kernels, at N = 93,431 /
+// 2,059,906 / 10,000,000: three radix passes, count, write and label remap, which recomputed the
+// scores in five of six launches, 38 / 57 / 120 us; these two 15 / 25 / 52 us.
 #include <math.h>
 #include <string.h>
 
@@ -18,17 +37,12 @@ namespace pfc {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kClassesPerBlock = 2048;                 // ordered passes: 2 x (256 threads x 4)
-constexpr int kItersPerBlock = kClassesPerBlock / (kThreads * 4);
-
-// Radix passes over the 32-bit score: bits [31:24], [23:12], [11:0].  The first pass sees every
-// class, so it is kept narrow (256 bins: few global atomics per block); the later passes see
-// only the classes inside the chosen bin, so their 4096-bin histograms are almost empty.
-constexpr int kHistStride = 4096;
-template <int P> struct Pass;
-template <> struct Pass<0> { static constexpr int kBins = 256, kShift = 24; };
-template <> struct Pass<1> { static constexpr int kBins = 4096, kShift = 12; };
-template <> struct Pass<2> { static constexpr int kBins = 4096, kShift = 0; };
+constexpr int kWriteThreads = 512;   // of sample_write
+constexpr int kBins = 1024;          // histogram of the window in sample_write (LDS)
+constexpr int kLocalList = 4096;     // classes of one workgroup that may lie in the window
+constexpr int kBinList = 256;        // classes that may share the bin in which the selection ends
+constexpr int kMaxClsLog2 = 15;      // classes per workgroup: 2^10 .. 2^15
+constexpr int kMaxBlocks = 640;      // workgroups, as long as 2^15 classes each suffice for that
 
 struct PhiloxKey {
   uint32_t k0, k1;   // lo32(seed), hi32(seed)
@@ -53,227 +67,40 @@ __device__ __forceinline__ void philox_block(uint32_t q, const PhiloxKey& key, u
   out[0] = c0 & key.mask; out[1] = c1 & key.mask; out[2] = c2 & key.mask; out[3] = c3 & key.mask;
 }
 
-// The four "is positive" bits of classes 4q..4q+3 (bit e = class 4q+e).
-__device__ __forceinline__ uint32_t pos_nibble(const uint32_t* __restrict__ pos_bits, uint32_t q) {
-  return (pos_bits[q >> 3] >> ((q & 7u) * 4u)) & 0xFu;
+// The window: scores lo .. lo + width (both inside).  Scores above it are taken, below it not.
+struct Window {
+  uint32_t lo, width;
+  int shift;        // bin of a score inside: (score - lo) >> shift, below kBins
+  __device__ __forceinline__ bool inside(uint32_t u) const { return u - lo <= width; }
+  __device__ __forceinline__ bool above(uint32_t u) const { return u > lo + width; }
+};
+
+// Ascending order of keys = order of preference: larger score first, then smaller class id.
+__device__ __forceinline__ uint64_t select_key(uint32_t score, uint32_t id) {
+  return ((uint64_t)(~score) << 32) | id;
 }
 
-// Between two calls the sampler's scratch is all zero (bitmap, histograms, counter of positives):
-// pfc_create clears it once, and the last reader of each piece clears it again -- the scan of a
-// pass its histogram, the first scan the counter, the label remap the bitmap words it knows to be
-// set -- so no call starts with a clearing pass.  The batch classes are marked inside the launch
-// of the first radix pass (see sample_hist_kernel), not by a launch of their own.
+// Everything that carries counts or marks of one call exists twice (SampleState::hdr, pos_bits,
+// blk_pos, pos_list).  A call works on one set and, in its second launch, clears what the call
+// before left in the other, so no call starts with a clearing pass; which set is next is kept on
+// the device, so that a captured and replayed call alternates as well.
 
-// All 256 threads of a workgroup: walk the merged histogram of pass P from the largest bin
-// downwards until `need` classes are covered.  Returns (to every thread) the bin that holds the
-// threshold and how many classes are still to be taken from inside it.  Every workgroup of the
-// launch that follows pass P does this for itself -- the same integers everywhere -- instead of a
-// one-workgroup launch in between.
-template <int P>
-__device__ __forceinline__ void find_bin(const uint32_t* __restrict__ hist, uint32_t need,
-                                         uint32_t& bin, uint32_t& need_inside) {
-  __shared__ uint32_t wsum[4];
-  __shared__ uint32_t s_bin, s_need;
-  constexpr int kBins = Pass<P>::kBins;
-  constexpr int kPer = kBins / kThreads;
-  const int t = threadIdx.x;
-  // thread t owns the descending bins kBins-1-t*kPer .. kBins-1-(t*kPer+kPer-1)
-  uint32_t own[kPer];
-  uint32_t mine = 0;
-#pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    own[e] = hist[P * kHistStride + (kBins - 1 - (t * kPer + e))];
-    mine += own[e];
-  }
-  uint32_t inc = mine;   // inclusive scan over threads
-  const int lane = t & 63, w = t >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t n = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += n;
-  }
-  if (lane == 63) wsum[w] = inc;
-  if (t == 0) {
-    s_bin = 0u;
-    s_need = 0u;
-  }
-  __syncthreads();
-  uint32_t base = 0;
-  for (int i = 0; i < w; ++i) base += wsum[i];
-  inc += base;
-  const uint32_t exc = inc - mine;
-  if (exc < need && need <= inc) {   // true in exactly one thread (if need >= 1)
-    uint32_t cum = exc;
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      if (cum + own[e] >= need) {
-        s_bin = (uint32_t)(kBins - 1 - (t * kPer + e));
-        s_need = need - cum;
-        break;
-      }
-      cum += own[e];
-    }
-  }
-  __syncthreads();
-  bin = s_bin;
-  need_inside = s_need;
-  __syncthreads();
-}
-
-// State of the select after pass P-1, found by every workgroup of the launch of pass P (or of the
-// count launch, P = 3) from the histogram of pass P-1 and what workgroup 0 of the launch before
-// left in `sel`.  Workgroup 0 records the new state for the next launch and clears what nobody
-// reads any more (the histogram of pass P-2, the count of positives).
-template <int P>
-__device__ __forceinline__ void select_state(uint32_t* __restrict__ hist, SelState* __restrict__ sel,
-                                             uint32_t ceil_rN, uint32_t& prefix, uint32_t& need,
-                                             uint32_t& none) {
-  static_assert(P >= 1 && P <= 3, "state after pass P-1");
-  uint32_t need_in, prefix_in;
-  if constexpr (P == 1) {
-    const uint32_t U = sel->U;
-    const uint32_t k = U > ceil_rN ? U : ceil_rN;
-    none = (k == U) ? 1u : 0u;
-    need_in = k - U;
-    prefix_in = 0u;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      sel->k = k;
-      sel->none = none;
-    }
-  } else {
-    none = sel->none;
-    need_in = sel->need[P - 2];
-    prefix_in = sel->prefix[P - 2];
-  }
-  uint32_t bin = 0u;
-  need = 0u;
-  if (!none) find_bin<P - 1>(hist, need_in, bin, need);
-  prefix = prefix_in | (bin << Pass<P - 1>::kShift);
-  if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) {
-      sel->need[P - 1] = need;
-      sel->prefix[P - 1] = prefix;
-      if (P == 2) sel->U = 0u;
-    }
-    if constexpr (P >= 2) {
-      constexpr int kOld = Pass<P - 2>::kBins;
-      for (int b = threadIdx.x; b < kOld; b += kThreads) hist[(P - 2) * kHistStride + b] = 0u;
-    }
-  }
-}
-
-// Radix pass P over the classes whose score agrees with the prefix found so far.
-// Passes 1 and 2 skip the classes of the batch (their bits are complete by then).  Pass 0 runs in
-// the same launch as the marking of the batch classes, so it cannot know them yet: it counts EVERY
-// class, and the workgroups behind the first `hist_blocks` mark the labels -- the one thread that
-// sets a class's bit first takes that class's score out of the merged histogram again and counts
-// the class as a positive.  Integer atomics only, so the histogram after the launch is the same
-// whatever the order.
-template <int P>
-__global__ void sample_hist_kernel(int64_t N, PhiloxKey key, uint32_t* __restrict__ pos_bits,
-                                   uint32_t* __restrict__ hist, SelState* __restrict__ sel,
-                                   uint32_t ceil_rN, const int64_t* __restrict__ labels, int B,
-                                   int hist_blocks, int32_t* __restrict__ err_flag) {
-  constexpr int kBins = Pass<P>::kBins, kShift = Pass<P>::kShift;
-  if constexpr (P == 0) {
-    if ((int)blockIdx.x >= hist_blocks) {   // marking part of the launch
-      const int i = ((int)blockIdx.x - hist_blocks) * kThreads + threadIdx.x;
-      const int64_t y = i < B ? labels[i] : 0;
-      const bool valid = i < B && y >= 0 && y < N;
-      if (i < B && !valid) atomicOr(err_flag, 1);
-      // One lane per distinct label of the wavefront goes on: with long-tailed labels a frequent
-      // class would otherwise bring thousands of atomics onto one word.
-      bool lead = false;
-      unsigned long long todo = __ballot(valid);
-      while (todo) {   // wave-uniform loop over the distinct labels
-        const int src = __ffsll(todo) - 1;
-        const int64_t y0 = __shfl(y, src, 64);
-        lead = lead || (int)(threadIdx.x & 63) == src;
-        todo &= ~__ballot(valid && y == y0);
-      }
-      if (!lead) return;
-      const uint32_t bit = 1u << (y & 31);
-      const uint32_t old = atomicOr(&pos_bits[y >> 5], bit);
-      if (!(old & bit)) {   // first to mark class y
-        uint32_t u[4];
-        philox_block((uint32_t)(y >> 2), key, u);
-        atomicSub(&hist[u[y & 3] >> kShift], 1u);
-        atomicAdd(&sel->U, 1u);
-      }
-      return;
-    }
-  }
-  __shared__ uint32_t lh[kBins];
-  for (int b = threadIdx.x; b < kBins; b += blockDim.x) lh[b] = 0u;
-  uint32_t prefix = 0u, need = 0u, none = 0u;
-  if constexpr (P > 0) select_state<P>(hist, sel, ceil_rN, prefix, need, none);
-  __syncthreads();
-  if (!(P > 0 && none)) {
-    const uint32_t nq = (uint32_t)((N + 3) >> 2);
-    const uint32_t stride = (uint32_t)hist_blocks * blockDim.x;
-    for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < nq; q += stride) {
-      uint32_t u[4];
-      philox_block(q, key, u);
-      uint32_t pb = 0u;
-      if constexpr (P > 0) pb = pos_nibble(pos_bits, q);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t j = (int64_t)q * 4 + e;
-        if (j >= N || ((pb >> e) & 1u)) continue;
-        if (P == 0) {
-          atomicAdd(&lh[u[e] >> kShift], 1u);
-        } else {
-          // bits above this pass's field must equal the prefix
-          constexpr int kAbove = kShift + 12;
-          if ((u[e] >> kAbove) == (prefix >> kAbove))
-            atomicAdd(&lh[(u[e] >> kShift) & (kBins - 1)], 1u);
-        }
-      }
-    }
-  }
-  __syncthreads();
-  for (int b = threadIdx.x; b < kBins; b += blockDim.x) {
-    const uint32_t c = lh[b];
-    if (c) atomicAdd(&hist[P * kHistStride + b], c);
-  }
-}
-
-// Selection predicate pieces for classes 4q..4q+3: bit e of `sure` = positive or score above the
-// threshold; bit e of `eq` = non-positive and score equal to the threshold.
-__device__ __forceinline__ void classify(uint32_t q, int64_t N, const PhiloxKey& key,
-                                         const uint32_t* __restrict__ pos_bits, uint32_t T,
-                                         uint32_t none, uint32_t& sure, uint32_t& eq) {
-  sure = 0u;
-  eq = 0u;
-  const uint32_t nq = (uint32_t)((N + 3) >> 2);
-  if (q >= nq) return;
-  uint32_t u[4];
-  philox_block(q, key, u);
-  const uint32_t pb = pos_nibble(pos_bits, q);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int64_t j = (int64_t)q * 4 + e;
-    if (j >= N) continue;
-    if ((pb >> e) & 1u) {
-      sure |= 1u << e;
-    } else if (!none) {
-      if (u[e] > T) sure |= 1u << e;
-      else if (u[e] == T) eq |= 1u << e;
-    }
-  }
-}
-
+// Sum over the NT threads of a block, to every thread; sm: NT / 64 words.
+template <int NT>
 __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* sm) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
   __syncthreads();
-  const uint32_t r = sm[0] + sm[1] + sm[2] + sm[3];
+  uint32_t r = 0;
+#pragma unroll
+  for (int i = 0; i < NT / 64; ++i) r += sm[i];
   __syncthreads();
   return r;
 }
 
-// exclusive scan over the 256 threads of a block; also returns the block total
+// exclusive scan over the NT threads of a block; also returns the block total
+template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* sm, uint32_t& total) {
   uint32_t inc = v;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -285,112 +112,512 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* sm, ui
   if (lane == 63) sm[w] = inc;
   __syncthreads();
   uint32_t base = 0;
-  for (int i = 0; i < w; ++i) base += sm[i];
-  total = sm[0] + sm[1] + sm[2] + sm[3];
+  total = 0;
+#pragma unroll
+  for (int i = 0; i < NT / 64; ++i) {
+    const uint32_t x = sm[i];
+    if (i < w) base += x;
+    total += x;
+  }
   __syncthreads();
   return base + inc - v;
 }
 
-__global__ void sample_count_kernel(int64_t N, PhiloxKey key, const uint32_t* __restrict__ pos_bits,
-                                    uint32_t* __restrict__ hist, SelState* __restrict__ sel,
-                                    uint32_t ceil_rN, uint32_t* __restrict__ blk_cnt) {
-  __shared__ uint32_t sm[4];
-  uint32_t T, need, none;
-  select_state<3>(hist, sel, ceil_rN, T, need, none);   // the full 32-bit threshold
-  uint32_t nsure = 0, neq = 0;
+// All NT threads: walk a histogram of NB bins in LDS from the largest bin downwards until `need`
+// (>= 1) entries are covered.  Returns the bin that holds the last of them and how many are to be
+// taken from inside it (bin 0 and 0 if the histogram holds fewer than `need`).
+template <int NT, int NB>
+__device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t need, uint32_t* sm,
+                                         uint32_t& bin, uint32_t& need_inside) {
+  __shared__ uint32_t s_bin, s_need;
+  constexpr int kPer = NB / NT;
+  const int t = threadIdx.x;
+  uint32_t own[kPer], mine = 0, total;
 #pragma unroll
-  for (int it = 0; it < kItersPerBlock; ++it) {
-    const uint32_t q = blockIdx.x * (kClassesPerBlock / 4) + it * kThreads + threadIdx.x;
-    uint32_t sure, eq;
-    classify(q, N, key, pos_bits, T, none, sure, eq);
-    nsure += __popc(sure);
-    neq += __popc(eq);
+  for (int e = 0; e < kPer; ++e) {   // thread t owns bins NB-1-t*kPer downwards
+    own[e] = hist[NB - 1 - (t * kPer + e)];
+    mine += own[e];
   }
-  const uint32_t bs = block_sum(nsure, sm);
-  const uint32_t be = block_sum(neq, sm);
-  if (threadIdx.x == 0) {
-    blk_cnt[2 * blockIdx.x] = bs;
-    blk_cnt[2 * blockIdx.x + 1] = be;
+  if (t == 0) {
+    s_bin = 0u;
+    s_need = 0u;
   }
+  const uint32_t exc = block_excl_scan<NT>(mine, sm, total);
+  if (exc < need && need <= exc + mine) {   // exactly one thread
+    uint32_t cum = exc;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      if (cum < need && need <= cum + own[e]) {
+        s_bin = (uint32_t)(NB - 1 - (t * kPer + e));
+        s_need = need - cum;
+      }
+      cum += own[e];
+    }
+  }
+  __syncthreads();
+  bin = s_bin;
+  need_inside = s_need;
 }
 
-// Ordered write of S.  Every block first adds up the counts of the blocks in front of it: its
-// output offset is their "sure" classes plus the equal-to-threshold ones they were allowed to
-// keep -- the quota sel->need is used up in ascending class id, so that is min(quota, number of
-// equal classes in front).  The last block also leaves the total in sel->total.
-__global__ void sample_write_kernel(int64_t N, PhiloxKey key, const uint32_t* __restrict__ pos_bits,
-                                    SelState* __restrict__ sel, uint32_t* __restrict__ hist,
-                                    const uint32_t* __restrict__ blk_cnt, int64_t cap,
-                                    int32_t* __restrict__ idx_out) {
-  __shared__ uint32_t sm[4];
-  const uint32_t T = sel->prefix[2], none = sel->none;
-  const uint32_t need_eq = none ? 0u : sel->need[2];
-  if (blockIdx.x == 0)   // nobody reads the last pass's histogram any more
-    for (int b = threadIdx.x; b < Pass<2>::kBins; b += kThreads) hist[2 * kHistStride + b] = 0u;
-  uint32_t front_sure = 0, front_eq = 0;
-  for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kThreads) {
-    front_sure += blk_cnt[2 * b];
-    front_eq += blk_cnt[2 * b + 1];
-  }
-  front_sure = block_sum(front_sure, sm);
-  front_eq = block_sum(front_eq, sm);
-  uint32_t out = front_sure + (front_eq < need_eq ? front_eq : need_eq);
-  uint32_t eq_run = front_eq;
-#pragma unroll
-  for (int it = 0; it < kItersPerBlock; ++it) {
-    const uint32_t q = blockIdx.x * (kClassesPerBlock / 4) + it * kThreads + threadIdx.x;
-    uint32_t sure, eq;
-    classify(q, N, key, pos_bits, T, none, sure, eq);
-    uint32_t tot_e, tot_s;
-    uint32_t eq_rank = eq_run + block_excl_scan(__popc(eq), sm, tot_e);
-    // keep an equal-score class only while the quota lasts (ascending class id)
-    uint32_t chosen = sure;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if ((eq >> e) & 1u) {
-        if (eq_rank < need_eq) chosen |= 1u << e;
-        ++eq_rank;
+// ---------------------------------------------------------------------------------------------
+// sample_scan.  Workgroup b < nblk scores the classes [b << cls_log2, (b + 1) << cls_log2); the
+// workgroups behind those mark the batch classes in the same launch: the one thread that sets a
+// class's bit first counts the class, as one that the bits of the first part hold already or not,
+// and lists its key if its score lies in the window (the first part lists it too, not knowing the
+// batch).  Integer atomics only: the counts do not depend on the order, and the lists are read as
+// sets.
+// ---------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kThreads) void sample_scan_kernel(
+    int64_t N, PhiloxKey key, Window win, SampleScratch sc, int cls_log2, int nblk,
+    const int64_t* __restrict__ labels, int B, int32_t* __restrict__ err_flag) {
+  const uint32_t par = sc.st->next & 1u;
+  SampleHdr* hdr = &sc.st->hdr[par];
+  const int lane = threadIdx.x & 63;
+  if ((int)blockIdx.x >= nblk) {   // marking part of the launch
+    const int i = ((int)blockIdx.x - nblk) * kThreads + threadIdx.x;
+    const int64_t y = i < B ? labels[i] : 0;
+    const bool valid = i < B && y >= 0 && y < N;
+    if (i < B && !valid) atomicOr(err_flag, 1);
+    // One lane per distinct label of the wavefront goes on: with long-tailed labels a frequent
+    // class would otherwise bring thousands of atomics onto one word.
+    bool lead = false;
+    unsigned long long todo = __ballot(valid);
+    while (todo) {   // wave-uniform loop over the distinct labels
+      const int src = __ffsll(todo) - 1;
+      const int64_t y0 = __shfl(y, src, 64);
+      lead = lead || lane == src;
+      todo &= ~__ballot(valid && y == y0);
+    }
+    bool first = false, above = false;
+    if (lead) {
+      const uint32_t bit = 1u << (y & 31);
+      first = !(atomicOr(&sc.pos_bits[par][y >> 5], bit) & bit);
+      if (first) {   // first to mark class y
+        uint32_t u[4];
+        philox_block((uint32_t)(y >> 2), key, u);
+        const uint32_t uy = u[y & 3];
+        above = win.above(uy);
+        atomicAdd(&sc.blk_pos[par][y >> cls_log2], above ? 0x10000u : 1u);
+        if (win.inside(uy)) {
+          const uint32_t p = atomicAdd(&hdr->npos, 1u);
+          if (p < sc.pos_cap) sc.pos_list[par][p] = select_key(uy, (uint32_t)y);
+        }
       }
     }
-    uint32_t pos = out + block_excl_scan(__popc(chosen), sm, tot_s);
+    const uint32_t nf = __popcll(__ballot(first)), na = __popcll(__ballot(above));
+    if (lane == 0) {
+      if (nf) atomicAdd(&hdr->U, nf);
+      if (na) atomicAdd(&hdr->pos_above, na);
+    }
+    return;
+  }
+  __shared__ uint64_t s_list[kLocalList];
+  __shared__ uint32_t s_n, s_base, sm[4];
+  if (threadIdx.x == 0) s_n = 0u;
+  __syncthreads();
+  const uint32_t nq = (uint32_t)((N + 3) >> 2);
+  const uint32_t q0 = blockIdx.x << (cls_log2 - 2);
+  const int iters = 1 << (cls_log2 - 10);
+  uint32_t cnt = 0;
+  for (int it = 0; it < iters; ++it) {
+    const uint32_t q = q0 + it * kThreads + threadIdx.x;
+    uint32_t nib = 0u;
+    if (q < nq) {
+      uint32_t u[4];
+      philox_block(q, key, u);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t j = q * 4u + e;
+        if ((int64_t)j >= N) continue;
+        if (win.above(u[e])) nib |= 1u << e;
+        if (win.inside(u[e])) {
+          const uint32_t p = atomicAdd(&s_n, 1u);
+          if (p < (uint32_t)kLocalList) s_list[p] = select_key(u[e], j);
+        }
+      }
+    }
+    cnt += __popc(nib);
+    // eight neighbouring lanes hold one word of bits: combine them through the vector ALU
+    uint32_t v = nib << ((lane & 7) * 4);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);    // lane ^ 1
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);    // lane ^ 2
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);   // 7 - lane
+    if ((lane & 7) == 0 && q < nq) sc.above_bits[q >> 3] = v;
+  }
+  const uint32_t total = block_sum<kThreads>(cnt, sm);   // also a barrier behind the list
+  const uint32_t n = s_n;
+  if (threadIdx.x == 0) {
+    sc.above_cnt[blockIdx.x] = total;
+    if (n) s_base = atomicAdd(&hdr->listed, n);
+    if (n > (uint32_t)kLocalList) atomicOr(&hdr->overflow, 1u);
+    if (blockIdx.x == 0) {
+      sc.st->cur = par;
+      hdr->nblk = (uint32_t)nblk;
+      hdr->nwords = (uint32_t)((N + 31) >> 5);
+    }
+  }
+  if (n == 0) return;
+  __syncthreads();
+  const uint32_t base = s_base;
+  for (uint32_t e = threadIdx.x; e < n && e < (uint32_t)kLocalList; e += kThreads)
+    if (base + e < sc.list_cap) sc.list[base + e] = s_list[e];
+}
+
+// ---------------------------------------------------------------------------------------------
+// sample_write.
+// ---------------------------------------------------------------------------------------------
+struct WriteShared {
+  uint32_t sm[kWriteThreads / 64];
+  uint32_t hist[4096];                      // window bins, or radix bins of the slow select
+  uint32_t word[1 << (kMaxClsLog2 - 5)];    // chosen classes of this workgroup
+  uint32_t pre[1 << (kMaxClsLog2 - 5)];     // chosen classes in front of each word
+  uint64_t bin_list[kBinList];
+  uint32_t bin_n;
+  uint64_t key_end;
+};
+
+// The window missed: a radix select over all scores (bits 31..24, 23..12, 11..0), run by every
+// workgroup for itself.  Leaves this workgroup's chosen classes in s.word and returns how many
+// chosen classes lie in front.
+__device__ __forceinline__ uint32_t slow_select(int64_t N, const PhiloxKey& key,
+                                             const uint32_t* pos_bits, uint32_t need, int cls_log2,
+                                             WriteShared& s) {
+  const uint32_t nq = (uint32_t)((N + 3) >> 2);
+  const uint32_t q0 = blockIdx.x << (cls_log2 - 2), q1 = q0 + (1u << (cls_log2 - 2));
+  uint32_t prefix = 0u;
+#pragma unroll 1
+  for (int pass = 0; pass < 3; ++pass) {
+    const int sh = pass == 0 ? 24 : pass == 1 ? 12 : 0;
+    const int above = pass == 0 ? 32 : sh + 12;   // bits that are fixed already start here
+    for (int b = threadIdx.x; b < 4096; b += kWriteThreads) s.hist[b] = 0u;
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t q = threadIdx.x; q < nq; q += kWriteThreads) {
+      uint32_t u[4];
+      philox_block(q, key, u);
+      const uint32_t pb = pos_bits[q >> 3] >> ((q & 7u) * 4u);
+      for (int e = 0; e < 4; ++e) {
+        if ((int64_t)q * 4 + e >= N || ((pb >> e) & 1u)) continue;
+        if (above < 32 && (u[e] >> above) != (prefix >> above)) continue;
+        atomicAdd(&s.hist[(u[e] >> sh) & 0xFFFu], 1u);
+      }
+    }
+    __syncthreads();
+    uint32_t bin, inside;
+    find_bin<kWriteThreads, 4096>(s.hist, need, s.sm, bin, inside);
+    prefix |= bin << sh;
+    need = inside;
+    __syncthreads();
+  }
+  // scores above `prefix` are taken, and the first `need` classes (ascending id) that equal it
+  uint32_t sure = 0, eq = 0;
+#pragma unroll 1
+  for (uint32_t q = threadIdx.x; q < nq && q < q0; q += kWriteThreads) {
+    uint32_t u[4];
+    philox_block(q, key, u);
+    const uint32_t pb = pos_bits[q >> 3] >> ((q & 7u) * 4u);
+    for (int e = 0; e < 4; ++e) {
+      if ((pb >> e) & 1u) ++sure;
+      else if (u[e] > prefix) ++sure;
+      else if (u[e] == prefix) ++eq;
+    }
+  }
+  sure = block_sum<kWriteThreads>(sure, s.sm);
+  eq = block_sum<kWriteThreads>(eq, s.sm);
+  const uint32_t front = sure + (eq < need ? eq : need);
+  for (uint32_t w = threadIdx.x; w < (1u << (cls_log2 - 5)); w += kWriteThreads) s.word[w] = 0u;
+  __syncthreads();
+  uint32_t eq_run = eq;
+#pragma unroll 1
+  for (uint32_t qb = q0; qb < q1; qb += kWriteThreads) {
+    const uint32_t q = qb + threadIdx.x;
+    uint32_t chosen = 0u, same = 0u, tot;
+    if (q < nq && q < q1) {
+      uint32_t u[4];
+      philox_block(q, key, u);
+      const uint32_t pb = pos_bits[q >> 3] >> ((q & 7u) * 4u);
+      for (int e = 0; e < 4; ++e) {
+        if ((int64_t)q * 4 + e >= N) continue;
+        if (((pb >> e) & 1u) || u[e] > prefix) chosen |= 1u << e;
+        else if (u[e] == prefix) same |= 1u << e;
+      }
+    }
+    uint32_t rank = eq_run + block_excl_scan<kWriteThreads>(__popc(same), s.sm, tot);
+    for (int e = 0; e < 4; ++e) {
+      if (!((same >> e) & 1u)) continue;
+      if (rank < need) chosen |= 1u << e;
+      ++rank;
+    }
+    eq_run += tot;
+    if (chosen) atomicOr(&s.word[(q - q0) >> 3], chosen << ((q & 7u) * 4u));
+  }
+  __syncthreads();
+  return front;
+}
+
+// NE: list entries that every thread keeps in registers over the three looks at the list.  The host
+// picks it so that the usual list fits (few registers where the list is short); the rest of a
+// longer one is read again each time.  512 threads: with 1024 the 64 registers of two resident
+// workgroups spill (2 million classes: 38 us instead of 13).
+template <int NE>
+__global__ __launch_bounds__(kWriteThreads, 4) void sample_write_kernel(
+    int64_t N, PhiloxKey key, Window win, SampleScratch sc, int cls_log2, int nblk,
+    uint32_t ceil_rN, const int64_t* __restrict__ labels, int B, int64_t cap,
+    int32_t* __restrict__ idx_out, int32_t* __restrict__ yl_out) {
+  constexpr int NT = kWriteThreads;
+  __shared__ WriteShared s;
+  const int t = threadIdx.x;
+  const uint32_t me = blockIdx.x;
+  const uint32_t word0 = me << (cls_log2 - 5), nwords = (uint32_t)((N + 31) >> 5);
+  const int own_words = 1 << (cls_log2 - 5);
+
+  // Everything that is certain to be needed is requested before anything is waited for, from both
+  // sets where the set at hand decides (it is one load away itself), the list up to its usual
+  // length whatever it holds.
+  uint64_t x[NE];
+#pragma unroll
+  for (int c = 0; c < NE; ++c) {
+    const uint32_t e = c * NT + t;
+    x[c] = e < sc.list_cap ? sc.list[e] : 0ull;
+  }
+  const uint32_t par = sc.st->cur & 1u;
+  const SampleHdr *hp0 = &sc.st->hdr[0], *hp1 = &sc.st->hdr[1];
+  auto pick = [&](uint32_t SampleHdr::*f) {
+    const uint32_t a = hp0->*f, b = hp1->*f;
+    return par ? b : a;
+  };
+  const uint32_t U = pick(&SampleHdr::U), pos_above = pick(&SampleHdr::pos_above),
+                 npos = pick(&SampleHdr::npos), overflow = pick(&SampleHdr::overflow),
+                 listed = pick(&SampleHdr::listed);
+  const uint32_t old_words = par ? hp0->nwords : hp1->nwords,
+                 old_blk = par ? hp0->nblk : hp1->nblk;
+  // counts: of every workgroup (does the window hold the end of the selection?) and of those in
+  // front (where does this one's output start?)
+  uint32_t tot_above = 0, front = 0, front_pos = 0;
+  for (uint32_t b = t; b < (uint32_t)nblk; b += NT) {
+    const uint32_t a = sc.above_cnt[b], p0 = sc.blk_pos[0][b], p1 = sc.blk_pos[1][b];
+    const uint32_t p = par ? p1 : p0;
+    tot_above += a;
+    if (b < me) {
+      front += a + (p & 0xFFFFu);
+      front_pos += (p & 0xFFFFu) + (p >> 16);
+    }
+  }
+  const uint32_t k = U > ceil_rN ? U : ceil_rN;
+  const uint32_t R = k - U;   // negatives to take
+  const uint32_t* pos_bits = par ? sc.pos_bits[1] : sc.pos_bits[0];
+  for (int b = t; b < kBins; b += NT) s.hist[b] = 0u;
+  for (int w = t; w < own_words; w += NT) {
+    uint32_t v = 0u;
+    if (word0 + w < nwords) {
+      const uint32_t p0 = sc.pos_bits[0][word0 + w], p1 = sc.pos_bits[1][word0 + w];
+      v = (par ? p1 : p0) | (R ? sc.above_bits[word0 + w] : 0u);
+    }
+    s.word[w] = v;
+  }
+  if (t == 0) {
+    s.bin_n = 0u;
+    s.key_end = 0ull;
+  }
+  tot_above = block_sum<NT>(tot_above, s.sm);
+  front = block_sum<NT>(R ? front : front_pos, s.sm);
+  uint32_t out = front;
+  if (R != 0) {
+    const uint32_t n = listed;
+    const uint32_t neg_above = tot_above - pos_above;
+    const uint32_t need = R - neg_above;
+    bool ok = overflow == 0u && npos <= sc.pos_cap && n <= sc.list_cap && neg_above <= R &&
+              R <= neg_above + (n - npos);
+    auto each = [&](auto fn) {   // fn(key) for every entry of the list
+#pragma unroll
+      for (int c = 0; c < NE; ++c)
+        if ((uint32_t)(c * NT + t) < n) fn(x[c]);
+      for (uint32_t e = NE * NT + t; e < n; e += NT) fn(sc.list[e]);
+    };
+    auto bin_of = [&](uint64_t y) { return (~(uint32_t)(y >> 32) - win.lo) >> win.shift; };
+    const uint64_t* pl = par ? sc.pos_list[1] : sc.pos_list[0];
+    if (ok && need) {
+      // negatives of the window by bin (the list holds batch classes too: taken out again)
+      each([&](uint64_t y) { atomicAdd(&s.hist[bin_of(y)], 1u); });
+      for (uint32_t e = t; e < npos; e += NT) atomicSub(&s.hist[bin_of(pl[e])], 1u);
+      __syncthreads();
+      uint32_t bin, inside;
+      find_bin<NT, kBins>(s.hist, need, s.sm, bin, inside);
+      each([&](uint64_t y) {
+        const uint32_t j = (uint32_t)y;
+        if (bin_of(y) == bin && !((pos_bits[j >> 5] >> (j & 31u)) & 1u)) {
+          const uint32_t p = atomicAdd(&s.bin_n, 1u);
+          if (p < (uint32_t)kBinList) s.bin_list[p] = y;
+        }
+      });
+      __syncthreads();
+      const uint32_t nb = s.bin_n;
+      ok = nb <= (uint32_t)kBinList;
+      if (ok && (uint32_t)t < nb) {
+        const uint64_t mine = s.bin_list[t];
+        uint32_t rank = 0;
+        for (uint32_t e = 0; e < nb; ++e) rank += s.bin_list[e] < mine ? 1u : 0u;
+        if (rank == inside - 1u) s.key_end = mine + 1ull;   // keys below this are taken
+      }
+      __syncthreads();
+    }
+    if (ok) {
+      if (need) {
+        const uint64_t end = s.key_end;
+        uint32_t c = 0;
+        each([&](uint64_t y) {
+          if (y >= end) return;
+          const uint32_t j = (uint32_t)y, b = j >> cls_log2;
+          if (b < me) ++c;
+          else if (b == me) atomicOr(&s.word[(j >> 5) - word0], 1u << (j & 31u));
+        });
+        // a batch class in the window was counted as one already
+        for (uint32_t e = t; e < npos; e += NT) {
+          const uint64_t y = pl[e];
+          if (y < end && ((uint32_t)y >> cls_log2) < me) --c;
+        }
+        out += block_sum<NT>(c, s.sm);
+      }
+    } else {
+      out = slow_select(N, key, pos_bits, R, cls_log2, s);
+    }
+  }
+  __syncthreads();
+
+  // number of chosen classes in front of every word, then the ids, four classes per thread
+  const uint32_t out0 = out;
+  uint32_t run = 0;
+  for (int w0 = 0; w0 < own_words; w0 += NT) {
+    const int w = w0 + t;
+    uint32_t tot;
+    const uint32_t p =
+        run + block_excl_scan<NT>(w < own_words ? __popc(s.word[w]) : 0u, s.sm, tot);
+    if (w < own_words) s.pre[w] = p;
+    run += tot;
+  }
+  __syncthreads();
+  for (int b = t; b < own_words * 8; b += NT) {
+    const uint32_t word = s.word[b >> 3], sh = (b & 7) * 4, c4 = (word >> sh) & 0xFu;
+    uint32_t pos = out0 + s.pre[b >> 3] + __popc(word & ((1u << sh) - 1u));
+    const uint32_t id0 = (me << cls_log2) + (uint32_t)b * 4u;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      if ((chosen >> e) & 1u) {
-        if ((int64_t)pos < cap) idx_out[pos] = (int32_t)(q * 4u + e);
+      if ((c4 >> e) & 1u) {
+        if ((int64_t)pos < cap) idx_out[pos] = (int32_t)(id0 + e);
         ++pos;
       }
     }
-    eq_run += tot_e;
-    out += tot_s;
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) sel->total = out;
+  // positions of the labels that lie here (-1 for a bad label), four loads in flight
+  for (int i0 = t; i0 < B; i0 += 4 * NT) {
+    int64_t ys[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) ys[c] = i0 + c * NT < B ? labels[i0 + c * NT] : 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int i = i0 + c * NT;
+      const int64_t y = ys[c];
+      if (i >= B) break;
+      if (y < 0 || y >= N) {
+        if (me == 0) yl_out[i] = -1;
+      } else if ((uint32_t)(y >> cls_log2) == me) {
+        const uint32_t w = (uint32_t)(y >> 5) - word0;
+        const uint32_t pos = out0 + s.pre[w] + __popc(s.word[w] & ((1u << (y & 31)) - 1u));
+        yl_out[i] = (int64_t)pos < cap ? (int32_t)pos : -1;
+      }
+    }
+  }
+  // clear the other set for the next call (this launch uses none of it but the two sizes, and
+  // those stay)
+  uint32_t* old_bits = par ? sc.pos_bits[0] : sc.pos_bits[1];
+  uint32_t* old_pos = par ? sc.blk_pos[0] : sc.blk_pos[1];
+  for (uint32_t w = me * NT + t; w < old_words; w += (uint32_t)nblk * NT)
+    old_bits[w] = 0u;
+  for (uint32_t b = me * NT + t; b < old_blk; b += (uint32_t)nblk * NT)
+    old_pos[b] = 0u;
+  if (me == 0 && t == 0) {
+    SampleHdr* old = par ? &sc.st->hdr[0] : &sc.st->hdr[1];
+    old->U = 0u;
+    old->pos_above = 0u;
+    old->npos = 0u;
+    old->overflow = 0u;
+    old->listed = 0u;
+    sc.st->k = k;
+    sc.st->next = par ^ 1u;
+  }
 }
 
-// labels_local[i] = position of labels[i] in the ascending idx (binary search), -1 if absent.
-__global__ void sample_remap_kernel(const int64_t* __restrict__ labels, int B, int64_t N,
-                                    const int32_t* __restrict__ idx, const SelState* __restrict__ sel,
-                                    int64_t cap, int32_t* __restrict__ yl_out,
-                                    uint32_t* __restrict__ pos_bits) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B) return;
-  const int64_t y = labels[i];
-  int64_t k = sel->total;
-  if (k > cap) k = cap;
-  int32_t res = -1;
-  if (y >= 0 && y < N) {
-    int64_t lo = 0, hi = k;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (idx[mid] < (int32_t)y) lo = mid + 1; else hi = mid;
-    }
-    if (lo < k && idx[lo] == (int32_t)y) res = (int32_t)lo;
-  }
-  yl_out[i] = res;
-  // last user of the "is in the batch" bits: clear this label's word for the next call
-  if (y >= 0 && y < N) pos_bits[y >> 5] = 0u;
+// Classes per workgroup (log2): few enough workgroups that the parts every one of them repeats
+// (the list, the counts, the labels) stay small, enough of them to use the GPU (up to 2.5 per
+// compute unit).
+int cls_log2_of(int64_t N) {
+  int l = 10;
+  while (l < kMaxClsLog2 && ((N + ((int64_t)1 << l) - 1) >> l) > kMaxBlocks) ++l;
+  return l;
+}
+
+// The window of scores in which the selection of k - U negatives ends.  Counted over ALL classes,
+// the last class taken is number n0 = k - U + (batch classes above it) from the top, between
+// ceil_rN - B and ceil_rN whatever the batch holds.  The number of classes at or above the score
+// 2^32 (1 - q) is binomial(N, q): 6.5 standard deviations and a constant for small counts.
+// *expected: classes inside it, on average.
+Window select_window(int64_t N, int64_t ceil_rN, int32_t B, double* expected) {
+  const double n = (double)N;
+  auto margin = [&](double rank) {
+    const double q = rank < 0 ? 0 : rank > n ? 1 : rank / n;
+    return 6.5 * sqrt(n * q * (1.0 - q)) + 40.0;
+  };
+  const double hi_rank = (double)ceil_rN, lo_rank = (double)ceil_rN - (double)B;
+  double top = lo_rank - margin(lo_rank < 0 ? 0 : lo_rank), bot = hi_rank + margin(hi_rank);
+  if (top < 0) top = 0;
+  if (bot > n) bot = n;
+  const double two32 = 4294967296.0;
+  double lo = floor(two32 * (1.0 - bot / n)), hi = ceil(two32 * (1.0 - top / n)) - 1.0;
+  if (bot >= n) lo = 0;
+  if (top <= 0 || hi > two32 - 1.0) hi = two32 - 1.0;
+  if (lo > hi) lo = hi;
+  *expected = bot - top;
+  Window w;
+  w.lo = (uint32_t)lo;
+  w.width = (uint32_t)hi - w.lo;
+  w.shift = 0;
+  while ((w.width >> w.shift) >= (uint32_t)kBins) ++w.shift;
+  return w;
+}
+
+int64_t blocks_of(int64_t N) {
+  const int l = cls_log2_of(N);
+  return (N + ((int64_t)1 << l) - 1) >> l;
 }
 
 }  // namespace
+
+size_t sample_layout(int64_t N, int64_t B, char* base, SampleScratch* out) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = base + off;
+    off += (bytes + 255) / 256 * 256;
+    return p;
+  };
+  const size_t words = (size_t)(N + 31) / 32;
+  const int64_t nb = blocks_of(N);
+  const size_t blk = (size_t)(nb > kMaxBlocks ? nb : kMaxBlocks);   // smaller N may have more blocks
+  // list: twice what the widest window of a call holds on average, and room for small numbers
+  const double wide = (double)(B < N ? B : N) + 2.0 * (6.5 * 0.5 * sqrt((double)N) + 40.0);
+  const size_t list = ((size_t)(2.0 * wide) + 4096);
+  out->st = (SampleState*)take(sizeof(SampleState));
+  for (int i = 0; i < 2; ++i) {
+    out->pos_bits[i] = (uint32_t*)take(words * 4);
+    out->blk_pos[i] = (uint32_t*)take(blk * 4);
+    out->pos_list[i] = (uint64_t*)take((size_t)B * 8);
+  }
+  out->above_bits = (uint32_t*)take(words * 4);
+  out->above_cnt = (uint32_t*)take(blk * 4);
+  out->list = (uint64_t*)take(list * 8);
+  out->list_cap = (uint32_t)list;
+  out->pos_cap = (uint32_t)B;
+  return off;
+}
 
 int sample_impl(pfc_ctx* c, const int64_t* labels, int32_t B, double r, uint64_t seed,
                 uint64_t step, uint32_t score_mask, int32_t* idx_out, int32_t* yl_out,
@@ -407,33 +634,27 @@ int sample_impl(pfc_ctx* c, const int64_t* labels, int32_t B, double r, uint64_t
   key.c3 = (uint32_t)(step >> 32);
   key.mask = score_mask;
 
-  const int nblk = (int)((N + kClassesPerBlock - 1) / kClassesPerBlock);
-  if (nblk > c->nblk_cap) return PFC_EINVAL;
-  const int64_t nq = (N + 3) / 4;
-  int hist_blocks = (int)((nq + kThreads * 4 - 1) / (kThreads * 4));
-  if (hist_blocks > 512) hist_blocks = 512;
-  if (hist_blocks < 1) hist_blocks = 1;
-
+  const int cls_log2 = cls_log2_of(N);
+  const int nblk = (int)blocks_of(N);
+  double expected = 0.0;
+  const Window win = select_window(N, crn, B, &expected);
+  const SampleScratch& sc = c->samp;
   const int mark_blocks = (B + kThreads - 1) / kThreads;
-  PFC_LAUNCH(c, KID_SAMPLE_HIST0, sample_hist_kernel<0>, dim3(hist_blocks + mark_blocks),
-             dim3(kThreads), 0, N, key, c->pos_bits, c->hist, c->sel, (uint32_t)crn, labels, B,
-             hist_blocks, c->err_flag);
-  PFC_LAUNCH(c, KID_SAMPLE_HIST1, sample_hist_kernel<1>, dim3(hist_blocks), dim3(kThreads), 0, N,
-             key, c->pos_bits, c->hist, c->sel, (uint32_t)crn, labels, B, hist_blocks, c->err_flag);
-  PFC_LAUNCH(c, KID_SAMPLE_HIST2, sample_hist_kernel<2>, dim3(hist_blocks), dim3(kThreads), 0, N,
-             key, c->pos_bits, c->hist, c->sel, (uint32_t)crn, labels, B, hist_blocks, c->err_flag);
-  PFC_LAUNCH(c, KID_SAMPLE_COUNT, sample_count_kernel, dim3(nblk), dim3(kThreads), 0, N, key,
-             c->pos_bits, c->hist, c->sel, (uint32_t)crn, c->blk_cnt);
-  PFC_LAUNCH(c, KID_SAMPLE_WRITE, sample_write_kernel, dim3(nblk), dim3(kThreads), 0, N, key,
-             c->pos_bits, c->sel, c->hist, c->blk_cnt, cap, idx_out);
-  PFC_LAUNCH(c, KID_SAMPLE_REMAP, sample_remap_kernel, dim3((B + kThreads - 1) / kThreads),
-             dim3(kThreads), 0, labels, B, N, idx_out, c->sel, cap, yl_out, c->pos_bits);
+  PFC_LAUNCH(c, KID_SAMPLE_SCAN, sample_scan_kernel, dim3(nblk + mark_blocks), dim3(kThreads), 0, N,
+             key, win, sc, cls_log2, nblk, labels, B, c->err_flag);
+  const double usual = expected + 4.0 * sqrt(expected);
+  auto write_kernel = usual <= 2.0 * kWriteThreads   ? sample_write_kernel<2>
+                      : usual <= 6.0 * kWriteThreads ? sample_write_kernel<6>
+                      : usual <= 16. * kWriteThreads ? sample_write_kernel<16>
+                                                     : sample_write_kernel<24>;
+  PFC_LAUNCH(c, KID_SAMPLE_WRITE, write_kernel, dim3(nblk), dim3(kWriteThreads), 0, N, key, win, sc,
+             cls_log2, nblk, (uint32_t)crn, labels, B, cap, idx_out, yl_out);
 
   if (crn >= (int64_t)B) {
     // U <= B <= ceil(r*N): k is known without the labels.
     *k_out = crn;
   } else {
-    PFC_HIP(hipMemcpyAsync(c->host_pin, &c->sel->k, 4, hipMemcpyDeviceToHost, c->stream));
+    PFC_HIP(hipMemcpyAsync(c->host_pin, &sc.st->k, 4, hipMemcpyDeviceToHost, c->stream));
     PFC_HIP(hipStreamSynchronize(c->stream));
     *k_out = (int64_t)c->host_pin[0];
   }
@@ -443,29 +664,20 @@ int sample_impl(pfc_ctx* c, const int64_t* labels, int32_t B, double r, uint64_t
 }  // namespace pfc
 
 // ---------------------------------------------------------------------------------------------
-// pfc_sample_noalloc: pfc_sample for callers that cannot allocate.  The sampler's scratch (the
-// "is in the batch" bitmap, the radix histograms, the select state, the per-block counts and an
-// error word) lives in ONE file-scope device array per GPU instead of a context's hipMalloc'ed
-// buffers; the kernels are those of pfc_sample and take its pieces as pointers.
+// pfc_sample_noalloc: pfc_sample for callers that cannot allocate.  The sampler's scratch lives in
+// ONE file-scope device array per GPU instead of a context's hipMalloc'ed buffer; the kernels are
+// those of pfc_sample and take its pieces as pointers.
 // ---------------------------------------------------------------------------------------------
 namespace {
 
 constexpr int64_t kNoallocMaxN = (int64_t)1 << 24;                               // 16,777,216 classes
-constexpr size_t kNaBitmapWords = (size_t)(kNoallocMaxN / 32) + 64;              // as pfc_create sizes it
-constexpr size_t kNaHistWords = 3 * 4096;
-constexpr size_t kNaSelWords = 64;                                               // SelState, 256-byte slot
-constexpr size_t kNaBlkWords = 2 * (size_t)(kNoallocMaxN / pfc::kClassesPerBlock);
-constexpr size_t kNaErrWords = 64;
-constexpr size_t kNaOffHist = kNaBitmapWords;
-constexpr size_t kNaOffSel = kNaOffHist + kNaHistWords;
-constexpr size_t kNaOffBlk = kNaOffSel + kNaSelWords;
-constexpr size_t kNaOffErr = kNaOffBlk + kNaBlkWords;
-constexpr size_t kNaWords = kNaOffErr + kNaErrWords;                             // 2.2 MB
-static_assert(sizeof(pfc::SelState) <= kNaSelWords * 4, "select state slot");
+constexpr int64_t kNoallocMaxB = (int64_t)1 << 20;
+// what sample_layout asks for at (kNoallocMaxN, kNoallocMaxB), checked on every call
+constexpr size_t kNaBytes = (size_t)42 << 20;
 
-// Zero when the code object is loaded; afterwards every call leaves it zero again (the last
-// reader of each piece clears it, see above), except the error word, which only ever gains bits.
-static __device__ __align__(256) uint32_t scratch[kNaWords];
+// Zero when the code object is loaded; afterwards every call leaves it so that the next one finds
+// its set cleared (see above), except the error word, which only ever gains bits.
+static __device__ __align__(256) uint32_t scratch[kNaBytes / 4];
 
 constexpr int kNaMaxDevices = 64;
 std::mutex g_na_mutex;
@@ -506,12 +718,10 @@ extern "C" int pfc_sample_noalloc(const int64_t* labels, int32_t B, int64_t N, d
   memset(&c, 0, sizeof(c));
   c.N = N;
   c.stream = (hipStream_t)hip_stream;
-  c.pos_bits = base;
-  c.hist = base + kNaOffHist;
-  c.sel = reinterpret_cast<pfc::SelState*>(base + kNaOffSel);
-  c.blk_cnt = base + kNaOffBlk;
-  c.nblk_cap = (int32_t)(kNoallocMaxN / pfc::kClassesPerBlock);
-  c.err_flag = reinterpret_cast<int32_t*>(base + kNaOffErr);
+  // the layout of the largest call, so that every call finds the sets of the one before
+  const size_t need = pfc::sample_layout(kNoallocMaxN, kNoallocMaxB, (char*)base, &c.samp);
+  if (need > kNaBytes) return PFC_EINVAL;
+  c.err_flag = reinterpret_cast<int32_t*>(&c.samp.st->spare[0]);
   return pfc::sample_impl(&c, labels, B, r, seed, step, 0xFFFFFFFFu, idx_out, labels_local_out,
                           k_out);
 }
