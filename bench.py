@@ -30,12 +30,9 @@ PEAK_FP32_MFMA_TFLOPS = 157.3  # fp32 MFMA
 # summarised in profiles/headline_step_hbm_traffic.md, keyed by (workload, r, kernel).  None where
 # no counter run has been recorded.
 MEASURED_TRAFFIC_BYTES: dict = {
-    ("headline", 0.1, "gemm_dweight_update"): 2171342916,
     ("headline", 0.1, "update"): 2115907072,
     ("headline", 0.1, "gather_normalize_w"): 636338241,
     ("headline", 0.1, "gemm_logits"): 723901584,
-    ("headline", 0.1, "gemm_dweight"): 905431780,
-    ("headline", 0.1, "gemm_dfeatures"): 700291405,
 }
 
 # Fraction of a GEMM kernel's own cycles in which an MFMA pipe was busy, from the rocprofv3 --pmc
@@ -43,9 +40,6 @@ MEASURED_TRAFFIC_BYTES: dict = {
 # the kernel's SQ_BUSY_CYCLES: independent of the clock the kernel ran at).
 MEASURED_MFMA_BUSY: dict = {
     ("headline", 0.1, "gemm_logits"): 0.352,
-    ("headline", 0.1, "gemm_dweight"): 0.373,
-    ("headline", 0.1, "gemm_dfeatures"): 0.591,
-    ("headline", 0.1, "gemm_dweight_update"): 0.196,
 }
 
 
@@ -63,6 +57,10 @@ def algorithmic_work(B: int, D: int, k: int, precision: int) -> dict:
         # the dweight GEMM that ends in the update of its rows: E and Xs in, W and v in and out;
         # its 2*B*D*k flops need less time at the MFMA peak than these bytes at the HBM peak
         "gemm_dweight_update": ("hbm", float(B) * k * es + float(B) * D * es + 4.0 * k * D * 4),
+        # both backward products in one launch, and the same with the update of the rows
+        "gemm_backward": ("mfma", 2.0 * gemm),
+        "gemm_backward_update": ("hbm", float(B) * k * es + float(B) * D * es + float(k) * D * es
+                                 + 4.0 * k * D * 4),
     }
 
 
@@ -252,7 +250,7 @@ def main() -> int:
                 ent.update(bound="hbm", achieved=round(ach, 1), peak=PEAK_HBM_GBS, unit="GB/s",
                            frac=round(ach / PEAK_HBM_GBS, 4),
                            traffic=MEASURED_TRAFFIC_BYTES.get((wl.name, wl.r, name)))
-                if name == "gemm_dweight_update":
+                if name == "gemm_backward_update":
                     ent["mfma_busy_frac"] = MEASURED_MFMA_BUSY.get((wl.name, wl.r, name))
         kernels[name] = ent
     # the sampler: integer work only (one sweep of one Philox4x32-10 block per four classes, about

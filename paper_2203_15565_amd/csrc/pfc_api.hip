@@ -18,8 +18,8 @@ void set_hip_error(hipError_t e, const char* what) {
 static const char* const kKernelNames[KID_COUNT] = {
     "sample_scan", "sample_write", "normalize_x",  "gather_normalize_w", "gemm_rowmax",
     "row_ref", "gemm_logits",
-    "row_combine",   "gemm_dweight", "dweight_reduce", "dweight_label", "dweight_label_combine",
-    "gemm_dfeatures", "dfeatures_final", "update", "gemm_dweight_update"};
+    "row_combine", "gemm_backward", "dweight_reduce", "dweight_label", "dweight_label_combine",
+    "dfeatures_final", "update", "gemm_backward_update"};
 
 static int64_t ceil_rN(int64_t N, double r) { return (int64_t)ceil(r * (double)N); }
 
@@ -148,7 +148,8 @@ int pfc_create(pfc_ctx** out, int64_t N, int32_t D, int32_t B_max, double r_max,
   ALLOC(rowscale, Bp * 4);
   ALLOC(dlabel, Bp * 4);
   ALLOC(lossrow, Bp * 4);
-  ALLOC(dXpart, (size_t)kMaxSplits * Bp * Dpz * 4);
+  ALLOC(dXpart, ((size_t)kPartSlices * Dpz + Dz) * Bp * 4);
+  if (rc == PFC_OK) c->wlab = c->dXpart + (size_t)kPartSlices * Bp * Dpz;
   ALLOC(dlab, Bp * Dz * 4);
   ALLOC(dWtmp, (size_t)c->k_cap * Dz * 4);
   ALLOC(spare, 2 * Dz * 4);

@@ -14,7 +14,9 @@ namespace pfc {
 // ---------------------------------------------------------------------------------------------
 constexpr int kPadB = 256;   // batch rows are padded to a multiple of this
 constexpr int kPadK = 256;   // sampled rows are padded to a multiple of this
-constexpr int kMaxSplits = 64;
+constexpr int kMaxSplits = 32;    // slices of S in the dfeatures product
+constexpr int kPartSlices = 64;   // slices the buffer of partial sums has room for: those of dfeatures
+                                  // in front, those of a dweight product cut over the batch behind
 constexpr int kLabelWindow = 1024;     // samples per window of the label part of dWn
 constexpr int kMaxLabelWindows = 64;   // one lane of a wavefront initialises one window's head
 
@@ -30,14 +32,13 @@ enum KernelId {
   KID_ROW_REF,
   KID_GEMM_LOGITS,
   KID_ROW_COMBINE,
-  KID_GEMM_DW,
+  KID_GEMM_BACKWARD,
   KID_DW_REDUCE,
   KID_DW_LABEL,
   KID_DW_LABEL_SUM,
-  KID_GEMM_DX,
   KID_DX_FINAL,
   KID_UPDATE,
-  KID_GEMM_DW_UPDATE,
+  KID_GEMM_BACKWARD_UPDATE,
   KID_COUNT
 };
 
@@ -109,7 +110,8 @@ struct pfc_ctx {
   float* rowscale; // [Bp] s/(B*l_i)
   float* dlabel;   // [Bp] (s/B)(p_iy - 1) rho_i
   float* lossrow;  // [Bp]
-  float* dXpart;   // [splits x Bp x Dp]
+  float* dXpart;   // [kPartSlices x Bp x Dp]
+  float* wlab;     // (behind dXpart) [Bp x D] row of W of every sample's label, as it was before the update (fused step)
   float* dlab;     // [Bp x D] label-column part of dWn, one row per first sample of a class (fused step)
   float* dWtmp;    // [k_cap x D] dWn of the fused step whenever its one-kernel form does not apply
   float* spare;    // [2 x D] a row of zeros (never written) and a row that only takes the stores of

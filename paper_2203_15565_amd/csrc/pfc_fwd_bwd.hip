@@ -8,10 +8,12 @@
 //   gemm_logits        c = Wn Xn^T, margin, e = exp(s c) -> E and per-tile row sums (MFMA)
 //   row_combine        l_i, lse_i, per-row loss, s/(B l_i), label-column coefficient,
 //                      Xs = (s/(B l_i)) xn_i
-//   gemm_dweight       dWn = E^T Xs  (off-label part)                (MFMA)
+//   gemm_backward      both backward products in one launch (MFMA): partial sums of E Wn over
+//                      slices of S, and dWn = E^T Xs (off-label part)
 //   dweight_label      adds the label-column term to the rows of positive classes (fp32)
-//   gemm_dfeatures     partial sums of E Wn over slices of S         (MFMA, split over S)
 //   dfeatures_final    reduce slices, scale, label term, project through x -> x/|x|; mean loss
+// In the fused call dweight_label (into a side buffer) comes before gemm_backward_update, whose
+// dweight tiles end in the update of their rows.
 //
 // Cosines lie in [-1,1]: up to s = 64, exp(s c) lies in [e^-64, e^64] and a row sum over at most
 // 2^31 classes stays below 3.4e38, so exp needs no running maximum and one fixed reference (zero)
@@ -23,6 +25,7 @@
 #include <limits.h>
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "pfc_common.h"
@@ -486,7 +489,9 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
                                    float* __restrict__ rowscale, float* __restrict__ dlabel,
                                    float* __restrict__ lossrow, float* __restrict__ rowmax,
                                    const int32_t* __restrict__ yl, int64_t k, int64_t kp,
-                                   int32_t* __restrict__ head, int nwin, T* __restrict__ Xs) {
+                                   int32_t* __restrict__ head, int nwin, T* __restrict__ Xs,
+                                   const float* __restrict__ W, int64_t N,
+                                   const int32_t* __restrict__ idx, float* __restrict__ wlab) {
   const int lane = threadIdx.x & 63;
   const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (i >= Bp) return;
@@ -550,6 +555,55 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
       *reinterpret_cast<uint4*>(Xs + (int64_t)i * (256 * NC) + d) = pk;
     }
   }
+  // fused step: keep the label's row of W for dfeatures_final, which runs after the update
+  if (wlab && i < B) {
+    const int32_t y = yl[i];
+    const int64_t row = (y >= 0 && (int64_t)y < k) ? idx[y] : -1;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int d = c * 256 + lane * 4;
+      if (row >= 0 && row < N && d < D)
+        *reinterpret_cast<float4*>(wlab + (int64_t)i * D + d) =
+            *reinterpret_cast<const float4*>(W + row * D + d);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// dfeatures: slice `sp` of S: part[sp][i][d] = sum_{j in slice} E[i][j] * Wn[j][d]
+// (A = E with k contiguous, B = Wn k-major).
+// ---------------------------------------------------------------------------------------------
+struct DxShape {
+  int slabs_total, slabs_per, splits, tiles_i, tiles_d;
+  int wgs;   // workgroups: tiles_i * tiles_d * splits, rounded up to 8
+};
+template <class Cfg>
+__device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
+                                               const typename Cfg::elem* __restrict__ E,
+                                               const typename Cfg::elem* __restrict__ Wn, int D,
+                                               int Bp, int64_t kp, const DxShape& dx,
+                                               float* __restrict__ part) {
+  int sp, tile;
+  if (!xcd_tile(wg, dx.tiles_i * dx.tiles_d, dx.splits, sp, tile)) return;
+  const int ti = tile / dx.tiles_d, td = tile % dx.tiles_d;
+  const int i0 = ti * Cfg::BM, d0 = td * Cfg::BN;
+  const int slab0 = sp * dx.slabs_per;
+  int ns = dx.slabs_total - slab0;
+  if (ns > dx.slabs_per) ns = dx.slabs_per;
+  f32x16 acc[Cfg::TM][Cfg::TN];
+  zero_acc<Cfg>(acc);
+  const int64_t koff = (int64_t)slab0 * Cfg::BK;
+  gemm_tile<Cfg>(E + (int64_t)i0 * kp + koff, kp, Wn + koff * D + d0, D, ns, smem, acc);
+  float* out = part + (int64_t)sp * Bp * D;
+#pragma unroll
+  for (int bm = 0; bm < Cfg::TM; ++bm)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = i0 + acc_row<Cfg>(bm, r);
+#pragma unroll
+      for (int bn = 0; bn < Cfg::TN; ++bn)
+        out[(int64_t)i * D + d0 + acc_col<Cfg>(bn)] = acc[bm][bn][r];
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -560,21 +614,20 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
 // partial tiles too; dWn (the caller's) has rows of D floats, columns from D on are not stored.
 // ---------------------------------------------------------------------------------------------
 template <class Cfg, bool SPLIT>
-__global__ __launch_bounds__(Cfg::THREADS) void gemm_dweight_kernel(
-    const typename Cfg::elem* __restrict__ E, const typename Cfg::elem* __restrict__ Xs, int D,
-    int Dp, int64_t k, int64_t kp, int Bp, float* __restrict__ out, int tiles_j, int tiles_d,
-    int slabs_per, int splits) {
-  extern __shared__ __align__(16) char smem[];
+__device__ __forceinline__ void dweight_tile(
+    int wg, char* smem, const typename Cfg::elem* __restrict__ E,
+    const typename Cfg::elem* __restrict__ Xs, int D, int Dp, int64_t k, int64_t kp, int Bp,
+    float* __restrict__ out, int tiles_j, int tiles_d, int slabs_per, int splits) {
   int tj, td, sp = 0, ns = Bp / Cfg::BK;
   if constexpr (SPLIT) {
     int tile;
-    if (!xcd_tile(blockIdx.x, tiles_j * tiles_d, splits, sp, tile)) return;
+    if (!xcd_tile(wg, tiles_j * tiles_d, splits, sp, tile)) return;
     tj = tile / tiles_d;
     td = tile % tiles_d;
     ns -= sp * slabs_per;
     if (ns > slabs_per) ns = slabs_per;
   } else {
-    if (!xcd_tile(blockIdx.x, tiles_d, tiles_j, tj, td)) return;
+    if (!xcd_tile(wg, tiles_d, tiles_j, tj, td)) return;
   }
   const int64_t j0 = (int64_t)tj * Cfg::BM;
   const int d0 = td * Cfg::BN;
@@ -608,6 +661,29 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_dweight_kernel(
   else
     store_tile(std::true_type{});
   PFC_PHASE(2, 2);
+}
+
+// gemm_backward: the two backward products need nothing of each other, so they share a launch: the
+// first dx.wgs workgroups (a multiple of 8, so that workgroup ids keep their XCD) work on dfeatures,
+// the others on dweight.  Alone, either leaves the GPU partly idle: small problems have too few
+// tiles and are bound by the latency of a tile (17 + 18 us one after the other, 24 together at 512
+// samples x 9,344 classes x 512), large ones lose the last round of dweight tiles and have all
+// compute units store their tiles at the same time (291 + 219 us, 495 together at 1024 x 205,991 x
+// 512).  The dfeatures workgroups are the longest and start first; dx_shape says how many there are.
+template <class CfgX, class CfgW, bool SPLIT>
+__global__ __launch_bounds__(CfgX::THREADS) void gemm_backward_kernel(
+    const typename CfgX::elem* __restrict__ E, const typename CfgX::elem* __restrict__ Wn,
+    const typename CfgX::elem* __restrict__ Xs, int D, int Dp, int64_t k, int64_t kp, int Bp,
+    DxShape dx, float* __restrict__ dXpart, float* __restrict__ dWout, int tiles_j, int tiles_d,
+    int slabs_per, int splits) {
+  static_assert(CfgX::THREADS == CfgW::THREADS, "one launch shape");
+  extern __shared__ __align__(16) char smem[];
+  const int b = blockIdx.x;
+  if (b < dx.wgs)
+    dfeatures_tile<CfgX>(b, smem, E, Wn, Dp, Bp, kp, dx, dXpart);
+  else
+    dweight_tile<CfgW, SPLIT>(b - dx.wgs, smem, E, Xs, D, Dp, k, kp, Bp, dWout, tiles_j, tiles_d,
+                              slabs_per, splits);
 }
 
 // dW[j][d] = sum over slices of part[slice][j][d], in slice order (rows of Dp floats in `part`, of
@@ -907,58 +983,33 @@ __device__ __forceinline__ void fused_update_tile(
   }
 }
 
-// The first n_big workgroups take tiles of CfgB::BM rows; the rows left over when those no longer
-// fill a whole round of workgroups on the GPU go to the following workgroups in tiles of
-// CfgS::BM rows, so that the last, partly filled round is short.
-template <class CfgB, class CfgS>
-__global__ __launch_bounds__(CfgB::THREADS) void gemm_dweight_update_kernel(
-    const typename CfgB::elem* __restrict__ E, const typename CfgB::elem* __restrict__ Xs,
-    int64_t k, int64_t kp, int Bp, const int32_t* __restrict__ idx,
+// gemm_backward_update: as gemm_backward, the dfeatures product (MFMA bound) shares the launch with
+// the dweight product that ends in the update (HBM bound more than half of its time): 715 us one
+// after the other, 698 together at 1024 samples x 205,991 classes x 512, 162 -> 137 at 36,024 classes.
+// Behind the dfeatures workgroups, n_big workgroups take tiles of CfgB::BM rows; the rows left over when
+// those no longer fill a whole round of workgroups on the GPU go to the following workgroups in
+// tiles of CfgS::BM rows, so that the last, partly filled round is short.
+template <class CfgX, class CfgB, class CfgS>
+__global__ __launch_bounds__(CfgB::THREADS) void gemm_backward_update_kernel(
+    const typename CfgB::elem* __restrict__ E, const typename CfgB::elem* __restrict__ Wn,
+    const typename CfgB::elem* __restrict__ Xs, DxShape dx, float* __restrict__ dXpart, int64_t k, int64_t kp, int Bp, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ head, const float* __restrict__ lab, float* spare,
     float* __restrict__ W, float* __restrict__ V, int64_t N, float lr, float mu,
     int32_t* __restrict__ err_flag, int n_big) {
-  static_assert(CfgB::THREADS == CfgS::THREADS && CfgB::BN == CfgS::BN, "one launch shape");
+  static_assert(CfgB::THREADS == CfgS::THREADS && CfgB::THREADS == CfgX::THREADS &&
+                CfgB::BN == CfgS::BN, "one launch shape");
   extern __shared__ __align__(16) char smem[];
-  const int b = blockIdx.x;
+  if ((int)blockIdx.x < dx.wgs) {
+    dfeatures_tile<CfgX>(blockIdx.x, smem, E, Wn, CfgB::BN, Bp, kp, dx, dXpart);
+    return;
+  }
+  const int b = (int)blockIdx.x - dx.wgs;
   if (b < n_big)
     fused_update_tile<CfgB>((int64_t)b * CfgB::BM, smem, E, Xs, k, kp, Bp, idx, head, lab, spare,
                             W, V, N, lr, mu, err_flag);
   else
     fused_update_tile<CfgS>((int64_t)n_big * CfgB::BM + (int64_t)(b - n_big) * CfgS::BM, smem, E,
                             Xs, k, kp, Bp, idx, head, lab, spare, W, V, N, lr, mu, err_flag);
-}
-
-// ---------------------------------------------------------------------------------------------
-// gemm_dfeatures: slice `sp` of S: part[sp][i][d] = sum_{j in slice} E[i][j] * Wn[j][d]
-// (A = E with k contiguous, B = Wn k-major).
-// ---------------------------------------------------------------------------------------------
-template <class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS) void gemm_dfeatures_kernel(
-    const typename Cfg::elem* __restrict__ E, const typename Cfg::elem* __restrict__ Wn, int D,
-    int Bp, int64_t kp, int slabs_total, int slabs_per, int splits, float* __restrict__ part,
-    int tiles_i, int tiles_d) {
-  extern __shared__ __align__(16) char smem[];
-  int sp, tile;
-  if (!xcd_tile(blockIdx.x, tiles_i * tiles_d, splits, sp, tile)) return;
-  const int ti = tile / tiles_d, td = tile % tiles_d;
-  const int i0 = ti * Cfg::BM, d0 = td * Cfg::BN;
-  const int slab0 = sp * slabs_per;
-  int ns = slabs_total - slab0;
-  if (ns > slabs_per) ns = slabs_per;
-  f32x16 acc[Cfg::TM][Cfg::TN];
-  zero_acc<Cfg>(acc);
-  const int64_t koff = (int64_t)slab0 * Cfg::BK;
-  gemm_tile<Cfg>(E + (int64_t)i0 * kp + koff, kp, Wn + koff * D + d0, D, ns, smem, acc);
-  float* out = part + (int64_t)sp * Bp * D;
-#pragma unroll
-  for (int bm = 0; bm < Cfg::TM; ++bm)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = i0 + acc_row<Cfg>(bm, r);
-#pragma unroll
-      for (int bn = 0; bn < Cfg::TN; ++bn)
-        out[(int64_t)i * D + d0 + acc_col<Cfg>(bn)] = acc[bm][bn][r];
-    }
 }
 
 // dfeatures_final: one wavefront per sample.
@@ -972,6 +1023,7 @@ __global__ void dfeatures_final_kernel(const float* __restrict__ part, int split
                                        const int32_t* __restrict__ yl, int64_t k,
                                        const float* __restrict__ rnormX,
                                        const float* __restrict__ rnormW,
+                                       const float* __restrict__ wlab,
                                        const float* __restrict__ rowscale,
                                        const float* __restrict__ dlabel, float* __restrict__ dX,
                                        const float* __restrict__ lossrow,
@@ -1042,6 +1094,10 @@ __global__ void dfeatures_final_kernel(const float* __restrict__ part, int split
     rnw = rnormW[y];
     if (wrow < 0 || wrow >= N) wrow = -1;
   }
+  if (wlab) {   // W has been updated already: the label's row as it was
+    W = wlab;
+    if (wrow >= 0) wrow = i;
+  }
   float4 g[NC], xn[NC];
   float u = 0.f;
 #pragma unroll
@@ -1083,7 +1139,7 @@ template <class CfgW>
 int dweight_slices(const pfc_ctx* c, int tiles, int Bp, int64_t kp) {
   const int slabs_total = Bp / CfgW::BK;
   int want = c->num_cu / tiles;
-  const int64_t room = (int64_t)kMaxSplits * Bp / kp;
+  const int64_t room = (int64_t)(kPartSlices - kMaxSplits) * Bp / kp;
   if (want > room) want = (int)room;
   if (want > slabs_total / 8) want = slabs_total / 8;   // a slice must stay long enough to pay
                                                         // for its own partial tile
@@ -1105,8 +1161,11 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   // as many workgroups, two of them resident per compute unit (74 KB of LDS each)
   using CfgFs = TileCfg<T, 128, 128, 2, 4, false, false>;
   using CfgWs = TileCfg<T, 128, 128, 2, 4, true, true>;
-  constexpr int kFusedLds = FusedUpdateLds<CfgU>::LDS > FusedUpdateLds<CfgUS>::LDS
-                                ? FusedUpdateLds<CfgU>::LDS : FusedUpdateLds<CfgUS>::LDS;
+  using CfgXs = TileCfg<T, 128, 128, 2, 4, false, true>;
+  constexpr int kFusedLds =
+      std::max({FusedUpdateLds<CfgU>::LDS, FusedUpdateLds<CfgUS>::LDS, CfgX::LDS_BYTES});
+  constexpr int kBackLds = std::max(CfgX::LDS_BYTES, CfgW::LDS_BYTES);
+  constexpr int kBackLdsS = std::max(CfgXs::LDS_BYTES, CfgWs::LDS_BYTES);
   static_assert(kFusedLds <= 160 * 1024, "LDS of one compute unit");
   const int D = c->D;
   constexpr int Dp = 256 * NC;   // row length of the library's own GEMM operands
@@ -1115,6 +1174,10 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   T* Xn = (T*)c->Xn; T* Xs = (T*)c->Xs; T* Wn = (T*)c->Wn; T* E = (T*)c->E;
   // windows of the label part (0: the batch fits one window, or the context has no room for them)
   const int nwin = (B > kLabelWindow && c->label_windows) ? (B + kLabelWindow - 1) / kLabelWindow : 0;
+
+  // fused call: one kernel for dweight and update only if D fits its tile and there is at least one
+  // tile per CU
+  const bool one_kernel = upd && D == CfgU::BN && kp / CfgU::BM >= c->num_cu;
 
   auto norm_kernel = normalize_x_kernel<T, NC>;
   PFC_LAUNCH(c, KID_NORM_X, norm_kernel, dim3((Bp + 3) / 4), dim3(256), 0, X, B, Bp, D,
@@ -1133,23 +1196,21 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
                                 hipFuncAttributeMaxDynamicSharedMemorySize, CfgF::LDS_BYTES));
     PFC_HIP(hipFuncSetAttribute((const void*)gemm_rowmax_kernel<CfgF>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, CfgF::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_dweight_kernel<CfgW, false>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgW::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_dweight_kernel<CfgW, true>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgW::LDS_BYTES));
     PFC_HIP(hipFuncSetAttribute((const void*)gemm_logits_kernel<CfgFs, false>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, CfgFs::LDS_BYTES));
     PFC_HIP(hipFuncSetAttribute((const void*)gemm_logits_kernel<CfgFs, true>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, CfgFs::LDS_BYTES));
     PFC_HIP(hipFuncSetAttribute((const void*)gemm_rowmax_kernel<CfgFs>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, CfgFs::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_dweight_kernel<CfgWs, false>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgWs::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_dweight_kernel<CfgWs, true>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgWs::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_dfeatures_kernel<CfgX>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgX::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_dweight_update_kernel<CfgU, CfgUS>),
+    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_kernel<CfgX, CfgW, false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kBackLds));
+    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_kernel<CfgX, CfgW, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kBackLds));
+    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_kernel<CfgXs, CfgWs, false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kBackLdsS));
+    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_kernel<CfgXs, CfgWs, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kBackLdsS));
+    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_update_kernel<CfgX, CfgU, CfgUS>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFusedLds));
     c->lds_attr_set = 1;
   }
@@ -1172,7 +1233,8 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     auto combine_kernel = row_combine_kernel<T, NC>;
     PFC_LAUNCH(c, KID_ROW_COMBINE, combine_kernel, dim3((Bp + 3) / 4), dim3(256), 0, c->rowpart,
                tiles_j, B, Bp, D, X, c->rnormX, c->clabel, lp, c->rowmaxpart, c->rowscale,
-               c->dlabel, c->lossrow, c->rowmax, yl, k, kp, c->head, nwin, Xs);
+               c->dlabel, c->lossrow, c->rowmax, yl, k, kp, c->head, nwin, Xs, W, c->N, idx,
+               one_kernel ? c->wlab : nullptr);
     return PFC_OK;
   };
   {
@@ -1201,87 +1263,93 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     }
     return PFC_OK;
   };
-  // dweight (+ label part) into dW_out
-  auto launch_dweight_cfg = [&](auto cfg) -> int {
+  // Shape of the dfeatures product: about `wgs` workgroups, at least 4 slabs each.  The callers ask
+  // for half of what the GPU holds at a time, or for all the room that the dweight tiles leave:
+  // measured against all of it and a quarter of it (us a step, quarter / half / all):
+  // 1024 samples x 205,991 classes x 512 1499 / 1302 / 1365, x 360,232 2511 / 2166 / 2251, fused
+  // x 205,991 1162 / 1098 / 1161.  Fewer workgroups write fewer partial sums (2 MB a slice there)
+  // but are longer than everything behind them.
+  auto dx_shape = [&](auto cfg, int64_t wgs) {
     using Cfg = decltype(cfg);
-    const int tiles_j = (int)(kp / Cfg::BM), tiles_d = Dp / Cfg::BN;
-    const int slabs_total = Bp / Cfg::BK;
-    // slices of the batch when the tiles alone leave most CUs idle; the partial tiles borrow the
-    // dfeatures split buffer, which is not in use at that point
-    const int want = dweight_slices<Cfg>(c, tiles_j * tiles_d, Bp, kp);
-    if (want >= 2) {
-      const int slabs_per = (slabs_total + want - 1) / want;
-      const int nsp = (slabs_total + slabs_per - 1) / slabs_per;
-      PFC_LAUNCH(c, KID_GEMM_DW, (gemm_dweight_kernel<Cfg, true>),
-                 dim3(xcd_grid(tiles_j * tiles_d, nsp)), dim3(Cfg::THREADS), Cfg::LDS_BYTES, E, Xs,
-                 D, Dp, k, kp, Bp, c->dXpart, tiles_j, tiles_d, slabs_per, nsp);
-      PFC_LAUNCH(c, KID_DW_REDUCE, dweight_reduce_kernel,
-                 dim3((unsigned)((k * D / 4 + 255) / 256)), dim3(256), 0, c->dXpart, nsp, k, kp, D,
-                 Dp, dW_out);
-    } else {
-      PFC_LAUNCH(c, KID_GEMM_DW, (gemm_dweight_kernel<Cfg, false>),
-                 dim3(xcd_grid(tiles_d, tiles_j)), dim3(Cfg::THREADS), Cfg::LDS_BYTES, E, Xs, D,
-                 Dp, k, kp, Bp, dW_out, tiles_j, tiles_d, slabs_total, 1);
-    }
-    return launch_label(false);
+    DxShape dx;
+    dx.tiles_i = Bp / Cfg::BM;
+    dx.tiles_d = Dp / Cfg::BN;
+    dx.slabs_total = (int)(kp / Cfg::BK);
+    int64_t want = wgs / (dx.tiles_i * dx.tiles_d);
+    want = std::min<int64_t>({want, kMaxSplits, dx.slabs_total / 4});
+    if (want < 1) want = 1;
+    dx.slabs_per = (int)((dx.slabs_total + want - 1) / want);
+    dx.splits = (dx.slabs_total + dx.slabs_per - 1) / dx.slabs_per;
+    dx.wgs = (int)round_up(xcd_grid(dx.tiles_i * dx.tiles_d, dx.splits), 8);
+    return dx;
   };
-  auto launch_dweight = [&]() -> int {
+  auto launch_final = [&](const DxShape& dx, const float* wlab) -> int {
+    PFC_LAUNCH(c, KID_DX_FINAL, dfeatures_final_kernel<NC>, dim3(B + 1), dim3(256), 0,
+               c->dXpart, dx.splits, B, Bp, D, X, W, c->N, idx, yl, k, c->rnormX, c->rnormW, wlab,
+               c->rowscale, c->dlabel, dX_out, c->lossrow, loss_out, c->clabel, c->rowmax,
+               stats_out);
+    return PFC_OK;
+  };
+  // both backward products in one launch; dW_out and the partial sums of dX are written
+  auto launch_backward_cfg = [&](auto cfgx, auto cfgw, int lds, int per_cu, DxShape& dx) -> int {
+    using CX = decltype(cfgx);
+    using CW = decltype(cfgw);
+    const int tiles_j = (int)(kp / CW::BM), tiles_d = Dp / CW::BN;
+    const int slabs_total = Bp / CW::BK;
+    const int64_t slots = (int64_t)c->num_cu * per_cu;
+    int want = dweight_slices<CW>(c, tiles_j * tiles_d, Bp, kp);
+    int nsp = 1, slabs_per = slabs_total;
+    if (want >= 2) {
+      slabs_per = (slabs_total + want - 1) / want;
+      nsp = (slabs_total + slabs_per - 1) / slabs_per;
+    }
+    const int64_t wgs_w = (int64_t)tiles_j * tiles_d * nsp;
+    dx = dx_shape(cfgx, std::max(slots / 2, slots - wgs_w));
+    float* dst = nsp > 1 ? c->dXpart + (int64_t)dx.splits * Bp * Dp : dW_out;
+    auto kernel = nsp > 1 ? gemm_backward_kernel<CX, CW, true> : gemm_backward_kernel<CX, CW, false>;
+    PFC_LAUNCH(c, KID_GEMM_BACKWARD, kernel, dim3((unsigned)(dx.wgs + wgs_w)), dim3(CX::THREADS), lds,
+               E, Wn, Xs, D, Dp, k, kp, Bp, dx, c->dXpart, dst, tiles_j, tiles_d, slabs_per, nsp);
+    if (nsp > 1) {
+      PFC_LAUNCH(c, KID_DW_REDUCE, dweight_reduce_kernel,
+                 dim3((unsigned)((k * D / 4 + 255) / 256)), dim3(256), 0, dst, nsp, k, kp, D, Dp,
+                 dW_out);
+    }
+    return PFC_OK;
+  };
+  auto launch_backward = [&](DxShape& dx) -> int {
     // small tiles only when the big ones, sliced over the batch as far as that goes, still leave
     // more than half of the compute units idle (a long batch is better cut into slices of big
     // tiles: half the LDS traffic per flop)
     const int64_t tiles_big = (kp / CfgW::BM) * (Dp / CfgW::BN);
     const bool small =
         tiles_big * dweight_slices<CfgW>(c, (int)tiles_big, Bp, kp) * 2 < (int64_t)c->num_cu;
-    return small ? launch_dweight_cfg(CfgWs{}) : launch_dweight_cfg(CfgW{});
-  };
-  // dfeatures GEMM (split over S) + final reduction, projection, loss
-  auto launch_dfeatures = [&]() -> int {
-    const int tiles_i = Bp / CfgX::BM, tiles_d = Dp / CfgX::BN;
-    const int slabs_total = (int)(kp / CfgX::BK);
-    int want = c->num_cu / (tiles_i * tiles_d);   // one workgroup per compute unit
-    if (want < 1) want = 1;
-    if (want > kMaxSplits) want = kMaxSplits;
-    if (want > slabs_total) want = slabs_total;
-    const int slabs_per = (slabs_total + want - 1) / want;
-    const int splits = (slabs_total + slabs_per - 1) / slabs_per;
-    PFC_LAUNCH(c, KID_GEMM_DX, gemm_dfeatures_kernel<CfgX>,
-               dim3(xcd_grid(tiles_i * tiles_d, splits)), dim3(CfgX::THREADS), CfgX::LDS_BYTES, E,
-               Wn, Dp, Bp, kp, slabs_total, slabs_per, splits, c->dXpart, tiles_i, tiles_d);
-    PFC_LAUNCH(c, KID_DX_FINAL, dfeatures_final_kernel<NC>, dim3(B + 1), dim3(256), 0,
-               c->dXpart, splits, B, Bp, D, X, W, c->N, idx, yl, k, c->rnormX, c->rnormW,
-               c->rowscale, c->dlabel, dX_out, c->lossrow, loss_out, c->clabel, c->rowmax,
-               stats_out);
-    return PFC_OK;
+    int rc = small ? launch_backward_cfg(CfgXs{}, CfgWs{}, kBackLdsS, 2, dx)
+                   : launch_backward_cfg(CfgX{}, CfgW{}, kBackLds, 1, dx);
+    return rc != PFC_OK ? rc : launch_label(false);
   };
 
-  if (!upd) {
-    int rc = launch_dweight();
-    if (rc != PFC_OK) return rc;
-    return launch_dfeatures();
-  }
-  // Fused step.  dfeatures goes first: its final kernel reads the label rows of W, which the
-  // update is about to change.
-  int rc = launch_dfeatures();
-  if (rc != PFC_OK) return rc;
-  // one kernel only if D fits its tile and there is at least one tile per CU
-  const bool one_kernel = D == CfgU::BN && kp / CfgU::BM >= c->num_cu;
-  if (!one_kernel) {   // dWn through memory (dW_out is the context's own buffer here)
-    rc = launch_dweight();
-    if (rc != PFC_OK) return rc;
-    return update_impl(c, upd->W, upd->v, idx, k, dW_out, upd->lr, upd->mu);
+  DxShape dx;
+  int rc;
+  if (!one_kernel) {
+    rc = launch_backward(dx);
+    if (rc == PFC_OK) rc = launch_final(dx, nullptr);
+    // fused call: dWn went through memory (dW_out is the context's own buffer here)
+    if (rc == PFC_OK && upd) rc = update_impl(c, upd->W, upd->v, idx, k, dW_out, upd->lr, upd->mu);
+    return rc;
   }
   rc = launch_label(true);
   if (rc != PFC_OK) return rc;
   {
+    dx = dx_shape(CfgX{}, c->num_cu / 2);
     const int tiles_big = (int)(kp / CfgU::BM);
     const int n_big = tiles_big / c->num_cu * c->num_cu;          // whole rounds
     const int n_small = (tiles_big - n_big) * (CfgU::BM / CfgUS::BM);
-    PFC_LAUNCH(c, KID_GEMM_DW_UPDATE, (gemm_dweight_update_kernel<CfgU, CfgUS>),
-               dim3((unsigned)(n_big + n_small)), dim3(CfgU::THREADS), kFusedLds, E, Xs, k, kp, Bp,
-               idx, c->head, c->dlab, c->spare, upd->W, upd->v, c->N, upd->lr, upd->mu, c->err_flag,
-               n_big);
+    PFC_LAUNCH(c, KID_GEMM_BACKWARD_UPDATE, (gemm_backward_update_kernel<CfgX, CfgU, CfgUS>),
+               dim3((unsigned)(dx.wgs + n_big + n_small)), dim3(CfgU::THREADS), kFusedLds, E, Wn, Xs,
+               dx, c->dXpart, k, kp, Bp, idx, c->head, c->dlab, c->spare, upd->W, upd->v, c->N,
+               upd->lr, upd->mu, c->err_flag, n_big);
   }
-  return PFC_OK;
+  return launch_final(dx, c->wlab);
 }
 
 }  // namespace
