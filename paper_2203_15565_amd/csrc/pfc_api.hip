@@ -140,8 +140,8 @@ int pfc_create(pfc_ctx** out, int64_t N, int32_t D, int32_t B_max, double r_max,
   }
   ALLOC(head, (size_t)(1 + c->label_windows) * kp * 4);
   ALLOC(E, Bp * kp * es);
-  ALLOC(rowpart, (kp / kPadK) * 2 * Bp * 4);
-  ALLOC(rowmaxpart, (kp / kPadK) * 2 * Bp * 4);
+  ALLOC(rowpart, (kp / 64) * Bp * 4);
+  ALLOC(rowmaxpart, (kp / 64) * Bp * 4);
   ALLOC(rowmax, Bp * 4);
   ALLOC(rowref, Bp * 4);
   ALLOC(clabel, Bp * 4);

@@ -12,7 +12,8 @@ namespace pfc {
 // Padded problem geometry.  Every scratch operand of the three GEMMs is padded with zeros to a
 // whole number of tiles, so the GEMM main loops need no bounds checks.
 // ---------------------------------------------------------------------------------------------
-constexpr int kPadB = 256;   // batch rows are padded to a multiple of this
+constexpr int kPadB = 256;   // batch rows are padded to at most a multiple of this
+constexpr int kPadD = 128;   // row length of the GEMM operands
 constexpr int kPadK = 256;   // sampled rows are padded to a multiple of this
 constexpr int kMaxSplits = 32;    // slices of S in the dfeatures product
 constexpr int kPartSlices = 64;   // slices the buffer of partial sums has room for: those of dfeatures

@@ -67,11 +67,12 @@ constexpr float kEpsSin2 = 1e-12f;
 //
 // Row length: the caller's arrays (X, W, v, dX, dWn) have rows of D floats, D a multiple of 64.
 // The library's own GEMM operands (Xn, Xs, Wn and the dfeatures partial sums) have rows of
-// Dp = 256 * NC >= D elements, the columns from D on being zero, so that the GEMMs only ever
-// see whole 256-column tiles; kernels that touch the caller's rows skip the columns from D on.
+// Dp >= D elements, D rounded up to 128, the columns from D on being zero, so that the GEMMs only
+// ever see whole tiles; a wavefront walks a row in NC chunks of 256 columns, and kernels that touch
+// the caller's rows skip the columns from D on.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NC>
-__global__ void normalize_x_kernel(const float* __restrict__ X, int B, int Bp, int D,
+__global__ void normalize_x_kernel(const float* __restrict__ X, int B, int Bp, int D, int Dp,
                                    const int32_t* __restrict__ yl, int64_t k, T* __restrict__ Xn,
                                    float* __restrict__ rnormX, float* __restrict__ clabel,
                                    int32_t* __restrict__ err_flag) {
@@ -79,7 +80,6 @@ __global__ void normalize_x_kernel(const float* __restrict__ X, int B, int Bp, i
   const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (i >= Bp) return;
   constexpr int nchunk = NC;   // float4 chunks per lane
-  constexpr int Dp = 256 * NC;
   float4 v[NC];
   float ss = 0.f;
 #pragma unroll
@@ -93,6 +93,7 @@ __global__ void normalize_x_kernel(const float* __restrict__ X, int B, int Bp, i
   const float rn = (i < B) ? 1.f / fmaxf(sqrtf(ss), kEpsNorm) : 0.f;
 #pragma unroll
   for (int c = 0; c < nchunk; ++c) {
+    if (c * 256 + lane * 4 >= Dp) continue;
     T* dst = Xn + (int64_t)i * Dp + c * 256 + lane * 4;   // rn == 0 for padded rows
     dst[0] = from_float<T>(v[c].x * rn);
     dst[1] = from_float<T>(v[c].y * rn);
@@ -117,11 +118,11 @@ __global__ void normalize_x_kernel(const float* __restrict__ X, int B, int Bp, i
 template <typename T, int NC>
 __global__ void gather_normalize_w_kernel(const float* __restrict__ W, int64_t N,
                                           const int32_t* __restrict__ idx, int64_t k, int64_t kp,
-                                          int D, T* __restrict__ Wn, float* __restrict__ rnormW,
+                                          int D, int Dp, T* __restrict__ Wn,
+                                          float* __restrict__ rnormW,
                                           int32_t* __restrict__ head, int nwin,
                                           int32_t* __restrict__ err_flag) {
   constexpr int NB = 4;
-  constexpr int Dp = 256 * NC;
   const int lane = threadIdx.x & 63;
   const int64_t jb = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * NB;
   if (jb >= kp) return;
@@ -172,6 +173,7 @@ __global__ void gather_normalize_w_kernel(const float* __restrict__ W, int64_t N
     if (lane < nwin) head[(int64_t)(1 + lane) * kp + j] = 0x7fffffff;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
+      if (c * 256 + lane * 4 >= Dp) continue;
       T o[4];
       if (ok[u]) {
         o[0] = from_float<T>(v[u][c].x * rn);
@@ -223,21 +225,28 @@ __device__ __forceinline__ float label_logit(const LossParams& lp, float c) {
   return lp.s * (c * lp.cos_m - sqrtf(fmaxf(1.f - c * c, 0.f)) * lp.sin_m);
 }
 
+// The row sum of exp(z) enters the gradient through p - 1, which for a confident sample is nothing
+// but its rounding: its additions therefore keep one order whether a tile has 128 classes or 64.
+// A wavefront of a 128-tile chains the 32 values a lane holds of 64 classes; a 64-tile, whose wavefronts
+// hold 32 classes each, chains the two of them, and row_combine adds the tiles in pairs.
+template <class Cfg>
+constexpr bool logits_chained() { return Cfg::BM == 64; }
+
 template <class Cfg, bool GUARDED, bool EXTRAS>
 __device__ __forceinline__ void logits_epilogue_columns(
     const f32x16 (&acc)[Cfg::TM][Cfg::TN], int64_t j0, int i0, int B, int klim, int64_t kp,
     const int (&ylane)[Cfg::TN], const LossParams& lp, char* smem, int SX,
     typename Cfg::elem* __restrict__ E, float* __restrict__ clabel, float (&colsum)[Cfg::TN],
-    float (&colmax)[Cfg::TN]) {
+    float (&collab)[Cfg::TN], float (&colmax)[Cfg::TN]) {
   using T = typename Cfg::elem;
-  constexpr bool kStage = (sizeof(T) == 2);
+  constexpr bool kStage = (sizeof(T) == 2), kChain = logits_chained<Cfg>();
 #pragma unroll
   for (int bn = 0; bn < Cfg::TN; ++bn) {
     const int il = acc_col<Cfg>(bn);
     const int i = i0 + il;
     const bool vi = i < B;
     const int yloc = ylane[bn];
-    float sum = 0.f, clab = 0.f, cmax = -2.f;
+    float sum = kChain ? colsum[bn] : 0.f, clab = 0.f, cmax = -2.f;
     float ref = 0.f;
     if constexpr (EXTRAS) ref = lp.rowref ? lp.rowref[i] : 0.f;   // i < Bp: padded entries are 0
     const float ref2 = ref * 1.44269504088896340736f;
@@ -283,10 +292,12 @@ __device__ __forceinline__ void logits_epilogue_columns(
     if constexpr (GUARDED) {
       if (yloc >= 0) {   // this lane holds sample i's label entry: it was left out of `sum`
         clabel[i] = clab;
-        sum += __expf(label_logit(lp, clab) - ref);
+        const float el = __expf(label_logit(lp, clab) - ref);
+        if constexpr (kChain) collab[bn] = el;
+        else sum += el;
       }
     }
-    sum += __shfl_xor(sum, 32, 64);
+    if constexpr (!kChain) sum += __shfl_xor(sum, 32, 64);
     colsum[bn] = sum;
     if constexpr (EXTRAS) colmax[bn] = fmaxf(cmax, __shfl_xor(cmax, 32, 64));
   }
@@ -295,7 +306,7 @@ __device__ __forceinline__ void logits_epilogue_columns(
 template <class Cfg, bool EXTRAS>
 __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
     const typename Cfg::elem* __restrict__ Wn, const typename Cfg::elem* __restrict__ Xn, int D,
-    int64_t k, int B, int Bp, int64_t kp, const int32_t* __restrict__ yl, LossParams lp,
+    int Dp, int64_t k, int B, int Bp, int64_t kp, const int32_t* __restrict__ yl, LossParams lp,
     typename Cfg::elem* __restrict__ E, float* __restrict__ rowpart,
     float* __restrict__ rowmaxpart, float* __restrict__ clabel, int tiles_j, int tiles_i,
     int ahead) {
@@ -309,7 +320,8 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
   PFC_PHASE(1, 0);
-  gemm_tile<Cfg>(Wn + j0 * D, D, Xn + (int64_t)i0 * D, D, D / Cfg::BK, smem, acc);
+  // the reduction ends with column D (a multiple of every slab): the rest of the rows is zero
+  gemm_tile<Cfg>(Wn + j0 * Dp, Dp, Xn + (int64_t)i0 * Dp, Dp, D / Cfg::BK, smem, acc);
   PFC_PHASE(1, 1);
   // Pull the Wn block of the class tile that the workgroups `ahead` ids later will multiply (same
   // XCD, about one round later) into this XCD's L2: the tiles_i workgroups of a class tile touch
@@ -321,9 +333,9 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
     const int nb = (int)blockIdx.x + ahead;
     if (nb < (int)gridDim.x && (int)(threadIdx.x >> 1) < Cfg::BM &&
         xcd_tile(nb, tiles_i, tiles_j, ntj, nti)) {
-      const int row_bytes = D * (int)sizeof(T);
+      const int row_bytes = Dp * (int)sizeof(T);
       const int off = ((nti * 256) % row_bytes) + (threadIdx.x & 1) * 128;
-      const char* p = reinterpret_cast<const char*>(Wn + (int64_t)ntj * Cfg::BM * D) +
+      const char* p = reinterpret_cast<const char*>(Wn + (int64_t)ntj * Cfg::BM * Dp) +
                       (int64_t)(threadIdx.x >> 1) * row_bytes + off;
       touched = *reinterpret_cast<const uint32_t*>(p);
     }
@@ -334,6 +346,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   constexpr int SX = Cfg::BM * 2 + 8;                // staging row (one sample) stride in bytes
   constexpr int RED_OFF = Cfg::BN * SX;              // cross-wave reduction scratch behind it
   static_assert(RED_OFF + 2 * Cfg::WM * Cfg::BN * 4 <= Cfg::LDS_BYTES, "epilogue LDS");
+  static_assert(!logits_chained<Cfg>() || 2 * Cfg::BN * 2 <= 2 * Cfg::WM * Cfg::BN, "chain LDS");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t krem = k - j0;
   const int klim = krem < (int64_t)Cfg::BM ? (int)krem : Cfg::BM;   // valid classes in this tile
@@ -357,19 +370,55 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   }
   const bool guarded = __any(any_label) || klim < Cfg::BM || i0 + Cfg::BN > B;   // wave-uniform
 
-  float colsum[Cfg::TN], colmax[Cfg::TN];
+  float* red = reinterpret_cast<float*>(smem + RED_OFF);   // [WM][BN] sums, then [WM][BN] maxima
+  float colsum[Cfg::TN], collab[Cfg::TN], colmax[Cfg::TN];
 #pragma unroll
   for (int bn = 0; bn < Cfg::TN; ++bn) colmax[bn] = -2.f;
-  if (guarded)
-    logits_epilogue_columns<Cfg, true, EXTRAS>(acc, j0, i0, B, klim, kp, ylane, lp, smem, SX, E,
-                                               clabel, colsum, colmax);
-  else
-    logits_epilogue_columns<Cfg, false, EXTRAS>(acc, j0, i0, B, klim, kp, ylane, lp, smem, SX, E,
-                                                clabel, colsum, colmax);
+  auto epilogue = [&]() {
+    if (guarded)
+      logits_epilogue_columns<Cfg, true, EXTRAS>(acc, j0, i0, B, klim, kp, ylane, lp, smem, SX, E,
+                                                 clabel, colsum, collab, colmax);
+    else
+      logits_epilogue_columns<Cfg, false, EXTRAS>(acc, j0, i0, B, klim, kp, ylane, lp, smem, SX, E,
+                                                  clabel, colsum, collab, colmax);
+  };
+  if constexpr (logits_chained<Cfg>()) {
+    // the second wavefront row goes on from the sums of the first: one chain over the tile's 64 rows
+    static_assert(Cfg::WM == 2 && Cfg::TM == 1, "a chain of two blocks");
+    const int o = (wave % Cfg::WN) * Cfg::TN * 64 + lane;
+#pragma unroll
+    for (int bn = 0; bn < Cfg::TN; ++bn) colsum[bn] = collab[bn] = 0.f;
+    if (wave / Cfg::WN == 0) {
+      epilogue();
+#pragma unroll
+      for (int bn = 0; bn < Cfg::TN; ++bn) {
+        red[o + bn * 64] = colsum[bn];
+        red[2 * Cfg::BN + o + bn * 64] = collab[bn];
+        colsum[bn] = 0.f;
+      }
+    }
+    __syncthreads();
+    if (wave / Cfg::WN == 1) {
+      float before[Cfg::TN];
+#pragma unroll
+      for (int bn = 0; bn < Cfg::TN; ++bn) {
+        colsum[bn] = red[o + bn * 64];
+        before[bn] = red[2 * Cfg::BN + o + bn * 64];
+      }
+      epilogue();
+#pragma unroll
+      for (int bn = 0; bn < Cfg::TN; ++bn) {
+        colsum[bn] += collab[bn] + before[bn];   // at most one of the two is not zero
+        colsum[bn] += __shfl_xor(colsum[bn], 32, 64);
+      }
+    }
+    __syncthreads();
+  } else {
+    epilogue();
+  }
 
   PFC_PHASE(1, 2);
   // cross-wave reduction over the WM wavefronts that share a column (fixed order)
-  float* red = reinterpret_cast<float*>(smem + RED_OFF);   // [WM][BN] sums, then [WM][BN] maxima
   if (lane < 32) {
 #pragma unroll
     for (int bn = 0; bn < Cfg::TN; ++bn) {
@@ -417,7 +466,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
 template <class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS) void gemm_rowmax_kernel(
     const typename Cfg::elem* __restrict__ Wn, const typename Cfg::elem* __restrict__ Xn, int D,
-    int64_t k, int B, const int32_t* __restrict__ yl, LossParams lp,
+    int Dp, int64_t k, int B, const int32_t* __restrict__ yl, LossParams lp,
     float* __restrict__ rowmaxpart, int tiles_j, int tiles_i) {
   extern __shared__ __align__(16) char smem[];
   int tj, ti;
@@ -426,7 +475,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_rowmax_kernel(
   const int i0 = ti * Cfg::BN;
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
-  gemm_tile<Cfg>(Wn + j0 * D, D, Xn + (int64_t)i0 * D, D, D / Cfg::BK, smem, acc);
+  gemm_tile<Cfg>(Wn + j0 * Dp, Dp, Xn + (int64_t)i0 * Dp, Dp, D / Cfg::BK, smem, acc);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t krem = k - j0;
   const int klim = krem < (int64_t)Cfg::BM ? (int)krem : Cfg::BM;
@@ -481,8 +530,9 @@ __global__ void row_ref_kernel(const float* __restrict__ rowmaxpart, int tiles_j
 // row of Xs = (s/(B l_i)) * x_i/|x_i| that feeds the dweight GEMM (zero for padded rows).
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NC>
-__global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_j, int B, int Bp,
-                                   int D, const float* __restrict__ X,
+__global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_j, int pairs, int B,
+                                   int Bp,
+                                   int D, int Dp, const float* __restrict__ X,
                                    const float* __restrict__ rnormX,
                                    const float* __restrict__ clabel, LossParams lp,
                                    const float* __restrict__ rowmaxpart,
@@ -498,7 +548,14 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
   float scale = 0.f;
   if (i < B) {
     float l = 0.f;
-    for (int t = lane; t < tiles_j; t += 64) l += rowpart[(int64_t)i * tiles_j + t];
+    if (pairs) {   // 64-tiles (their number is even: classes are padded to 256)
+      for (int t = lane; t < tiles_j / 2; t += 64) {
+        const float2 v = *reinterpret_cast<const float2*>(rowpart + (int64_t)i * tiles_j + 2 * t);
+        l += v.x + v.y;
+      }
+    } else {
+      for (int t = lane; t < tiles_j; t += 64) l += rowpart[(int64_t)i * tiles_j + t];
+    }
     l = wave_sum(l);
     scale = (lp.s / (float)B) / l;   // B * l could leave the fp32 range, s/B never does
     float mx = -2.f;
@@ -541,6 +598,7 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     const int d = c * 256 + lane * 4;
+    if (d >= Dp) continue;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < B && d < D) v = *reinterpret_cast<const float4*>(X + (int64_t)i * D + d);
     T o[4] = {from_float<T>(v.x * f), from_float<T>(v.y * f), from_float<T>(v.z * f),
@@ -548,11 +606,11 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
     if constexpr (sizeof(T) == 2) {
       uint2 pk;
       __builtin_memcpy(&pk, o, 8);
-      *reinterpret_cast<uint2*>(Xs + (int64_t)i * (256 * NC) + d) = pk;
+      *reinterpret_cast<uint2*>(Xs + (int64_t)i * Dp + d) = pk;
     } else {
       uint4 pk;
       __builtin_memcpy(&pk, o, 16);
-      *reinterpret_cast<uint4*>(Xs + (int64_t)i * (256 * NC) + d) = pk;
+      *reinterpret_cast<uint4*>(Xs + (int64_t)i * Dp + d) = pk;
     }
   }
   // fused step: keep the label's row of W for dfeatures_final, which runs after the update
@@ -1017,7 +1075,7 @@ __global__ __launch_bounds__(CfgB::THREADS) void gemm_backward_update_kernel(
 //   dx = (g - <g, xn_i> xn_i) / |x_i|
 template <int NC>
 __global__ void dfeatures_final_kernel(const float* __restrict__ part, int splits, int B, int Bp,
-                                       int D, const float* __restrict__ X,
+                                       int D, int Dp, const float* __restrict__ X,
                                        const float* __restrict__ W, int64_t N,
                                        const int32_t* __restrict__ idx,
                                        const int32_t* __restrict__ yl, int64_t k,
@@ -1058,7 +1116,6 @@ __global__ void dfeatures_final_kernel(const float* __restrict__ part, int split
   const int i = blockIdx.x;
   const int wave = threadIdx.x >> 6;
   constexpr int nchunk = NC;
-  constexpr int Dp = 256 * NC;   // row length of the partial sums
   __shared__ float4 s_part[3][NC][64];
   float4 sum[NC];
 #pragma unroll
@@ -1066,6 +1123,7 @@ __global__ void dfeatures_final_kernel(const float* __restrict__ part, int split
   for (int sp = wave; sp < splits; sp += 4) {
 #pragma unroll
     for (int c = 0; c < nchunk; ++c) {
+      if (c * 256 + lane * 4 >= D) continue;   // columns from D on are zero
       const float4 t = *reinterpret_cast<const float4*>(part + ((int64_t)sp * Bp + i) * Dp +
                                                         c * 256 + lane * 4);
       sum[c].x += t.x; sum[c].y += t.y; sum[c].z += t.z; sum[c].w += t.w;
@@ -1135,9 +1193,8 @@ __global__ void dfeatures_final_kernel(const float* __restrict__ part, int split
 // ---------------------------------------------------------------------------------------------
 // Number of batch slices of the dweight GEMM (1: none): slices only when the tiles alone leave
 // most CUs idle, limited by the room in the split buffer and by a minimum slice length.
-template <class CfgW>
-int dweight_slices(const pfc_ctx* c, int tiles, int Bp, int64_t kp) {
-  const int slabs_total = Bp / CfgW::BK;
+int dweight_slices(const pfc_ctx* c, int tiles, int Bp, int64_t kp, int bk) {
+  const int slabs_total = Bp / bk;
   int want = c->num_cu / tiles;
   const int64_t room = (int64_t)(kPartSlices - kMaxSplits) * Bp / kp;
   if (want > room) want = (int)room;
@@ -1146,31 +1203,103 @@ int dweight_slices(const pfc_ctx* c, int tiles, int Bp, int64_t kp) {
   return want < 1 ? 1 : want;
 }
 
+// Size of the GEMM tiles, one for the logits and one for the backward launch of a call.  256 x 256
+// moves the least data per flop and fills a compute unit with one workgroup, 128 x 128 puts two on
+// it, 64 x 64 three.  Measured on 256 compute units over batches of 48 .. 16,384 samples and 320 ..
+// 2 million classes (us for 256 / 128 / 64, D = 512 unless stated):
+//   bf16 logits: a round of 256-tiles costs the same however full it is, so they win only where the
+//     last round is nearly full (1024 x 205,991: 336 / 347 / 507; 768 x 20,599 x D 1024, 0.95 of a
+//     round: 41 / 45 / 64; 1024 x 36,024, 2.2 rounds: 71 / 58 / 83) and the reduction is long
+//     (8192 x 6,000 x D 256: 71 / 65 / 102); 64-tiles only for a handful of 128-tiles (512 x 4,000:
+//     24 / 9.8 / 8.7; 512 x 9,344: 24 / 14.7 / 16.0).
+//   bf16 backward: 256-tiles unless they leave compute units idle (512 x 4,000: 22 / 15 / 17;
+//     512 x 16,000: 29 / 30 / 45; 1024 x 205,991: 482 / 612 / 996), the batch would be padded much
+//     more (128 x 200,000: 210 / 179 / 260) or the reduction is short and the tiles few
+//     (256 x 36,000: 42 / 39 / 57; 256 x 200,000: 221 / 260 / 368); 64-tiles for the smallest
+//     problems (128 x 1,000: 15 / 7.3 / 5.8).
+//   fp32: the matrix cores are the bound at any of the sizes, so what counts is how evenly the
+//     compute units are loaded: 64-tiles where a few 128-tiles per compute unit do not come out
+//     even (logits 512 x 9,344: 135 / 77 / 57; 128 x 1,000: 129 / 37 / 15).  From one 256-tile per
+//     compute unit on the sizes are close (2048 x 60,000: 1144 / 1127 / 1207; 512 x 60,000: 299 /
+//     315 / 330) and the logits keep 256 and its order of the row sums.
+enum TileSize { TILES_64 = 64, TILES_128 = 128, TILES_256 = 256 };
+
+inline bool even_rounds(int64_t tiles, int64_t cu) {   // at most 15 % of the rounds' room is idle
+  return tiles > 4 * cu || (tiles + cu - 1) / cu * cu * 100 <= tiles * 115;
+}
+
+template <typename T>
+TileSize logits_tiles(const pfc_ctx* c, int B, int64_t kp, int D) {
+  const int64_t cu = c->num_cu, mid = kp / 128 * ((B + 127) / 128);
+  const int64_t big = kp / 256 * ((B + 255) / 256), rounds = (big + cu - 1) / cu;
+  if (sizeof(T) == 4) return big >= cu ? TILES_256 : even_rounds(mid, cu) ? TILES_128 : TILES_64;
+  if (D > 256 && rounds * cu * 4 * 100 <= mid * 109) return TILES_256;
+  return 2 * mid > cu ? TILES_128 : TILES_64;
+}
+
+template <typename T>
+TileSize backward_tiles(const pfc_ctx* c, int B, int64_t kp, int D) {
+  const int Bp = (int)round_up(B, 128), Bp256 = (int)round_up(B, 256);
+  const int Dp = (int)round_up(D, kPadD), Dp256 = (int)round_up(D, 256);
+  const int64_t cu = c->num_cu, mid = kp / 128 * (Dp / 128), big = kp / 256 * (Dp256 / 256);
+  if (sizeof(T) == 4)
+    return even_rounds(mid * dweight_slices(c, (int)mid, Bp, kp, 32), cu) ? TILES_128 : TILES_64;
+  // (columns: 640 -> 768 and 896 -> 1024 cost less than the smaller tile, 384 -> 512 more)
+  if (Dp256 * 100 <= Dp * 125 && Bp256 * 100 <= Bp * 115 &&
+      big * dweight_slices(c, (int)big, Bp256, kp, 64) * 2 >= cu && (B >= 512 || big * 2 >= cu * 3))
+    return TILES_256;
+  return B > 128 || 2 * mid > cu ? TILES_128 : TILES_64;
+}
+
+// One size of GEMM tiles: the tile of every product (BM x BN of its output, WM x WN wavefronts).
+template <typename T, int BM, int BN, int WM, int WN>
+struct Tiles {
+  using F = TileCfg<T, BM, BN, WM, WN, false, false>;   // logits: classes x samples
+  using W = TileCfg<T, BM, BN, WM, WN, true, true>;     // dweight: classes x columns
+  using X = TileCfg<T, BM, BN, WM, WN, false, true>;    // dfeatures: samples x columns
+  static constexpr int BACK_LDS = X::LDS_BYTES > W::LDS_BYTES ? X::LDS_BYTES : W::LDS_BYTES;
+  static constexpr int PER_CU = 160 * 1024 / BACK_LDS;   // workgroups a compute unit holds
+};
+
+template <class S>
+int set_lds_limits_logits(S) {
+  using F = typename S::F;
+  const void* f[] = {(const void*)gemm_logits_kernel<F, false>, (const void*)gemm_logits_kernel<F, true>,
+                     (const void*)gemm_rowmax_kernel<F>};
+  for (const void* p : f)
+    PFC_HIP(hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, F::LDS_BYTES));
+  return PFC_OK;
+}
+template <class S>
+int set_lds_limits_backward(S) {
+  const void* b[] = {(const void*)(gemm_backward_kernel<typename S::X, typename S::W, false>),
+                     (const void*)(gemm_backward_kernel<typename S::X, typename S::W, true>)};
+  for (const void* p : b)
+    PFC_HIP(hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, S::BACK_LDS));
+  return PFC_OK;
+}
+
 template <typename T, int NC>
 int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t k,
         const int32_t* yl, int32_t B, const LossParams& lp, float* loss_out, float* dX_out,
         float* dW_out, float* stats_out, const UpdateArgs* upd) {
-  using CfgF = TileCfg<T, 256, 256, 2, 4, false, false>;   // logits: 256 classes x 256 samples
-  using CfgW = TileCfg<T, 256, 256, 2, 4, true, true>;     // dweight: 256 classes x 256 of D
   // fused dweight + update: 128 classes x all 512 columns, half-size slabs so that the wide
   // operand fits; this one-kernel form exists for D == 512 only
   using CfgU = TileCfg<T, 128, 512, 2, 4, true, true, 64>;
   using CfgUS = TileCfg<T, 64, 512, 1, 8, true, true, 128>;   // its tiles for the last round
-  using CfgX = TileCfg<T, 256, 256, 2, 4, false, true>;    // dfeatures: 256 samples x 256 of D
-  // small problems (fewer big tiles than compute units): 128 x 128 tiles, four times
-  // as many workgroups, two of them resident per compute unit (74 KB of LDS each)
-  using CfgFs = TileCfg<T, 128, 128, 2, 4, false, false>;
-  using CfgWs = TileCfg<T, 128, 128, 2, 4, true, true>;
-  using CfgXs = TileCfg<T, 128, 128, 2, 4, false, true>;
+  using Big = Tiles<T, 256, 256, 2, 4>;
+  using Mid = Tiles<T, 128, 128, 2, 4>;
+  using BigBack = std::conditional_t<sizeof(T) == 2, Big, Mid>;   // fp32: backward_tiles never asks for it
+  using Small = Tiles<T, 64, 64, 2, 2>;
   constexpr int kFusedLds =
-      std::max({FusedUpdateLds<CfgU>::LDS, FusedUpdateLds<CfgUS>::LDS, CfgX::LDS_BYTES});
-  constexpr int kBackLds = std::max(CfgX::LDS_BYTES, CfgW::LDS_BYTES);
-  constexpr int kBackLdsS = std::max(CfgXs::LDS_BYTES, CfgWs::LDS_BYTES);
+      std::max({FusedUpdateLds<CfgU>::LDS, FusedUpdateLds<CfgUS>::LDS, Big::X::LDS_BYTES});
   static_assert(kFusedLds <= 160 * 1024, "LDS of one compute unit");
   const int D = c->D;
-  constexpr int Dp = 256 * NC;   // row length of the library's own GEMM operands
-  const int Bp = (int)round_up(B, kPadB);
   const int64_t kp = round_up(k, kPadK);
+  const TileSize size_f = logits_tiles<T>(c, B, kp, D), size_b = backward_tiles<T>(c, B, kp, D);
+  const int Bp = (int)round_up(B, std::max<int>(size_f, size_b));
+  // row length of the library's own GEMM operands
+  const int Dp = (int)round_up(D, size_b == TILES_256 ? 256 : kPadD);
   T* Xn = (T*)c->Xn; T* Xs = (T*)c->Xs; T* Wn = (T*)c->Wn; T* E = (T*)c->E;
   // windows of the label part (0: the batch fits one window, or the context has no room for them)
   const int nwin = (B > kLabelWindow && c->label_windows) ? (B + kLabelWindow - 1) / kLabelWindow : 0;
@@ -1181,45 +1310,34 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
 
   auto norm_kernel = normalize_x_kernel<T, NC>;
   PFC_LAUNCH(c, KID_NORM_X, norm_kernel, dim3((Bp + 3) / 4), dim3(256), 0, X, B, Bp, D,
-             yl, k, Xn, c->rnormX, c->clabel, c->err_flag);
+             Dp, yl, k, Xn, c->rnormX, c->clabel, c->err_flag);
 
   auto gather_kernel = gather_normalize_w_kernel<T, NC>;
   PFC_LAUNCH(c, KID_GATHER_W, gather_kernel, dim3((unsigned)((kp / 4 + 3) / 4)), dim3(256), 0, W,
-             c->N, idx, k, kp, D, Wn, c->rnormW, c->head, nwin, c->err_flag);
+             c->N, idx, k, kp, D, Dp, Wn, c->rnormW, c->head, nwin, c->err_flag);
 
   // raise the dynamic LDS limit of this context's kernels once (a context has one precision and
   // one D, hence one instantiation of run)
   if (!c->lds_attr_set) {
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_logits_kernel<CfgF, false>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgF::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_logits_kernel<CfgF, true>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgF::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_rowmax_kernel<CfgF>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgF::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_logits_kernel<CfgFs, false>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgFs::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_logits_kernel<CfgFs, true>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgFs::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)gemm_rowmax_kernel<CfgFs>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, CfgFs::LDS_BYTES));
-    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_kernel<CfgX, CfgW, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kBackLds));
-    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_kernel<CfgX, CfgW, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kBackLds));
-    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_kernel<CfgXs, CfgWs, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kBackLdsS));
-    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_kernel<CfgXs, CfgWs, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kBackLdsS));
-    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_update_kernel<CfgX, CfgU, CfgUS>),
+    int rc = set_lds_limits_logits(Big{});
+    if (rc == PFC_OK) rc = set_lds_limits_logits(Mid{});
+    if (rc == PFC_OK) rc = set_lds_limits_logits(Small{});
+    if (rc == PFC_OK) rc = set_lds_limits_backward(BigBack{});
+    if (rc == PFC_OK) rc = set_lds_limits_backward(Mid{});
+    if (rc == PFC_OK) rc = set_lds_limits_backward(Small{});
+    if (rc != PFC_OK) return rc;
+    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_update_kernel<typename Big::X, CfgU, CfgUS>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kFusedLds));
+    PFC_HIP(hipFuncSetAttribute((const void*)(gemm_backward_update_kernel<typename Mid::X, CfgU, CfgUS>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFusedLds));
     c->lds_attr_set = 1;
   }
-  auto launch_logits = [&](auto cfg) -> int {
-    using Cfg = decltype(cfg);
+  auto launch_logits = [&](auto tiles) -> int {
+    using Cfg = typename decltype(tiles)::F;
     const int tiles_j = (int)(kp / Cfg::BM), tiles_i = Bp / Cfg::BN;
     if (lp.rowref) {   // scale above 64: the largest logit of every sample first
       PFC_LAUNCH(c, KID_GEMM_ROWMAX, gemm_rowmax_kernel<Cfg>, dim3(xcd_grid(tiles_i, tiles_j)),
-                 dim3(Cfg::THREADS), Cfg::LDS_BYTES, Wn, Xn, Dp, k, B, yl, lp, c->rowmaxpart,
+                 dim3(Cfg::THREADS), Cfg::LDS_BYTES, Wn, Xn, D, Dp, k, B, yl, lp, c->rowmaxpart,
                  tiles_j, tiles_i);
       PFC_LAUNCH(c, KID_ROW_REF, row_ref_kernel, dim3((Bp + 3) / 4), dim3(256), 0, c->rowmaxpart,
                  tiles_j, B, Bp, c->rowref);
@@ -1228,18 +1346,19 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     // stays lean
     auto logits_kernel = lp.extras ? gemm_logits_kernel<Cfg, true> : gemm_logits_kernel<Cfg, false>;
     PFC_LAUNCH(c, KID_GEMM_LOGITS, logits_kernel, dim3(xcd_grid(tiles_i, tiles_j)),
-               dim3(Cfg::THREADS), Cfg::LDS_BYTES, Wn, Xn, Dp, k, B, Bp, kp, yl, lp, E, c->rowpart,
+               dim3(Cfg::THREADS), Cfg::LDS_BYTES, Wn, Xn, D, Dp, k, B, Bp, kp, yl, lp, E, c->rowpart,
                c->rowmaxpart, c->clabel, tiles_j, tiles_i, c->num_cu / 8 * 8);
     auto combine_kernel = row_combine_kernel<T, NC>;
     PFC_LAUNCH(c, KID_ROW_COMBINE, combine_kernel, dim3((Bp + 3) / 4), dim3(256), 0, c->rowpart,
-               tiles_j, B, Bp, D, X, c->rnormX, c->clabel, lp, c->rowmaxpart, c->rowscale,
+               tiles_j, logits_chained<Cfg>() ? 1 : 0, B, Bp, D, Dp, X, c->rnormX, c->clabel, lp, c->rowmaxpart, c->rowscale,
                c->dlabel, c->lossrow, c->rowmax, yl, k, kp, c->head, nwin, Xs, W, c->N, idx,
                one_kernel ? c->wlab : nullptr);
     return PFC_OK;
   };
   {
-    const bool small = (kp / CfgF::BM) * (Bp / CfgF::BN) < (int64_t)c->num_cu;
-    const int rc = small ? launch_logits(CfgFs{}) : launch_logits(CfgF{});
+    const int rc = size_f == TILES_256   ? launch_logits(Big{})
+                   : size_f == TILES_128 ? launch_logits(Mid{})
+                                         : launch_logits(Small{});
     if (rc != PFC_OK) return rc;
   }
   // label part of dWn: added to dW_out, or (compact) left in the side buffer for the fused kernel
@@ -1285,71 +1404,85 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   };
   auto launch_final = [&](const DxShape& dx, const float* wlab) -> int {
     PFC_LAUNCH(c, KID_DX_FINAL, dfeatures_final_kernel<NC>, dim3(B + 1), dim3(256), 0,
-               c->dXpart, dx.splits, B, Bp, D, X, W, c->N, idx, yl, k, c->rnormX, c->rnormW, wlab,
+               c->dXpart, dx.splits, B, Bp, D, Dp, X, W, c->N, idx, yl, k, c->rnormX, c->rnormW, wlab,
                c->rowscale, c->dlabel, dX_out, c->lossrow, loss_out, c->clabel, c->rowmax,
                stats_out);
     return PFC_OK;
   };
-  // both backward products in one launch; dW_out and the partial sums of dX are written
-  auto launch_backward_cfg = [&](auto cfgx, auto cfgw, int lds, int per_cu, DxShape& dx) -> int {
-    using CX = decltype(cfgx);
-    using CW = decltype(cfgw);
-    const int tiles_j = (int)(kp / CW::BM), tiles_d = Dp / CW::BN;
+  // slices of the batch in the dweight product, and the shape of the dfeatures product beside it
+  // (the same with and without the update, so that dX has the same bits)
+  auto backward_shape = [&](auto tiles, int& slabs_per, int& nsp) {
+    using CW = typename decltype(tiles)::W;
+    const int tiles_w = (int)(kp / CW::BM) * (Dp / CW::BN);
     const int slabs_total = Bp / CW::BK;
-    const int64_t slots = (int64_t)c->num_cu * per_cu;
-    int want = dweight_slices<CW>(c, tiles_j * tiles_d, Bp, kp);
-    int nsp = 1, slabs_per = slabs_total;
-    if (want >= 2) {
-      slabs_per = (slabs_total + want - 1) / want;
-      nsp = (slabs_total + slabs_per - 1) / slabs_per;
-    }
-    const int64_t wgs_w = (int64_t)tiles_j * tiles_d * nsp;
-    dx = dx_shape(cfgx, std::max(slots / 2, slots - wgs_w));
+    const int want = dweight_slices(c, tiles_w, Bp, kp, CW::BK);
+    slabs_per = (slabs_total + want - 1) / want;
+    nsp = (slabs_total + slabs_per - 1) / slabs_per;
+    const int64_t slots = (int64_t)c->num_cu * decltype(tiles)::PER_CU;
+    const int64_t wgs_w = (int64_t)tiles_w * nsp;
+    // fp32 tiles take long: dfeatures workgroups no longer than those, so that the end comes out even
+    // (fused, 1024 x 36,024 x 512: half of the GPU's room 1546 us a step, twice the room 1212)
+    const int64_t wgs = sizeof(T) == 4 && wgs_w > 2 * slots ? 2 * slots : std::max(slots / 2, slots - wgs_w);
+    return dx_shape(typename decltype(tiles)::X{}, wgs);
+  };
+  // both backward products in one launch; dW_out and the partial sums of dX are written
+  auto launch_backward = [&](auto tiles, DxShape& dx) -> int {
+    using CX = typename decltype(tiles)::X;
+    using CW = typename decltype(tiles)::W;
+    constexpr int lds = decltype(tiles)::BACK_LDS;
+    const int tiles_j = (int)(kp / CW::BM), tiles_d = Dp / CW::BN;
+    int slabs_per, nsp;
+    dx = backward_shape(tiles, slabs_per, nsp);
     float* dst = nsp > 1 ? c->dXpart + (int64_t)dx.splits * Bp * Dp : dW_out;
     auto kernel = nsp > 1 ? gemm_backward_kernel<CX, CW, true> : gemm_backward_kernel<CX, CW, false>;
-    PFC_LAUNCH(c, KID_GEMM_BACKWARD, kernel, dim3((unsigned)(dx.wgs + wgs_w)), dim3(CX::THREADS), lds,
-               E, Wn, Xs, D, Dp, k, kp, Bp, dx, c->dXpart, dst, tiles_j, tiles_d, slabs_per, nsp);
+    PFC_LAUNCH(c, KID_GEMM_BACKWARD, kernel, dim3((unsigned)(dx.wgs + tiles_j * tiles_d * nsp)),
+               dim3(CX::THREADS), lds, E, Wn, Xs, D, Dp, k, kp, Bp, dx, c->dXpart, dst, tiles_j,
+               tiles_d, slabs_per, nsp);
     if (nsp > 1) {
       PFC_LAUNCH(c, KID_DW_REDUCE, dweight_reduce_kernel,
                  dim3((unsigned)((k * D / 4 + 255) / 256)), dim3(256), 0, dst, nsp, k, kp, D, Dp,
                  dW_out);
     }
-    return PFC_OK;
+    return launch_label(false);
   };
-  auto launch_backward = [&](DxShape& dx) -> int {
-    // small tiles only when the big ones, sliced over the batch as far as that goes, still leave
-    // more than half of the compute units idle (a long batch is better cut into slices of big
-    // tiles: half the LDS traffic per flop)
-    const int64_t tiles_big = (kp / CfgW::BM) * (Dp / CfgW::BN);
-    const bool small =
-        tiles_big * dweight_slices<CfgW>(c, (int)tiles_big, Bp, kp) * 2 < (int64_t)c->num_cu;
-    int rc = small ? launch_backward_cfg(CfgXs{}, CfgWs{}, kBackLdsS, 2, dx)
-                   : launch_backward_cfg(CfgX{}, CfgW{}, kBackLds, 1, dx);
-    return rc != PFC_OK ? rc : launch_label(false);
+  // tiles: those of the dfeatures product.  Its slices are the ones that gemm_backward would take
+  // (size_b), whatever the tiles: dX has the same bits in either call.
+  auto launch_backward_update = [&](auto tiles, DxShape& dx) -> int {
+    using CX = typename decltype(tiles)::X;
+    int slabs_per, nsp;
+    dx = size_b == TILES_256 ? backward_shape(BigBack{}, slabs_per, nsp)
+                             : backward_shape(Mid{}, slabs_per, nsp);
+    dx.tiles_i = Bp / CX::BM;
+    dx.tiles_d = Dp / CX::BN;
+    dx.wgs = (int)round_up(xcd_grid(dx.tiles_i * dx.tiles_d, dx.splits), 8);
+    const int tiles_big = (int)(kp / CfgU::BM);
+    const int n_big = tiles_big / c->num_cu * c->num_cu;          // whole rounds
+    const int n_small = (tiles_big - n_big) * (CfgU::BM / CfgUS::BM);
+    PFC_LAUNCH(c, KID_GEMM_BACKWARD_UPDATE, (gemm_backward_update_kernel<CX, CfgU, CfgUS>),
+               dim3((unsigned)(dx.wgs + n_big + n_small)), dim3(CfgU::THREADS), kFusedLds, E, Wn, Xs,
+               dx, c->dXpart, k, kp, Bp, idx, c->head, c->dlab, c->spare, upd->W, upd->v, c->N,
+               upd->lr, upd->mu, c->err_flag, n_big);
+    return PFC_OK;
   };
 
   DxShape dx;
   int rc;
   if (!one_kernel) {
-    rc = launch_backward(dx);
+    rc = size_b == TILES_256   ? launch_backward(BigBack{}, dx)
+         : size_b == TILES_128 ? launch_backward(Mid{}, dx)
+                               : launch_backward(Small{}, dx);
     if (rc == PFC_OK) rc = launch_final(dx, nullptr);
     // fused call: dWn went through memory (dW_out is the context's own buffer here)
     if (rc == PFC_OK && upd) rc = update_impl(c, upd->W, upd->v, idx, k, dW_out, upd->lr, upd->mu);
     return rc;
   }
   rc = launch_label(true);
-  if (rc != PFC_OK) return rc;
-  {
-    dx = dx_shape(CfgX{}, c->num_cu / 2);
-    const int tiles_big = (int)(kp / CfgU::BM);
-    const int n_big = tiles_big / c->num_cu * c->num_cu;          // whole rounds
-    const int n_small = (tiles_big - n_big) * (CfgU::BM / CfgUS::BM);
-    PFC_LAUNCH(c, KID_GEMM_BACKWARD_UPDATE, (gemm_backward_update_kernel<CfgX, CfgU, CfgUS>),
-               dim3((unsigned)(dx.wgs + n_big + n_small)), dim3(CfgU::THREADS), kFusedLds, E, Wn, Xs,
-               dx, c->dXpart, k, kp, Bp, idx, c->head, c->dlab, c->spare, upd->W, upd->v, c->N,
-               upd->lr, upd->mu, c->err_flag, n_big);
+  if (rc == PFC_OK) {
+    // (never 64-tiles: D == 512 and a 128-row tile per compute unit are many 128-tiles)
+    // One workgroup per compute unit whatever the dfeatures tile, so the big one where it fits
+    rc = Bp % 256 == 0 ? launch_backward_update(Big{}, dx) : launch_backward_update(Mid{}, dx);
   }
-  return launch_final(dx, c->wlab);
+  return rc == PFC_OK ? launch_final(dx, c->wlab) : rc;
 }
 
 }  // namespace

@@ -258,7 +258,7 @@ __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__
   // the loads of a slab are placed in front of the MFMAs of the first one or two groups (of all
   // groups before the barrier if two do not have an MFMA for each load)
   constexpr int SPAN = (NL <= 2 * MM ? (HEAD < 2 ? HEAD : 2) : HEAD) * MM;
-  static_assert(HEAD >= 1 && NL <= SPAN, "one load per MFMA slot at most");
+  static_assert(HEAD >= 1, "the last group is multiplied behind the barrier");
 
   // prologue: slabs 0 and 1 are requested back to back; slab 0 goes to stage 0
   typename SA::Regs a0 = {};
