@@ -27,7 +27,6 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 enum KernelId {
   KID_SAMPLE_SCAN = 0,
   KID_SAMPLE_WRITE,
-  KID_NORM_X,
   KID_GATHER_W,
   KID_GEMM_ROWMAX,
   KID_ROW_REF,
