@@ -19,7 +19,7 @@ static const char* const kKernelNames[KID_COUNT] = {
     "sample_scan", "sample_write", "gather_normalize_w", "gemm_rowmax",
     "row_ref", "gemm_logits",
     "row_combine", "gemm_backward", "dweight_reduce", "dweight_label", "dweight_label_combine",
-    "dfeatures_final", "update", "gemm_backward_update"};
+    "gradients_final", "update", "gemm_backward_update"};
 
 static int64_t ceil_rN(int64_t N, double r) { return (int64_t)ceil(r * (double)N); }
 

@@ -36,7 +36,7 @@ enum KernelId {
   KID_DW_REDUCE,
   KID_DW_LABEL,
   KID_DW_LABEL_SUM,
-  KID_DX_FINAL,
+  KID_GRAD_FINAL,
   KID_UPDATE,
   KID_GEMM_BACKWARD_UPDATE,
   KID_COUNT

@@ -9,10 +9,10 @@
 //                      Xs = (s/(B l_i)) xn_i
 //   gemm_backward      both backward products in one launch (MFMA): partial sums of E Wn over
 //                      slices of S, and dWn = E^T Xs (off-label part)
-//   dweight_label      adds the label-column term to the rows of positive classes (fp32)
-//   dfeatures_final    reduce slices, scale, label term, project through x -> x/|x|; mean loss
-// In the fused call dweight_label (into a side buffer) comes before gemm_backward_update, whose
-// dweight tiles end in the update of their rows.
+//   gradients_final    adds the label-column term to the dWn rows of positive classes (fp32); features:
+//                      reduce slices, scale, label term, project through x -> x/|x|; mean loss
+// In the fused call the label-column term (dweight_label, into a side buffer) comes before
+// gemm_backward_update, whose dweight tiles end in the update of their rows.
 //
 // Cosines lie in [-1,1]: up to s = 64, exp(s c) lies in [e^-64, e^64] and a row sum over at most
 // 2^31 classes stays below 3.4e38, so exp needs no running maximum and one fixed reference (zero)
@@ -621,7 +621,7 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
       *reinterpret_cast<uint4*>(Xs + (int64_t)i * Dp + d) = pk;
     }
   }
-  // fused step: keep the label's row of W for dfeatures_final, which runs after the update
+  // fused step: keep the label's row of W for gradients_final, which runs after the update
   if (wlab && i < B) {
     const int32_t y = yl[i];
     const int64_t row = (y >= 0 && (int64_t)y < k) ? idx[y] : -1;
@@ -787,16 +787,22 @@ __global__ void dweight_reduce_kernel(const float* __restrict__ part, int splits
 constexpr int kLabelThreads = 1024;
 static_assert(kLabelWindow == kLabelThreads, "a window is scanned in one pass of the workgroup");
 enum LabelMode { LABEL_ADD, LABEL_COMPACT, LABEL_WINDOW };
+struct LabelLds {
+  float4 part[kLabelThreads];
+  int list[kLabelThreads];
+  float coef[kLabelThreads];   // dlabel_p / |x_p| of the listed samples
+  int wcnt[kLabelThreads / 64];
+};
 template <LabelMode MODE>
-__global__ __launch_bounds__(kLabelThreads) void dweight_label_kernel(
-    const float* __restrict__ X, int B, int D, const int32_t* __restrict__ yl, int64_t k,
-    const int32_t* __restrict__ head, int64_t kp, const float* __restrict__ rnormX,
-    const float* __restrict__ dlabel, float* __restrict__ dW) {
-  __shared__ int s_list[kLabelThreads];
-  __shared__ float s_coef[kLabelThreads];   // dlabel_p / |x_p| of the listed samples
-  __shared__ int s_wcnt[kLabelThreads / 64];
-  __shared__ float4 s_part[kLabelThreads];
-  const int i = blockIdx.x, t = threadIdx.x;
+__device__ __forceinline__ void dweight_label_block(
+    int i, LabelLds& lds, const float* __restrict__ X, int B, int D,
+    const int32_t* __restrict__ yl, int64_t k, const int32_t* __restrict__ head, int64_t kp,
+    const float* __restrict__ rnormX, const float* __restrict__ dlabel, float* __restrict__ dW) {
+  int* s_list = lds.list;
+  float* s_coef = lds.coef;
+  int* s_wcnt = lds.wcnt;
+  float4* s_part = lds.part;
+  const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int32_t y = yl[i];
   if (y < 0 || (int64_t)y >= k) return;
@@ -830,10 +836,10 @@ __global__ __launch_bounds__(kLabelThreads) void dweight_label_kernel(
       s_coef[base + before] = dlabel[p] * rnormX[p];
     }
     __syncthreads();
-    // group g takes list entries whose global ordinal is congruent to g modulo G; eight row
+    // group g takes list entries whose global ordinal is congruent to g modulo G; six row
     // loads are in flight at a time, the additions stay in list order
     int e = (g - ordinal0 % G + G) % G;
-    constexpr int UN = 8;
+    constexpr int UN = 6;
     for (; e + (UN - 1) * G < total; e += UN * G) {
       float4 x[UN];
       float a[UN];
@@ -874,6 +880,15 @@ __global__ __launch_bounds__(kLabelThreads) void dweight_label_kernel(
       *dst = cur;
     }
   }
+}
+
+template <LabelMode MODE>
+__global__ __launch_bounds__(kLabelThreads) void dweight_label_kernel(
+    const float* __restrict__ X, int B, int D, const int32_t* __restrict__ yl, int64_t k,
+    const int32_t* __restrict__ head, int64_t kp, const float* __restrict__ rnormX,
+    const float* __restrict__ dlabel, float* __restrict__ dW) {
+  __shared__ LabelLds lds;
+  dweight_label_block<MODE>(blockIdx.x, lds, X, B, D, yl, k, head, kp, rnormX, dlabel, dW);
 }
 
 // dweight_label_combine (after dweight_label<LABEL_WINDOW>): block i, if sample i is the first of
@@ -1078,90 +1093,104 @@ __global__ __launch_bounds__(CfgB::THREADS) void gemm_backward_update_kernel(
                             Xs, k, kp, Bp, idx, head, lab, spare, W, V, N, lr, mu, err_flag);
 }
 
-// dfeatures_final: one wavefront per sample.
+// dfeatures_final: WPS wavefronts per sample.
 //   g  = (s/(B l_i)) * sum_slices part + dlabel_i * wn_{y_i}        (dL/d xn_i)
 //   dx = (g - <g, xn_i> xn_i) / |x_i|
-template <int NC>
-__global__ void dfeatures_final_kernel(const float* __restrict__ part, int splits, int B, int Bp,
-                                       int D, int Dp, const float* __restrict__ X,
-                                       const float* __restrict__ W, int64_t N,
-                                       const int32_t* __restrict__ idx,
-                                       const int32_t* __restrict__ yl, int64_t k,
-                                       const float* __restrict__ rnormX,
-                                       const float* __restrict__ rnormW,
-                                       const float* __restrict__ wlab,
-                                       const float* __restrict__ rowscale,
-                                       const float* __restrict__ dlabel, float* __restrict__ dX,
-                                       const float* __restrict__ lossrow,
-                                       float* __restrict__ loss_out,
-                                       const float* __restrict__ clabel,
-                                       const float* __restrict__ rowmax,
-                                       float* __restrict__ stats_out) {
-  const int lane = threadIdx.x & 63;
-  if (blockIdx.x == gridDim.x - 1) {
-    // the extra last block: mean loss (and, on request, mean label cosine = APCS and mean largest
-    // non-label cosine = AMNCS), each summed in a fixed order (strided partials, then a tree)
-    __shared__ float sm[256];
-    const int nq = stats_out ? 3 : 1;
-    for (int q = 0; q < nq; ++q) {
-      const float* src = q == 0 ? lossrow : q == 1 ? clabel : rowmax;
-      float v = 0.f;
-      for (int r = threadIdx.x; r < B; r += 256) v += src[r];
+template <int NC, int WPS>
+struct FinalLds {
+  float4 part[kLabelThreads / 64 / WPS][WPS - 1][NC][64];
+};
+struct FinalArgs {
+  const float* part;
+  int splits, B, Bp, D, Dp;
+  const float* X;
+  const float* W;
+  int64_t N;
+  const int32_t* idx;
+  const int32_t* yl;
+  int64_t k;
+  const float *rnormX, *rnormW, *wlab, *rowscale, *dlabel;
+  float* dX;
+  const float* lossrow;
+  float* loss_out;
+  const float *clabel, *rowmax;
+  float* stats_out;
+};
+
+// Mean loss (and, on request, mean label cosine = APCS and mean largest non-label cosine = AMNCS),
+// each summed in a fixed order (256 strided partials, then a tree).
+__device__ __forceinline__ void mean_loss_block(float* sm, const FinalArgs& a) {
+  const int nq = a.stats_out ? 3 : 1;
+  for (int q = 0; q < nq; ++q) {
+    const float* src = q == 0 ? a.lossrow : q == 1 ? a.clabel : a.rowmax;
+    float v = 0.f;
+    if (threadIdx.x < 256) {
+      for (int r = threadIdx.x; r < a.B; r += 256) v += src[r];
       sm[threadIdx.x] = v;
-      __syncthreads();
-      for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sm[threadIdx.x] += sm[threadIdx.x + o];
-        __syncthreads();
-      }
-      if (threadIdx.x == 0) (q == 0 ? loss_out : stats_out + (q - 1))[0] = sm[0] / (float)B;
+    }
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+      if ((int)threadIdx.x < o) sm[threadIdx.x] += sm[threadIdx.x + o];
       __syncthreads();
     }
-    return;
+    if (threadIdx.x == 0) (q == 0 ? a.loss_out : a.stats_out + (q - 1))[0] = sm[0] / (float)a.B;
+    __syncthreads();
   }
-  // One workgroup per sample.  The four wavefronts share the slices of S (wavefront w takes
-  // slices w, w+4, ...: several independent loads in flight each); their partial rows are added
-  // in wavefront order by wavefront 0, which then finishes the row: the same order on every run.
-  const int i = blockIdx.x;
-  const int wave = threadIdx.x >> 6;
+}
+
+template <int NC, int WPS>
+__device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WPS>& lds,
+                                                      const FinalArgs& a) {
+  constexpr int SPB = kLabelThreads / 64 / WPS;   // samples per workgroup
+  const int lane = threadIdx.x & 63;
+  const int grp = (threadIdx.x >> 6) / WPS, wave = (threadIdx.x >> 6) % WPS;
+  const int i = block * SPB + grp;
+  const int D = a.D;
+  // The wavefronts of a sample share the slices of S (wavefront w takes slices w, w + WPS, ...:
+  // several independent loads in flight each); their partial rows are added in wavefront order by
+  // wavefront 0, which then finishes the row: the same order on every run.
   constexpr int nchunk = NC;
-  __shared__ float4 s_part[3][NC][64];
   float4 sum[NC];
 #pragma unroll
   for (int c = 0; c < nchunk; ++c) sum[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int sp = wave; sp < splits; sp += 4) {
+  for (int sp = wave; i < a.B && sp < a.splits; sp += WPS) {
 #pragma unroll
     for (int c = 0; c < nchunk; ++c) {
       if (c * 256 + lane * 4 >= D) continue;   // columns from D on are zero
-      const float4 t = *reinterpret_cast<const float4*>(part + ((int64_t)sp * Bp + i) * Dp +
+      const float4 t = *reinterpret_cast<const float4*>(a.part + ((int64_t)sp * a.Bp + i) * a.Dp +
                                                         c * 256 + lane * 4);
       sum[c].x += t.x; sum[c].y += t.y; sum[c].z += t.z; sum[c].w += t.w;
     }
   }
   if (wave > 0) {
 #pragma unroll
-    for (int c = 0; c < nchunk; ++c) s_part[wave - 1][c][lane] = sum[c];
+    for (int c = 0; c < nchunk; ++c) lds.part[grp][wave - 1][c][lane] = sum[c];
   }
   __syncthreads();
-  if (wave > 0) return;
+  if (wave > 0 || i >= a.B) return;
 #pragma unroll
   for (int c = 0; c < nchunk; ++c) {
 #pragma unroll
-    for (int w = 0; w < 3; ++w) {
-      const float4 t = s_part[w][c][lane];
+    for (int w = 0; w < WPS - 1; ++w) {
+      if (w + 1 >= a.splits) break;   // those wavefronts had no slice
+      const float4 t = lds.part[grp][w][c][lane];
       sum[c].x += t.x; sum[c].y += t.y; sum[c].z += t.z; sum[c].w += t.w;
     }
   }
-  const float rs = rowscale[i], rnx = rnormX[i], dl = dlabel[i];
-  const int32_t y = yl[i];
+  const float* W = a.W;
+  const float* X = a.X;
+  float* dX = a.dX;
+  const float rs = a.rowscale[i], rnx = a.rnormX[i], dl = a.dlabel[i];
+  const int32_t y = a.yl[i];
   int64_t wrow = -1;
   float rnw = 0.f;
-  if (y >= 0 && (int64_t)y < k) {
-    wrow = idx[y];
-    rnw = rnormW[y];
-    if (wrow < 0 || wrow >= N) wrow = -1;
+  if (y >= 0 && (int64_t)y < a.k) {
+    wrow = a.idx[y];
+    rnw = a.rnormW[y];
+    if (wrow < 0 || wrow >= a.N) wrow = -1;
   }
-  if (wlab) {   // W has been updated already: the label's row as it was
-    W = wlab;
+  if (a.wlab) {   // W has been updated already: the label's row as it was
+    W = a.wlab;
     if (wrow >= 0) wrow = i;
   }
   float4 g[NC], xn[NC];
@@ -1169,19 +1198,19 @@ __global__ void dfeatures_final_kernel(const float* __restrict__ part, int split
 #pragma unroll
   for (int c = 0; c < nchunk; ++c) {
     const int d = c * 256 + lane * 4;
-    float4 a = sum[c];
-    a.x *= rs; a.y *= rs; a.z *= rs; a.w *= rs;
+    float4 t = sum[c];
+    t.x *= rs; t.y *= rs; t.z *= rs; t.w *= rs;
     if (wrow >= 0 && d < D) {
       const float4 w = *reinterpret_cast<const float4*>(W + wrow * D + d);
       const float f = dl * rnw;
-      a.x += f * w.x; a.y += f * w.y; a.z += f * w.z; a.w += f * w.w;
+      t.x += f * w.x; t.y += f * w.y; t.z += f * w.z; t.w += f * w.w;
     }
     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);   // partial sums and x are zero from column D on
     if (d < D) x = *reinterpret_cast<const float4*>(X + (int64_t)i * D + d);
     x.x *= rnx; x.y *= rnx; x.z *= rnx; x.w *= rnx;
-    g[c] = a;
+    g[c] = t;
     xn[c] = x;
-    u += a.x * x.x + a.y * x.y + a.z * x.z + a.w * x.w;
+    u += t.x * x.x + t.y * x.y + t.z * x.z + t.w * x.w;
   }
   u = wave_sum(u);
 #pragma unroll
@@ -1194,6 +1223,35 @@ __global__ void dfeatures_final_kernel(const float* __restrict__ part, int split
     if (c * 256 + lane * 4 < D)
       *reinterpret_cast<float4*>(dX + (int64_t)i * D + c * 256 + lane * 4) = o;
   }
+}
+
+// gradients_final: what is left after the backward products, in one launch: the label part of dWn
+// (`label_blocks` workgroups), the finished rows of dX and the mean loss (workgroup 0: the longest with a
+// large batch).  None needs anything of the others; one after the other they are two chains of
+// dependent loads that leave the GPU idle, and with a large batch the mean loss runs alone at the end.
+// 64 registers: two workgroups on a compute unit.  Step, two launches -> one: 128 x 1,000 x 512 fp32 59.9 ->
+// 56.1 us, 512 x 9,344 x 512 104.4 -> 101.0, 256 x 25,723 x 128 79.5 -> 74.1, 768 x 20,599 x 1024 277 ->
+// 271, 16,384 samples x 3,592 476 -> 462.
+// From kFinalWideSplits slices on a sample gets 16 wavefronts instead of 4: below, most of the 16 would
+// have no slice to add.
+constexpr int kFinalWideSplits = 12;
+template <int NC, int WPS, LabelMode MODE>
+__global__ __launch_bounds__(kLabelThreads, 8) void gradients_final_kernel(
+    FinalArgs a, int label_blocks, const int32_t* __restrict__ head, int64_t kp,
+    float* __restrict__ label_out) {
+  __shared__ union Lds {
+    LabelLds label;
+    FinalLds<NC, WPS> final;
+    float sum[256];
+  } lds;
+  const int b = (int)blockIdx.x - 1;
+  if (b < 0)
+    mean_loss_block(lds.sum, a);
+  else if (b < label_blocks)
+    dweight_label_block<MODE>(b, lds.label, a.X, a.B, a.D, a.yl, a.k, head, kp, a.rnormX, a.dlabel,
+                              label_out);
+  else
+    dfeatures_final_block<NC, WPS>(b - label_blocks, lds.final, a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1368,26 +1426,19 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
                                          : launch_logits(Small{});
     if (rc != PFC_OK) return rc;
   }
-  // label part of dWn: added to dW_out, or (compact) left in the side buffer for the fused kernel
-  auto launch_label = [&](bool compact) -> int {
-    if (nwin) {
-      PFC_LAUNCH(c, KID_DW_LABEL, dweight_label_kernel<LABEL_WINDOW>, dim3(B), dim3(kLabelThreads),
-                 0, X, B, D, yl, k, c->head, kp, c->rnormX, c->dlabel, c->dlab);
-      if (compact) {
-        PFC_LAUNCH(c, KID_DW_LABEL_SUM, dweight_label_combine_kernel<true>, dim3(B), dim3(256), 0,
-                   B, D, yl, k, c->head, kp, nwin, c->dlab, dW_out);
-      } else {
-        PFC_LAUNCH(c, KID_DW_LABEL_SUM, dweight_label_combine_kernel<false>, dim3(B), dim3(256), 0,
-                   B, D, yl, k, c->head, kp, nwin, c->dlab, dW_out);
-      }
-    } else if (compact) {
-      PFC_LAUNCH(c, KID_DW_LABEL, dweight_label_kernel<LABEL_COMPACT>, dim3(B), dim3(kLabelThreads),
-                 0, X, B, D, yl, k, c->head, kp, c->rnormX, c->dlabel, c->dlab);
-    } else {
-      PFC_LAUNCH(c, KID_DW_LABEL, dweight_label_kernel<LABEL_ADD>, dim3(B), dim3(kLabelThreads), 0,
-                 X, B, D, yl, k, c->head, kp, c->rnormX, c->dlabel, dW_out);
-    }
+  // window sums of the label part, added up: to dW_out, or (compact) in the side buffer
+  auto launch_label_sum = [&](auto compact) -> int {
+    PFC_LAUNCH(c, KID_DW_LABEL_SUM, dweight_label_combine_kernel<compact.value>, dim3(B), dim3(256),
+               0, B, D, yl, k, c->head, kp, nwin, c->dlab, dW_out);
     return PFC_OK;
+  };
+  // label part of dWn in a launch of its own: added to dW_out, or (compact) left in the side buffer
+  auto launch_label = [&](auto compact) -> int {
+    auto kernel = nwin ? dweight_label_kernel<LABEL_WINDOW>
+                       : dweight_label_kernel<compact.value ? LABEL_COMPACT : LABEL_ADD>;
+    PFC_LAUNCH(c, KID_DW_LABEL, kernel, dim3(B), dim3(kLabelThreads), 0, X, B, D, yl, k, c->head, kp,
+               c->rnormX, c->dlabel, nwin || compact.value ? c->dlab : dW_out);
+    return nwin ? launch_label_sum(compact) : PFC_OK;
   };
   // Shape of the dfeatures product: about `wgs` workgroups, at least 4 slabs each.  The callers ask
   // for half of what the GPU holds at a time, or for all the room that the dweight tiles leave:
@@ -1409,12 +1460,28 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     dx.wgs = (int)round_up(xcd_grid(dx.tiles_i * dx.tiles_d, dx.splits), 8);
     return dx;
   };
-  auto launch_final = [&](const DxShape& dx, const float* wlab) -> int {
-    PFC_LAUNCH(c, KID_DX_FINAL, dfeatures_final_kernel<NC>, dim3(B + 1), dim3(256), 0,
-               c->dXpart, dx.splits, B, Bp, D, Dp, X, W, c->N, idx, yl, k, c->rnormX, c->rnormW, wlab,
-               c->rowscale, c->dlabel, dX_out, c->lossrow, loss_out, c->clabel, c->rowmax,
-               stats_out);
-    return PFC_OK;
+  // The rest of both gradients; with_label: the label part of dWn is still to be added to dW_out.
+  // (One thing keeps them apart: dX written over the features that the label part reads.)
+  auto launch_final = [&](const DxShape& dx, bool with_label, const float* wlab) -> int {
+    const uintptr_t x0 = (uintptr_t)X, dx0 = (uintptr_t)dX_out, bytes = (uintptr_t)B * D * 4;
+    if (with_label && x0 < dx0 + bytes && dx0 < x0 + bytes) {
+      const int rc = launch_label(std::false_type{});
+      if (rc != PFC_OK) return rc;
+      with_label = false;
+    }
+    const FinalArgs fa{c->dXpart, dx.splits, B, Bp, D, Dp, X, W, c->N, idx, yl, k, c->rnormX,
+                       c->rnormW, wlab, c->rowscale, c->dlabel, dX_out, c->lossrow, loss_out,
+                       c->clabel, c->rowmax, stats_out};
+    const int label_blocks = with_label ? B : 0;
+    const bool wide = dx.splits >= kFinalWideSplits;
+    const int spb = kLabelThreads / 64 / (wide ? 16 : 4);
+    auto kernel = nwin ? (wide ? gradients_final_kernel<NC, 16, LABEL_WINDOW>
+                               : gradients_final_kernel<NC, 4, LABEL_WINDOW>)
+                       : (wide ? gradients_final_kernel<NC, 16, LABEL_ADD>
+                               : gradients_final_kernel<NC, 4, LABEL_ADD>);
+    PFC_LAUNCH(c, KID_GRAD_FINAL, kernel, dim3((unsigned)(1 + label_blocks + (B + spb - 1) / spb)),
+               dim3(kLabelThreads), 0, fa, label_blocks, c->head, kp, nwin ? c->dlab : dW_out);
+    return with_label && nwin ? launch_label_sum(std::false_type{}) : PFC_OK;
   };
   // slices of the batch in the dweight product, and the shape of the dfeatures product beside it
   // (the same with and without the update, so that dX has the same bits)
@@ -1450,7 +1517,7 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
                  dim3((unsigned)((k * D / 4 + 255) / 256)), dim3(256), 0, dst, nsp, k, kp, D, Dp,
                  dW_out);
     }
-    return launch_label(false);
+    return PFC_OK;
   };
   // tiles: those of the dfeatures product.  Its slices are the ones that gemm_backward would take
   // (size_b), whatever the tiles: dX has the same bits in either call.
@@ -1478,18 +1545,18 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     rc = size_b == TILES_256   ? launch_backward(BigBack{}, dx)
          : size_b == TILES_128 ? launch_backward(Mid{}, dx)
                                : launch_backward(Small{}, dx);
-    if (rc == PFC_OK) rc = launch_final(dx, nullptr);
+    if (rc == PFC_OK) rc = launch_final(dx, true, nullptr);
     // fused call: dWn went through memory (dW_out is the context's own buffer here)
     if (rc == PFC_OK && upd) rc = update_impl(c, upd->W, upd->v, idx, k, dW_out, upd->lr, upd->mu);
     return rc;
   }
-  rc = launch_label(true);
+  rc = launch_label(std::true_type{});
   if (rc == PFC_OK) {
     // (never 64-tiles: D == 512 and a 128-row tile per compute unit are many 128-tiles)
     // One workgroup per compute unit whatever the dfeatures tile, so the big one where it fits
     rc = Bp % 256 == 0 ? launch_backward_update(Big{}, dx) : launch_backward_update(Mid{}, dx);
   }
-  return rc == PFC_OK ? launch_final(dx, c->wlab) : rc;
+  return rc == PFC_OK ? launch_final(dx, false, c->wlab) : rc;
 }
 
 }  // namespace

@@ -33,3 +33,47 @@ CASES = [
 @pytest.mark.parametrize("precision", [binding.PRECISION_FP32, binding.PRECISION_BF16])
 def test_backward_launch_edges(precision, N, B, D, r):
     _fb_parity(precision, N, B, D, r, 64.0, 0.5, seed=5)
+
+
+# (N, B, D, r): the last launch (label parts, rows of dfeatures, loss) takes four samples to a
+# workgroup, or one where the classes were cut into at least 12 slices.  Scale 16: with a few samples
+# a peaked softmax leaves most rows of the center gradient below the floor of the row-wise bar.
+FINAL_CASES = [
+    (5_000, 1, 64, 0.01),       # one sample
+    (5_000, 5, 1_024, 0.01),    # one sample in the second workgroup, few slices
+    (40_000, 7, 1_024, 1.0),    # one sample to a workgroup
+    (40_000, 1_023, 192, 0.5),  # last workgroup with three samples
+    (40_000, 1_025, 192, 0.5),  # window sums of the label part, the second of one sample
+]
+
+
+@pytest.mark.parametrize("N,B,D,r", FINAL_CASES)
+@pytest.mark.parametrize("precision", [binding.PRECISION_FP32, binding.PRECISION_BF16])
+def test_final_launch_edges(precision, N, B, D, r):
+    _fb_parity(precision, N, B, D, r, 16.0, 0.5, seed=6)
+
+
+@pytest.mark.parametrize("B", [96, 1_100])
+def test_dfeatures_over_features(B):
+    """dfeatures written over the features: the bits of a call with a buffer of its own."""
+    import torch
+    N, D, r = 20_000, 256, 0.2
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn((B, D), generator=g, device="cuda")
+    W = torch.randn((N, D), generator=g, device="cuda").mul_(0.01)
+    labels = torch.randint(0, 40, (B,), generator=g, device="cuda")
+    ctx = binding.Context(N, D, B, r, binding.PRECISION_BF16)
+    cap = binding.pfc_num_sampled(N, B, r)
+    idx = torch.zeros(cap, dtype=torch.int32, device="cuda")
+    yl = torch.zeros(B, dtype=torch.int32, device="cuda")
+    k = ctx.pfc_sample(labels, r, 1, 0, idx, yl)
+    out = []
+    for own in (True, False):
+        feats = X.clone()
+        dX = torch.zeros_like(X) if own else feats
+        loss, dW = torch.zeros(1, device="cuda"), torch.zeros((cap, D), device="cuda")
+        ctx.pfc_forward_backward(feats, W, idx, k, yl, 64.0, 0.5, loss, dX, dW)
+        torch.cuda.synchronize()
+        out.append((loss, dX, dW))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
