@@ -537,8 +537,47 @@ __global__ void row_ref_kernel(const float* __restrict__ rowmaxpart, int tiles_j
 // strided, then a fixed shuffle tree: the same order on every run), the per-row scalars, and the
 // row of Xs = (s/(B l_i)) * x_i/|x_i| that feeds the dweight GEMM (zero for padded rows).
 // ---------------------------------------------------------------------------------------------
+// The first workgroups of the launch (label_heads) find the first sample of every class, one window of
+// kLabelWindow samples each: an LDS hash table of its distinct labels, then one atomic for each of
+// them.  (One per sample from the rows themselves: thousands meet on the word of a frequent class
+// with a large batch, and in a small one they are the end of the chain of every wavefront.  Step
+// 16,384 samples x 3,592 x 512 460.6 -> 438.4 us, 512 x 9,344 101.0 -> 99.9.)
+struct HeadsLds {
+  static constexpr int SLOTS = 2 * kLabelWindow;   // at most half full
+  int32_t key[SLOTS], first[SLOTS];
+};
+__device__ __forceinline__ void label_heads(int w, HeadsLds& lds, int B,
+                                            const int32_t* __restrict__ yl, int64_t k, int64_t kp,
+                                            int32_t* __restrict__ head, int nwin) {
+  for (int t = threadIdx.x; t < HeadsLds::SLOTS; t += blockDim.x) {
+    lds.key[t] = -1;
+    lds.first[t] = INT_MAX;
+  }
+  __syncthreads();
+  const int end = min(B, (w + 1) * kLabelWindow);
+  for (int p = w * kLabelWindow + threadIdx.x; p < end; p += blockDim.x) {
+    const int32_t y = yl[p];
+    if (y < 0 || (int64_t)y >= k) continue;
+    unsigned slot = ((unsigned)y * 2654435761u) % HeadsLds::SLOTS;
+    for (;;) {   // ends: there are more slots than samples in a window
+      const int32_t seen = atomicCAS(&lds.key[slot], -1, y);
+      if (seen == -1 || seen == y) break;
+      slot = (slot + 1) % HeadsLds::SLOTS;
+    }
+    atomicMin(&lds.first[slot], p);
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < HeadsLds::SLOTS; t += blockDim.x) {
+    const int32_t y = lds.key[t];
+    if (y < 0) continue;
+    atomicMin(&head[y], lds.first[t]);   // integer: order-independent
+    if (nwin) head[(int64_t)(1 + w) * kp + y] = lds.first[t];
+  }
+}
+
 template <typename T, int NC>
-__global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_j, int pairs, int B,
+__global__ void row_combine_kernel(int head_blocks, const float* __restrict__ rowpart, int tiles_j,
+                                   int pairs, int B,
                                    int Bp,
                                    int D, int Dp, const float* __restrict__ X,
                                    const float* __restrict__ rnormX,
@@ -550,8 +589,13 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
                                    int32_t* __restrict__ head, int nwin, T* __restrict__ Xs,
                                    const float* __restrict__ W, int64_t N,
                                    const int32_t* __restrict__ idx, float* __restrict__ wlab) {
+  __shared__ HeadsLds lds;
+  if ((int)blockIdx.x < head_blocks) {
+    label_heads(blockIdx.x, lds, B, yl, k, kp, head, nwin);
+    return;
+  }
   const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int i = ((int)blockIdx.x - head_blocks) * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (i >= Bp) return;
   float scale = 0.f;
   if (i < B) {
@@ -584,17 +628,6 @@ __global__ void row_combine_kernel(const float* __restrict__ rowpart, int tiles_
       rowscale[i] = scale;
       dlabel[i] = (lp.s / (float)B) * (p - 1.f) * rho;
       rowmax[i] = mx;
-      const int32_t y = yl[i];
-      if (y >= 0 && (int64_t)y < k) {   // integer atomics: order-independent
-        // A frequent class would bring thousands of atomics onto one word: look first (past the
-        // L1, which may hold an old value; a value read too high only costs the atomic)
-        int32_t* h = &head[y];
-        if (__hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > i) atomicMin(h, i);
-        if (nwin) {
-          h = &head[(int64_t)(1 + i / kLabelWindow) * kp + y];
-          if (__hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > i) atomicMin(h, i);
-        }
-      }
     }
   } else if (lane == 0) {
     lossrow[i] = 0.f;
@@ -1414,7 +1447,9 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
                dim3(Cfg::THREADS), Cfg::LDS_BYTES, Wn, Xn, D, Dp, k, B, Bp, kp, yl, lp, E, c->rowpart,
                c->rowmaxpart, c->clabel, tiles_j, tiles_i, c->num_cu / 8 * 8);
     auto combine_kernel = row_combine_kernel<T, NC>;
-    PFC_LAUNCH(c, KID_ROW_COMBINE, combine_kernel, dim3((Bp + 3) / 4), dim3(256), 0, c->rowpart,
+    const int head_blocks = (B + kLabelWindow - 1) / kLabelWindow;
+    PFC_LAUNCH(c, KID_ROW_COMBINE, combine_kernel, dim3(head_blocks + (Bp + 3) / 4), dim3(256), 0,
+               head_blocks, c->rowpart,
                tiles_j, logits_chained<Cfg>() ? 1 : 0, B, Bp, D, Dp, X, c->rnormX, c->clabel, lp, c->rowmaxpart, c->rowscale,
                c->dlabel, c->lossrow, c->rowmax, yl, k, kp, c->head, nwin, Xs, W, c->N, idx,
                one_kernel ? c->wlab : nullptr);

@@ -2,10 +2,14 @@
 problem: parity where the launch changes its shape -- from one tile size to the next, from one slice
 of the classes to several, with the batch cut into slices, with a last slice shorter than the
 others, and with batches and rows that end inside a tile."""
+import numpy as np
 import pytest
+import torch
 
+from oracle import pfc_oracle as O
 from paper_2203_15565_amd import binding
-from test_gpu_step import _fb_parity
+from pfc_harness import gpu_forward_backward, gpu_sample, rel_max
+from test_gpu_step import GRAD_TOL, LOSS_TOL, _fb_parity
 
 pytestmark = pytest.mark.gpu
 
@@ -56,7 +60,6 @@ def test_final_launch_edges(precision, N, B, D, r):
 @pytest.mark.parametrize("B", [96, 1_100])
 def test_dfeatures_over_features(B):
     """dfeatures written over the features: the bits of a call with a buffer of its own."""
-    import torch
     N, D, r = 20_000, 256, 0.2
     g = torch.Generator(device="cuda").manual_seed(3)
     X = torch.randn((B, D), generator=g, device="cuda")
@@ -77,3 +80,23 @@ def test_dfeatures_over_features(B):
         out.append((loss, dX, dW))
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,classes", [(1_024, 1), (1_024, 1_024), (1_023, 7), (3_000, 2), (3_000, 2_900)])
+def test_first_sample_of_a_class(B, classes):
+    """One label in the whole batch, as many labels as samples (the hash table of a window at its
+    fullest), windows that share labels or hardly any."""
+    N, D, r = 6_000, 256, 0.5
+    rng = np.random.default_rng(7)
+    X = rng.standard_normal((B, D)).astype(np.float32)
+    W = (rng.standard_normal((N, D)) * 0.01).astype(np.float32)
+    labels = rng.permutation(N)[np.arange(B) % classes]
+    ctx = binding.Context(N, D, B, r, binding.PRECISION_FP32)
+    idx, yl, k = gpu_sample(ctx, labels, r, 0, 0)
+    idx = idx[:k]
+    loss, dX, dWn = gpu_forward_backward(ctx, X, torch.from_numpy(W).cuda(), idx, yl, 16.0, 0.5)
+    assert ctx.pfc_check() == binding.PFC_OK
+    o = O.forward_backward(X, W[idx.astype(np.int64)], yl, 16.0, 0.5)
+    tol = GRAD_TOL[binding.PRECISION_FP32]
+    assert abs(loss - o["loss"]) <= LOSS_TOL[binding.PRECISION_FP32] * abs(o["loss"])
+    assert rel_max(dX, o["dX"]) <= tol and rel_max(dWn, o["dWn"]) <= tol
