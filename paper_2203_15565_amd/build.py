@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpfc.so")
-SOURCES = ["pfc_api.hip", "pfc_sample.hip", "pfc_fwd_bwd.hip", "pfc_update.hip"]
+SOURCES = ["pfc_api.hip", "pfc_sample.hip", "pfc_sample_radix.hip", "pfc_fwd_bwd.hip", "pfc_update.hip"]
 # calibration probes of the benchmark: a library of their own, not part of the product ABI
 PROBE_LIB = os.path.join(HERE, "libpfc_probe.so")
 PROBE_SOURCES = ["pfc_probe.hip"]

@@ -16,7 +16,8 @@ void set_hip_error(hipError_t e, const char* what) {
 }
 
 static const char* const kKernelNames[KID_COUNT] = {
-    "sample_scan", "sample_write", "gather_normalize_w", "gemm_rowmax",
+    "sample_scan", "sample_write", "sample_hist0", "sample_hist1", "sample_hist2", "sample_count",
+    "sample_compact", "sample_remap", "gather_normalize_w", "gemm_rowmax",
     "row_ref", "gemm_logits",
     "row_combine", "gemm_backward", "dweight_reduce", "dweight_label", "dweight_label_combine",
     "gradients_final", "update", "gemm_backward_update"};

@@ -27,6 +27,12 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 enum KernelId {
   KID_SAMPLE_SCAN = 0,
   KID_SAMPLE_WRITE,
+  KID_SAMPLE_HIST0,
+  KID_SAMPLE_HIST1,
+  KID_SAMPLE_HIST2,
+  KID_SAMPLE_COUNT,
+  KID_SAMPLE_COMPACT,
+  KID_SAMPLE_REMAP,
   KID_GATHER_W,
   KID_GEMM_ROWMAX,
   KID_ROW_REF,
@@ -53,12 +59,24 @@ struct SampleHdr {
   uint32_t listed;      // entries of list
   uint32_t pad[9];
 };
+// State of the radix selection between its launches (pfc_sample_radix.hip).
+struct RadixState {
+  uint32_t U;          // number of distinct labels; cleared again once consumed
+  uint32_t none;       // 1: no negative is taken at all (k == U)
+  uint32_t total;      // number of ids written (must equal k)
+  uint32_t need[3];    // after pass P: negatives still to be taken inside the chosen bin
+  uint32_t prefix[3];  // after pass P: threshold bits fixed so far (in place, low bits zero)
+  uint32_t pad[7];
+};
 struct SampleState {
-  uint32_t next, cur;   // set of the next call / of the call at hand
+  uint32_t next, cur;   // set of the next window selection / of the one at hand
   uint32_t k;           // |S| = max(U, ceil(r*N))
   uint32_t spare[13];
   SampleHdr hdr[2];
+  RadixState radix;
 };
+constexpr int kRadixHistWords = 3 * 4096;   // histograms of the radix passes
+constexpr int kRadixClasses = 2048;         // classes per workgroup of its ordered launches
 struct SampleScratch {
   SampleState* st;
   uint32_t* pos_bits[2];   // bit j set <=> class j is in the batch
@@ -68,6 +86,8 @@ struct SampleScratch {
   uint32_t* above_cnt;     // their number, per workgroup
   uint64_t* list;          // keys of all classes inside the window
   uint32_t list_cap, pos_cap;
+  uint32_t* hist;          // kRadixHistWords
+  uint32_t* radix_cnt;     // per kRadixClasses classes: taken for sure, equal to the threshold
 };
 
 }  // namespace pfc

@@ -16,9 +16,11 @@
 //                 offset from the counts of the workgroups in front, and writes its part of S and
 //                 the positions of the labels that fall into it
 //
-// A window that misses (about once in 10^10 calls; always if a score mask makes the scores far
-// from uniform) is seen by sample_write from the counts, and its workgroups then run a full radix
-// select each for themselves: the same result, slowly.
+// A window that misses (about once in 10^10 calls; or because a score mask has moved the scores) is
+// seen by sample_write from the counts, and its workgroups then run a full radix select each for
+// themselves: the same result, slowly.  Where the window is not the better way -- it is at least the
+// batch wide, so with large batches -- or known to miss, the call takes the radix passes of
+// pfc_sample_radix.hip instead (window_select in pfc_sample_plan.h).
 //
 // What bounds it: latency (a launch takes 5 us whatever it does; sample_write is a chain of four
 // dependent reads) and, for many classes, the one Philox block per four of them (13 us of integer
@@ -31,6 +33,8 @@
 #include <mutex>
 
 #include "pfc_common.h"
+#include "pfc_sample_device.h"
+#include "pfc_sample_plan.h"
 
 namespace pfc {
 
@@ -38,39 +42,11 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWriteThreads = 512;   // of sample_write
-constexpr int kBins = 1024;          // histogram of the window in sample_write (LDS)
-constexpr int kLocalList = 4096;     // classes of one workgroup that may lie in the window
-constexpr int kBinList = 256;        // classes that may share the bin in which the selection ends
-constexpr int kMaxClsLog2 = 15;      // classes per workgroup: 2^10 .. 2^15
-constexpr int kMaxBlocks = 640;      // workgroups, as long as 2^15 classes each suffice for that
-
-struct PhiloxKey {
-  uint32_t k0, k1;   // lo32(seed), hi32(seed)
-  uint32_t c2, c3;   // lo32(step), hi32(step)
-  uint32_t mask;     // ANDed onto every score
-};
-
-// Scores of classes 4q .. 4q+3.
-__device__ __forceinline__ void philox_block(uint32_t q, const PhiloxKey& key, uint32_t out[4]) {
-  uint32_t c0 = q, c1 = 0u, c2 = key.c2, c3 = key.c3;   // class ids are < 2^31, so hi32(j/4) = 0
-  uint32_t k0 = key.k0, k1 = key.k1;
-#pragma unroll
-  for (int round = 0; round < 10; ++round) {
-    const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-    const uint32_t n0 = hi1 ^ c1 ^ k0;
-    const uint32_t n2 = hi0 ^ c3 ^ k1;
-    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-  }
-  out[0] = c0 & key.mask; out[1] = c1 & key.mask; out[2] = c2 & key.mask; out[3] = c3 & key.mask;
-}
 
 // The window: scores lo .. lo + width (both inside).  Scores above it are taken, below it not.
 struct Window {
   uint32_t lo, width;
-  int shift;        // bin of a score inside: (score - lo) >> shift, below kBins
+  int shift;        // bin of a score inside: (score - lo) >> shift, below kWindowBins
   __device__ __forceinline__ bool inside(uint32_t u) const { return u - lo <= width; }
   __device__ __forceinline__ bool above(uint32_t u) const { return u > lo + width; }
 };
@@ -84,80 +60,6 @@ __device__ __forceinline__ uint64_t select_key(uint32_t score, uint32_t id) {
 // blk_pos, pos_list).  A call works on one set and, in its second launch, clears what the call
 // before left in the other, so no call starts with a clearing pass; which set is next is kept on
 // the device, so that a captured and replayed call alternates as well.
-
-// Sum over the NT threads of a block, to every thread; sm: NT / 64 words.
-template <int NT>
-__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* sm) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  uint32_t r = 0;
-#pragma unroll
-  for (int i = 0; i < NT / 64; ++i) r += sm[i];
-  __syncthreads();
-  return r;
-}
-
-// exclusive scan over the NT threads of a block; also returns the block total
-template <int NT>
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* sm, uint32_t& total) {
-  uint32_t inc = v;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t n = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += n;
-  }
-  if (lane == 63) sm[w] = inc;
-  __syncthreads();
-  uint32_t base = 0;
-  total = 0;
-#pragma unroll
-  for (int i = 0; i < NT / 64; ++i) {
-    const uint32_t x = sm[i];
-    if (i < w) base += x;
-    total += x;
-  }
-  __syncthreads();
-  return base + inc - v;
-}
-
-// All NT threads: walk a histogram of NB bins in LDS from the largest bin downwards until `need`
-// (>= 1) entries are covered.  Returns the bin that holds the last of them and how many are to be
-// taken from inside it (bin 0 and 0 if the histogram holds fewer than `need`).
-template <int NT, int NB>
-__device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t need, uint32_t* sm,
-                                         uint32_t& bin, uint32_t& need_inside) {
-  __shared__ uint32_t s_bin, s_need;
-  constexpr int kPer = NB / NT;
-  const int t = threadIdx.x;
-  uint32_t own[kPer], mine = 0, total;
-#pragma unroll
-  for (int e = 0; e < kPer; ++e) {   // thread t owns bins NB-1-t*kPer downwards
-    own[e] = hist[NB - 1 - (t * kPer + e)];
-    mine += own[e];
-  }
-  if (t == 0) {
-    s_bin = 0u;
-    s_need = 0u;
-  }
-  const uint32_t exc = block_excl_scan<NT>(mine, sm, total);
-  if (exc < need && need <= exc + mine) {   // exactly one thread
-    uint32_t cum = exc;
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      if (cum < need && need <= cum + own[e]) {
-        s_bin = (uint32_t)(NB - 1 - (t * kPer + e));
-        s_need = need - cum;
-      }
-      cum += own[e];
-    }
-  }
-  __syncthreads();
-  bin = s_bin;
-  need_inside = s_need;
-}
 
 // ---------------------------------------------------------------------------------------------
 // sample_scan.  Workgroup b < nblk scores the classes [b << cls_log2, (b + 1) << cls_log2); the
@@ -178,16 +80,7 @@ __global__ __launch_bounds__(kThreads) void sample_scan_kernel(
     const int64_t y = i < B ? labels[i] : 0;
     const bool valid = i < B && y >= 0 && y < N;
     if (i < B && !valid) atomicOr(err_flag, 1);
-    // One lane per distinct label of the wavefront goes on: with long-tailed labels a frequent
-    // class would otherwise bring thousands of atomics onto one word.
-    bool lead = false;
-    unsigned long long todo = __ballot(valid);
-    while (todo) {   // wave-uniform loop over the distinct labels
-      const int src = __ffsll(todo) - 1;
-      const int64_t y0 = __shfl(y, src, 64);
-      lead = lead || lane == src;
-      todo &= ~__ballot(valid && y == y0);
-    }
+    const bool lead = first_of_label(y, valid);
     bool first = false, above = false;
     if (lead) {
       const uint32_t bit = 1u << (y & 31);
@@ -406,7 +299,7 @@ __global__ __launch_bounds__(kWriteThreads, 4) void sample_write_kernel(
   const uint32_t k = U > ceil_rN ? U : ceil_rN;
   const uint32_t R = k - U;   // negatives to take
   const uint32_t* pos_bits = par ? sc.pos_bits[1] : sc.pos_bits[0];
-  for (int b = t; b < kBins; b += NT) s.hist[b] = 0u;
+  for (int b = t; b < kWindowBins; b += NT) s.hist[b] = 0u;
   for (int w = t; w < own_words; w += NT) {
     uint32_t v = 0u;
     if (word0 + w < nwords) {
@@ -442,7 +335,7 @@ __global__ __launch_bounds__(kWriteThreads, 4) void sample_write_kernel(
       for (uint32_t e = t; e < npos; e += NT) atomicSub(&s.hist[bin_of(pl[e])], 1u);
       __syncthreads();
       uint32_t bin, inside;
-      find_bin<NT, kBins>(s.hist, need, s.sm, bin, inside);
+      find_bin<NT, kWindowBins>(s.hist, need, s.sm, bin, inside);
       each([&](uint64_t y) {
         const uint32_t j = (uint32_t)y;
         if (bin_of(y) == bin && !((pos_bits[j >> 5] >> (j & 31u)) & 1u)) {
@@ -547,49 +440,6 @@ __global__ __launch_bounds__(kWriteThreads, 4) void sample_write_kernel(
   }
 }
 
-// Classes per workgroup (log2): few enough workgroups that the parts every one of them repeats
-// (the list, the counts, the labels) stay small, enough of them to use the GPU (up to 2.5 per
-// compute unit).
-int cls_log2_of(int64_t N) {
-  int l = 10;
-  while (l < kMaxClsLog2 && ((N + ((int64_t)1 << l) - 1) >> l) > kMaxBlocks) ++l;
-  return l;
-}
-
-// The window of scores in which the selection of k - U negatives ends.  Counted over ALL classes,
-// the last class taken is number n0 = k - U + (batch classes above it) from the top, between
-// ceil_rN - B and ceil_rN whatever the batch holds.  The number of classes at or above the score
-// 2^32 (1 - q) is binomial(N, q): 6.5 standard deviations and a constant for small counts.
-// *expected: classes inside it, on average.
-Window select_window(int64_t N, int64_t ceil_rN, int32_t B, double* expected) {
-  const double n = (double)N;
-  auto margin = [&](double rank) {
-    const double q = rank < 0 ? 0 : rank > n ? 1 : rank / n;
-    return 6.5 * sqrt(n * q * (1.0 - q)) + 40.0;
-  };
-  const double hi_rank = (double)ceil_rN, lo_rank = (double)ceil_rN - (double)B;
-  double top = lo_rank - margin(lo_rank < 0 ? 0 : lo_rank), bot = hi_rank + margin(hi_rank);
-  if (top < 0) top = 0;
-  if (bot > n) bot = n;
-  const double two32 = 4294967296.0;
-  double lo = floor(two32 * (1.0 - bot / n)), hi = ceil(two32 * (1.0 - top / n)) - 1.0;
-  if (bot >= n) lo = 0;
-  if (top <= 0 || hi > two32 - 1.0) hi = two32 - 1.0;
-  if (lo > hi) lo = hi;
-  *expected = bot - top;
-  Window w;
-  w.lo = (uint32_t)lo;
-  w.width = (uint32_t)hi - w.lo;
-  w.shift = 0;
-  while ((w.width >> w.shift) >= (uint32_t)kBins) ++w.shift;
-  return w;
-}
-
-int64_t blocks_of(int64_t N) {
-  const int l = cls_log2_of(N);
-  return (N + ((int64_t)1 << l) - 1) >> l;
-}
-
 }  // namespace
 
 size_t sample_layout(int64_t N, int64_t B, char* base, SampleScratch* out) {
@@ -600,11 +450,9 @@ size_t sample_layout(int64_t N, int64_t B, char* base, SampleScratch* out) {
     return p;
   };
   const size_t words = (size_t)(N + 31) / 32;
-  const int64_t nb = blocks_of(N);
+  const int64_t nb = sample_blocks(N);
   const size_t blk = (size_t)(nb > kMaxBlocks ? nb : kMaxBlocks);   // smaller N may have more blocks
-  // list: twice what the widest window of a call holds on average, and room for small numbers
-  const double wide = (double)(B < N ? B : N) + 2.0 * (6.5 * 0.5 * sqrt((double)N) + 40.0);
-  const size_t list = ((size_t)(2.0 * wide) + 4096);
+  const size_t list = (size_t)window_list_cap(N, B);
   out->st = (SampleState*)take(sizeof(SampleState));
   for (int i = 0; i < 2; ++i) {
     out->pos_bits[i] = (uint32_t*)take(words * 4);
@@ -616,6 +464,8 @@ size_t sample_layout(int64_t N, int64_t B, char* base, SampleScratch* out) {
   out->list = (uint64_t*)take(list * 8);
   out->list_cap = (uint32_t)list;
   out->pos_cap = (uint32_t)B;
+  out->hist = (uint32_t*)take(kRadixHistWords * 4);
+  out->radix_cnt = (uint32_t*)take((size_t)((N + kRadixClasses - 1) / kRadixClasses) * 8);
   return off;
 }
 
@@ -634,21 +484,27 @@ int sample_impl(pfc_ctx* c, const int64_t* labels, int32_t B, double r, uint64_t
   key.c3 = (uint32_t)(step >> 32);
   key.mask = score_mask;
 
-  const int cls_log2 = cls_log2_of(N);
-  const int nblk = (int)blocks_of(N);
-  double expected = 0.0;
-  const Window win = select_window(N, crn, B, &expected);
+  const SelectWindow sw = select_window(N, crn, B);
   const SampleScratch& sc = c->samp;
-  const int mark_blocks = (B + kThreads - 1) / kThreads;
-  PFC_LAUNCH(c, KID_SAMPLE_SCAN, sample_scan_kernel, dim3(nblk + mark_blocks), dim3(kThreads), 0, N,
-             key, win, sc, cls_log2, nblk, labels, B, c->err_flag);
-  const double usual = expected + 4.0 * sqrt(expected);
-  auto write_kernel = usual <= 2.0 * kWriteThreads   ? sample_write_kernel<2>
-                      : usual <= 6.0 * kWriteThreads ? sample_write_kernel<6>
-                      : usual <= 16. * kWriteThreads ? sample_write_kernel<16>
-                                                     : sample_write_kernel<24>;
-  PFC_LAUNCH(c, KID_SAMPLE_WRITE, write_kernel, dim3(nblk), dim3(kWriteThreads), 0, N, key, win, sc,
-             cls_log2, nblk, (uint32_t)crn, labels, B, cap, idx_out, yl_out);
+  // the timing hooks report the launches of this call, not those of an earlier one on the other way
+  for (int id = KID_SAMPLE_SCAN; id <= KID_SAMPLE_REMAP; ++id) c->ev_used[id] = 0;
+  if (window_select(N, crn, B, score_mask, sw)) {
+    const int cls_log2 = sample_cls_log2(N), nblk = (int)sample_blocks(N);
+    const Window win{sw.lo, sw.width, sw.shift};
+    const int mark_blocks = (B + kThreads - 1) / kThreads;
+    PFC_LAUNCH(c, KID_SAMPLE_SCAN, sample_scan_kernel, dim3(nblk + mark_blocks), dim3(kThreads), 0, N,
+               key, win, sc, cls_log2, nblk, labels, B, c->err_flag);
+    const double usual = sw.expected + 4.0 * sqrt(sw.expected);
+    auto write_kernel = usual <= 2.0 * kWriteThreads   ? sample_write_kernel<2>
+                        : usual <= 6.0 * kWriteThreads ? sample_write_kernel<6>
+                        : usual <= 16. * kWriteThreads ? sample_write_kernel<16>
+                                                       : sample_write_kernel<24>;
+    PFC_LAUNCH(c, KID_SAMPLE_WRITE, write_kernel, dim3(nblk), dim3(kWriteThreads), 0, N, key, win, sc,
+               cls_log2, nblk, (uint32_t)crn, labels, B, cap, idx_out, yl_out);
+  } else {
+    const int rc = sample_radix(c, labels, B, (uint32_t)crn, cap, key, idx_out, yl_out);
+    if (rc != PFC_OK) return rc;
+  }
 
   if (crn >= (int64_t)B) {
     // U <= B <= ceil(r*N): k is known without the labels.
@@ -673,7 +529,7 @@ namespace {
 constexpr int64_t kNoallocMaxN = (int64_t)1 << 24;                               // 16,777,216 classes
 constexpr int64_t kNoallocMaxB = (int64_t)1 << 20;
 // what sample_layout asks for at (kNoallocMaxN, kNoallocMaxB), checked on every call
-constexpr size_t kNaBytes = (size_t)42 << 20;
+constexpr size_t kNaBytes = (size_t)43 << 20;
 
 // Zero when the code object is loaded; afterwards every call leaves it so that the next one finds
 // its set cleared (see above), except the error word, which only ever gains bits.

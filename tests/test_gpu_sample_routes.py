@@ -1,0 +1,156 @@
+"""pfc_sample on both of its selections: large batches and masks that move the scores take the radix
+passes; the result is the oracle's either way, and calls of both kinds follow each other on one
+scratch."""
+import statistics
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import pfc_oracle as O
+from paper_2203_15565_amd import binding
+from pfc_harness import gpu_sample
+
+pytestmark = pytest.mark.gpu
+
+WINDOW = {"sample_scan", "sample_write"}
+RADIX = {"sample_hist0", "sample_hist1", "sample_hist2", "sample_count", "sample_compact",
+         "sample_remap"}
+
+
+def _say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+# N against 4, 32 and 2048 classes (Philox block, bitmap word, workgroup of the ordered launches)
+@pytest.mark.parametrize("N,B,r,mask,route", [
+    (93_431, 32_768, 0.4, None, RADIX), (20_000, 16_384, 0.9, None, RADIX),
+    (20_000, 16_384, 1.0, None, RADIX), (131_072, 60_001, 0.001, None, RADIX),
+    (70_001, 300, 0.05, 0x3FF, RADIX), (65_537, 300, 0.05, 0, RADIX),
+    (2_059_906, 512, 0.02, 0xFFF00000, RADIX), (10_240, 100, 0.2, 0, WINDOW),
+    (10_241, 100, 0.2, 0, RADIX), (93_431, 2048, 0.1, None, WINDOW),
+    (655_361, 300, 0.01, 0xFFFFF000, WINDOW), (2_059_906, 16_384, 1e-9, None, WINDOW)])
+def test_sample_routes(N, B, r, mask, route):
+    ctx = binding.Context(N, 64, B, max(r, 0.01), binding.PRECISION_BF16)
+    ctx.pfc_set_timing(True)
+    rng = np.random.default_rng(N + B)
+    # the route at hand, a small call on the window, the route again with other labels
+    for step, (b, ratio, m) in enumerate([(B, r, mask), (64, 0.01, None), (B, r, mask),
+                                          (max(1, B // 2), r, mask)]):
+        labels = rng.integers(0, N, size=b)
+        if step == 2:
+            labels[: b // 2] = labels[0]
+        _say("sample route", N, b, ratio, m, step)
+        idx, yl, k = gpu_sample(ctx, labels, ratio, 5, step, score_mask=m)
+        ran = {n for n in ctx.pfc_get_timing() if n.startswith("sample_")}
+        assert ran == (WINDOW if step == 1 else route) or step == 3
+        oidx, oyl, ok = O.sample(labels, N, ratio, 5, step,
+                                 score_mask=0xFFFFFFFF if m is None else m)
+        assert k == ok
+        assert np.array_equal(idx[:k], oidx) and (idx[k:] == -7).all()
+        assert np.array_equal(yl, oyl)
+    assert ctx.pfc_check() == binding.PFC_OK
+    ctx.close()
+
+
+def test_radix_reports_bad_labels():
+    N, B = 65_600, 40_000
+    ctx = binding.Context(N, 64, B, 0.7, binding.PRECISION_BF16)
+    labels = np.random.default_rng(4).integers(0, N, size=B)
+    labels[3], labels[B - 1] = N, -1
+    _say("sample radix bad labels")
+    idx, yl, k = gpu_sample(ctx, labels, 0.7, 0, 0)
+    assert ctx.pfc_check() == binding.PFC_ELABEL
+    assert yl[3] == -1 and yl[B - 1] == -1
+    good = np.delete(labels, [3, B - 1])
+    oidx, oyl, ok = O.sample(good, N, 0.7, 0, 0)
+    assert k == ok and np.array_equal(idx[:k], oidx)
+    assert np.array_equal(np.delete(yl, [3, B - 1]), oyl)
+    ctx.close()
+
+
+# The window selection has to hold a bin of the window in LDS; with these batches it cannot, and every
+# workgroup then selected for itself: 3.9 and 5.9 ms (radix passes: 0.19 and 0.56).  The bound of 2 ms is
+# far from either.
+@pytest.mark.parametrize("N,B,r", [(2_059_906, 1 << 18, 0.15), (1 << 21, 1 << 20, 0.51)])
+def test_large_batches_keep_their_pace(N, B, r):
+    import torch
+    g = np.random.default_rng(B)
+    labels_np = g.integers(0, N, size=B)
+    labels = torch.from_numpy(labels_np).cuda()
+    cap = binding.pfc_num_sampled(N, B, r)
+    idx = torch.full((cap,), -7, dtype=torch.int32, device="cuda")
+    yl = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    ms = []
+    for step in range(4):
+        _say("large batch", N, B, step)
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        k = binding.pfc_sample_noalloc(labels, N, r, 3, step, idx, yl)
+        t1.record()
+        t1.synchronize()
+        ms.append(t0.elapsed_time(t1))
+    oidx, oyl, ok = O.sample(labels_np, N, r, 3, 3)
+    assert k == ok and np.array_equal(idx.cpu().numpy()[:k], oidx)
+    assert np.array_equal(yl.cpu().numpy(), oyl)
+    assert statistics.median(ms[1:]) < 2.0, ms
+    # a small call on the same scratch afterwards
+    few = torch.from_numpy(labels_np[:300].copy()).cuda()
+    k = binding.pfc_sample_noalloc(few, N, 0.01, 3, 9, idx, yl[:300])
+    oidx, oyl, ok = O.sample(labels_np[:300], N, 0.01, 3, 9)
+    assert k == ok and np.array_equal(idx.cpu().numpy()[:k], oidx)
+    assert np.array_equal(yl.cpu().numpy()[:300], oyl)
+
+
+def test_masked_scores_keep_their_pace():
+    """Every window missed: 8.2 ms at 2 million classes, against 0.07 ms of the radix passes."""
+    N, B = 2_059_906, 512
+    ctx = binding.Context(N, 64, B, 0.01, binding.PRECISION_BF16)
+    ctx.pfc_set_timing(True)
+    labels = np.random.default_rng(6).integers(0, N, size=B)
+    ms = []
+    for step in range(3):
+        _say("masked", step)
+        gpu_sample(ctx, labels, 0.01, 3, step, score_mask=0x3FF)
+        ms.append(sum(v for n, v in ctx.pfc_get_timing().items() if n.startswith("sample_")))
+    assert statistics.median(ms) < 2.0, ms
+    ctx.close()
+
+
+def test_both_selections_replay_from_a_graph():
+    """A captured call leaves the scratch as the next one, captured or not, on either selection needs
+    it."""
+    import torch
+    N = 93_431
+    sizes = [(2048, 0.1), (40_000, 0.45)]           # window, radix
+    s = torch.cuda.Stream()
+    rng = np.random.default_rng(12)
+    with torch.cuda.stream(s):
+        calls = []
+        for B, r in sizes:
+            lab = torch.from_numpy(rng.integers(0, N, size=B)).cuda()
+            idx = torch.zeros(binding.pfc_num_sampled(N, B, r), dtype=torch.int32, device="cuda")
+            calls.append((lab, r, idx, torch.zeros(B, dtype=torch.int32, device="cuda")))
+
+        def both(step):
+            for lab, r, idx, yl in calls:
+                binding.pfc_sample_noalloc(lab, N, r, 21, step, idx, yl, stream=s.cuda_stream)
+        both(0)
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        both(5)
+    want = [O.sample(lab.cpu().numpy(), N, r, 21, 5) for lab, r, _, _ in calls]
+    for replay in range(4):
+        _say("graph replay", replay)
+        with torch.cuda.stream(s):
+            both(replay + 1)                         # eager work in between
+            for _, _, idx, yl in calls:
+                idx.zero_()
+                yl.zero_()
+            g.replay()
+        s.synchronize()
+        for (lab, r, idx, yl), (oidx, oyl, ok) in zip(calls, want):
+            assert np.array_equal(idx.cpu().numpy()[:ok], oidx)
+            assert np.array_equal(yl.cpu().numpy(), oyl)

@@ -1,0 +1,102 @@
+"""Host rules of pfc_sample (csrc/pfc_sample_plan.h), compiled for the CPU: wherever the window
+selection is chosen, its lists hold what falls into them, for everything the entry points accept."""
+import ctypes
+import math
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2203_15565_amd", "csrc")
+FULL = 0xFFFFFFFF
+
+_SRC = r"""
+#include "pfc_sample_plan.h"
+extern "C" int plan(int64_t N, int64_t crn, int64_t B, uint32_t mask, double* out) {
+  const pfc::SelectWindow w = pfc::select_window(N, crn, B);
+  out[0] = w.lo; out[1] = w.width; out[2] = w.shift; out[3] = w.expected;
+  out[4] = pfc::window_bin_classes(N, w);
+  out[5] = pfc::window_list_cap(N, B);
+  out[6] = pfc::sample_cls_log2(N); out[7] = pfc::sample_blocks(N);
+  out[8] = pfc::kBinList; out[9] = pfc::kLocalList; out[10] = pfc::kWindowBatch;
+  out[11] = pfc::kWindowBins; out[12] = pfc::kMissClasses;
+  return pfc::window_select(N, crn, B, mask, w) ? 1 : 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    gxx = shutil.which("g++") or shutil.which("c++")
+    if not gxx:
+        pytest.skip("no host C++ compiler")
+    d = tmp_path_factory.mktemp("plan")
+    src, lib = d / "plan.cpp", d / "libplan.so"
+    src.write_text(_SRC)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(lib)],
+                   check=True)
+    f = ctypes.CDLL(str(lib)).plan
+    f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_uint32,
+                  ctypes.POINTER(ctypes.c_double)]
+    keys = ("lo", "width", "shift", "expected", "bin", "list_cap", "cls_log2", "blocks", "bin_list",
+            "local_list", "window_batch", "bins", "miss_classes")
+
+    def call(N, crn, B, mask=FULL):
+        out = (ctypes.c_double * len(keys))()
+        taken = f(N, crn, B, mask, out)
+        return bool(taken), dict(zip(keys, out))
+    return call
+
+
+def _forms(n):
+    rng = random.Random(1)
+    for _ in range(n):
+        N = int(math.exp(rng.uniform(0.0, math.log(2**31 - 1))))
+        B = int(math.exp(rng.uniform(0.0, math.log(2**20))))
+        r = math.exp(rng.uniform(math.log(1e-9), 0.0))
+        yield max(N, 1), max(1, min(N, math.ceil(r * N))), max(B, 1)
+    for N in (2**20, 2**24, 20_971_520, 2**31 - 1):
+        for B in (2**16, 2**17, 2**18, 2**20):
+            yield N, N // 2, B
+            yield N, max(1, N // 8), B
+
+
+def test_window_lists_hold_what_falls_into_them(plan):
+    taken = 0
+    for N, crn, B in _forms(20_000):
+        window, p = plan(N, crn, B)
+        assert (int(p["width"]) >> int(p["shift"])) < p["bins"], (N, crn, B)
+        assert p["blocks"] <= 640 or N > 20_971_520, (N, crn, B)
+        if not window:
+            continue
+        taken += 1
+        assert B <= p["window_batch"]
+        # the end bin, the list of one workgroup, the list of the call: 8 standard deviations
+        assert p["bin"] + 8 * math.sqrt(p["bin"]) <= p["bin_list"], (N, crn, B)
+        mean = p["expected"] / N * min(N, 2.0 ** p["cls_log2"])
+        assert mean + 8 * math.sqrt(mean) <= p["local_list"], (N, crn, B)
+        assert p["expected"] + 8 * math.sqrt(p["expected"]) <= p["list_cap"], (N, crn, B)
+        # 6 standard deviations around every rank at which the selection can end
+        for rank, edge in ((crn, p["lo"]), (max(0, crn - B), p["lo"] + p["width"] + 1)):
+            q = rank / N
+            sigma = math.sqrt(N * q * (1 - q))
+            got = N * (1 - edge / 2**32)      # classes at or above that edge of the window
+            if rank == crn:
+                assert got >= min(N, crn + 6 * sigma) - 1e-3, (N, crn, B)
+            else:
+                assert got <= max(0.0, rank - 6 * sigma) + 1e-3, (N, crn, B)
+    assert taken > 5_000
+
+
+def test_large_batches_and_moved_scores_take_the_radix_passes(plan):
+    for N in (93_431, 2_059_906, 10_000_000, 2**24):
+        assert plan(N, max(N // 10, 2048), 2048)[0]
+        assert not plan(N, max(N // 10, min(N, 2**17)), 2**17)[0]
+        assert not plan(N, N // 10, 512, 0x3FF)[0] and not plan(N, N // 10, 512, 0)[0]
+    assert plan(9001, 1801, 40, 0x3FF)[0]                       # a miss costs little there
+    assert plan(655_361, 6554, 300, 0xFFFFF000)[0]              # ties, but where the window is
+    assert not plan(655_361, 6554, 300, 0xFFFF0000)[0]          # ten classes to a score: not any more
+    assert plan(2_059_906, 1, 16_384)[0]                        # the classes of the batch alone
