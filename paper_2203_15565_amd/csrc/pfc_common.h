@@ -15,7 +15,7 @@ namespace pfc {
 constexpr int kPadB = 256;   // batch rows are padded to at most a multiple of this
 constexpr int kPadD = 128;   // row length of the GEMM operands
 constexpr int kPadK = 256;   // sampled rows are padded to a multiple of this
-constexpr int kMaxSplits = 32;    // slices of S in the dfeatures product
+constexpr int kMaxSplits = 32;    // slices of S in the dfeatures product (long fp32 sums: twice that)
 constexpr int kPartSlices = 64;   // slices the buffer of partial sums has room for: those of dfeatures
                                   // in front, those of a dweight product cut over the batch behind
 constexpr int kLabelWindow = 1024;     // samples per window of the label part of dWn

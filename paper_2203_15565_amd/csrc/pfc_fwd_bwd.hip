@@ -672,11 +672,21 @@ __global__ void row_combine_kernel(int head_blocks, const float* __restrict__ ro
 // dfeatures: slice `sp` of S: part[sp][i][d] = sum_{j in slice} E[i][j] * Wn[j][d]
 // (A = E with k contiguous, B = Wn k-major).
 // ---------------------------------------------------------------------------------------------
+// Products of one uninterrupted sum (gemm_tile's CHAIN) in the two backward products with fp32 operands.
+// Their 128- and 64-tiles need fewer slices than 256-tiles to fill the GPU, and a slice of many thousand
+// products adds up rounding errors: 8192 samples x 8,120 classes x 512 in one slice is 7.7e-7 off (2-norm, both
+// gradients, against 64 bits), in the four slices of 256-tiles 6.9e-7, with these pieces 6.7e-7.  They cost
+// 0 - 1 % of a step (1000 x 50,000 x 320 1041 -> 1047 us; batches cut into slices up to 3 %, 4096 x 3,990 x 512 474 ->
+// 490), as many slices as 256-tiles take up to 18 %.
+constexpr int kDxSumSteps = 256, kDwSumSteps = 512;
+template <class Cfg, int STEPS, bool PIECES>
+constexpr int sum_slabs() { return PIECES ? STEPS / Cfg::BK : 0; }
+
 struct DxShape {
   int slabs_total, slabs_per, splits, tiles_i, tiles_d;
   int wgs;   // workgroups: tiles_i * tiles_d * splits, rounded up to 8
 };
-template <class Cfg>
+template <class Cfg, bool PIECES>
 __device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
                                                const typename Cfg::elem* __restrict__ E,
                                                const typename Cfg::elem* __restrict__ Wn, int D,
@@ -692,7 +702,8 @@ __device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
   const int64_t koff = (int64_t)slab0 * Cfg::BK;
-  gemm_tile<Cfg>(E + (int64_t)i0 * kp + koff, kp, Wn + koff * D + d0, D, ns, smem, acc);
+  gemm_tile<Cfg, sum_slabs<Cfg, kDxSumSteps, PIECES>()>(E + (int64_t)i0 * kp + koff, kp,
+                                                        Wn + koff * D + d0, D, ns, smem, acc);
   float* out = part + (int64_t)sp * Bp * D;
 #pragma unroll
   for (int bm = 0; bm < Cfg::TM; ++bm)
@@ -712,7 +723,7 @@ __device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
 // write partial tiles, summed in fixed order by dweight_reduce.  Xs has rows of Dp elements; the
 // partial tiles too; dWn (the caller's) has rows of D floats, columns from D on are not stored.
 // ---------------------------------------------------------------------------------------------
-template <class Cfg, bool SPLIT>
+template <class Cfg, bool SPLIT, bool PIECES>
 __device__ __forceinline__ void dweight_tile(
     int wg, char* smem, const typename Cfg::elem* __restrict__ E,
     const typename Cfg::elem* __restrict__ Xs, int D, int Dp, int64_t k, int64_t kp, int Bp,
@@ -734,7 +745,8 @@ __device__ __forceinline__ void dweight_tile(
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
   PFC_PHASE(2, 0);
-  gemm_tile<Cfg>(E + i0 * kp + j0, kp, Xs + i0 * Dp + d0, Dp, ns, smem, acc);
+  gemm_tile<Cfg, sum_slabs<Cfg, kDwSumSteps, PIECES>()>(E + i0 * kp + j0, kp, Xs + i0 * Dp + d0, Dp, ns,
+                                                        smem, acc);
   PFC_PHASE(2, 1);
   float* dst = SPLIT ? out + (int64_t)sp * kp * Dp : out;
   const int ld = SPLIT ? Dp : D;
@@ -769,7 +781,7 @@ __device__ __forceinline__ void dweight_tile(
 // samples x 9,344 classes x 512), large ones lose the last round of dweight tiles and have all
 // compute units store their tiles at the same time (291 + 219 us, 495 together at 1024 x 205,991 x
 // 512).  The dfeatures workgroups are the longest and start first; dx_shape says how many there are.
-template <class CfgX, class CfgW, bool SPLIT>
+template <class CfgX, class CfgW, bool SPLIT, bool PIECES>
 __global__ __launch_bounds__(CfgX::THREADS) void gemm_backward_kernel(
     const typename CfgX::elem* __restrict__ E, const typename CfgX::elem* __restrict__ Wn,
     const typename CfgX::elem* __restrict__ Xs, int D, int Dp, int64_t k, int64_t kp, int Bp,
@@ -779,10 +791,10 @@ __global__ __launch_bounds__(CfgX::THREADS) void gemm_backward_kernel(
   extern __shared__ __align__(16) char smem[];
   const int b = blockIdx.x;
   if (b < dx.wgs)
-    dfeatures_tile<CfgX>(b, smem, E, Wn, Dp, Bp, kp, dx, dXpart);
+    dfeatures_tile<CfgX, PIECES>(b, smem, E, Wn, Dp, Bp, kp, dx, dXpart);
   else
-    dweight_tile<CfgW, SPLIT>(b - dx.wgs, smem, E, Xs, D, Dp, k, kp, Bp, dWout, tiles_j, tiles_d,
-                              slabs_per, splits);
+    dweight_tile<CfgW, SPLIT, PIECES>(b - dx.wgs, smem, E, Xs, D, Dp, k, kp, Bp, dWout, tiles_j,
+                                      tiles_d, slabs_per, splits);
 }
 
 // dW[j][d] = sum over slices of part[slice][j][d], in slice order (rows of Dp floats in `part`, of
@@ -1114,7 +1126,7 @@ __global__ __launch_bounds__(CfgB::THREADS) void gemm_backward_update_kernel(
                 CfgB::BN == CfgS::BN, "one launch shape");
   extern __shared__ __align__(16) char smem[];
   if ((int)blockIdx.x < dx.wgs) {
-    dfeatures_tile<CfgX>(blockIdx.x, smem, E, Wn, CfgB::BN, Bp, kp, dx, dXpart);
+    dfeatures_tile<CfgX, false>(blockIdx.x, smem, E, Wn, CfgB::BN, Bp, kp, dx, dXpart);
     return;
   }
   const int b = (int)blockIdx.x - dx.wgs;
@@ -1358,6 +1370,7 @@ struct Tiles {
   using X = TileCfg<T, BM, BN, WM, WN, false, true>;    // dfeatures: samples x columns
   static constexpr int BACK_LDS = X::LDS_BYTES > W::LDS_BYTES ? X::LDS_BYTES : W::LDS_BYTES;
   static constexpr int PER_CU = 160 * 1024 / BACK_LDS;   // workgroups a compute unit holds
+  static constexpr bool PIECES = sizeof(T) == 4;         // sums in pieces (kDxSumSteps)
 };
 
 template <class S>
@@ -1371,8 +1384,12 @@ int set_lds_limits_logits(S) {
 }
 template <class S>
 int set_lds_limits_backward(S) {
-  const void* b[] = {(const void*)(gemm_backward_kernel<typename S::X, typename S::W, false>),
-                     (const void*)(gemm_backward_kernel<typename S::X, typename S::W, true>)};
+  using X = typename S::X;
+  using W = typename S::W;
+  constexpr bool kPieces = S::PIECES;
+  const void* b[] = {(const void*)(gemm_backward_kernel<X, W, false, false>),
+                     (const void*)(gemm_backward_kernel<X, W, false, kPieces>),
+                     (const void*)(gemm_backward_kernel<X, W, true, kPieces>)};
   for (const void* p : b)
     PFC_HIP(hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, S::BACK_LDS));
   return PFC_OK;
@@ -1405,7 +1422,8 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
 
   // fused call: one kernel for dweight and update only if D fits its tile and there is at least one
   // tile per CU
-  const bool one_kernel = upd && D == CfgU::BN && kp / CfgU::BM >= c->num_cu;
+  const bool fits_one_kernel = D == CfgU::BN && kp / CfgU::BM >= c->num_cu;
+  const bool one_kernel = upd && fits_one_kernel;
 
   auto norm_kernel = gather_normalize_kernel<T, NC>;
   const int x_blocks = (Bp + kNormWaves - 1) / kNormWaves;
@@ -1488,7 +1506,11 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     dx.tiles_d = Dp / Cfg::BN;
     dx.slabs_total = (int)(kp / Cfg::BK);
     int64_t want = wgs / (dx.tiles_i * dx.tiles_d);
-    want = std::min<int64_t>({want, kMaxSplits, dx.slabs_total / 4});
+    // fp32 sums that are not cut into pieces: slices of more than 4096 classes are halved, for the
+    // rounding of the sums (100 samples x 400,000 classes dX 2.81e-7 off, halved 2.70e-7) and, fused, for
+    // workgroups that are not the end of the launch (4.23 -> 3.18 ms; 512 x 200,000 2.85 -> 2.92)
+    const bool halve = sizeof(T) == 4 && fits_one_kernel && kp > (int64_t)kMaxSplits * 4096;
+    want = std::min<int64_t>({want, halve ? 2 * kMaxSplits : kMaxSplits, dx.slabs_total / 4});
     if (want < 1) want = 1;
     dx.slabs_per = (int)((dx.slabs_total + want - 1) / want);
     dx.splits = (dx.slabs_total + dx.slabs_per - 1) / dx.slabs_per;
@@ -1543,7 +1565,12 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     int slabs_per, nsp;
     dx = backward_shape(tiles, slabs_per, nsp);
     float* dst = nsp > 1 ? c->dXpart + (int64_t)dx.splits * Bp * Dp : dW_out;
-    auto kernel = nsp > 1 ? gemm_backward_kernel<CX, CW, true> : gemm_backward_kernel<CX, CW, false>;
+    // a class set that the one-kernel form takes: the sums of that form (which has no registers for a
+    // second set of accumulators), so that dX has the same bits in either call
+    constexpr bool kPieces = decltype(tiles)::PIECES;
+    auto kernel = nsp > 1           ? gemm_backward_kernel<CX, CW, true, kPieces>
+                  : fits_one_kernel ? gemm_backward_kernel<CX, CW, false, false>
+                                    : gemm_backward_kernel<CX, CW, false, kPieces>;
     PFC_LAUNCH(c, KID_GEMM_BACKWARD, kernel, dim3((unsigned)(dx.wgs + tiles_j * tiles_d * nsp)),
                dim3(CX::THREADS), lds, E, Wn, Xs, D, Dp, k, kp, Bp, dx, c->dXpart, dst, tiles_j,
                tiles_d, slabs_per, nsp);

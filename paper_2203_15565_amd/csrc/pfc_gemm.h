@@ -88,15 +88,20 @@ __device__ __forceinline__ void mfma_group<__bf16>(const u32x4& a, const u32x4& 
                                               __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-template <>
-__device__ __forceinline__ void mfma_group<float>(const u32x4& a, const u32x4& b, f32x16& c) {
+// fp32: elements 2 * HALF and 2 * HALF + 1 of the group.
+template <int HALF>
+__device__ __forceinline__ void mfma_half(const u32x4& a, const u32x4& b, f32x16& c) {
   // whole-vector casts: a bit_cast applied to a single vector element reads element 0
   const f32x4 af = __builtin_bit_cast(f32x4, a);
   const f32x4 bf = __builtin_bit_cast(f32x4, b);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(af[0], bf[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(af[1], bf[1], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(af[2], bf[2], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(af[3], bf[3], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(af[2 * HALF], bf[2 * HALF], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(af[2 * HALF + 1], bf[2 * HALF + 1], c, 0, 0, 0);
+}
+
+template <>
+__device__ __forceinline__ void mfma_group<float>(const u32x4& a, const u32x4& b, f32x16& c) {
+  mfma_half<0>(a, b, c);
+  mfma_half<1>(a, b, c);
 }
 
 // Global -> register -> LDS staging of one operand slab.  Thread t owns chunk (t % CPR) of LDS
@@ -216,6 +221,27 @@ __device__ __forceinline__ void mma_group(const Frags<Cfg>& f, f32x16 (&acc)[Cfg
     for (int bn = 0; bn < Cfg::TN; ++bn) mfma_group<T>(f.a[bm], f.b[bn], acc[bm][bn]);
 }
 
+template <class Cfg>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
+#pragma unroll
+  for (int a = 0; a < Cfg::TM; ++a)
+#pragma unroll
+    for (int b = 0; b < Cfg::TN; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+}
+
+template <class Cfg>
+__device__ __forceinline__ void add_acc(f32x16 (&to)[Cfg::TM][Cfg::TN],
+                                        const f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
+#pragma unroll
+  for (int a = 0; a < Cfg::TM; ++a)
+#pragma unroll
+    for (int b = 0; b < Cfg::TN; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) to[a][b][r] += acc[a][b][r];
+}
+
 // Accumulate acc += A_tile * B_tile^T over `nslabs` slabs of K.
 //   A: element (first of this workgroup's BM tile rows, first reduction step of its range)
 //   B: likewise for its BN tile rows;  lda / ldb in elements.
@@ -232,7 +258,9 @@ __device__ __forceinline__ void mma_group(const Frags<Cfg>& f, f32x16 (&acc)[Cfg
 //     of the next slab, so the LDS latency at the slab boundary is covered as well.
 // Slab numbers past the end are clamped to the last slab: such loads and LDS stores are
 // redundant but in bounds, and keep the loop body free of branches.
-template <class Cfg>
+// CHAIN > 0 (fp32): every CHAIN slabs the accumulators are added to a second set and start again from
+// zero, so that no sum is a chain of more than CHAIN * BK additions.
+template <class Cfg, int CHAIN = 0>
 __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__ A, int64_t lda,
                                           const typename Cfg::elem* __restrict__ B, int64_t ldb,
                                           int nslabs, char* smem,
@@ -259,6 +287,7 @@ __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__
   // groups before the barrier if two do not have an MFMA for each load)
   constexpr int SPAN = (NL <= 2 * MM ? (HEAD < 2 ? HEAD : 2) : HEAD) * MM;
   static_assert(HEAD >= 1, "the last group is multiplied behind the barrier");
+  static_assert(CHAIN == 0 || sizeof(T) == 4, "bf16 operands: their rounding is what counts");
 
   // prologue: slabs 0 and 1 are requested back to back; slab 0 goes to stage 0
   typename SA::Regs a0 = {};
@@ -274,6 +303,8 @@ __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__
   __syncthreads();
   Frags<Cfg> fc;
   read_group<Cfg>(st0, 0, wm, wn, fc);
+  f32x16 sums[Cfg::TM][Cfg::TN];
+  if constexpr (CHAIN > 0) zero_acc<Cfg>(sums);
   for (int s = 0; s < nslabs; ++s) {
     char* cur = (s & 1) ? st1 : st0;
     char* nxt = (s & 1) ? st0 : st1;
@@ -288,6 +319,14 @@ __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__
       __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs they do not feed
 #pragma unroll
       for (int q = 0; q < MM; ++q) {
+        // one block to a wavefront, sums in pieces: the loads go between the MFMAs of the group, and stay
+        // there (left to the compiler they end up in front of all four: 512 samples x 9,344 classes x 512
+        // 168 us, so 163; larger tiles lose 2 % by it)
+        constexpr bool kBetween = CHAIN > 0 && MM == 1;
+        if constexpr (kBetween) {
+          mfma_half<0>(fc.a[0], fc.b[0], acc[0][0]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int c = 0; c < NL; ++c) {     // chunk c is requested in front of MFMA c*SPAN/NL
           if (c * SPAN / NL == g * MM + q) {
@@ -295,7 +334,12 @@ __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__
             else sb.load_chunk(s2, c - NA, b0);
           }
         }
-        mfma_group<T>(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
+        if constexpr (kBetween) {
+          __builtin_amdgcn_sched_barrier(0);
+          mfma_half<1>(fc.a[0], fc.b[0], acc[0][0]);
+        } else {
+          mfma_group<T>(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
       fc = fn;
@@ -307,18 +351,15 @@ __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__
     mma_group<Cfg>(fc, acc);
     __builtin_amdgcn_sched_barrier(0);
     fc = fn;
+    if constexpr (CHAIN > 0) {
+      if ((s + 1) % CHAIN == 0 && s < last) {
+        add_acc<Cfg>(sums, acc);
+        zero_acc<Cfg>(acc);
+      }
+    }
   }
+  if constexpr (CHAIN > 0) add_acc<Cfg>(acc, sums);
   __syncthreads();
-}
-
-template <class Cfg>
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
-#pragma unroll
-  for (int a = 0; a < Cfg::TM; ++a)
-#pragma unroll
-    for (int b = 0; b < Cfg::TN; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 }
 
 // Row / column of accumulator register r of block (bm, bn) inside the workgroup tile.
