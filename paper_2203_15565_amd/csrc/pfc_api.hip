@@ -141,16 +141,18 @@ int pfc_create(pfc_ctx** out, int64_t N, int32_t D, int32_t B_max, double r_max,
   }
   ALLOC(head, (size_t)(1 + c->label_windows) * kp * 4);
   ALLOC(E, Bp * kp * es);
-  ALLOC(rowpart, (kp / 64) * Bp * 4);
-  ALLOC(rowmaxpart, (kp / 64) * Bp * 4);
+  const size_t rowparts = (size_t)rowpart_floats(c->num_cu, B_max, c->kp_cap);
+  const size_t parts = (size_t)part_floats(c->num_cu, D, B_max);
+  ALLOC(rowpart, rowparts * 4);
+  ALLOC(rowmaxpart, rowparts * 4);
   ALLOC(rowmax, Bp * 4);
   ALLOC(rowref, Bp * 4);
   ALLOC(clabel, Bp * 4);
   ALLOC(rowscale, Bp * 4);
   ALLOC(dlabel, Bp * 4);
   ALLOC(lossrow, Bp * 4);
-  ALLOC(dXpart, ((size_t)kPartSlices * Dpz + Dz) * Bp * 4);
-  if (rc == PFC_OK) c->wlab = c->dXpart + (size_t)kPartSlices * Bp * Dpz;
+  ALLOC(dXpart, (parts + Bp * Dz) * 4);
+  if (rc == PFC_OK) c->wlab = c->dXpart + parts;
   ALLOC(dlab, Bp * Dz * 4);
   ALLOC(dWtmp, (size_t)c->k_cap * Dz * 4);
   ALLOC(spare, 2 * Dz * 4);

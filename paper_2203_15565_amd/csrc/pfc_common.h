@@ -5,23 +5,12 @@
 #include <stdint.h>
 
 #include "pfc.h"
+#include "pfc_step_plan.h"
 
 namespace pfc {
 
-// ---------------------------------------------------------------------------------------------
-// Padded problem geometry.  Every scratch operand of the three GEMMs is padded with zeros to a
-// whole number of tiles, so the GEMM main loops need no bounds checks.
-// ---------------------------------------------------------------------------------------------
-constexpr int kPadB = 256;   // batch rows are padded to at most a multiple of this
-constexpr int kPadD = 128;   // row length of the GEMM operands
-constexpr int kPadK = 256;   // sampled rows are padded to a multiple of this
-constexpr int kMaxSplits = 32;    // slices of S in the dfeatures product (long fp32 sums: twice that)
-constexpr int kPartSlices = 64;   // slices the buffer of partial sums has room for: those of dfeatures
-                                  // in front, those of a dweight product cut over the batch behind
 constexpr int kLabelWindow = 1024;     // samples per window of the label part of dWn
 constexpr int kMaxLabelWindows = 64;   // one lane of a wavefront initialises one window's head
-
-inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
 // Kernel ids for the optional per-kernel timing.
 enum KernelId {
@@ -112,7 +101,8 @@ struct pfc_ctx {
   uint32_t* host_pin;     // pinned host words for read-backs
 
   // forward/backward scratch (T = float or bf16 according to precision)
-  void* Xn;        // [Bp x Dp]  normalised features (Dp = D rounded up to 256, zero columns)
+  void* Xn;        // [Bp x Dp]  normalised features (Dp = D rounded up to 128, or to 256 where the
+                   // backward launch takes 256-tiles; zero columns)
   void* Xs;        // [Bp x Dp]  (s/(B*l_i)) * xn_i
   float* rnormX;   // [Bp]
   void* Wn;        // [kp x Dp]  normalised sampled centers
@@ -130,7 +120,7 @@ struct pfc_ctx {
   float* rowscale; // [Bp] s/(B*l_i)
   float* dlabel;   // [Bp] (s/B)(p_iy - 1) rho_i
   float* lossrow;  // [Bp]
-  float* dXpart;   // [kPartSlices x Bp x Dp]
+  float* dXpart;   // partial sums of the backward launch (part_floats)
   float* wlab;     // (behind dXpart) [Bp x D] row of W of every sample's label, as it was before the update (fused step)
   float* dlab;     // [Bp x D] label-column part of dWn, one row per first sample of a class (fused step)
   float* dWtmp;    // [k_cap x D] dWn of the fused step whenever its one-kernel form does not apply

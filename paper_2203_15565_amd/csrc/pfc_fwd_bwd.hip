@@ -29,6 +29,7 @@
 
 #include "pfc_common.h"
 #include "pfc_gemm.h"
+#include "pfc_step_plan.h"
 
 // Phase clocks for tuning, compiled in only with -DPFC_PHASES (never in the shipped library):
 // thread 0 of every workgroup of the selected kernel stores the constant-rate clock at up to 8
@@ -682,10 +683,6 @@ constexpr int kDxSumSteps = 256, kDwSumSteps = 512;
 template <class Cfg, int STEPS, bool PIECES>
 constexpr int sum_slabs() { return PIECES ? STEPS / Cfg::BK : 0; }
 
-struct DxShape {
-  int slabs_total, slabs_per, splits, tiles_i, tiles_d;
-  int wgs;   // workgroups: tiles_i * tiles_d * splits, rounded up to 8
-};
 template <class Cfg, bool PIECES>
 __device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
                                                const typename Cfg::elem* __restrict__ E,
@@ -1302,66 +1299,6 @@ __global__ __launch_bounds__(kLabelThreads, 8) void gradients_final_kernel(
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-// Number of batch slices of the dweight GEMM (1: none): slices only when the tiles alone leave
-// most CUs idle, limited by the room in the split buffer and by a minimum slice length.
-int dweight_slices(const pfc_ctx* c, int tiles, int Bp, int64_t kp, int bk) {
-  const int slabs_total = Bp / bk;
-  int want = c->num_cu / tiles;
-  const int64_t room = (int64_t)(kPartSlices - kMaxSplits) * Bp / kp;
-  if (want > room) want = (int)room;
-  if (want > slabs_total / 8) want = slabs_total / 8;   // a slice must stay long enough to pay
-                                                        // for its own partial tile
-  return want < 1 ? 1 : want;
-}
-
-// Size of the GEMM tiles, one for the logits and one for the backward launch of a call.  256 x 256
-// moves the least data per flop and fills a compute unit with one workgroup, 128 x 128 puts two on
-// it, 64 x 64 three.  Measured on 256 compute units over batches of 48 .. 16,384 samples and 320 ..
-// 2 million classes (us for 256 / 128 / 64, D = 512 unless stated):
-//   bf16 logits: a round of 256-tiles costs the same however full it is, so they win only where the
-//     last round is nearly full (1024 x 205,991: 336 / 347 / 507; 768 x 20,599 x D 1024, 0.95 of a
-//     round: 41 / 45 / 64; 1024 x 36,024, 2.2 rounds: 71 / 58 / 83) and the reduction is long
-//     (8192 x 6,000 x D 256: 71 / 65 / 102); 64-tiles only for a handful of 128-tiles (512 x 4,000:
-//     24 / 9.8 / 8.7; 512 x 9,344: 24 / 14.7 / 16.0).
-//   bf16 backward: 256-tiles unless they leave compute units idle (512 x 4,000: 22 / 15 / 17;
-//     512 x 16,000: 29 / 30 / 45; 1024 x 205,991: 482 / 612 / 996), the batch would be padded much
-//     more (128 x 200,000: 210 / 179 / 260) or the reduction is short and the tiles few
-//     (256 x 36,000: 42 / 39 / 57; 256 x 200,000: 221 / 260 / 368); 64-tiles for the smallest
-//     problems (128 x 1,000: 15 / 7.3 / 5.8).
-//   fp32: the matrix cores are the bound at any of the sizes, so what counts is how evenly the
-//     compute units are loaded: 64-tiles where a few 128-tiles per compute unit do not come out
-//     even (logits 512 x 9,344: 135 / 77 / 57; 128 x 1,000: 129 / 37 / 15).  From one 256-tile per
-//     compute unit on the sizes are close (2048 x 60,000: 1144 / 1127 / 1207; 512 x 60,000: 299 /
-//     315 / 330) and the logits keep 256 and its order of the row sums.
-enum TileSize { TILES_64 = 64, TILES_128 = 128, TILES_256 = 256 };
-
-inline bool even_rounds(int64_t tiles, int64_t cu) {   // at most 15 % of the rounds' room is idle
-  return tiles > 4 * cu || (tiles + cu - 1) / cu * cu * 100 <= tiles * 115;
-}
-
-template <typename T>
-TileSize logits_tiles(const pfc_ctx* c, int B, int64_t kp, int D) {
-  const int64_t cu = c->num_cu, mid = kp / 128 * ((B + 127) / 128);
-  const int64_t big = kp / 256 * ((B + 255) / 256), rounds = (big + cu - 1) / cu;
-  if (sizeof(T) == 4) return big >= cu ? TILES_256 : even_rounds(mid, cu) ? TILES_128 : TILES_64;
-  if (D > 256 && rounds * cu * 4 * 100 <= mid * 109) return TILES_256;
-  return 2 * mid > cu ? TILES_128 : TILES_64;
-}
-
-template <typename T>
-TileSize backward_tiles(const pfc_ctx* c, int B, int64_t kp, int D) {
-  const int Bp = (int)round_up(B, 128), Bp256 = (int)round_up(B, 256);
-  const int Dp = (int)round_up(D, kPadD), Dp256 = (int)round_up(D, 256);
-  const int64_t cu = c->num_cu, mid = kp / 128 * (Dp / 128), big = kp / 256 * (Dp256 / 256);
-  if (sizeof(T) == 4)
-    return even_rounds(mid * dweight_slices(c, (int)mid, Bp, kp, 32), cu) ? TILES_128 : TILES_64;
-  // (columns: 640 -> 768 and 896 -> 1024 cost less than the smaller tile, 384 -> 512 more)
-  if (Dp256 * 100 <= Dp * 125 && Bp256 * 100 <= Bp * 115 &&
-      big * dweight_slices(c, (int)big, Bp256, kp, 64) * 2 >= cu && (B >= 512 || big * 2 >= cu * 3))
-    return TILES_256;
-  return B > 128 || 2 * mid > cu ? TILES_128 : TILES_64;
-}
-
 // One size of GEMM tiles: the tile of every product (BM x BN of its output, WM x WN wavefronts).
 template <typename T, int BM, int BN, int WM, int WN>
 struct Tiles {
@@ -1369,7 +1306,6 @@ struct Tiles {
   using W = TileCfg<T, BM, BN, WM, WN, true, true>;     // dweight: classes x columns
   using X = TileCfg<T, BM, BN, WM, WN, false, true>;    // dfeatures: samples x columns
   static constexpr int BACK_LDS = X::LDS_BYTES > W::LDS_BYTES ? X::LDS_BYTES : W::LDS_BYTES;
-  static constexpr int PER_CU = 160 * 1024 / BACK_LDS;   // workgroups a compute unit holds
   static constexpr bool PIECES = sizeof(T) == 4;         // sums in pieces (kDxSumSteps)
 };
 
@@ -1412,7 +1348,8 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   static_assert(kFusedLds <= 160 * 1024, "LDS of one compute unit");
   const int D = c->D;
   const int64_t kp = round_up(k, kPadK);
-  const TileSize size_f = logits_tiles<T>(c, B, kp, D), size_b = backward_tiles<T>(c, B, kp, D);
+  const TileSize size_f = logits_tiles(c->num_cu, sizeof(T), B, kp, D),
+                 size_b = backward_tiles(c->num_cu, sizeof(T), B, kp, D);
   const int Bp = (int)round_up(B, std::max<int>(size_f, size_b));
   // row length of the library's own GEMM operands
   const int Dp = (int)round_up(D, size_b == TILES_256 ? 256 : kPadD);
@@ -1422,8 +1359,8 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
 
   // fused call: one kernel for dweight and update only if D fits its tile and there is at least one
   // tile per CU
-  const bool fits_one_kernel = D == CfgU::BN && kp / CfgU::BM >= c->num_cu;
-  const bool one_kernel = upd && fits_one_kernel;
+  static_assert(CfgU::BM == 128 && CfgU::BN == 512, "fits_one_kernel");
+  const bool plain_sums = fits_one_kernel(c->num_cu, D, kp), one_kernel = upd && plain_sums;
 
   auto norm_kernel = gather_normalize_kernel<T, NC>;
   const int x_blocks = (Bp + kNormWaves - 1) / kNormWaves;
@@ -1493,30 +1430,6 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
                c->rnormX, c->dlabel, nwin || compact.value ? c->dlab : dW_out);
     return nwin ? launch_label_sum(compact) : PFC_OK;
   };
-  // Shape of the dfeatures product: about `wgs` workgroups, at least 4 slabs each.  The callers ask
-  // for half of what the GPU holds at a time, or for all the room that the dweight tiles leave:
-  // measured against all of it and a quarter of it (us a step, quarter / half / all):
-  // 1024 samples x 205,991 classes x 512 1499 / 1302 / 1365, x 360,232 2511 / 2166 / 2251, fused
-  // x 205,991 1162 / 1098 / 1161.  Fewer workgroups write fewer partial sums (2 MB a slice there)
-  // but are longer than everything behind them.
-  auto dx_shape = [&](auto cfg, int64_t wgs) {
-    using Cfg = decltype(cfg);
-    DxShape dx;
-    dx.tiles_i = Bp / Cfg::BM;
-    dx.tiles_d = Dp / Cfg::BN;
-    dx.slabs_total = (int)(kp / Cfg::BK);
-    int64_t want = wgs / (dx.tiles_i * dx.tiles_d);
-    // fp32 sums that are not cut into pieces: slices of more than 4096 classes are halved, for the
-    // rounding of the sums (100 samples x 400,000 classes dX 2.81e-7 off, halved 2.70e-7) and, fused, for
-    // workgroups that are not the end of the launch (4.23 -> 3.18 ms; 512 x 200,000 2.85 -> 2.92)
-    const bool halve = sizeof(T) == 4 && fits_one_kernel && kp > (int64_t)kMaxSplits * 4096;
-    want = std::min<int64_t>({want, halve ? 2 * kMaxSplits : kMaxSplits, dx.slabs_total / 4});
-    if (want < 1) want = 1;
-    dx.slabs_per = (int)((dx.slabs_total + want - 1) / want);
-    dx.splits = (dx.slabs_total + dx.slabs_per - 1) / dx.slabs_per;
-    dx.wgs = (int)round_up(xcd_grid(dx.tiles_i * dx.tiles_d, dx.splits), 8);
-    return dx;
-  };
   // The rest of both gradients; with_label: the label part of dWn is still to be added to dW_out.
   // (One thing keeps them apart: dX written over the features that the label part reads.)
   auto launch_final = [&](const DxShape& dx, bool with_label, const float* wlab) -> int {
@@ -1540,37 +1453,22 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
                dim3(kLabelThreads), 0, fa, label_blocks, c->head, kp, nwin ? c->dlab : dW_out);
     return with_label && nwin ? launch_label_sum(std::false_type{}) : PFC_OK;
   };
-  // slices of the batch in the dweight product, and the shape of the dfeatures product beside it
-  // (the same with and without the update, so that dX has the same bits)
-  auto backward_shape = [&](auto tiles, int& slabs_per, int& nsp) {
-    using CW = typename decltype(tiles)::W;
-    const int tiles_w = (int)(kp / CW::BM) * (Dp / CW::BN);
-    const int slabs_total = Bp / CW::BK;
-    const int want = dweight_slices(c, tiles_w, Bp, kp, CW::BK);
-    slabs_per = (slabs_total + want - 1) / want;
-    nsp = (slabs_total + slabs_per - 1) / slabs_per;
-    const int64_t slots = (int64_t)c->num_cu * decltype(tiles)::PER_CU;
-    const int64_t wgs_w = (int64_t)tiles_w * nsp;
-    // fp32 tiles take long: dfeatures workgroups no longer than those, so that the end comes out even
-    // (fused, 1024 x 36,024 x 512: half of the GPU's room 1546 us a step, twice the room 1212)
-    const int64_t wgs = sizeof(T) == 4 && wgs_w > 2 * slots ? 2 * slots : std::max(slots / 2, slots - wgs_w);
-    return dx_shape(typename decltype(tiles)::X{}, wgs);
-  };
+  const BackwardShape shape = backward_shape(c->num_cu, sizeof(T), size_b, Bp, Dp, D, kp);
   // both backward products in one launch; dW_out and the partial sums of dX are written
   auto launch_backward = [&](auto tiles, DxShape& dx) -> int {
     using CX = typename decltype(tiles)::X;
     using CW = typename decltype(tiles)::W;
     constexpr int lds = decltype(tiles)::BACK_LDS;
     const int tiles_j = (int)(kp / CW::BM), tiles_d = Dp / CW::BN;
-    int slabs_per, nsp;
-    dx = backward_shape(tiles, slabs_per, nsp);
+    dx = shape.dx;
+    const int slabs_per = shape.slabs_per, nsp = shape.splits;
     float* dst = nsp > 1 ? c->dXpart + (int64_t)dx.splits * Bp * Dp : dW_out;
     // a class set that the one-kernel form takes: the sums of that form (which has no registers for a
     // second set of accumulators), so that dX has the same bits in either call
     constexpr bool kPieces = decltype(tiles)::PIECES;
-    auto kernel = nsp > 1           ? gemm_backward_kernel<CX, CW, true, kPieces>
-                  : fits_one_kernel ? gemm_backward_kernel<CX, CW, false, false>
-                                    : gemm_backward_kernel<CX, CW, false, kPieces>;
+    auto kernel = nsp > 1      ? gemm_backward_kernel<CX, CW, true, kPieces>
+                  : plain_sums ? gemm_backward_kernel<CX, CW, false, false>
+                               : gemm_backward_kernel<CX, CW, false, kPieces>;
     PFC_LAUNCH(c, KID_GEMM_BACKWARD, kernel, dim3((unsigned)(dx.wgs + tiles_j * tiles_d * nsp)),
                dim3(CX::THREADS), lds, E, Wn, Xs, D, Dp, k, kp, Bp, dx, c->dXpart, dst, tiles_j,
                tiles_d, slabs_per, nsp);
@@ -1585,9 +1483,7 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   // (size_b), whatever the tiles: dX has the same bits in either call.
   auto launch_backward_update = [&](auto tiles, DxShape& dx) -> int {
     using CX = typename decltype(tiles)::X;
-    int slabs_per, nsp;
-    dx = size_b == TILES_256 ? backward_shape(BigBack{}, slabs_per, nsp)
-                             : backward_shape(Mid{}, slabs_per, nsp);
+    dx = shape.dx;
     dx.tiles_i = Bp / CX::BM;
     dx.tiles_d = Dp / CX::BN;
     dx.wgs = (int)round_up(xcd_grid(dx.tiles_i * dx.tiles_d, dx.splits), 8);

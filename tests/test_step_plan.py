@@ -1,0 +1,120 @@
+"""Host rules of forward/backward (csrc/pfc_step_plan.h), compiled for the CPU: the scratch of a context
+holds what every call of its range leaves there, and is no larger than it has to be."""
+import ctypes
+import math
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2203_15565_amd", "csrc")
+
+_SRC = r"""
+#include "pfc_step_plan.h"
+using namespace pfc;
+extern "C" void plan(int cu, int es, int D, int B, int64_t k, double* out) {
+  const int64_t kp = round_up(k, kPadK);
+  const TileSize f = logits_tiles(cu, es, B, kp, D), b = backward_tiles(cu, es, B, kp, D);
+  const int Bp = (int)round_up(B, std::max<int>(f, b)), Dp = (int)round_up(D, b == TILES_256 ? 256 : kPadD);
+  const BackwardShape s = backward_shape(cu, es, b, Bp, Dp, D, kp);
+  out[0] = f; out[1] = b; out[2] = Bp; out[3] = Dp; out[4] = kp;
+  out[5] = s.splits; out[6] = s.slabs_per; out[7] = s.dx.splits; out[8] = s.dx.slabs_per;
+  out[9] = s.dx.wgs; out[10] = s.dx.tiles_i; out[11] = s.dx.tiles_d; out[12] = s.dx.slabs_total;
+  out[13] = fits_one_kernel(cu, D, kp); out[14] = tile_bk(es);
+}
+extern "C" void scratch(int cu, int D, int B_max, int64_t k_cap, double* out) {
+  out[0] = (double)part_floats(cu, D, B_max);
+  out[1] = (double)rowpart_floats(cu, B_max, round_up(k_cap, kPadK));
+}
+"""
+_KEYS = ("logits", "backward", "Bp", "Dp", "kp", "dw_splits", "dw_slabs", "dx_splits", "dx_slabs", "dx_wgs",
+         "tiles_i", "tiles_d", "dx_total", "one_kernel", "bk")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    gxx = shutil.which("g++") or shutil.which("c++")
+    if not gxx:
+        pytest.skip("no host C++ compiler")
+    d = tmp_path_factory.mktemp("step_plan")
+    src, out = d / "plan.cpp", d / "libplan.so"
+    src.write_text(_SRC)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(out)],
+                   check=True)
+    so = ctypes.CDLL(str(out))
+    vp = ctypes.POINTER(ctypes.c_double)
+    so.plan.argtypes = [ctypes.c_int] * 4 + [ctypes.c_int64, vp]
+    so.scratch.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64, vp]
+    return so
+
+
+def _plan(lib, cu, es, D, B, k):
+    out = (ctypes.c_double * len(_KEYS))()
+    lib.plan(cu, es, D, B, k, out)
+    return {n: int(v) for n, v in zip(_KEYS, out)}
+
+
+def _scratch(lib, cu, D, B, k):
+    out = (ctypes.c_double * 2)()
+    lib.scratch(cu, D, B, k, out)
+    return int(out[0]), int(out[1])
+
+
+def _up(x, m):
+    return -(-x // m) * m
+
+
+def _log(rng, hi):
+    return max(1, int(math.exp(rng.uniform(0.0, math.log(hi)))))
+
+
+def _forms(n):
+    """(compute units, bytes of an operand, D, largest batch, largest class set) and calls in that range"""
+    rng = random.Random(2)
+    for i in range(n):
+        cu = 256 if i % 8 else rng.choice([64, 208, 304])
+        es = rng.choice([2, 4])
+        D = 64 * rng.randint(1, 16)
+        B_max, k_cap = _log(rng, 2**20), _log(rng, 2**25 if es == 2 else 2**24)
+        calls = [(B_max, k_cap), (1, k_cap), (B_max, 1), (_log(rng, B_max), k_cap), (B_max, _log(rng, k_cap)),
+                 (_log(rng, B_max), _log(rng, k_cap))]
+        yield cu, es, D, B_max, k_cap, calls
+
+
+def test_scratch_holds_every_call(lib):
+    tiles = set()
+    for cu, es, D, B_max, k_cap, calls in _forms(20_000):
+        parts, rows = _scratch(lib, cu, D, B_max, k_cap)
+        for B, k in calls:
+            p = _plan(lib, cu, es, D, B, k)
+            form = (cu, es, D, B_max, k_cap, B, k, p)
+            tiles.add((es, p["logits"], p["backward"]))
+            front = p["dx_splits"] * p["Bp"] * p["Dp"]
+            behind = p["dw_splits"] * p["kp"] * p["Dp"] if p["dw_splits"] > 1 else 0
+            assert front + behind <= parts, form
+            assert p["kp"] // p["logits"] * p["Bp"] <= rows, form
+            # whole tiles, slices that cover the sums, none of them empty
+            assert p["Bp"] % p["backward"] == 0 and p["Dp"] % p["backward"] == 0, form
+            assert p["kp"] % p["backward"] == 0 and p["Bp"] >= B and p["Dp"] >= D, form
+            assert (p["dx_splits"] - 1) * p["dx_slabs"] < p["dx_total"] <= p["dx_splits"] * p["dx_slabs"], form
+            total = p["Bp"] // p["bk"]
+            assert (p["dw_splits"] - 1) * p["dw_slabs"] < total <= p["dw_splits"] * p["dw_slabs"], form
+            assert p["dx_wgs"] % 8 == 0 and p["dx_wgs"] >= p["tiles_i"] * p["tiles_d"] * p["dx_splits"], form
+            if p["one_kernel"]:      # its dfeatures tiles are 128 or 256 wide, and dweight is in one piece
+                assert p["backward"] >= 128 and p["dw_splits"] == 1, form
+    assert len(tiles) >= 12
+
+
+def test_scratch_stays_small(lib):
+    """64 slices of the whole batch and two row sums for every 128 classes are what a context took before
+    64-tiles and the saved label rows: what was accepted then has to fit now."""
+    for cu, es, D, B_max, k_cap, _ in _forms(5_000):
+        parts, rows = _scratch(lib, cu, D, B_max, k_cap)
+        Bp, Dp, kp = _up(B_max, 256), _up(D, 256), _up(k_cap, 256)
+        before = 64 * Bp * Dp + 2 * (kp // 128) * Bp
+        assert parts + Bp * D + 2 * rows <= before + 2 * 2048 * cu + Bp * D * (Bp <= 4 * cu), (cu, D, B_max, k_cap)
+    parts, rows = _scratch(lib, 256, 1024, 2**20, 2**20)
+    assert 4 * parts <= 5 << 30 and 4 * rows <= 33 << 30
