@@ -87,7 +87,7 @@ int pfc_sample_masked(pfc_ctx* ctx, const int64_t* labels, int32_t B, double r,
 /*
  * pfc_sample_noalloc -- pfc_sample for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  It needs no context: the
- * sampler's scratch (bitmaps, candidate lists, counts; 42 MB) is a file-scope
+ * sampler's scratch (bitmaps, candidate lists, counts; 9 MB) is a file-scope
  * device array of the library, one copy per GPU, held until the process ends.  The
  * call allocates nothing, frees nothing, never waits for the GPU and records no memset: it only
  * launches the kernels of pfc_sample on `hip_stream` (a hipStream_t, NULL = the default stream)

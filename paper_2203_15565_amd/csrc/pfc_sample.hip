@@ -452,18 +452,18 @@ size_t sample_layout(int64_t N, int64_t B, char* base, SampleScratch* out) {
   const size_t words = (size_t)(N + 31) / 32;
   const int64_t nb = sample_blocks(N);
   const size_t blk = (size_t)(nb > kMaxBlocks ? nb : kMaxBlocks);   // smaller N may have more blocks
-  const size_t list = (size_t)window_list_cap(N, B);
+  const size_t list = (size_t)window_list_cap(N, B), pos = (size_t)window_pos_cap(B);
   out->st = (SampleState*)take(sizeof(SampleState));
   for (int i = 0; i < 2; ++i) {
     out->pos_bits[i] = (uint32_t*)take(words * 4);
     out->blk_pos[i] = (uint32_t*)take(blk * 4);
-    out->pos_list[i] = (uint64_t*)take((size_t)B * 8);
+    out->pos_list[i] = (uint64_t*)take(pos * 8);
   }
   out->above_bits = (uint32_t*)take(words * 4);
   out->above_cnt = (uint32_t*)take(blk * 4);
   out->list = (uint64_t*)take(list * 8);
   out->list_cap = (uint32_t)list;
-  out->pos_cap = (uint32_t)B;
+  out->pos_cap = (uint32_t)pos;
   out->hist = (uint32_t*)take(kRadixHistWords * 4);
   out->radix_cnt = (uint32_t*)take((size_t)((N + kRadixClasses - 1) / kRadixClasses) * 8);
   return off;
@@ -529,7 +529,7 @@ namespace {
 constexpr int64_t kNoallocMaxN = (int64_t)1 << 24;                               // 16,777,216 classes
 constexpr int64_t kNoallocMaxB = (int64_t)1 << 20;
 // what sample_layout asks for at (kNoallocMaxN, kNoallocMaxB), checked on every call
-constexpr size_t kNaBytes = (size_t)43 << 20;
+constexpr size_t kNaBytes = (size_t)9 << 20;
 
 // Zero when the code object is loaded; afterwards every call leaves it so that the next one finds
 // its set cleared (see above), except the error word, which only ever gains bits.

@@ -76,6 +76,10 @@ inline int64_t window_list_cap(int64_t N, int64_t B) {
   return (int64_t)(2.0 * ((double)b + 2.0 * window_margin((double)N, 0.5))) + 4096;
 }
 
+// Entries that the list of the batch classes inside the window needs: all of them may lie there.  Larger
+// batches never take the window.
+inline int64_t window_pos_cap(int64_t B) { return B < kWindowBatch ? B : kWindowBatch; }
+
 // Whether a mask leaves the scores where the window expects them: it only clears low bits, and there
 // is no more than one class to a step of what is left, on average.
 inline bool mask_keeps_window(int64_t N, uint32_t mask) {

@@ -4,6 +4,8 @@ import ctypes
 import math
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -41,6 +43,19 @@ def test_probe_header_symbols_are_exported():
     if os.path.exists(binding.LIB_PATH):
         prod = ctypes.CDLL(binding.LIB_PATH)
         assert not any(hasattr(prod, name) for name in declared)
+
+
+def test_static_scratch_is_what_the_header_states():
+    """The one large object of the library is the scratch of pfc_sample_noalloc, on the host (its
+    shadow, in .bss) as on every GPU that loads the library."""
+    size = shutil.which("size")
+    if not size or not os.path.exists(binding.LIB_PATH):
+        pytest.skip("no binutils, or libpfc.so not built")
+    out = subprocess.run([size, "-A", binding.LIB_PATH], capture_output=True, text=True, check=True)
+    bss = int(re.search(r"^\.bss\s+(\d+)", out.stdout, re.M).group(1))
+    text = open(os.path.join(ROOT, "include", "pfc.h")).read()
+    stated = int(re.search(r"candidate lists, counts; (\d+) MB\)", text).group(1))
+    assert stated <= 10 and bss <= (stated << 20) + (1 << 16), (stated, bss)
 
 
 def test_num_sampled_host_function():

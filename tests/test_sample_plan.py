@@ -22,7 +22,7 @@ extern "C" int plan(int64_t N, int64_t crn, int64_t B, uint32_t mask, double* ou
   out[5] = pfc::window_list_cap(N, B);
   out[6] = pfc::sample_cls_log2(N); out[7] = pfc::sample_blocks(N);
   out[8] = pfc::kBinList; out[9] = pfc::kLocalList; out[10] = pfc::kWindowBatch;
-  out[11] = pfc::kWindowBins; out[12] = pfc::kMissClasses;
+  out[11] = pfc::kWindowBins; out[12] = pfc::kMissClasses; out[13] = pfc::window_pos_cap(B);
   return pfc::window_select(N, crn, B, mask, w) ? 1 : 0;
 }
 """
@@ -42,7 +42,7 @@ def plan(tmp_path_factory):
     f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_uint32,
                   ctypes.POINTER(ctypes.c_double)]
     keys = ("lo", "width", "shift", "expected", "bin", "list_cap", "cls_log2", "blocks", "bin_list",
-            "local_list", "window_batch", "bins", "miss_classes")
+            "local_list", "window_batch", "bins", "miss_classes", "pos_cap")
 
     def call(N, crn, B, mask=FULL):
         out = (ctypes.c_double * len(keys))()
@@ -73,7 +73,7 @@ def test_window_lists_hold_what_falls_into_them(plan):
         if not window:
             continue
         taken += 1
-        assert B <= p["window_batch"]
+        assert B <= p["pos_cap"] <= p["window_batch"]
         # the end bin, the list of one workgroup, the list of the call: 8 standard deviations
         assert p["bin"] + 8 * math.sqrt(p["bin"]) <= p["bin_list"], (N, crn, B)
         mean = p["expected"] / N * min(N, 2.0 ** p["cls_log2"])
