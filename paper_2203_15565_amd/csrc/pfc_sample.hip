@@ -68,6 +68,10 @@ __device__ __forceinline__ uint64_t select_key(uint32_t score, uint32_t id) {
 // and lists its key if its score lies in the window (the first part lists it too, not knowing the
 // batch).  Integer atomics only: the counts do not depend on the order, and the lists are read as
 // sets.
+// The counts of the workgroups' classes are added up in LDS first: with ids in the order of the classes'
+// frequency one range of them owns thousands of the batch's classes, whose atomics on its one count queue
+// up (2,059,906 classes without negatives, labels dense in the low ids: 16,384 samples 52 -> 39 us,
+// 65,536 114 -> 78; spread evenly 38 -> 36 and 75 -> 66).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void sample_scan_kernel(
     int64_t N, PhiloxKey key, Window win, SampleScratch sc, int cls_log2, int nblk,
@@ -75,7 +79,14 @@ __global__ __launch_bounds__(kThreads) void sample_scan_kernel(
   const uint32_t par = sc.st->next & 1u;
   SampleHdr* hdr = &sc.st->hdr[par];
   const int lane = threadIdx.x & 63;
+  __shared__ uint64_t s_list[kLocalList];
   if ((int)blockIdx.x >= nblk) {   // marking part of the launch
+    uint32_t* s_pos = reinterpret_cast<uint32_t*>(s_list);
+    const bool gather = nblk <= kMaxBlocks;
+    if (gather) {
+      for (int b = threadIdx.x; b < nblk; b += kThreads) s_pos[b] = 0u;
+      __syncthreads();
+    }
     const int i = ((int)blockIdx.x - nblk) * kThreads + threadIdx.x;
     const int64_t y = i < B ? labels[i] : 0;
     const bool valid = i < B && y >= 0 && y < N;
@@ -90,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void sample_scan_kernel(
         philox_block((uint32_t)(y >> 2), key, u);
         const uint32_t uy = u[y & 3];
         above = win.above(uy);
-        atomicAdd(&sc.blk_pos[par][y >> cls_log2], above ? 0x10000u : 1u);
+        atomicAdd(gather ? &s_pos[y >> cls_log2] : &sc.blk_pos[par][y >> cls_log2], above ? 0x10000u : 1u);
         if (win.inside(uy)) {
           const uint32_t p = atomicAdd(&hdr->npos, 1u);
           if (p < sc.pos_cap) sc.pos_list[par][p] = select_key(uy, (uint32_t)y);
@@ -102,9 +113,13 @@ __global__ __launch_bounds__(kThreads) void sample_scan_kernel(
       if (nf) atomicAdd(&hdr->U, nf);
       if (na) atomicAdd(&hdr->pos_above, na);
     }
+    if (gather) {
+      __syncthreads();
+      for (int b = threadIdx.x; b < nblk; b += kThreads)
+        if (s_pos[b]) atomicAdd(&sc.blk_pos[par][b], s_pos[b]);
+    }
     return;
   }
-  __shared__ uint64_t s_list[kLocalList];
   __shared__ uint32_t s_n, s_base, sm[4];
   if (threadIdx.x == 0) s_n = 0u;
   __syncthreads();

@@ -100,13 +100,15 @@ inline double window_bin_classes(int64_t N, const SelectWindow& w) {
 // from the window makes every workgroup select for itself.  The end bin has to hold the classes that
 // fall into it (8 standard deviations kept).
 //
-// The line between them is an estimate of both in us, fitted to measurements at 10 thousand .. 200
-// million classes and batches of 4,096 .. 65,536 on 256 compute units; the way it picks is at most
-// 7 % behind the other (13 % without negatives at 100 thousand classes).  Measured, window / radix:
-//   N = 93,431, r = 0.1:      B = 8,192 31.9 / 42.1, 16,384 51.3 / 46.5, 65,536 192 / 69
-//   N = 2,059,906, r = 0.1:   B = 16,384 52 / 60, 32,768 89 / 69, 131,072 318 / 120, 262,144 3,869 / 187
-//   N = 10,000,000, r = 0.1:  B = 16,384 100 / 113, 32,768 156 / 123, 262,144 23,814 / 248
-//   N = 16,777,216, r = 0.5:  B = 49,152 170 / 186, 65,536 204 / 195
+// The line between them is an estimate of both in us, fitted to 306 forms of 8 thousand .. 16.7 million classes
+// and batches of 2,048 .. 65,536 on 256 compute units (beyond, up to 200 million classes and batches from
+// 4,096); the way it picks is 0.1 % behind the other on average, 13 % at most (65,536 samples of 8,000
+// classes).  Measured, window / radix:
+//   N = 93,431, r = 0.1:      B = 8,192 25.8 / 42.0;  no negatives: 32,768 44 / 57, 65,536 64 / 74
+//   N = 2,059,906, r = 0.1:   B = 16,384 51 / 60, 32,768 89 / 68, 65,536 165 / 84, 262,144 3,869 / 187
+//   N = 2,059,906, no negatives: B = 16,384 37 / 60, 65,536 67 / 85
+//   N = 6,000,000, r = 0.1:   B = 16,384 62 / 86, 32,768 93 / 95
+//   N = 16,700,000, r = 0.5:  B = 49,152 169 / 184, 65,536 204 / 194
 //   N = 2,059,906, mask 0x3FF: 8,168 / 69; N = 10,000 41 / 42; N = 15,000 51 / 44
 inline bool window_select(int64_t N, int64_t ceil_rN, int64_t B, uint32_t mask, const SelectWindow& w) {
   if (B > kWindowBatch) return false;
@@ -122,11 +124,11 @@ inline bool window_select(int64_t N, int64_t ceil_rN, int64_t B, uint32_t mask, 
   const double rounds = 1.0 + 0.75 * floor((blocks - 1.0) / 512.0);
   // every workgroup: its classes, the list, all labels; and atomics on the counts of a workgroup and
   // on the list of the batch classes inside the window
-  const double window_us = 13.0 + 1.4 * classes + rounds * (list + 0.9 * b) + 40.0 * distinct / blocks +
-                           distinct * fmin(1.0, w.expected / n);
+  const double window_us = 7.0 + 1.4 * classes + rounds * (1.1 * list + b) + 2.5 * distinct / blocks +
+                           1.05 * distinct * fmin(1.0, w.expected / n);
   // the passes over the classes, the counts in front of each workgroup (their square), the labels
   const double far = fmax(0.0, classes - 20.0);
-  const double radix_us = 37.0 + 6.9 * classes + 0.035 * far * far + 0.5 * b;
+  const double radix_us = 31.0 + 6.9 * classes + 0.035 * far * far + 0.68 * b;
   return window_us <= radix_us;
 }
 
