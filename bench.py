@@ -50,15 +50,13 @@ def algorithmic_work(B: int, D: int, k: int, precision: int) -> dict:
     gemm = 2.0 * B * D * k
     return {
         "gemm_logits": ("mfma", gemm),
-        "gemm_dweight": ("mfma", gemm),
-        "gemm_dfeatures": ("mfma", gemm),
-        "gather_normalize_w": ("hbm", k * D * (4 + es) + 4.0 * k),
+        # sampled centers and features in (fp32) and out (operand type), and 1/|w|, 1/|x|
+        "gather_normalize_w": ("hbm", (k + B) * D * (4.0 + es) + 4.0 * (k + B)),
         "update": ("hbm", 5.0 * k * D * 4),
-        # the dweight GEMM that ends in the update of its rows: E and Xs in, W and v in and out;
-        # its 2*B*D*k flops need less time at the MFMA peak than these bytes at the HBM peak
-        "gemm_dweight_update": ("hbm", float(B) * k * es + float(B) * D * es + 4.0 * k * D * 4),
-        # both backward products in one launch, and the same with the update of the rows
+        # both backward products in one launch
         "gemm_backward": ("mfma", 2.0 * gemm),
+        # the same with the update of the rows: E, Xs and Wn in, W and v in and out; its 4*B*D*k flops
+        # need less time at the MFMA peak than these bytes at the HBM peak
         "gemm_backward_update": ("hbm", float(B) * k * es + float(B) * D * es + float(k) * D * es
                                  + 4.0 * k * D * 4),
     }

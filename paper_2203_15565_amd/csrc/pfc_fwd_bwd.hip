@@ -67,9 +67,10 @@ constexpr float kEpsSin2 = 1e-12f;
 //
 // Row length: the caller's arrays (X, W, v, dX, dWn) have rows of D floats, D a multiple of 64.
 // The library's own GEMM operands (Xn, Xs, Wn and the dfeatures partial sums) have rows of
-// Dp >= D elements, D rounded up to 128, the columns from D on being zero, so that the GEMMs only
-// ever see whole tiles; a wavefront walks a row in NC chunks of 256 columns, and kernels that touch
-// the caller's rows skip the columns from D on.
+// Dp >= D elements, D rounded up to 128 (to 256 where the backward launch takes 256-tiles), the
+// columns from D on being zero, so that the GEMMs only ever see whole tiles; a wavefront walks a
+// row in NC chunks of 256 columns, and kernels that touch the caller's rows skip the columns from
+// D on.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NC>
 __device__ __forceinline__ void normalize_x_row(int i, const float* __restrict__ X, int B, int D,
@@ -670,7 +671,7 @@ __global__ void row_combine_kernel(int head_blocks, const float* __restrict__ ro
 }
 
 // ---------------------------------------------------------------------------------------------
-// dfeatures: slice `sp` of S: part[sp][i][d] = sum_{j in slice} E[i][j] * Wn[j][d]
+// dfeatures_tile (in gemm_backward): slice `sp` of S: part[sp][i][d] = sum_{j in slice} E[i][j] * Wn[j][d]
 // (A = E with k contiguous, B = Wn k-major).
 // ---------------------------------------------------------------------------------------------
 // Products of one uninterrupted sum (gemm_tile's CHAIN) in the two backward products with fp32 operands.
@@ -714,7 +715,7 @@ __device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
 }
 
 // ---------------------------------------------------------------------------------------------
-// gemm_dweight: dWn[j][d] = sum_i E[i][j] * Xs[i][d] (both operands k-major); rows j < k are
+// dweight_tile (in gemm_backward): dWn[j][d] = sum_i E[i][j] * Xs[i][d] (both operands k-major); rows j < k are
 // written.  When k is small and the batch large (the regime without extra negatives, Sec. 3.3)
 // there are too few tiles to fill the GPU: SPLIT cuts the batch (the reduction) into slices that
 // write partial tiles, summed in fixed order by dweight_reduce.  Xs has rows of Dp elements; the
@@ -811,7 +812,7 @@ __global__ void dweight_reduce_kernel(const float* __restrict__ part, int splits
   *reinterpret_cast<float4*>(dW + e4 * 4) = a;
 }
 
-// dweight_label: dWn[y] += sum over samples i with label y of dlabel_i * xn_i.
+// dweight_label_block (in gradients_final, or dweight_label in a launch of its own): dWn[y] += sum over samples i with label y of dlabel_i * xn_i.
 // Block i does the whole sum for its class if i is the first sample carrying that label
 // (head[y] == i, found with an integer atomicMin by row_combine).  The
 // matching samples are listed in ascending order; thread group g (one float4 column per thread)
@@ -855,7 +856,7 @@ __device__ __forceinline__ void dweight_label_block(
     p_end = min(B, (w + 1) * kLabelWindow);
   }
   if (head[y] != i) return;   // an earlier sample carries this label and does the sum
-  const int cols = D >> 2;                 // float4 columns: 64 .. 256
+  const int cols = D >> 2;                 // float4 columns: 16 .. 256
   const int G = kLabelThreads / cols;      // thread groups
   const int col = t % cols, g = t / cols;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -964,7 +965,8 @@ __global__ void dweight_label_combine_kernel(int B, int D, const int32_t* __rest
 }
 
 // ---------------------------------------------------------------------------------------------
-// gemm_dweight_update (fused step): the dweight GEMM on tiles that span all D columns, followed
+// fused_update_tile (in gemm_backward_update, fused step): the dweight product on tiles that span all D
+// columns, followed
 // in the same workgroup by the SGD-momentum update of the tile's rows (Eq. 3; text after Eq. 4),
 // so dWn is never written to memory: dWn_j = GEMM row + label part, g = (dWn - <dWn,wn> wn)/|w|,
 // v <- mu v + g, W <- W - lr v, with the arithmetic of update_kernel in the same order.
@@ -1135,7 +1137,7 @@ __global__ __launch_bounds__(CfgB::THREADS) void gemm_backward_update_kernel(
                             Xs, k, kp, Bp, idx, head, lab, spare, W, V, N, lr, mu, err_flag);
 }
 
-// dfeatures_final: WPS wavefronts per sample.
+// dfeatures_final_block (in gradients_final): WPS wavefronts per sample.
 //   g  = (s/(B l_i)) * sum_slices part + dlabel_i * wn_{y_i}        (dL/d xn_i)
 //   dx = (g - <g, xn_i> xn_i) / |x_i|
 template <int NC, int WPS>
@@ -1274,8 +1276,8 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
 // 64 registers: two workgroups on a compute unit.  Step, two launches -> one: 128 x 1,000 x 512 fp32 59.9 ->
 // 56.1 us, 512 x 9,344 x 512 104.4 -> 101.0, 256 x 25,723 x 128 79.5 -> 74.1, 768 x 20,599 x 1024 277 ->
 // 271, 16,384 samples x 3,592 476 -> 462.
-// From kFinalWideSplits slices on a sample gets 16 wavefronts instead of 4: below, most of the 16 would
-// have no slice to add.
+// From kFinalWideSplits slices on a sample gets 16 wavefronts instead of 4: below, a third of the 16 and more
+// would have no slice to add.
 constexpr int kFinalWideSplits = 12;
 template <int NC, int WPS, LabelMode MODE>
 __global__ __launch_bounds__(kLabelThreads, 8) void gradients_final_kernel(

@@ -3,6 +3,7 @@ bookkeeping and its refusal of more than one GPU."""
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 
@@ -26,12 +27,18 @@ def test_algorithmic_work_of_the_headline_step():
     import bench
     B, D, k = 1024, 512, 205_991
     w = bench.algorithmic_work(B, D, k, 1)
-    for name in ("gemm_logits", "gemm_dweight", "gemm_dfeatures"):
-        assert w[name] == ("mfma", 2.0 * B * D * k)
+    assert w["gemm_logits"] == ("mfma", 2.0 * B * D * k)
+    assert w["gemm_backward"] == ("mfma", 4.0 * B * D * k)        # both backward products
     assert w["update"] == ("hbm", 5.0 * k * D * 4)
-    assert w["gather_normalize_w"] == ("hbm", k * D * 6 + 4.0 * k)
-    # fused kernel: E and Xs (bf16) in, W and v (fp32) in and out
-    assert w["gemm_dweight_update"] == ("hbm", B * k * 2.0 + B * D * 2.0 + 4.0 * k * D * 4)
+    # centers and features: fp32 in, bf16 out, one norm each
+    assert w["gather_normalize_w"] == ("hbm", (k + B) * D * 6 + 4.0 * (k + B))
+    # fused kernel: E, Xs and Wn (bf16) in, W and v (fp32) in and out
+    assert w["gemm_backward_update"] == (
+        "hbm", B * k * 2.0 + B * D * 2.0 + k * D * 2.0 + 4.0 * k * D * 4)
+    # no entry but for kernels that the library reports
+    text = open(os.path.join(ROOT, "paper_2203_15565_amd", "csrc", "pfc_api.hip")).read()
+    names = re.findall(r'"(\w+)"', text[text.index("kKernelNames[KID_COUNT] = {"):].split("};")[0])
+    assert set(w) <= set(names)
 
 
 def test_workload_table_matches_the_benchmark_configurations():
