@@ -779,15 +779,18 @@ __device__ __forceinline__ void dweight_tile(
 // samples x 9,344 classes x 512), large ones lose the last round of dweight tiles and have all
 // compute units store their tiles at the same time (291 + 219 us, 495 together at 1024 x 205,991 x
 // 512).  The dfeatures workgroups are the longest and start first; dx_shape says how many there are.
+// (Large batches can have the longer reduction in dweight: its workgroups are then in front, w_first of them.)
 template <class CfgX, class CfgW, bool SPLIT, bool PIECES>
 __global__ __launch_bounds__(CfgX::THREADS) void gemm_backward_kernel(
     const typename CfgX::elem* __restrict__ E, const typename CfgX::elem* __restrict__ Wn,
     const typename CfgX::elem* __restrict__ Xs, int D, int Dp, int64_t k, int64_t kp, int Bp,
     DxShape dx, float* __restrict__ dXpart, float* __restrict__ dWout, int tiles_j, int tiles_d,
-    int slabs_per, int splits) {
+    int slabs_per, int splits,
+    int w_first) {
   static_assert(CfgX::THREADS == CfgW::THREADS, "one launch shape");
   extern __shared__ __align__(16) char smem[];
-  const int b = blockIdx.x;
+  // (an offset that is no multiple of 8 turns all ids to other XCDs alike)
+  const int b = (int)blockIdx.x < w_first ? (int)blockIdx.x + dx.wgs : (int)blockIdx.x - w_first;
   if (b < dx.wgs)
     dfeatures_tile<CfgX, PIECES>(b, smem, E, Wn, Dp, Bp, kp, dx, dXpart);
   else
@@ -1308,7 +1311,8 @@ struct Tiles {
   using W = TileCfg<T, BM, BN, WM, WN, true, true>;     // dweight: classes x columns
   using X = TileCfg<T, BM, BN, WM, WN, false, true>;    // dfeatures: samples x columns
   static constexpr int BACK_LDS = X::LDS_BYTES > W::LDS_BYTES ? X::LDS_BYTES : W::LDS_BYTES;
-  static constexpr bool PIECES = sizeof(T) == 4;         // sums in pieces (kDxSumSteps)
+  // sums in pieces (kDxSumSteps); a 256-tile has no registers for them
+  static constexpr bool PIECES = sizeof(T) == 4 && BM < 256;
 };
 
 template <class S>
@@ -1343,7 +1347,6 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   using CfgUS = TileCfg<T, 64, 512, 1, 8, true, true, 128>;   // its tiles for the last round
   using Big = Tiles<T, 256, 256, 2, 4>;
   using Mid = Tiles<T, 128, 128, 2, 4>;
-  using BigBack = std::conditional_t<sizeof(T) == 2, Big, Mid>;   // fp32: backward_tiles never asks for it
   using Small = Tiles<T, 64, 64, 2, 2>;
   constexpr int kFusedLds =
       std::max({FusedUpdateLds<CfgU>::LDS, FusedUpdateLds<CfgUS>::LDS, Big::X::LDS_BYTES});
@@ -1377,7 +1380,7 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     int rc = set_lds_limits_logits(Big{});
     if (rc == PFC_OK) rc = set_lds_limits_logits(Mid{});
     if (rc == PFC_OK) rc = set_lds_limits_logits(Small{});
-    if (rc == PFC_OK) rc = set_lds_limits_backward(BigBack{});
+    if (rc == PFC_OK) rc = set_lds_limits_backward(Big{});
     if (rc == PFC_OK) rc = set_lds_limits_backward(Mid{});
     if (rc == PFC_OK) rc = set_lds_limits_backward(Small{});
     if (rc != PFC_OK) return rc;
@@ -1471,9 +1474,10 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     auto kernel = nsp > 1      ? gemm_backward_kernel<CX, CW, true, kPieces>
                   : plain_sums ? gemm_backward_kernel<CX, CW, false, false>
                                : gemm_backward_kernel<CX, CW, false, kPieces>;
-    PFC_LAUNCH(c, KID_GEMM_BACKWARD, kernel, dim3((unsigned)(dx.wgs + tiles_j * tiles_d * nsp)),
-               dim3(CX::THREADS), lds, E, Wn, Xs, D, Dp, k, kp, Bp, dx, c->dXpart, dst, tiles_j,
-               tiles_d, slabs_per, nsp);
+    const int wgs_w = tiles_j * tiles_d * nsp;
+    PFC_LAUNCH(c, KID_GEMM_BACKWARD, kernel, dim3((unsigned)(dx.wgs + wgs_w)), dim3(CX::THREADS), lds, E,
+               Wn, Xs, D, Dp, k, kp, Bp, dx, c->dXpart, dst, tiles_j, tiles_d, slabs_per, nsp,
+               shape.dw_first ? wgs_w : 0);
     if (nsp > 1) {
       PFC_LAUNCH(c, KID_DW_REDUCE, dweight_reduce_kernel,
                  dim3((unsigned)((k * D / 4 + 255) / 256)), dim3(256), 0, dst, nsp, k, kp, D, Dp,
@@ -1502,7 +1506,7 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   DxShape dx;
   int rc;
   if (!one_kernel) {
-    rc = size_b == TILES_256   ? launch_backward(BigBack{}, dx)
+    rc = size_b == TILES_256   ? launch_backward(Big{}, dx)
          : size_b == TILES_128 ? launch_backward(Mid{}, dx)
                                : launch_backward(Small{}, dx);
     if (rc == PFC_OK) rc = launch_final(dx, true, nullptr);

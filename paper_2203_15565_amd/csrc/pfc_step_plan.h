@@ -3,6 +3,7 @@
 // CPU over everything that the entry points accept.
 #pragma once
 
+#include <limits.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -31,6 +32,112 @@ inline int dweight_slices(int cu, int tiles, int Bp, int64_t kp, int bk) {
                                                         // for its own partial tile
   return want < 1 ? 1 : want;
 }
+
+// Geometry of the tiles: reduction steps of a slab.
+inline int tile_bk(int es) { return 128 / es; }
+
+// Whether the one-kernel form of the fused call takes the class set: its tile (128 classes x 512 columns)
+// spans the rows, and there is at least one for every compute unit.
+inline bool fits_one_kernel(int cu, int D, int64_t kp) { return D == 512 && kp / 128 >= cu; }
+
+// ---------------------------------------------------------------------------------------------
+// Large batches: 256-tiles, one workgroup to a compute unit, and both reductions so long that the slices
+// decide how evenly the launch ends.  With slices by number alone (dfeatures half of the GPU, the batch
+// cut only below one tile for every compute unit) 4096 samples x 20,000 classes x 512 in bf16 made 128
+// workgroups of 79 slabs and 158 of 64: 286 on 256 compute units, two rounds.
+// ---------------------------------------------------------------------------------------------
+constexpr int kLongBatch = 2048;      // up to here slices are short and the rules below measured no slower
+constexpr int kLongRoom = 3;          // partial tiles of either product for every compute unit, at most
+constexpr int kMaxLongSplits = 16;    // slices of the classes
+constexpr int kPlainSum = 2048, kMaxPlainSum = 4096;   // products of one fp32 sum without pieces: where
+                                                       // the room allows it / at most
+
+// Slabs until the last compute unit is done: `na` workgroups of `a` slabs each, then `nb` of `b` <= a,
+// each to the compute unit that is free first.
+inline int64_t launch_slabs(int64_t cu, int64_t na, int64_t a, int64_t nb, int64_t b) {
+  const int64_t late = na % cu, t0 = na / cu * a, t1 = t0 + a;   // cu - late are free at t0, late at t1
+  auto room = [&](int64_t t) {
+    return (cu - late) * ((t - t0) / b) + (t >= t1 ? late * ((t - t1) / b) : 0);
+  };
+  int64_t end = late ? t1 : t0;
+  if (nb == 0 || room(end) >= nb) return end;   // b <= a: whatever ends by t1 fits in front of it
+  // the end is t0 or t1 plus whole workgroups; no earlier than the mean
+  const int64_t mean = (na * a + nb * b + cu - 1) / cu;
+  int64_t i0 = std::max<int64_t>((mean - t0) / b, 0), i1 = std::max<int64_t>((mean - t1) / b, 0);
+  for (;;) {
+    const int64_t e0 = t0 + i0 * b, e1 = t1 + i1 * b;
+    const bool first = !late || e0 <= e1;
+    const int64_t t = first ? e0 : e1;
+    if (t >= end && room(t) >= nb) return t;
+    ++(first ? i0 : i1);
+  }
+}
+
+// Whether there is room for fp32 sums of at most `most` products.
+inline bool plain_sums_fit(int cu, int Bp, int Dp, int64_t kp, int most) {
+  const int64_t w = (Bp + most - 1) / most, x = (kp + most - 1) / most;
+  const int64_t tiles_w = kp / 256 * (Dp / 256), tiles_x = (int64_t)(Bp / 256) * (Dp / 256);
+  const int64_t room = (int64_t)kLongRoom * cu;
+  return w <= kMaxSplits && x <= kMaxLongSplits &&
+         (w == 1 || (w * tiles_w <= room && w * kp <= (int64_t)kMaxSplits * Bp)) &&
+         (x == 1 || x * tiles_x <= room);
+}
+
+// Slices of the classes (dfeatures) and of the batch (dweight), and which product's workgroups start first.
+struct LongSlices {
+  int dx, dw;
+  bool dw_first;
+  bool even;   // the launch ends at most a fifth later than with the slabs spread over all compute units
+};
+
+// The fewest microseconds by an estimate: a slab of a 256-tile takes 1.45 us (bf16; start and end of a
+// workgroup like 10 slabs) or 7.7 us (fp32, 2 slabs), a partial tile of dfeatures 0.06 us to add up later, one
+// of dweight 0.05, the result likewise, and the launch that does it 3 us.  Fitted to 45 forms of 2,100 .. 65,536 samples, 2,000 .. 30,000
+// classes, D 128 .. 1024 and all slices that fit (7,730 measurements): the pick is 0.5 % behind the best of
+// a form on average, 3 % at most.  Against the rules for smaller batches (us, both products):
+//   bf16 4096 x 20,000 x 512 217 -> 179, 3000 x 20,000 x 512 166 -> 136, 8192 x 20,000 x 512 423 -> 315,
+//     4096 x 20,000 x 1024 338 -> 304, 16,384 x 3,592 x 512 141 -> 130
+//   fp32 (128- and 64-tiles in pieces -> 256) 16,384 x 3,000 x 512 1076 -> 797, 8192 x 16,000 x 512 2239 ->
+//     2003, 8192 x 5,000 x 512 815 -> 678, 4096 x 20,000 x 512 1508 -> 1341, 3000 x 8,000 x 512 480 -> 419
+// fp32 sums run without pieces here: only slices of at most kPlainSum products are taken, or kMaxPlainSum
+// where those do not fit (the caller sees to it that there are such).  Error against 64 bits, 2-norm, both
+// gradients, slices by number alone -> now: 16,384 x 15,700 x 512 7.6e-7 -> 6.2e-7, 8192 x 8,100 x 512 7.7e-7 ->
+// 6.9e-7, 4096 x 8,000 x 1024 3.3e-7 -> 2.9e-7.
+inline LongSlices long_batch_slices(int cu, int es, int Bp, int Dp, int64_t kp) {
+  const int bk = tile_bk(es);
+  const int slabs_w = Bp / bk, slabs_x = (int)(kp / bk);
+  const int64_t tiles_w = kp / 256 * (Dp / 256), tiles_x = (int64_t)(Bp / 256) * (Dp / 256);
+  const int64_t room = (int64_t)kLongRoom * cu, edge = es == 2 ? 10 : 2;
+  const int most = es == 2 ? INT_MAX : plain_sums_fit(cu, Bp, Dp, kp, kPlainSum) ? kPlainSum : kMaxPlainSum;
+  const double slab_us = es == 2 ? 1.45 : 7.7, dw_tile_us = 0.05, dx_tile_us = 0.06;
+  const int64_t work = tiles_w * slabs_w + tiles_x * slabs_x;
+  LongSlices best = {0, 0, false, false};
+  double best_us = 0;
+  for (int w = 1; w <= kMaxSplits && w * 8 <= slabs_w; ++w) {
+    if (w > 1 && (w * tiles_w > room || w * kp > (int64_t)kMaxSplits * Bp)) break;
+    const int per_w = (slabs_w + w - 1) / w, n_w = (slabs_w + per_w - 1) / per_w;
+    if (n_w != w || per_w * bk > most) continue;
+    for (int x = 1; x <= kMaxLongSplits && (x == 1 || x * 4 <= slabs_x); ++x) {
+      if (x > 1 && x * tiles_x > room) break;
+      const int per_x = (slabs_x + x - 1) / x, n_x = (slabs_x + per_x - 1) / per_x;
+      if (n_x != x || (int64_t)per_x * bk > most) continue;
+      const bool dw_first = per_w > per_x;
+      const int64_t slabs = dw_first ? launch_slabs(cu, w * tiles_w, per_w + edge, x * tiles_x, per_x + edge)
+                                     : launch_slabs(cu, x * tiles_x, per_x + edge, w * tiles_w, per_w + edge);
+      const double us = slab_us * slabs + dx_tile_us * x * tiles_x +
+                        (w > 1 ? dw_tile_us * (w + 1) * tiles_w + 3.0 : 0.0);
+      if (best.dw == 0 || us < best_us) {
+        best = {x, w, dw_first, (slabs - edge) * cu * 5 <= work * 6};
+        best_us = us;
+      }
+    }
+  }
+  return best;
+}
+
+// Whether the backward launch of the call takes them, given 256-tiles.  Not the class sets of the one-kernel
+// form, whose dX has the same bits in either call and whose many tiles come out even.
+inline bool long_batch(int cu, int D, int Bp, int64_t kp) { return Bp > kLongBatch && !fits_one_kernel(cu, D, kp); }
 
 // Size of the GEMM tiles, one for the logits and one for the backward launch of a call.  256 x 256
 // moves the least data per flop and fills a compute unit with one workgroup, 128 x 128 puts two on
@@ -69,6 +176,12 @@ inline TileSize backward_tiles(int cu, int es, int B, int64_t kp, int D) {
   const int Bp = (int)round_up(B, 128), Bp256 = (int)round_up(B, 256);
   const int Dp = (int)round_up(D, kPadD), Dp256 = (int)round_up(D, 256);
   const int64_t mid = kp / 128 * (Dp / 128), big = kp / 256 * (Dp256 / 256);
+  // (fp32, large batches: the 256-tile reads half as much from LDS for every product; 2100 x 3,000 x 512 140 / 144
+  // us with 10 % of the batch padding, 4096 x 9,000 x 320 529 / 624 with a third of the columns, 2500 x 40,000 x
+  // 256 890 / 954 with a fourth of the compute units idle)
+  if (es == 4 && long_batch(cu, D, Bp256, kp) && Dp256 * 100 <= Dp * 115 && Bp256 * 100 <= B * 105 &&
+      plain_sums_fit(cu, Bp256, Dp256, kp, kMaxPlainSum) && long_batch_slices(cu, es, Bp256, Dp256, kp).even)
+    return TILES_256;
   if (es == 4)
     return even_rounds(mid * dweight_slices(cu, (int)mid, Bp, kp, 32), cu) ? TILES_128 : TILES_64;
   // (columns: 640 -> 768 and 896 -> 1024 cost less than the smaller tile, 384 -> 512 more)
@@ -78,21 +191,28 @@ inline TileSize backward_tiles(int cu, int es, int B, int64_t kp, int D) {
   return B > 128 || 2 * mid > cu ? TILES_128 : TILES_64;
 }
 
-// Geometry of the tiles: reduction steps of a slab, workgroups that a compute unit holds.
-inline int tile_bk(int es) { return 128 / es; }
+// Workgroups that a compute unit holds.
 inline int tiles_per_cu(TileSize t, int es) {
   return t == TILES_256 ? 1 : t == TILES_128 ? 2 : es == 2 ? 3 : 4;
 }
-
-// Whether the one-kernel form of the fused call takes the class set: its tile (128 classes x 512 columns)
-// spans the rows, and there is at least one for every compute unit.
-inline bool fits_one_kernel(int cu, int D, int64_t kp) { return D == 512 && kp / 128 >= cu; }
 
 // The dfeatures product: slices of S, and workgroups of one tile and slice each.
 struct DxShape {
   int slabs_total, slabs_per, splits, tiles_i, tiles_d;
   int wgs;   // workgroups: tiles_i * tiles_d * splits, rounded up to 8
 };
+
+// `want` slices of the classes, at least one slab each.
+inline DxShape dx_cut(int es, TileSize t, int Bp, int Dp, int64_t kp, int64_t want) {
+  DxShape dx;
+  dx.tiles_i = Bp / t;
+  dx.tiles_d = Dp / t;
+  dx.slabs_total = (int)(kp / tile_bk(es));
+  dx.slabs_per = (int)((dx.slabs_total + want - 1) / want);
+  dx.splits = (dx.slabs_total + dx.slabs_per - 1) / dx.slabs_per;
+  dx.wgs = (int)round_up((int64_t)dx.tiles_i * dx.tiles_d * dx.splits, 8);
+  return dx;
+}
 
 // About `wgs` workgroups, at least 4 slabs each.  The callers ask
 // for half of what the GPU holds at a time, or for all the room that the dweight tiles leave:
@@ -101,36 +221,37 @@ struct DxShape {
 // x 205,991 1162 / 1098 / 1161.  Fewer workgroups write fewer partial sums (2 MB a slice there)
 // but are longer than everything behind them.
 inline DxShape dx_shape(int cu, int es, TileSize t, int Bp, int Dp, int D, int64_t kp, int64_t wgs) {
-  DxShape dx;
-  dx.tiles_i = Bp / t;
-  dx.tiles_d = Dp / t;
-  dx.slabs_total = (int)(kp / tile_bk(es));
-  int64_t want = wgs / (dx.tiles_i * dx.tiles_d);
+  const int slabs_total = (int)(kp / tile_bk(es));
+  int64_t want = wgs / ((int64_t)(Bp / t) * (Dp / t));
   // fp32 sums that are not cut into pieces: slices of more than 4096 classes are halved, for the
   // rounding of the sums (100 samples x 400,000 classes dX 2.81e-7 off, halved 2.70e-7) and, fused, for
   // workgroups that are not the end of the launch (4.23 -> 3.18 ms; 512 x 200,000 2.85 -> 2.92)
   const bool halve = es == 4 && fits_one_kernel(cu, D, kp) && kp > (int64_t)kMaxSplits * 4096;
-  want = std::min<int64_t>({want, halve ? 2 * kMaxSplits : kMaxSplits, dx.slabs_total / 4});
-  if (want < 1) want = 1;
-  dx.slabs_per = (int)((dx.slabs_total + want - 1) / want);
-  dx.splits = (dx.slabs_total + dx.slabs_per - 1) / dx.slabs_per;
-  dx.wgs = (int)round_up((int64_t)dx.tiles_i * dx.tiles_d * dx.splits, 8);
-  return dx;
+  want = std::min<int64_t>({want, halve ? 2 * kMaxSplits : kMaxSplits, slabs_total / 4});
+  return dx_cut(es, t, Bp, Dp, kp, want < 1 ? 1 : want);
 }
 
 // Slices of the batch in the dweight product, and the shape of the dfeatures product beside it
 // (the same with and without the update, so that dX has the same bits).
 struct BackwardShape {
   int slabs_per, splits;   // of the batch
+  bool dw_first;           // the dweight workgroups are the longer ones and start first
   DxShape dx;
 };
 inline BackwardShape backward_shape(int cu, int es, TileSize t, int Bp, int Dp, int D, int64_t kp) {
   BackwardShape s;
   const int tiles_w = (int)(kp / t) * (Dp / t);
   const int slabs_total = Bp / tile_bk(es);
-  const int want = dweight_slices(cu, tiles_w, Bp, kp, tile_bk(es));
+  const LongSlices cut = t == TILES_256 && long_batch(cu, D, Bp, kp) ? long_batch_slices(cu, es, Bp, Dp, kp)
+                                                                     : LongSlices{0, 0, false, false};
+  const int want = cut.dw ? cut.dw : dweight_slices(cu, tiles_w, Bp, kp, tile_bk(es));
+  s.dw_first = cut.dw_first;
   s.slabs_per = (slabs_total + want - 1) / want;
   s.splits = (slabs_total + s.slabs_per - 1) / s.slabs_per;
+  if (cut.dw) {
+    s.dx = dx_cut(es, t, Bp, Dp, kp, cut.dx);
+    return s;
+  }
   const int64_t slots = (int64_t)cu * tiles_per_cu(t, es);
   const int64_t wgs_w = (int64_t)tiles_w * s.splits;
   // fp32 tiles take long: dfeatures workgroups no longer than those, so that the end comes out even
@@ -145,10 +266,14 @@ inline BackwardShape backward_shape(int cu, int es, TileSize t, int Bp, int Dp, 
 // ---------------------------------------------------------------------------------------------
 // Partial sums of the backward launch: those of dfeatures in front, those of a dweight product cut over
 // the batch behind.  A product is cut only as far as its workgroups fill the GPU, so either stays
-// below one 256 x 256 tile for every compute unit, or is one copy of its result.
+// below one 256 x 256 tile for every compute unit (large batches: kLongRoom of them), or is one copy of
+// its result.
 inline int64_t part_floats(int cu, int D, int B_max) {
   const int64_t Bp = round_up(B_max, kPadB), Dp = round_up(D, 256), all = (int64_t)cu * 256 * 256;
-  return std::min(2 * kMaxSplits * Bp * Dp, std::max(all, Bp * Dp) + all);
+  const int64_t any = std::min(2 * kMaxSplits * Bp * Dp, std::max(all, Bp * Dp) + all);
+  if (Bp <= kLongBatch) return any;
+  return std::max(any, std::min((kMaxLongSplits + kMaxSplits) * Bp * Dp,
+                                std::max(kLongRoom * all, Bp * Dp) + kLongRoom * all));
 }
 
 // Partial row sums of the logits: one for every sample and tile.  64-tiles are taken only for few tiles.

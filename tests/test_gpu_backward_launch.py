@@ -30,6 +30,11 @@ CASES = [
     (16_000, 1_000, 512, 1.0),  # 256-tiles everywhere, batch ends inside a tile
     (9_000, 300, 640, 1.0),     # fp32: 64-tiles, bf16: 128-tiles; five column tiles
     (8_192, 256, 512, 1.0),     # fp32: exactly one 128-tile per compute unit
+    # batches above 2048, 256-tiles in both precisions:
+    (3_000, 8_100, 512, 1.0),   # batch and classes cut, dweight in front, last slices shorter
+    (16_100, 4_000, 512, 1.0),  # batch in one piece, dweight in front
+    (2_000, 4_096, 768, 1.0),   # dfeatures in front; three column tiles
+    (5_000, 2_250, 1_024, 1.0),  # bf16: batch in one piece
 ]
 
 

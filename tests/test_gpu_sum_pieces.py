@@ -3,7 +3,8 @@
 All features are one vector and all centers another one orthogonal to it, so every entry of a gradient
 is a sum of equal terms: the worst case of a running sum, whose roundings all go the same way inside a
 power of two (16,384 of them in one chain come out up to 2e-4 off).  The sums run in pieces of 256
-(dfeatures) and 512 (dweight) products."""
+(dfeatures) and 512 (dweight) products, or, with the 256-tiles of large batches, in slices of at most 4096
+that are added afterwards."""
 import math
 
 import numpy as np
@@ -17,9 +18,12 @@ pytestmark = pytest.mark.gpu
 U = 2.0 ** -24   # half an ulp
 
 
-# 128-tiles in one slice, 64-tiles, 128-tiles with the batch cut into slices
-@pytest.mark.parametrize("B,k,D", [(16_384, 15_000, 256), (4_096, 33_000, 64), (16_384, 3_000, 256)])
-def test_sums_of_equal_terms(B, k, D):
+# 128-tiles with the batch in one slice, 64-tiles, 128-tiles with the batch cut into slices: in pieces.
+# 256-tiles: the classes in four slices, or the batch in many.
+@pytest.mark.parametrize("B,k,D,piece_w,piece_x", [
+    (2_048, 16_000, 512, 512, 256), (4_096, 33_000, 64, 512, 256), (16_384, 3_000, 128, 512, 256),
+    (16_384, 15_000, 256, 4_096, 4_096), (16_384, 3_000, 256, 4_096, 4_096)])
+def test_sums_of_equal_terms(B, k, D, piece_w, piece_x):
     s, m = 64.0, 1.5
     rng = np.random.default_rng(B + k)
     x, w = np.zeros(D, np.float32), np.zeros(D, np.float32)
@@ -49,7 +53,7 @@ def test_sums_of_equal_terms(B, k, D):
         g = got[:, torch.from_numpy(sel).cuda()].double().cpu().numpy()
         return float(np.max(np.abs(g / want[sel] - 1.0)))
     # a piece, the sum of the pieces, at most 64 slices, and 16 roundings of the factors
-    assert off(dW[1:], want_W) <= (512 + B / 512 + 64 + 16) * U
+    assert off(dW[1:], want_W) <= (piece_w + B / piece_w + 64 + 16) * U
     # the label part takes cos(m) = 7 % of the sum away
-    assert off(dX, want_X) <= (256 + k / 256 + 64 + 16) * U / (1 - math.cos(m))
+    assert off(dX, want_X) <= (piece_x + k / piece_x + 64 + 16) * U / (1 - math.cos(m))
     assert (dX[:, : D // 2].abs().max() <= 1e-6 * dX.abs().max()).item()
