@@ -1343,7 +1343,7 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
         float* dW_out, float* stats_out, const UpdateArgs* upd) {
   // fused dweight + update: 128 classes x all 512 columns, half-size slabs so that the wide
   // operand fits; this one-kernel form exists for D == 512 only
-  using CfgU = TileCfg<T, 128, 512, 2, 4, true, true, 64>;
+  using CfgU = TileCfg<T, 128, 512, 2, 4, true, true, 64, 4, 4>;
   using CfgUS = TileCfg<T, 64, 512, 1, 8, true, true, 128>;   // its tiles for the last round
   using Big = Tiles<T, 256, 256, 2, 4>;
   using Mid = Tiles<T, 128, 128, 2, 4>;

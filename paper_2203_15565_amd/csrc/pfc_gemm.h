@@ -11,15 +11,14 @@
 // producers: the main loop has no bounds checks.
 //
 // A workgroup of WM x WN wavefronts (64 lanes each) owns a BM x BN tile of C.  K is walked in
-// slabs of BK = 64 (bf16) or 32 (fp32) reduction steps, double buffered in LDS; slab s+1 waits in
-// the second LDS stage and the global loads of slab s+2 are in flight in registers while slab s
-// is multiplied.
+// slabs of BK = 64 (bf16) or 32 (fp32) reduction steps.  bf16 operands go from global memory to LDS
+// without registers (gemm_tile_dma); fp32 operands through registers, double buffered in LDS, slab s+1
+// waiting in the second LDS stage and the global loads of slab s+2 in flight while slab s is multiplied.
 //
-// LDS layouts of one operand slab (R = BM or BN rows of the operand tile):
+// LDS layouts of one fp32 operand slab (R = BM or BN rows of the operand tile; bf16: DmaLds):
 //   k contiguous: R rows of 128 bytes, row stride 144: a 16-byte fragment read by 16 consecutive
 //                 rows touches every bank once.
-//   k-major:      BK rows of R*sizeof(T) bytes, row stride + 64: the four k-rows that one
-//                 transpose read gathers fall into different banks.
+//   k-major:      BK rows of R*sizeof(T) bytes, row stride + 64.
 //
 // Fragment convention (the same for A and B, which is all a dot product needs): a group of 16
 // (bf16) or 8 (fp32) reduction steps is split between the lane halves, lanes 0..31 taking the
@@ -56,13 +55,15 @@ struct OperandLds {
   static constexpr int CHUNKS = ROWS * CHUNKS_PER_ROW;                           // 16-byte chunks
 };
 
-template <typename T, int BM_, int BN_, int WM_, int WN_, bool AKM, bool BKM, int SLAB = 128>
+template <typename T, int BM_, int BN_, int WM_, int WN_, bool AKM, bool BKM, int SLAB = 128, int ABUF_ = 3,
+          int BBUF_ = 2>
 struct TileCfg {
   using elem = T;
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr bool A_KMAJOR = AKM, B_KMAJOR = BKM;
   static constexpr int BK = SLAB / (int)sizeof(T);   // reduction steps per slab
   static constexpr int GROUPS = SLAB / 32;           // reduction groups (fragment reads) per slab
+  static constexpr int SLAB_BYTES = SLAB, ABUF = ABUF_, BBUF = BBUF_;   // slabs of A and B in LDS (bf16)
   static constexpr int THREADS = WM * WN * 64;
   static constexpr int WTM = BM / WM, WTN = BN / WN;       // tile of one wavefront
   static constexpr int TM = WTM / 32, TN = WTN / 32;       // 32x32 blocks per wavefront
@@ -70,7 +71,8 @@ struct TileCfg {
   using LB = OperandLds<T, BN, BKM, SLAB>;
   static constexpr int A_BYTES = LA::BYTES, B_BYTES = LB::BYTES;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  static constexpr int LDS_BYTES = 2 * STAGE_BYTES;
+  static constexpr bool DMA = sizeof(T) == 2;
+  static constexpr int LDS_BYTES = DMA ? (ABUF * BM + BBUF * BN) * SLAB : 2 * STAGE_BYTES;
   static constexpr int A_CHUNKS = LA::CHUNKS / THREADS;    // 16-byte chunks per thread per slab
   static constexpr int B_CHUNKS = LB::CHUNKS / THREADS;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be whole 32x32 blocks");
@@ -157,31 +159,16 @@ struct Stager {
   }
 };
 
-// One 16-byte MFMA fragment of 32 tile rows starting at row `r0`, reduction group `g`
-// (16 steps for bf16, 8 for fp32), from an operand slab in LDS.
+// One 16-byte MFMA fragment of 32 tile rows starting at row `r0`, reduction group `g` (8 steps), from an
+// fp32 operand slab in LDS.
 template <typename T, class L, bool KMAJOR>
 __device__ __forceinline__ u32x4 read_frag(const char* region, int r0, int g) {
   const int lane = threadIdx.x & 63;
   if constexpr (!KMAJOR) {
     return *reinterpret_cast<const u32x4*>(region + (r0 + (lane & 31)) * L::STRIDE + g * 32 +
                                            (lane >> 5) * 16);
-  } else if constexpr (sizeof(T) == 2) {
-    // ds_read_b64_tr_b16: inside each group of 16 lanes, lane s addresses the 4 consecutive tile
-    // rows r0' + 4*(s%4).. of reduction step k0 + s/4, and lane i receives tile row r0' + i for
-    // the 4 steps k0..k0+3.  Lane groups: (rows 0..15 | 16..31) x (first | second half of the group).
-    const int grp = lane >> 4, s = lane & 15;
-    const int k0 = g * 16 + (grp >> 1) * 8 + (s >> 2);
-    const int col = r0 + (grp & 1) * 16 + (s & 3) * 4;
-    const char* p = region + k0 * L::STRIDE + col * 2;
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * L::STRIDE));
-    const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
-    u32x4 r;
-    r[0] = l2[0]; r[1] = l2[1]; r[2] = h2[0]; r[3] = h2[1];
-    return r;
   } else {
-    // fp32: four scalar reads, reduction steps g*8 + half*4 + 0..3 of tile row r0 + lane%32
+    // four scalar reads, reduction steps g*8 + half*4 + 0..3 of tile row r0 + lane%32
     const char* p = region + (g * 8 + (lane >> 5) * 4) * L::STRIDE + (r0 + (lane & 31)) * 4;
     u32x4 r;
     r[0] = *reinterpret_cast<const uint32_t*>(p);
@@ -242,11 +229,225 @@ __device__ __forceinline__ void add_acc(f32x16 (&to)[Cfg::TM][Cfg::TN],
       for (int r = 0; r < 16; ++r) to[a][b][r] += acc[a][b][r];
 }
 
+// ---------------------------------------------------------------------------------------------
+// bf16 operands: global memory -> LDS without registers (global_load_lds_dwordx4).
+// ---------------------------------------------------------------------------------------------
+// A wavefront's load fills 1 KB of consecutive LDS (16 bytes a lane), so rows cannot be padded; what keeps
+// the fragment reads off each other's banks is the order of the 16-byte chunks inside a row, chosen by the
+// lane's global address:
+//   k contiguous: chunk c of row r lies at position c ^ (r/2 % 8): a fragment read by 16 consecutive rows
+//                 touches every bank once.
+//   k-major:      likewise for units of 64 bytes, so that the four k-rows of one transpose read fall into
+//                 different banks.
+template <typename T, int R, bool KMAJOR, int SLAB>
+struct DmaLds {
+  static constexpr int BK = SLAB / (int)sizeof(T);
+  static constexpr int ROW_BYTES = KMAJOR ? R * (int)sizeof(T) : SLAB;
+  static constexpr int BYTES = (KMAJOR ? BK : R) * ROW_BYTES;
+  static constexpr int CPR = ROW_BYTES / 16;
+  static_assert(KMAJOR ? ROW_BYTES >= 128 : ROW_BYTES == 128, "what the order of the chunks is made for");
+  // what the position of a chunk of row r is xor-ed with
+  static __device__ __forceinline__ int turn(int r) {
+    if constexpr (!KMAJOR) return (r >> 1) & 7;
+    else return (ROW_BYTES >= 256 ? r & 3 : (r >> 1) & 1) * 4;
+  }
+};
+
+template <typename T, class L, int THREADS, bool KMAJOR>
+struct DmaStager {
+  static constexpr int NCH = L::BYTES / 16 / THREADS;        // loads per wavefront and slab
+  static constexpr int RPP = THREADS * 16 / L::ROW_BYTES;    // LDS rows that one load of every wavefront fills
+  static_assert(NCH >= 1 && L::BYTES % (THREADS * 16) == 0, "slab must divide evenly");
+  static_assert(RPP % (KMAJOR ? 4 : 16) == 0, "one order of the chunks for all loads of a lane");
+  const char* base;   // wave-uniform: first byte of the operand tile at the first k of the range
+  uint32_t toff;      // this lane's byte offset from there
+  int64_t pass, slab; // global byte steps between a lane's loads of one slab / between slabs (uniform)
+
+  __device__ __forceinline__ void init(const T* tile, int64_t ld) {
+    const int t = threadIdx.x;
+    const int row = t / L::CPR, ch = (t % L::CPR) ^ L::turn(row);
+    base = reinterpret_cast<const char*>(tile);
+    toff = (uint32_t)((int64_t)row * ld * (int64_t)sizeof(T) + ch * 16);
+    pass = (int64_t)RPP * ld * (int64_t)sizeof(T);
+    slab = KMAJOR ? (int64_t)L::BK * ld * (int64_t)sizeof(T) : (int64_t)L::BK * (int64_t)sizeof(T);
+  }
+  // Load p of slab s into the LDS region at byte `lds` (this wavefront's first byte there).
+  // Assembly, because the compiler makes every LDS read that follows the builtin wait for all loads in
+  // flight.  The load has no output register; who reads the region waits for it (dma_wait).  M0 needs a
+  // wait state before it is used.
+  __device__ __forceinline__ void load(int s, int p, uint32_t lds) const {
+    const uint64_t at = (uint64_t)(base + (int64_t)s * slab + p * pass);
+    const uint64_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(lds + p * THREADS * 16)), "v"(toff), "s"(g));
+  }
+};
+
+// Waits until at most N of this wavefront's loads are in flight and its LDS reads are back, then meets the
+// workgroup: what all wavefronts have loaded before is in LDS, what they have read may be overwritten.
+template <int N>
+__device__ __forceinline__ void dma_wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// Byte offsets of this lane's fragment reads in an operand slab.
+template <class L, bool KMAJOR, int GROUPS, int NB>
+struct FragAddr;
+template <class L, int GROUPS, int NB>
+struct FragAddr<L, false, GROUPS, NB> {
+  uint32_t a[GROUPS];   // of each reduction group; blocks of 32 rows follow at constant distances
+  __device__ __forceinline__ void init(int r0) {
+    const int lane = threadIdx.x & 63, row = r0 + (lane & 31);
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) a[g] = row * L::ROW_BYTES + (((g * 2 + (lane >> 5)) ^ L::turn(row)) * 16);
+  }
+  __device__ __forceinline__ u32x4 read(const char* region, int b, int g) const {
+    return *reinterpret_cast<const u32x4*>(region + a[g] + b * 32 * L::ROW_BYTES);
+  }
+};
+template <class L, int GROUPS, int NB>
+struct FragAddr<L, true, GROUPS, NB> {
+  uint32_t a[NB];       // of each block of 32 rows; groups follow at constant distances
+  __device__ __forceinline__ void init(int r0) {
+    // ds_read_b64_tr_b16: inside each group of 16 lanes, lane s addresses the 4 consecutive tile
+    // rows r0' + 4*(s%4).. of reduction step k0 + s/4, and lane i receives tile row r0' + i for
+    // the 4 steps k0..k0+3.  Lane groups: (rows 0..15 | 16..31) x (first | second half of the group).
+    const int lane = threadIdx.x & 63, grp = lane >> 4, s = lane & 15;
+    const int k0 = (grp >> 1) * 8 + (s >> 2);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int byte = (r0 + b * 32 + (grp & 1) * 16 + (s & 3) * 4) * 2;
+      a[b] = k0 * L::ROW_BYTES + (((byte >> 4) ^ L::turn(k0)) << 4) + (byte & 15);
+    }
+  }
+  __device__ __forceinline__ u32x4 read(const char* region, int b, int g) const {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const char* p = region + a[b] + g * 16 * L::ROW_BYTES;
+    // (four k-rows further the order of the chunks is the same)
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * L::ROW_BYTES));
+    const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+    u32x4 r;
+    r[0] = l2[0]; r[1] = l2[1]; r[2] = h2[0]; r[3] = h2[1];
+    return r;
+  }
+};
+
+// gemm_tile (below) for bf16 operands.  LDS holds ABUF slabs of A and BBUF of B:
+//   * the barrier in front of the last group of slab s frees its buffers (all fragments are read by then)
+//     and publishes slab s+1; behind it B of slab s+BBUF and A of slab s+ABUF are requested, one load
+//     between two MFMAs, so a load has BBUF - 1 (A: ABUF - 1) whole slabs of MFMAs to arrive;
+//   * fragments are read one group ahead, the last group is multiplied behind the barrier.
+// Against staging through registers (two stages of 64 steps, 8 ds_write_b128 a wavefront and slab), both in
+// turn, us: logits 1024 x 205,991 x 512 296 -> 276, both backward products there 450 -> 401, 1024 x
+// 360,232 766 -> 690, 16,384 x 3,592 125 -> 113; products alone, 256 tiles of 256 x 256 over 6,400 steps,
+// 1.00 - 1.17 -> 1.28 - 1.36 PFLOP/s (both k contiguous), 1.03 -> 1.21 (both k-major), 0.97 -> 1.07 (dfeatures).
+// What bounds it now, by counters and variants of the loop: both k contiguous, the matrix cores are busy 82 %
+// of the cycles at 1.46 GHz, the clock that the power leaves; with operands from HBM (dfeatures: 57 % at
+// 1.76 GHz) the loads are: a compute unit's misses return in order, at about 33 GB/s whatever is
+// requested earlier (waits taken out: the same; requesting lines of later slabs by one of the workgroups that
+// share them: 17 % slower; rows of E stored in blocks of 64 classes: the same).
+template <class Cfg>
+__device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restrict__ A, int64_t lda,
+                                              const typename Cfg::elem* __restrict__ B, int64_t ldb, int nslabs,
+                                              char* smem, f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
+  using T = typename Cfg::elem;
+  typedef DmaLds<T, Cfg::BM, Cfg::A_KMAJOR, Cfg::SLAB_BYTES> LA;
+  typedef DmaLds<T, Cfg::BN, Cfg::B_KMAJOR, Cfg::SLAB_BYTES> LB;
+  constexpr int ABUF = Cfg::ABUF, BBUF = Cfg::BBUF;
+  static_assert(ABUF == BBUF || ABUF == BBUF + 1, "the counts of loads in flight");
+  typedef DmaStager<T, LA, Cfg::THREADS, Cfg::A_KMAJOR> SA;
+  typedef DmaStager<T, LB, Cfg::THREADS, Cfg::B_KMAJOR> SB;
+  constexpr int NA = SA::NCH, NB = SB::NCH, MM = Cfg::TM * Cfg::TN, HEAD = Cfg::GROUPS - 1;
+  // loads that may be in flight when slab s+1 (or slab 0) has to be there, nothing being left out at the end
+  constexpr int FLY = ABUF == BBUF ? (BBUF - 2) * (NA + NB) : (BBUF - 1) * NA + (BBUF - 2) * NB;
+  constexpr int FLY0 = (BBUF - 1) * (NA + NB) + (ABUF - BBUF) * NA;
+  const int wave = threadIdx.x >> 6;
+  const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
+  SA sa;
+  SB sb;
+  sa.init(A, lda);
+  sb.init(B, ldb);
+  FragAddr<LA, Cfg::A_KMAJOR, Cfg::GROUPS, Cfg::TM> ra;
+  FragAddr<LB, Cfg::B_KMAJOR, Cfg::GROUPS, Cfg::TN> rb;
+  ra.init(wm * Cfg::WTM);
+  rb.init(wn * Cfg::WTN);
+  constexpr uint32_t B0 = ABUF * LA::BYTES;   // the B buffers lie behind those of A
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem +
+                       __builtin_amdgcn_readfirstlane(wave) * 1024;
+  const int last = nslabs - 1;
+  auto load_a = [&](int s, int p, uint32_t buf) { sa.load(s, p, lds + buf); };
+  auto load_b = [&](int s, int p, uint32_t buf) { sb.load(s, p, lds + B0 + buf); };
+#pragma unroll
+  for (int u = 0; u < ABUF; ++u) {
+    if (u > last) break;
+    if (u < BBUF) {
+#pragma unroll
+      for (int p = 0; p < NB; ++p) load_b(u, p, u * LB::BYTES);
+    }
+#pragma unroll
+    for (int p = 0; p < NA; ++p) load_a(u, p, u * LA::BYTES);
+  }
+  if (last >= ABUF - 1) dma_wait_barrier<FLY0>();
+  else dma_wait_barrier<0>();
+
+  Frags<Cfg> fc;
+  auto read = [&](uint32_t abuf, uint32_t bbuf, int g, Frags<Cfg>& f) {
+#pragma unroll
+    for (int b = 0; b < Cfg::TM; ++b) f.a[b] = ra.read(smem + abuf, b, g);
+#pragma unroll
+    for (int b = 0; b < Cfg::TN; ++b) f.b[b] = rb.read(smem + B0 + bbuf, b, g);
+  };
+  read(0, 0, 0, fc);
+  uint32_t ab = 0, bb = 0, ab_before = 0;   // buffers of slab s; that of A of slab s-1
+  for (int s = 0; s <= last; ++s) {
+    const bool more_a = s > 0 && s - 1 + ABUF <= last, more_b = s + BBUF <= last;
+#pragma unroll
+    for (int g = 0; g < HEAD; ++g) {
+      Frags<Cfg> fn;
+      read(ab, bb, g + 1, fn);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < MM; ++q) {
+        if (g == 0) {
+#pragma unroll
+          for (int c = 0; c < NA; ++c)
+            if (c * MM / NA == q && more_a) load_a(s - 1 + ABUF, c, ab_before);
+        }
+        mfma_group<T>(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      fc = fn;
+    }
+    if (s - 1 + ABUF <= last) dma_wait_barrier<FLY>();
+    else dma_wait_barrier<0>();
+    ab_before = ab;
+    const uint32_t bb_before = bb;
+    ab = ab == (ABUF - 1) * LA::BYTES ? 0 : ab + LA::BYTES;
+    bb = bb == (BBUF - 1) * LB::BYTES ? 0 : bb + LB::BYTES;
+    Frags<Cfg> fn;
+    read(ab, bb, 0, fn);   // (behind the last slab: a buffer's old contents, not used)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < MM; ++q) {
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+        if (c * MM / NB == q && more_b) load_b(s + BBUF, c, bb_before);
+      mfma_group<T>(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    fc = fn;
+  }
+  __syncthreads();
+}
+
 // Accumulate acc += A_tile * B_tile^T over `nslabs` slabs of K.
 //   A: element (first of this workgroup's BM tile rows, first reduction step of its range)
 //   B: likewise for its BN tile rows;  lda / ldb in elements.
 //   smem: Cfg::LDS_BYTES bytes, 16-byte aligned.  Ends with a barrier (smem may be reused).
-// Software pipeline (two LDS stages, one register set, global loads two slabs ahead):
+// Software pipeline with fp32 operands (two LDS stages, one register set, global loads two slabs ahead):
 //   * at the top of iteration s the registers hold slab s+1, loaded during iteration s-1, so it
 //     has had a whole iteration to arrive; it goes to the idle LDS stage at once, and the barrier
 //     at the end of the iteration publishes it;
@@ -268,6 +469,10 @@ __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__
   using T = typename Cfg::elem;
   using LA = typename Cfg::LA;
   using LB = typename Cfg::LB;
+  if constexpr (Cfg::DMA) {
+    gemm_tile_dma<Cfg>(A, lda, B, ldb, nslabs, smem, acc);
+    return;
+  }
   const int wave = threadIdx.x >> 6;
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
 
