@@ -354,7 +354,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
 
   constexpr bool kStage = (sizeof(T) == 2);          // bf16: transpose the tile through LDS
   constexpr int SX = Cfg::BM * 2 + 8;                // staging row (one sample) stride in bytes
-  constexpr int RED_OFF = Cfg::BN * SX;              // cross-wave reduction scratch behind it
+  constexpr int RED_OFF = kStage ? Cfg::BN * SX : 0; // cross-wave reduction scratch behind it
   static_assert(RED_OFF + 2 * Cfg::WM * Cfg::BN * 4 <= Cfg::LDS_BYTES, "epilogue LDS");
   static_assert(!logits_chained<Cfg>() || 2 * Cfg::BN * 2 <= 2 * Cfg::WM * Cfg::BN, "chain LDS");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -676,10 +676,7 @@ __global__ void row_combine_kernel(int head_blocks, const float* __restrict__ ro
 // ---------------------------------------------------------------------------------------------
 // Products of one uninterrupted sum (gemm_tile's CHAIN) in the two backward products with fp32 operands.
 // Their 128- and 64-tiles need fewer slices than 256-tiles to fill the GPU, and a slice of many thousand
-// products adds up rounding errors: 8192 samples x 8,120 classes x 512 in one slice is 7.7e-7 off (2-norm, both
-// gradients, against 64 bits), in the four slices of 256-tiles 6.9e-7, with these pieces 6.7e-7.  They cost
-// 0 - 1 % of a step (1000 x 50,000 x 320 1041 -> 1047 us; batches cut into slices up to 3 %, 4096 x 3,990 x 512 474 ->
-// 490), as many slices as 256-tiles take up to 18 %.
+// products adds up rounding errors.  The pieces cost 0 - 3 % of a step, as many slices as 256-tiles take up to 18 %.
 constexpr int kDxSumSteps = 256, kDwSumSteps = 512;
 template <class Cfg, int STEPS, bool PIECES>
 constexpr int sum_slabs() { return PIECES ? STEPS / Cfg::BK : 0; }
@@ -781,7 +778,7 @@ __device__ __forceinline__ void dweight_tile(
 // 512).  The dfeatures workgroups are the longest and start first; dx_shape says how many there are.
 // (Large batches can have the longer reduction in dweight: its workgroups are then in front, w_first of them.)
 template <class CfgX, class CfgW, bool SPLIT, bool PIECES>
-__global__ __launch_bounds__(CfgX::THREADS) void gemm_backward_kernel(
+__global__ __launch_bounds__(CfgX::THREADS, CfgX::MIN_WAVES) void gemm_backward_kernel(
     const typename CfgX::elem* __restrict__ E, const typename CfgX::elem* __restrict__ Wn,
     const typename CfgX::elem* __restrict__ Xs, int D, int Dp, int64_t k, int64_t kp, int Bp,
     DxShape dx, float* __restrict__ dXpart, float* __restrict__ dWout, int tiles_j, int tiles_d,

@@ -12,48 +12,38 @@
 //
 // A workgroup of WM x WN wavefronts (64 lanes each) owns a BM x BN tile of C.  K is walked in
 // slabs of BK = 64 (bf16) or 32 (fp32) reduction steps.  bf16 operands go from global memory to LDS
-// without registers (gemm_tile_dma); fp32 operands through registers, double buffered in LDS, slab s+1
-// waiting in the second LDS stage and the global loads of slab s+2 in flight while slab s is multiplied.
+// without registers (gemm_tile_dma).  fp32 operands are split into planes of 16 bits on the way
+// (gemm_tile_split): three bf16 planes and six products, or for the logits two fp16 planes and three.
 //
-// LDS layouts of one fp32 operand slab (R = BM or BN rows of the operand tile; bf16: DmaLds):
-//   k contiguous: R rows of 128 bytes, row stride 144: a 16-byte fragment read by 16 consecutive
-//                 rows touches every bank once.
-//   k-major:      BK rows of R*sizeof(T) bytes, row stride + 64.
-//
-// Fragment convention (the same for A and B, which is all a dot product needs): a group of 16
-// (bf16) or 8 (fp32) reduction steps is split between the lane halves, lanes 0..31 taking the
-// first half and lanes 32..63 the second; for bf16 that is one v_mfma_f32_32x32x16_bf16 per
-// group, for fp32 four v_mfma_f32_32x32x2_f32, the t-th of which pairs element t of every lane.
+// Fragment convention (the same for A and B, which is all a dot product needs): a group of 16 reduction
+// steps is split between the lane halves, lanes 0..31 taking the first half and lanes 32..63 the
+// second; one v_mfma_f32_32x32x16 per group.
 //
 // Accumulator layout of a 32x32 block (16 floats per lane): register r of lane l holds
 //   row = (r / 4) * 8 + (l / 32) * 4 + (r % 4),  col = l % 32.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "pfc_common.h"
 
 namespace pfc {
 
+struct SplitUnit;
+struct SplitBf16;
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-
-// Geometry of one operand slab in LDS.
-// SLAB: bytes of K per operand row per slab (128, or 64 for tiles whose wide operand would not fit).
-template <typename T, int R, bool KMAJOR, int SLAB>
-struct OperandLds {
-  static constexpr int SLAB_BYTES = SLAB;
-  static constexpr int BK = SLAB / (int)sizeof(T);
-  static constexpr int ROWS = KMAJOR ? BK : R;                                   // LDS rows
-  static constexpr int ROW_BYTES = KMAJOR ? R * (int)sizeof(T) : SLAB;     // payload
-  static constexpr int STRIDE = ROW_BYTES + (KMAJOR ? 64 : 16);                  // padded
-  static constexpr int BYTES = ROWS * STRIDE;
-  static constexpr int CHUNKS_PER_ROW = ROW_BYTES / 16;
-  static constexpr int CHUNKS = ROWS * CHUNKS_PER_ROW;                           // 16-byte chunks
-};
 
 template <typename T, int BM_, int BN_, int WM_, int WN_, bool AKM, bool BKM, int SLAB = 128, int ABUF_ = 3,
           int BBUF_ = 2>
@@ -65,118 +55,21 @@ struct TileCfg {
   static constexpr int GROUPS = SLAB / 32;           // reduction groups (fragment reads) per slab
   static constexpr int SLAB_BYTES = SLAB, ABUF = ABUF_, BBUF = BBUF_;   // slabs of A and B in LDS (bf16)
   static constexpr int THREADS = WM * WN * 64;
+  // two workgroups of 128-tiles on a compute unit: at most 128 registers
+  static constexpr int MIN_WAVES = BM == 128 && BN == 128 ? 4 : 1;
   static constexpr int WTM = BM / WM, WTN = BN / WN;       // tile of one wavefront
   static constexpr int TM = WTM / 32, TN = WTN / 32;       // 32x32 blocks per wavefront
-  using LA = OperandLds<T, BM, AKM, SLAB>;
-  using LB = OperandLds<T, BN, BKM, SLAB>;
-  static constexpr int A_BYTES = LA::BYTES, B_BYTES = LB::BYTES;
-  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   static constexpr bool DMA = sizeof(T) == 2;
-  static constexpr int LDS_BYTES = DMA ? (ABUF * BM + BBUF * BN) * SLAB : 2 * STAGE_BYTES;
-  static constexpr int A_CHUNKS = LA::CHUNKS / THREADS;    // 16-byte chunks per thread per slab
-  static constexpr int B_CHUNKS = LB::CHUNKS / THREADS;
+  // both operands k contiguous: the logits, products of unit vectors
+  using Split = std::conditional_t<!AKM && !BKM, SplitUnit, SplitBf16>;
+  static constexpr int PLANES = !AKM && !BKM ? 2 : 3;
+  static constexpr int LDS_BYTES = DMA ? (ABUF * BM + BBUF * BN) * SLAB : 2 * PLANES * 32 * (BM + BN);
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be whole 32x32 blocks");
-  static_assert(LA::CHUNKS % THREADS == 0 && LB::CHUNKS % THREADS == 0, "slab must divide evenly");
-  static_assert(THREADS % LA::CHUNKS_PER_ROW == 0 && THREADS % LB::CHUNKS_PER_ROW == 0,
-                "a staging pass must cover whole LDS rows");
 };
 
-template <typename T>
-__device__ __forceinline__ void mfma_group(const u32x4& a, const u32x4& b, f32x16& c);
-
-template <>
-__device__ __forceinline__ void mfma_group<__bf16>(const u32x4& a, const u32x4& b, f32x16& c) {
-  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                              __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-// fp32: elements 2 * HALF and 2 * HALF + 1 of the group.
-template <int HALF>
-__device__ __forceinline__ void mfma_half(const u32x4& a, const u32x4& b, f32x16& c) {
-  // whole-vector casts: a bit_cast applied to a single vector element reads element 0
-  const f32x4 af = __builtin_bit_cast(f32x4, a);
-  const f32x4 bf = __builtin_bit_cast(f32x4, b);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(af[2 * HALF], bf[2 * HALF], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_32x32x2f32(af[2 * HALF + 1], bf[2 * HALF + 1], c, 0, 0, 0);
-}
-
-template <>
-__device__ __forceinline__ void mfma_group<float>(const u32x4& a, const u32x4& b, f32x16& c) {
-  mfma_half<0>(a, b, c);
-  mfma_half<1>(a, b, c);
-}
-
-// Global -> register -> LDS staging of one operand slab.  Thread t owns chunk (t % CPR) of LDS
-// rows (t / CPR) + p * (THREADS / CPR), p = 0 .. NCH-1.  Addresses are a wave-uniform 64-bit
-// base (tile, slab, pass) plus one 32-bit per-thread offset, which lets the loads use the
-// scalar-base addressing form and keeps address registers out of the vector register budget.
-template <typename T, class L, int THREADS, int NCH, bool KMAJOR>
-struct Stager {
-  const char* base;   // wave-uniform: first byte of the operand tile at the first k of the range
-  uint32_t toff;      // this thread's byte offset from the pass base
-  int64_t pass;       // global byte step between passes (uniform)
-  int64_t slab;       // global byte step between slabs (uniform)
-  int lds;            // this thread's first LDS byte offset inside the operand region
-  static constexpr int RPP = THREADS / L::CHUNKS_PER_ROW;   // LDS rows per pass
-
-  // tile: element (row 0 of the operand tile, first k of the range); ld in elements.
-  __device__ __forceinline__ void init(const T* tile, int64_t ld) {
-    const int t = threadIdx.x;
-    const int row = t / L::CHUNKS_PER_ROW, ch = t % L::CHUNKS_PER_ROW;
-    // k contiguous: LDS row = tile row, advancing a slab moves 128 bytes along the row.
-    // k-major:      LDS row = reduction step, advancing a slab moves BK rows down.
-    base = reinterpret_cast<const char*>(tile);
-    toff = (uint32_t)((int64_t)row * ld * (int64_t)sizeof(T) + ch * 16);
-    pass = (int64_t)RPP * ld * (int64_t)sizeof(T);
-    slab = KMAJOR ? (int64_t)L::BK * ld * (int64_t)sizeof(T) : (int64_t)L::SLAB_BYTES;
-    lds = row * L::STRIDE + ch * 16;
-  }
-  // The chunks of one slab live in ONE vector value (not an array), so they are registers by
-  // construction whatever the control flow around the loads.
-  typedef uint32_t Regs __attribute__((ext_vector_type(NCH * 4)));
-  __device__ __forceinline__ Regs load(int s) const {
-    const char* sb = base + (int64_t)s * slab;
-    Regs r;
-#pragma unroll
-    for (int p = 0; p < NCH; ++p) {
-      const u32x4 t = *reinterpret_cast<const u32x4*>(sb + p * pass + toff);
-      r[4 * p + 0] = t[0]; r[4 * p + 1] = t[1]; r[4 * p + 2] = t[2]; r[4 * p + 3] = t[3];
-    }
-    return r;
-  }
-  // chunk p of slab s alone (lets the caller spread the loads of a slab between its MFMAs)
-  __device__ __forceinline__ void load_chunk(int s, int p, Regs& r) const {
-    const u32x4 t = *reinterpret_cast<const u32x4*>(base + (int64_t)s * slab + p * pass + toff);
-    r[4 * p + 0] = t[0]; r[4 * p + 1] = t[1]; r[4 * p + 2] = t[2]; r[4 * p + 3] = t[3];
-  }
-  __device__ __forceinline__ void store(char* region, const Regs& r) const {
-#pragma unroll
-    for (int p = 0; p < NCH; ++p) {
-      u32x4 t;
-      t[0] = r[4 * p + 0]; t[1] = r[4 * p + 1]; t[2] = r[4 * p + 2]; t[3] = r[4 * p + 3];
-      *reinterpret_cast<u32x4*>(region + lds + p * RPP * L::STRIDE) = t;
-    }
-  }
-};
-
-// One 16-byte MFMA fragment of 32 tile rows starting at row `r0`, reduction group `g` (8 steps), from an
-// fp32 operand slab in LDS.
-template <typename T, class L, bool KMAJOR>
-__device__ __forceinline__ u32x4 read_frag(const char* region, int r0, int g) {
-  const int lane = threadIdx.x & 63;
-  if constexpr (!KMAJOR) {
-    return *reinterpret_cast<const u32x4*>(region + (r0 + (lane & 31)) * L::STRIDE + g * 32 +
-                                           (lane >> 5) * 16);
-  } else {
-    // four scalar reads, reduction steps g*8 + half*4 + 0..3 of tile row r0 + lane%32
-    const char* p = region + (g * 8 + (lane >> 5) * 4) * L::STRIDE + (r0 + (lane & 31)) * 4;
-    u32x4 r;
-    r[0] = *reinterpret_cast<const uint32_t*>(p);
-    r[1] = *reinterpret_cast<const uint32_t*>(p + L::STRIDE);
-    r[2] = *reinterpret_cast<const uint32_t*>(p + 2 * L::STRIDE);
-    r[3] = *reinterpret_cast<const uint32_t*>(p + 3 * L::STRIDE);
-    return r;
-  }
+__device__ __forceinline__ void mfma_bf16(const u32x4& a, const u32x4& b, f32x16& c) {
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                              0, 0);
 }
 
 // The MFMA fragments of one reduction group for a whole wavefront tile.
@@ -185,28 +78,6 @@ struct Frags {
   u32x4 a[Cfg::TM];
   u32x4 b[Cfg::TN];
 };
-
-template <class Cfg>
-__device__ __forceinline__ void read_group(const char* stage, int g, int wm, int wn,
-                                           Frags<Cfg>& f) {
-  using T = typename Cfg::elem;
-#pragma unroll
-  for (int bm = 0; bm < Cfg::TM; ++bm)
-    f.a[bm] = read_frag<T, typename Cfg::LA, Cfg::A_KMAJOR>(stage, wm * Cfg::WTM + bm * 32, g);
-#pragma unroll
-  for (int bn = 0; bn < Cfg::TN; ++bn)
-    f.b[bn] = read_frag<T, typename Cfg::LB, Cfg::B_KMAJOR>(stage + Cfg::A_BYTES,
-                                                            wn * Cfg::WTN + bn * 32, g);
-}
-
-template <class Cfg>
-__device__ __forceinline__ void mma_group(const Frags<Cfg>& f, f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
-  using T = typename Cfg::elem;
-#pragma unroll
-  for (int bm = 0; bm < Cfg::TM; ++bm)
-#pragma unroll
-    for (int bn = 0; bn < Cfg::TN; ++bn) mfma_group<T>(f.a[bm], f.b[bn], acc[bm][bn]);
-}
 
 template <class Cfg>
 __device__ __forceinline__ void zero_acc(f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
@@ -245,10 +116,10 @@ struct DmaLds {
   static constexpr int ROW_BYTES = KMAJOR ? R * (int)sizeof(T) : SLAB;
   static constexpr int BYTES = (KMAJOR ? BK : R) * ROW_BYTES;
   static constexpr int CPR = ROW_BYTES / 16;
-  static_assert(KMAJOR ? ROW_BYTES >= 128 : ROW_BYTES == 128, "what the order of the chunks is made for");
+  static_assert(KMAJOR ? ROW_BYTES >= 128 : ROW_BYTES == 128 || ROW_BYTES == 32, "what the order of the chunks is made for");
   // what the position of a chunk of row r is xor-ed with
   static __device__ __forceinline__ int turn(int r) {
-    if constexpr (!KMAJOR) return (r >> 1) & 7;
+    if constexpr (!KMAJOR) return ROW_BYTES == 32 ? (r >> 3) & 1 : (r >> 1) & 7;
     else return (ROW_BYTES >= 256 ? r & 3 : (r >> 1) & 1) * 4;
   }
 };
@@ -416,7 +287,7 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
           for (int c = 0; c < NA; ++c)
             if (c * MM / NA == q && more_a) load_a(s - 1 + ABUF, c, ab_before);
         }
-        mfma_group<T>(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
+        mfma_bf16(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
       }
       __builtin_amdgcn_sched_barrier(0);
       fc = fn;
@@ -435,10 +306,230 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
 #pragma unroll
       for (int c = 0; c < NB; ++c)
         if (c * MM / NB == q && more_b) load_b(s + BBUF, c, bb_before);
-      mfma_group<T>(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
+      mfma_bf16(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
     }
     __builtin_amdgcn_sched_barrier(0);
     fc = fn;
+  }
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------------------------
+// fp32 operands, split into planes of 16 bits.
+// ---------------------------------------------------------------------------------------------
+// Any values: x = h + m + l in bf16, exactly, each rounded to nearest, so that a plane is at most 2^-9 of the one
+// above.  Of the nine products of two values six are added up; those left out (m l, l m, l l) are at most 2^-26.
+struct SplitBf16 {
+  static constexpr int PLANES = 3, PRODUCTS = 6;
+  static constexpr int A[PRODUCTS] = {0, 0, 0, 1, 2, 1}, B[PRODUCTS] = {0, 1, 2, 0, 0, 1};
+  static constexpr float UNSCALE = 1.f;
+  // words of one pair of neighbours in the planes; the remainders are exact, the dot instruction takes a plane
+  // off without widening it first (x - 1 * h + 0 * h')
+  static __device__ __forceinline__ void pair(float a, float b, uint32_t (&w)[PLANES]) {
+    // (the constants come from registers: as an inline constant of the instruction, (-1, 0) reads (0, -1))
+    uint32_t c_lo = 0x0000bf80u, c_hi = 0xbf800000u;
+    asm("" : "+s"(c_lo), "+s"(c_hi));
+    const bf16x2 lo = __builtin_bit_cast(bf16x2, c_lo), hi = __builtin_bit_cast(bf16x2, c_hi);
+#pragma unroll
+    for (int q = 0; q < PLANES; ++q) {
+      const bf16x2 v = __builtin_convertvector(f32x2{a, b}, bf16x2);
+      w[q] = __builtin_bit_cast(uint32_t, v);
+      if (q + 1 < PLANES) {
+        a = __builtin_amdgcn_fdot2_f32_bf16(v, lo, a, false);
+        b = __builtin_amdgcn_fdot2_f32_bf16(v, hi, b, false);
+      }
+    }
+  }
+  static __device__ __forceinline__ void mfma(const u32x4& a, const u32x4& b, f32x16& c) { mfma_bf16(a, b, c); }
+};
+
+// Components of unit vectors: 2^12 x = h + l in fp16, to 2^-23 of the value (2^-37 of the vector's length for small
+// ones); l l, at most 2^-24 of a product, is left out.
+struct SplitUnit {
+  static constexpr int PLANES = 2, PRODUCTS = 3;
+  static constexpr int A[PRODUCTS] = {0, 0, 1}, B[PRODUCTS] = {0, 1, 0};
+  static constexpr float SCALE = 4096.f, UNSCALE = 1.f / (SCALE * SCALE);
+  static __device__ __forceinline__ void pair(float a, float b, uint32_t (&w)[PLANES]) {
+    const f16x2 h = __builtin_convertvector(f32x2{a * SCALE, b * SCALE}, f16x2);
+    const f16x2 l = __builtin_convertvector(
+        f32x2{__builtin_fmaf(a, SCALE, -(float)h[0]), __builtin_fmaf(b, SCALE, -(float)h[1])}, f16x2);
+    w[0] = __builtin_bit_cast(uint32_t, h);
+    w[1] = __builtin_bit_cast(uint32_t, l);
+  }
+  static __device__ __forceinline__ void mfma(const u32x4& a, const u32x4& b, f32x16& c) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
+                                               0, 0);
+  }
+};
+
+// f(0th), .., f(last) with the index as a type: the bodies are whole before any loop optimisation.
+template <int FROM, class F, int... I>
+__device__ __forceinline__ void static_for_seq(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, FROM + I>{}), ...);
+}
+template <int FROM, int TO, class F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_seq<FROM>(std::make_integer_sequence<int, TO - FROM>{}, f);
+}
+// Pieces in front of product q when n of them are spread over `span` products from q0 on.
+constexpr int pieces_before(int q, int q0, int span, int n) {
+  const int p = q <= q0 ? 0 : ((q - q0) * n + span - 1) / span;
+  return p < n ? p : n;
+}
+
+// 8 neighbouring values of an operand that a thread splits in every slab.
+struct SplitChunk {
+  const float* src;     // at slab 0
+  int64_t step;         // floats from slab to slab
+  uint32_t dst, plane;  // LDS byte offset in a stage, and from plane to plane
+};
+template <class L, bool KMAJOR>
+__device__ __forceinline__ SplitChunk split_chunk(int c, const float* base, int64_t ld, uint32_t region) {
+  const int row = c / L::CPR, ch = c % L::CPR;
+  return {base + row * ld + ch * 8, KMAJOR ? 16 * ld : 16, region + row * L::ROW_BYTES + ((ch ^ L::turn(row)) * 16),
+          L::BYTES};
+}
+
+// gemm_tile (below) for fp32 operands.  LDS holds two stages of 16 reduction steps, each the planes of both operands
+// (layout: DmaLds).  Every thread loads 8 neighbouring values of an operand, one slab or more ahead, splits them
+// between the MFMAs of the slab at hand and stores one 16-byte chunk to each plane of the other stage; the last product
+// of a slab is added up behind the barrier, under the first fragment reads of the next one.
+// What it replaces: v_mfma_f32_32x32x2_f32, whose rate (157 TFLOP/s nominal) was the bound at any tile size; six bf16
+// products are 2.7 times that, three fp16 products 5.3 times.  Forward/backward, us, before -> now: 2048 x 30,000 x
+// 512 1588 -> 858, 1907 x 20,355 x 512 1134 -> 641, 512 x 9,344 x 512 163 -> 131, 1024 x 36,024 x 512 with the
+// update 1183 -> 701, 300 x 40,000 x 512 642 -> 278, 128 x 1,000 x 512 35.4 -> 34.7 (latency).
+// Error against 64 bits (2-norm), fp32 products -> now: feature gradient 512 x 9,344 x 512 6.4e-7 -> 4.2e-7, 64 x
+// 8,000 x 64 9.2e-7 -> 6.8e-7, 4096 x 8,000 x 512 6.8e-7 -> 4.4e-7; center gradient off the labels 2.9e-6 -> 1.9e-6,
+// 1.6e-6 -> 1.2e-6, 2.8e-6 -> 1.8e-6: an accumulator takes 3 or 6 roundings for 16 products instead of 8.
+// What bounds it: large problems the clock that the power leaves (1.1 PFLOP/s of 16-bit products), small ones
+// the way from global memory through registers and LDS to the fragments in every slab.
+template <class Cfg, int CHAIN>
+__device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int64_t lda,
+                                                const float* __restrict__ B, int64_t ldb, int nslabs, char* smem,
+                                                f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
+  typedef DmaLds<__bf16, Cfg::BM, Cfg::A_KMAJOR, 32> LA;   // a plane of 16 reduction steps
+  typedef DmaLds<__bf16, Cfg::BN, Cfg::B_KMAJOR, 32> LB;
+  typedef typename Cfg::Split S;
+  constexpr int NP = S::PLANES, NPR = S::PRODUCTS;
+  constexpr int STAGE = NP * (LA::BYTES + LB::BYTES), B0 = NP * LA::BYTES;
+  constexpr int CA = LA::BYTES / 16, CB = LB::BYTES / 16, THREADS = Cfg::THREADS;
+  constexpr int NPT = (CA + CB + THREADS - 1) / THREADS;   // chunks of 8 values per thread and slab
+  static_assert(CA % 64 == 0 && CB % 64 == 0, "a wavefront's chunks are of one operand");
+  constexpr int MM = Cfg::TM * Cfg::TN;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
+  FragAddr<LA, Cfg::A_KMAJOR, 1, Cfg::TM> ra;
+  FragAddr<LB, Cfg::B_KMAJOR, 1, Cfg::TN> rb;
+  ra.init(wm * Cfg::WTM);
+  rb.init(wn * Cfg::WTN);
+  // this thread's chunks: those of A first
+  SplitChunk ch[NPT];
+  bool has[NPT];
+#pragma unroll
+  for (int p = 0; p < NPT; ++p) {
+    const int first = wave * 64 + p * THREADS, id = first + (threadIdx.x & 63);
+    has[p] = first < CA + CB;
+    if (first < CA) ch[p] = split_chunk<LA, Cfg::A_KMAJOR>(id, A, lda, 0);
+    else ch[p] = split_chunk<LB, Cfg::B_KMAJOR>(has[p] ? id - CA : 0, B, ldb, B0);
+  }
+  const int last = nslabs * (Cfg::BK / 16) - 1;
+  // values of the next DEPTH slabs, requested as soon as those before them are split
+  constexpr int DEPTH = THREADS == 256 ? 4 : 1;   // (128-tiles: the registers of a second workgroup)
+  f32x4 x[DEPTH][NPT][2];
+  auto load = [&](int s, int u) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < NPT; ++p) {
+      if (NPT * THREADS > CA + CB && !has[p]) continue;
+      x[u][p][0] = *reinterpret_cast<const f32x4*>(ch[p].src + s * ch[p].step);
+      x[u][p][1] = *reinterpret_cast<const f32x4*>(ch[p].src + s * ch[p].step + 4);
+    }
+  };
+  u32x4 w[NPT][NP];
+  // pair i of this thread's chunks; the last of a chunk stores it to the stage
+  auto split = [&](int i, int u, char* stage) __attribute__((always_inline)) {
+    const int p = i / 4, e = i % 4;
+    uint32_t v[NP];
+    S::pair(x[u][p][e / 2][e % 2 * 2], x[u][p][e / 2][e % 2 * 2 + 1], v);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) w[p][q][e] = v[q];
+    if (e == 3) {
+      if (NPT * THREADS > CA + CB && !has[p]) return;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) *reinterpret_cast<u32x4*>(stage + ch[p].dst + q * ch[p].plane) = w[p][q];
+    }
+  };
+  u32x4 a[NP][Cfg::TM], b[NP][Cfg::TN];
+  auto read_a = [&](const char* stage, int q, u32x4 (&f)[Cfg::TM]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < Cfg::TM; ++t) f[t] = ra.read(stage + q * LA::BYTES, t, 0);
+  };
+  auto read_b = [&](const char* stage, int q, u32x4 (&f)[Cfg::TN]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < Cfg::TN; ++t) f[t] = rb.read(stage + B0 + q * LB::BYTES, t, 0);
+  };
+  load(0, 0);
+#pragma unroll
+  for (int u = 1; u < DEPTH; ++u) load(u < last ? u : last, u);
+#pragma unroll
+  for (int i = 0; i < 4 * NPT; ++i) split(i, 0, smem);
+  load(DEPTH < last ? DEPTH : last, 0);
+  __syncthreads();
+  read_a(smem, 0, a[0]);
+  read_b(smem, 0, b[0]);
+  f32x16 sums[Cfg::TM][Cfg::TN];
+  if constexpr (CHAIN > 0) zero_acc<Cfg>(sums);
+  for (int s0 = 0; s0 <= last; s0 += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      const int s = s0 + d, u = (d + 1) % DEPTH;   // set of slab s+1
+      if (s > last) break;
+      char* cur = smem + (s & 1) * STAGE;
+      char* nxt = smem + (~s & 1) * STAGE;
+#pragma unroll
+      for (int q = 1; q < NP; ++q) read_b(cur, q, b[q]);
+#pragma unroll
+      for (int q = 1; q < NP; ++q) read_a(cur, q, a[q]);
+      __builtin_amdgcn_sched_barrier(0);
+      // between the products of this slab the values of the next one are split, from the second product (the
+      // third of six) on
+      constexpr int Q = (NPR - 1) * MM, Q0 = NPR > 3 ? MM : 0, SPAN = NPR > 3 ? 3 * MM : Q;
+      static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value, t = q % MM, o = q / MM;
+        constexpr int from = pieces_before(q, Q0, SPAN, 4 * NPT), to = pieces_before(q + 1, Q0, SPAN, 4 * NPT);
+        static_for<from, to>([&](auto i) __attribute__((always_inline)) { split(decltype(i)::value, u, nxt); });
+        if constexpr (q == (NPR > 3 ? 4 * MM : Q - 1)) load(s + 1 + DEPTH < last ? s + 1 + DEPTH : last, u);
+        S::mfma(a[S::A[o]][t / Cfg::TN], b[S::B[o]][t % Cfg::TN], acc[t / Cfg::TN][t % Cfg::TN]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      __syncthreads();
+      u32x4 an[Cfg::TM], bn[Cfg::TN];
+      read_a(nxt, 0, an);
+      read_b(nxt, 0, bn);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < MM; ++t)
+        S::mfma(a[S::A[NPR - 1]][t / Cfg::TN], b[S::B[NPR - 1]][t % Cfg::TN], acc[t / Cfg::TN][t % Cfg::TN]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < Cfg::TM; ++t) a[0][t] = an[t];
+#pragma unroll
+      for (int t = 0; t < Cfg::TN; ++t) b[0][t] = bn[t];
+      if constexpr (CHAIN > 0) {
+        if ((s + 1) % (CHAIN * Cfg::BK / 16) == 0 && s < last) {
+          add_acc<Cfg>(sums, acc);
+          zero_acc<Cfg>(acc);
+        }
+      }
+    }
+  }
+  if constexpr (CHAIN > 0) add_acc<Cfg>(acc, sums);
+  if constexpr (S::UNSCALE != 1.f) {
+#pragma unroll
+    for (int i = 0; i < Cfg::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < Cfg::TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] *= S::UNSCALE;
   }
   __syncthreads();
 }
@@ -447,124 +538,16 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
 //   A: element (first of this workgroup's BM tile rows, first reduction step of its range)
 //   B: likewise for its BN tile rows;  lda / ldb in elements.
 //   smem: Cfg::LDS_BYTES bytes, 16-byte aligned.  Ends with a barrier (smem may be reused).
-// Software pipeline with fp32 operands (two LDS stages, one register set, global loads two slabs ahead):
-//   * at the top of iteration s the registers hold slab s+1, loaded during iteration s-1, so it
-//     has had a whole iteration to arrive; it goes to the idle LDS stage at once, and the barrier
-//     at the end of the iteration publishes it;
-//   * the loads of slab s+2 then refill the registers, issued one at a time between the MFMAs of
-//     the first groups: a wavefront that issues a whole slab in one burst queues up at the
-//     memory pipe (measured: up to 1400 cycles) with its MFMAs stuck behind the loads;
-//   * inside a slab the fragments of group g+1 are read from LDS while group g is multiplied;
-//   * the last group of a slab is multiplied AFTER the barrier, behind the first fragment reads
-//     of the next slab, so the LDS latency at the slab boundary is covered as well.
-// Slab numbers past the end are clamped to the last slab: such loads and LDS stores are
-// redundant but in bounds, and keep the loop body free of branches.
 // CHAIN > 0 (fp32): every CHAIN slabs the accumulators are added to a second set and start again from
-// zero, so that no sum is a chain of more than CHAIN * BK additions.
+// zero, so that no sum is a chain of more than CHAIN * BK products.
 template <class Cfg, int CHAIN = 0>
 __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__ A, int64_t lda,
                                           const typename Cfg::elem* __restrict__ B, int64_t ldb,
                                           int nslabs, char* smem,
                                           f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
-  using T = typename Cfg::elem;
-  using LA = typename Cfg::LA;
-  using LB = typename Cfg::LB;
-  if constexpr (Cfg::DMA) {
-    gemm_tile_dma<Cfg>(A, lda, B, ldb, nslabs, smem, acc);
-    return;
-  }
-  const int wave = threadIdx.x >> 6;
-  const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
-
-  typedef Stager<T, LA, Cfg::THREADS, Cfg::A_CHUNKS, Cfg::A_KMAJOR> SA;
-  typedef Stager<T, LB, Cfg::THREADS, Cfg::B_CHUNKS, Cfg::B_KMAJOR> SB;
-  SA sa;
-  SB sb;
-  sa.init(A, lda);
-  sb.init(B, ldb);
-  char* st0 = smem;
-  char* st1 = smem + Cfg::STAGE_BYTES;
-  const int last = nslabs - 1;
-  constexpr int NA = Cfg::A_CHUNKS, NL = Cfg::A_CHUNKS + Cfg::B_CHUNKS;
-  constexpr int MM = Cfg::TM * Cfg::TN;            // MFMAs per group
-  constexpr int HEAD = Cfg::GROUPS - 1;            // groups multiplied before the barrier
-  // the loads of a slab are placed in front of the MFMAs of the first one or two groups (of all
-  // groups before the barrier if two do not have an MFMA for each load)
-  constexpr int SPAN = (NL <= 2 * MM ? (HEAD < 2 ? HEAD : 2) : HEAD) * MM;
-  static_assert(HEAD >= 1, "the last group is multiplied behind the barrier");
-  static_assert(CHAIN == 0 || sizeof(T) == 4, "bf16 operands: their rounding is what counts");
-
-  // prologue: slabs 0 and 1 are requested back to back; slab 0 goes to stage 0
-  typename SA::Regs a0 = {};
-  typename SB::Regs b0 = {};
-  {
-    typename SA::Regs af = sa.load(0);
-    typename SB::Regs bf = sb.load(0);
-    a0 = sa.load(last < 1 ? last : 1);
-    b0 = sb.load(last < 1 ? last : 1);
-    sa.store(st0, af);
-    sb.store(st0 + Cfg::A_BYTES, bf);
-  }
-  __syncthreads();
-  Frags<Cfg> fc;
-  read_group<Cfg>(st0, 0, wm, wn, fc);
-  f32x16 sums[Cfg::TM][Cfg::TN];
-  if constexpr (CHAIN > 0) zero_acc<Cfg>(sums);
-  for (int s = 0; s < nslabs; ++s) {
-    char* cur = (s & 1) ? st1 : st0;
-    char* nxt = (s & 1) ? st0 : st1;
-    const int s2 = s + 2 < last ? s + 2 : last;
-    sa.store(nxt, a0);
-    sb.store(nxt + Cfg::A_BYTES, b0);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int g = 0; g < HEAD; ++g) {
-      Frags<Cfg> fn;
-      read_group<Cfg>(cur, g + 1, wm, wn, fn);
-      __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs they do not feed
-#pragma unroll
-      for (int q = 0; q < MM; ++q) {
-        // one block to a wavefront, sums in pieces: the loads go between the MFMAs of the group, and stay
-        // there (left to the compiler they end up in front of all four: 512 samples x 9,344 classes x 512
-        // 168 us, so 163; larger tiles lose 2 % by it)
-        constexpr bool kBetween = CHAIN > 0 && MM == 1;
-        if constexpr (kBetween) {
-          mfma_half<0>(fc.a[0], fc.b[0], acc[0][0]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int c = 0; c < NL; ++c) {     // chunk c is requested in front of MFMA c*SPAN/NL
-          if (c * SPAN / NL == g * MM + q) {
-            if (c < NA) sa.load_chunk(s2, c, a0);
-            else sb.load_chunk(s2, c - NA, b0);
-          }
-        }
-        if constexpr (kBetween) {
-          __builtin_amdgcn_sched_barrier(0);
-          mfma_half<1>(fc.a[0], fc.b[0], acc[0][0]);
-        } else {
-          mfma_group<T>(fc.a[q / Cfg::TN], fc.b[q % Cfg::TN], acc[q / Cfg::TN][q % Cfg::TN]);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      fc = fn;
-    }
-    __syncthreads();
-    Frags<Cfg> fn;
-    read_group<Cfg>(nxt, 0, wm, wn, fn);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_group<Cfg>(fc, acc);
-    __builtin_amdgcn_sched_barrier(0);
-    fc = fn;
-    if constexpr (CHAIN > 0) {
-      if ((s + 1) % CHAIN == 0 && s < last) {
-        add_acc<Cfg>(sums, acc);
-        zero_acc<Cfg>(acc);
-      }
-    }
-  }
-  if constexpr (CHAIN > 0) add_acc<Cfg>(acc, sums);
-  __syncthreads();
+  static_assert(CHAIN == 0 || !Cfg::DMA, "bf16 operands: their rounding is what counts");
+  if constexpr (Cfg::DMA) gemm_tile_dma<Cfg>(A, lda, B, ldb, nslabs, smem, acc);
+  else gemm_tile_split<Cfg, CHAIN>(A, lda, B, ldb, nslabs, smem, acc);
 }
 
 // Row / column of accumulator register r of block (bm, bn) inside the workgroup tile.

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, float* __res
     for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) mfma_group<__bf16>(a, b, acc[q]);
+    for (int q = 0; q < 8; ++q) mfma_bf16(a, b, acc[q]);
     // flip mantissa bits every round: operand toggling is what a real GEMM presents to the
     // MFMA pipe, and the sustained clock depends on it
     const uint32_t flip = ((uint32_t)it * 0x9E3779B9u) & 0x007F007Fu;

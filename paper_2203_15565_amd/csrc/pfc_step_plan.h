@@ -73,11 +73,14 @@ inline int64_t launch_slabs(int64_t cu, int64_t na, int64_t a, int64_t nb, int64
   }
 }
 
+// Partial tiles of either product that there is room for.
+inline int64_t slice_room(int cu, int Bp) { return (int64_t)(Bp > kLongBatch ? kLongRoom : 1) * cu; }
+
 // Whether there is room for fp32 sums of at most `most` products.
 inline bool plain_sums_fit(int cu, int Bp, int Dp, int64_t kp, int most) {
   const int64_t w = (Bp + most - 1) / most, x = (kp + most - 1) / most;
   const int64_t tiles_w = kp / 256 * (Dp / 256), tiles_x = (int64_t)(Bp / 256) * (Dp / 256);
-  const int64_t room = (int64_t)kLongRoom * cu;
+  const int64_t room = slice_room(cu, Bp);
   return w <= kMaxSplits && x <= kMaxLongSplits &&
          (w == 1 || (w * tiles_w <= room && w * kp <= (int64_t)kMaxSplits * Bp)) &&
          (x == 1 || x * tiles_x <= room);
@@ -91,14 +94,13 @@ struct LongSlices {
 };
 
 // The fewest microseconds by an estimate: a slab of a 256-tile takes 1.45 us (bf16; start and end of a
-// workgroup like 10 slabs) or 7.7 us (fp32, 2 slabs), a partial tile of dfeatures 0.06 us to add up later, one
+// workgroup like 10 slabs) or 3.2 us (fp32, 4 slabs), a partial tile of dfeatures 0.06 us to add up later, one
 // of dweight 0.05, the result likewise, and the launch that does it 3 us.  Fitted to 45 forms of 2,100 .. 65,536 samples, 2,000 .. 30,000
 // classes, D 128 .. 1024 and all slices that fit (7,730 measurements): the pick is 0.5 % behind the best of
 // a form on average, 3 % at most.  Against the rules for smaller batches (us, both products):
 //   bf16 4096 x 20,000 x 512 217 -> 179, 3000 x 20,000 x 512 166 -> 136, 8192 x 20,000 x 512 423 -> 315,
 //     4096 x 20,000 x 1024 338 -> 304, 16,384 x 3,592 x 512 141 -> 130
-//   fp32 (128- and 64-tiles in pieces -> 256) 16,384 x 3,000 x 512 1076 -> 797, 8192 x 16,000 x 512 2239 ->
-//     2003, 8192 x 5,000 x 512 815 -> 678, 4096 x 20,000 x 512 1508 -> 1341, 3000 x 8,000 x 512 480 -> 419
+// fp32: a slab of 3.2 us, from the measurements at backward_tiles; every batch that 256-tiles suit takes these slices.
 // fp32 sums run without pieces here: only slices of at most kPlainSum products are taken, or kMaxPlainSum
 // where those do not fit (the caller sees to it that there are such).  Error against 64 bits, 2-norm, both
 // gradients, slices by number alone -> now: 16,384 x 15,700 x 512 7.6e-7 -> 6.2e-7, 8192 x 8,100 x 512 7.7e-7 ->
@@ -107,9 +109,9 @@ inline LongSlices long_batch_slices(int cu, int es, int Bp, int Dp, int64_t kp) 
   const int bk = tile_bk(es);
   const int slabs_w = Bp / bk, slabs_x = (int)(kp / bk);
   const int64_t tiles_w = kp / 256 * (Dp / 256), tiles_x = (int64_t)(Bp / 256) * (Dp / 256);
-  const int64_t room = (int64_t)kLongRoom * cu, edge = es == 2 ? 10 : 2;
+  const int64_t room = slice_room(cu, Bp), edge = es == 2 ? 10 : 4;
   const int most = es == 2 ? INT_MAX : plain_sums_fit(cu, Bp, Dp, kp, kPlainSum) ? kPlainSum : kMaxPlainSum;
-  const double slab_us = es == 2 ? 1.45 : 7.7, dw_tile_us = 0.05, dx_tile_us = 0.06;
+  const double slab_us = es == 2 ? 1.45 : 3.2, dw_tile_us = 0.05, dx_tile_us = 0.06;
   const int64_t work = tiles_w * slabs_w + tiles_x * slabs_x;
   LongSlices best = {0, 0, false, false};
   double best_us = 0;
@@ -137,7 +139,9 @@ inline LongSlices long_batch_slices(int cu, int es, int Bp, int Dp, int64_t kp) 
 
 // Whether the backward launch of the call takes them, given 256-tiles.  Not the class sets of the one-kernel
 // form, whose dX has the same bits in either call and whose many tiles come out even.
-inline bool long_batch(int cu, int D, int Bp, int64_t kp) { return Bp > kLongBatch && !fits_one_kernel(cu, D, kp); }
+inline bool long_batch(int cu, int es, int D, int Bp, int64_t kp) {
+  return (es == 4 || Bp > kLongBatch) && !fits_one_kernel(cu, D, kp);
+}
 
 // Size of the GEMM tiles, one for the logits and one for the backward launch of a call.  256 x 256
 // moves the least data per flop and fills a compute unit with one workgroup, 128 x 128 puts two on
@@ -153,42 +157,33 @@ inline bool long_batch(int cu, int D, int Bp, int64_t kp) { return Bp > kLongBat
 //     more (128 x 200,000: 210 / 179 / 260) or the reduction is short and the tiles few
 //     (256 x 36,000: 42 / 39 / 57; 256 x 200,000: 221 / 260 / 368); 64-tiles for the smallest
 //     problems (128 x 1,000: 15 / 7.3 / 5.8).
-//   fp32: the matrix cores are the bound at any of the sizes, so what counts is how evenly the
-//     compute units are loaded: 64-tiles where a few 128-tiles per compute unit do not come out
-//     even (logits 512 x 9,344: 135 / 77 / 57; 128 x 1,000: 129 / 37 / 15).  From one 256-tile per
-//     compute unit on the sizes are close (2048 x 60,000: 1144 / 1127 / 1207; 512 x 60,000: 299 /
-//     315 / 330) and the logits keep 256 and its order of the row sums.
+//   fp32: by estimate.  A compute unit full of tiles of one size takes fp32_slab_us for a slab of 32 steps of
+//     one tile: a 256-tile reads the least from LDS and splits the fewest values for every product, smaller
+//     ones come out more even.  Forward/backward with the logits in 64 / 128 / 256 (backward 128): 1907 x 20,355
+//     835 / 783 / 781, 4096 x 8,000 711 / 645 / 622, 2048 x 30,000 1316 / 1183 / 1142, 512 x 9,344 148 / 152 /
+//     172, 230 x 3,000 61 / 69 / 111; with the backward launch in 64 / 128 / 256 (logits 128): 837 / 783 / 821,
+//     731 / 645 / 577, 1288 / 1183 / 1025, 147 / 152 / 140, 63 / 69 / 83.
 enum TileSize { TILES_64 = 64, TILES_128 = 128, TILES_256 = 256 };
 
-inline bool even_rounds(int64_t tiles, int64_t cu) {   // at most 15 % of the rounds' room is idle
-  return tiles > 4 * cu || (tiles + cu - 1) / cu * cu * 100 <= tiles * 115;
-}
+// fp32: microseconds a compute unit takes for one slab of one tile, full of tiles of that size.
+inline double fp32_slab_us(TileSize t) { return t == TILES_256 ? 3.2 : t == TILES_128 ? 0.98 : 0.36; }
 
 inline TileSize logits_tiles(int64_t cu, int es, int B, int64_t kp, int D) {
   const int64_t mid = kp / 128 * ((B + 127) / 128);
   const int64_t big = kp / 256 * ((B + 255) / 256), rounds = (big + cu - 1) / cu;
-  if (es == 4) return big >= cu ? TILES_256 : even_rounds(mid, cu) ? TILES_128 : TILES_64;
+  if (es == 4) {
+    const int64_t small = kp / 64 * ((B + 63) / 64);
+    TileSize best = TILES_128;
+    auto us = [&](TileSize t, int64_t tiles) { return (double)((tiles + cu - 1) / cu) * fp32_slab_us(t); };
+    if (us(TILES_256, big) < us(TILES_128, mid)) best = TILES_256;
+    // (row sums of 64-tiles: what rowpart_floats has room for)
+    if (kp / 64 * round_up(B, kPadB) <= (int64_t)2048 * cu &&
+        us(TILES_64, small) < std::min(us(TILES_128, mid), us(TILES_256, big)))
+      best = TILES_64;
+    return best;
+  }
   if (D > 256 && rounds * cu * 4 * 100 <= mid * 109) return TILES_256;
   return 2 * mid > cu ? TILES_128 : TILES_64;
-}
-
-inline TileSize backward_tiles(int cu, int es, int B, int64_t kp, int D) {
-  const int Bp = (int)round_up(B, 128), Bp256 = (int)round_up(B, 256);
-  const int Dp = (int)round_up(D, kPadD), Dp256 = (int)round_up(D, 256);
-  const int64_t mid = kp / 128 * (Dp / 128), big = kp / 256 * (Dp256 / 256);
-  // (fp32, large batches: the 256-tile reads half as much from LDS for every product; 2100 x 3,000 x 512 140 / 144
-  // us with 10 % of the batch padding, 4096 x 9,000 x 320 529 / 624 with a third of the columns, 2500 x 40,000 x
-  // 256 890 / 954 with a fourth of the compute units idle)
-  if (es == 4 && long_batch(cu, D, Bp256, kp) && Dp256 * 100 <= Dp * 115 && Bp256 * 100 <= B * 105 &&
-      plain_sums_fit(cu, Bp256, Dp256, kp, kMaxPlainSum) && long_batch_slices(cu, es, Bp256, Dp256, kp).even)
-    return TILES_256;
-  if (es == 4)
-    return even_rounds(mid * dweight_slices(cu, (int)mid, Bp, kp, 32), cu) ? TILES_128 : TILES_64;
-  // (columns: 640 -> 768 and 896 -> 1024 cost less than the smaller tile, 384 -> 512 more)
-  if (Dp256 * 100 <= Dp * 125 && Bp256 * 100 <= Bp * 115 &&
-      big * dweight_slices(cu, (int)big, Bp256, kp, 64) * 2 >= cu && (B >= 512 || big * 2 >= cu * 3))
-    return TILES_256;
-  return B > 128 || 2 * mid > cu ? TILES_128 : TILES_64;
 }
 
 // Workgroups that a compute unit holds.
@@ -242,7 +237,7 @@ inline BackwardShape backward_shape(int cu, int es, TileSize t, int Bp, int Dp, 
   BackwardShape s;
   const int tiles_w = (int)(kp / t) * (Dp / t);
   const int slabs_total = Bp / tile_bk(es);
-  const LongSlices cut = t == TILES_256 && long_batch(cu, D, Bp, kp) ? long_batch_slices(cu, es, Bp, Dp, kp)
+  const LongSlices cut = t == TILES_256 && long_batch(cu, es, D, Bp, kp) ? long_batch_slices(cu, es, Bp, Dp, kp)
                                                                      : LongSlices{0, 0, false, false};
   const int want = cut.dw ? cut.dw : dweight_slices(cu, tiles_w, Bp, kp, tile_bk(es));
   s.dw_first = cut.dw_first;
@@ -255,10 +250,46 @@ inline BackwardShape backward_shape(int cu, int es, TileSize t, int Bp, int Dp, 
   const int64_t slots = (int64_t)cu * tiles_per_cu(t, es);
   const int64_t wgs_w = (int64_t)tiles_w * s.splits;
   // fp32 tiles take long: dfeatures workgroups no longer than those, so that the end comes out even
-  // (fused, 1024 x 36,024 x 512: half of the GPU's room 1546 us a step, twice the room 1212)
   const int64_t wgs = es == 4 && wgs_w > 2 * slots ? 2 * slots : std::max(slots / 2, slots - wgs_w);
   s.dx = dx_shape(cu, es, t, Bp, Dp, D, kp, wgs);
   return s;
+}
+
+// Microseconds of the backward launch with fp32 operands, by estimate: the longer workgroups first, each to the
+// slot that is free first, 4 slabs for its start and end; partial sums at 5 TB/s.
+inline double fp32_backward_us(int cu, TileSize t, int Bp, int Dp, int D, int64_t kp) {
+  const BackwardShape s = backward_shape(cu, 4, t, Bp, Dp, D, kp);
+  const int per = tiles_per_cu(t, 4), edge = 4, w = s.slabs_per + edge, x = s.dx.slabs_per + edge;
+  const int64_t nw = kp / t * (Dp / t) * s.splits, nx = (int64_t)s.dx.tiles_i * s.dx.tiles_d * s.dx.splits;
+  const int64_t slabs = w > x ? launch_slabs((int64_t)cu * per, nw, w, nx, x) : launch_slabs((int64_t)cu * per, nx, x, nw, w);
+  return (double)slabs * fp32_slab_us(t) * per + 0.8e-6 * s.dx.splits * Bp * Dp +
+         (s.splits > 1 ? 3.0 + 0.8e-6 * (s.splits + 1) * kp * Dp : 0.0);
+}
+
+inline TileSize backward_tiles(int cu, int es, int B, int64_t kp, int D) {
+  const int Bp = (int)round_up(B, 128), Bp256 = (int)round_up(B, 256);
+  const int Dp = (int)round_up(D, kPadD), Dp256 = (int)round_up(D, 256);
+  const int64_t mid = kp / 128 * (Dp / 128), big = kp / 256 * (Dp256 / 256);
+  if (es == 4) {
+    // the launch that ends first by estimate; 64-tiles are no tiles of the one-kernel form, 256-tiles need
+    // slices that keep the sums short
+    TileSize best = TILES_128;
+    double best_us = fp32_backward_us(cu, TILES_128, Bp, Dp, D, kp);
+    auto take = [&](TileSize t, double us) {
+      if (us < best_us) best = t, best_us = us;
+    };
+    if (!fits_one_kernel(cu, D, kp)) {
+      take(TILES_64, fp32_backward_us(cu, TILES_64, (int)round_up(B, logits_tiles(cu, es, B, kp, D)), Dp, D, kp));
+      if (plain_sums_fit(cu, Bp256, Dp256, kp, kMaxPlainSum))
+        take(TILES_256, fp32_backward_us(cu, TILES_256, Bp256, Dp256, D, kp));
+    }
+    return best;
+  }
+  // (columns: 640 -> 768 and 896 -> 1024 cost less than the smaller tile, 384 -> 512 more)
+  if (Dp256 * 100 <= Dp * 125 && Bp256 * 100 <= Bp * 115 &&
+      big * dweight_slices(cu, (int)big, Bp256, kp, 64) * 2 >= cu && (B >= 512 || big * 2 >= cu * 3))
+    return TILES_256;
+  return B > 128 || 2 * mid > cu ? TILES_128 : TILES_64;
 }
 
 // ---------------------------------------------------------------------------------------------
