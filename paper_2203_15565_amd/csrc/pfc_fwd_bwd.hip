@@ -327,6 +327,14 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   const int64_t j0 = (int64_t)tj * Cfg::BM;
   const int i0 = ti * Cfg::BN;
 
+  // labels: requested in front of the reduction (behind it they were a wait of 2 us of their own)
+  int32_t ylab[Cfg::TN];
+#pragma unroll
+  for (int bn = 0; bn < Cfg::TN; ++bn) {
+    const int i = i0 + acc_col<Cfg>(bn);
+    ylab[bn] = i < B ? yl[i] : -1;
+  }
+
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
   PFC_PHASE(1, 0);
@@ -370,7 +378,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
     const int i = i0 + acc_col<Cfg>(bn);
     ylane[bn] = -1;
     if (i < B) {
-      const int64_t y = (int64_t)yl[i] - j0;
+      const int64_t y = (int64_t)ylab[bn] - j0;
       if (y >= 0 && y < (int64_t)klim) {
         const int rel = (int)y - (wave / Cfg::WN) * Cfg::WTM;
         if (rel >= 0 && rel < Cfg::WTM && ((rel >> 2) & 1) == (lane >> 5)) ylane[bn] = (int)y;
@@ -994,15 +1002,16 @@ __device__ __forceinline__ void fused_update_tile(
   constexpr int D = Cfg::BN, NC = D / 256, HR = FL::HR, SROW = FL::SROW;
   constexpr int WAVES = Cfg::THREADS / 64, RPW = HR / WAVES;   // rows per wavefront and half
   constexpr int ROWS = Cfg::WM * RPW;                           // rows per wavefront and tile
-  constexpr int WIN = 3;                                        // rows of W, v and label part in flight
+  constexpr int WIN = 5;   // rows of W and v in flight (3 rows and the label part of each: 1024 x 205,991 with the
+                           // update 1099 us a step, 3 rows 1089, 5 rows 1083)
   static_assert(D % 256 == 0 && HR % WAVES == 0 && ROWS <= 64 && WIN <= ROWS, "fused update geometry");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // Two spare rows of D floats: the first holds zeros (never written) and is what a center that
-  // is nobody's label reads instead of a label part, and what a padding row of the last tile
+  // Two spare rows of D floats: the first holds zeros (never written) and is what a padding row of the last tile
   // reads instead of W and v; the second takes the stores of the padding rows and is never read.
-  // Every row thus issues the same loads and stores in the same order with no branch in between,
-  // which is what lets the wait for row n's operands leave the younger requests of rows
-  // n+1 .. n+WIN in flight.
+  // Every row thus issues the same loads of W and v and the same stores in the same order with no branch in
+  // between, which is what lets the wait for row n's operands leave the younger requests of rows
+  // n+1 .. n+WIN in flight.  The few centers that are the label of a sample read their label part when
+  // they are at it: as part of the window it was a third of all loads, of a row of zeros for nearly every center.
   const float* zero_row = spare;
   float* trash_row = spare + D;
 
@@ -1028,21 +1037,18 @@ __device__ __forceinline__ void fused_update_tile(
   gemm_tile<Cfg>(E + j0, kp, Xs, D, Bp / Cfg::BK, smem, acc);
   PFC_PHASE(3, 1);
 
-  // A window of WIN rows of W, v and the label part is kept in flight: the loads of row n+WIN
+  // A window of WIN rows of W and v is kept in flight: the loads of row n+WIN
   // are issued as soon as row n has been used, across the two halves.  (Native vector types:
   // arrays of them stay in registers.)
-  f32x4 w[WIN][NC], v[WIN][NC], lb[WIN][NC];
+  f32x4 w[WIN][NC], v[WIN][NC];
   auto request = [&](int n) {
     const int64_t row = __builtin_amdgcn_readlane(idxv, n);   // wave-uniform
-    const int hd = __builtin_amdgcn_readlane(headv, n);
     const float* wsrc = row >= 0 ? W + row * D : zero_row;    // scalar selects, no branch
     const float* vsrc = row >= 0 ? V + row * D : zero_row;
-    const float* lsrc = hd != INT_MAX ? lab + (int64_t)hd * D : zero_row;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       w[n % WIN][c] = *reinterpret_cast<const f32x4*>(wsrc + c * 256 + lane * 4);
       v[n % WIN][c] = *reinterpret_cast<const f32x4*>(vsrc + c * 256 + lane * 4);
-      lb[n % WIN][c] = *reinterpret_cast<const f32x4*>(lsrc + c * 256 + lane * 4);
     }
   };
 #pragma unroll
@@ -1076,8 +1082,17 @@ __device__ __forceinline__ void fused_update_tile(
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         const int d = c * 256 + lane * 4;
-        // GEMM row + label part (zeros unless this center is the label of a sample)
-        g[c] = *reinterpret_cast<const f32x4*>(stage + r * SROW + d) + lb[n % WIN][c];
+        g[c] = *reinterpret_cast<const f32x4*>(stage + r * SROW + d);
+      }
+      // the label part of a center that is the label of a sample
+      const int hd = __builtin_amdgcn_readlane(headv, n);
+      if (hd != INT_MAX) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          g[c] += *reinterpret_cast<const f32x4*>(lab + (int64_t)hd * D + c * 256 + lane * 4);
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
         const f32x4 wc = w[n % WIN][c];
         ww += wc[0] * wc[0] + wc[1] * wc[1] + wc[2] * wc[2] + wc[3] * wc[3];
         gw += g[c][0] * wc[0] + g[c][1] * wc[1] + g[c][2] * wc[2] + g[c][3] * wc[3];
