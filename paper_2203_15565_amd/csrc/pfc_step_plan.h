@@ -226,6 +226,36 @@ inline DxShape dx_shape(int cu, int es, TileSize t, int Bp, int Dp, int D, int64
   return dx_cut(es, t, Bp, Dp, kp, want < 1 ? 1 : want);
 }
 
+// bf16: no more slices than `most` has, and as few of them as let the launch end within 2 % of the earliest by an
+// estimate: a slab takes a workgroup 0.75 us (128- and 64-tiles; its start and end 6 slabs) or 1.75 us (256-tiles, 4),
+// a slice of partial sums goes to memory and back.  What this avoids is a few workgroups in a round of their own, and
+// partial sums of dfeatures workgroups that are shorter than those of dweight.  Forward/backward by the share of
+// the GPU's room that dfeatures takes, us, 0.2 / 0.3 / 0.4 / half and more -> taken: 512 samples x 9,344 classes x
+// 512 58.2 / 55.0 / 55.6 / 60.8 -> 0.4; 800 x 3,000 x 512 45.1 / 45.8 / 48.3 / 49.0 -> 0.2; 200 x 3,000 x 768 40.1 /
+// 41.9 / 42.2 / 42.1 -> 0.2; 1700 x 12,547 x 512 176 / 157 / 151 / 150 -> 0.4; 1000 x 30,000 x 256 119 / 110 / 112 /
+// 113 -> 0.4; 768 x 20,599 x 1024 191 / 167 / 162 / 163 -> 0.4.  (More than two rounds of dweight tiles fill every gap: 1024 x
+// 205,991 with 14 slices in place of 16 is 1 % slower.)
+inline DxShape dx_even(int64_t slots, TileSize t, int Bp, int Dp, int64_t kp, int64_t wgs_w, int slabs_w,
+                       const DxShape& most) {
+  const int edge = t == TILES_256 ? 4 : 6;
+  const double slab_us = t == TILES_256 ? 1.75 : 0.75, slice_us = (double)Bp * Dp * 8 / 3e6;
+  auto us = [&](const DxShape& d) {
+    const int64_t n = (int64_t)d.tiles_i * d.tiles_d * d.splits;
+    const int x = d.slabs_per + edge, w = slabs_w + edge;
+    return slab_us * (x >= w ? launch_slabs(slots, n, x, wgs_w, w) : launch_slabs(slots, wgs_w, w, n, x)) +
+           slice_us * d.splits;
+  };
+  double best = us(most);
+  for (int pass = 0; pass < 2; ++pass)
+    for (int n = 1; n < most.splits; ++n) {
+      const DxShape d = dx_cut(2, t, Bp, Dp, kp, n);
+      const double d_us = us(d);
+      if (pass == 1 && d_us <= 1.02 * best) return d;
+      if (d_us < best) best = d_us;
+    }
+  return most;
+}
+
 // Slices of the batch in the dweight product, and the shape of the dfeatures product beside it
 // (the same with and without the update, so that dX has the same bits).
 struct BackwardShape {
@@ -252,6 +282,7 @@ inline BackwardShape backward_shape(int cu, int es, TileSize t, int Bp, int Dp, 
   // fp32 tiles take long: dfeatures workgroups no longer than those, so that the end comes out even
   const int64_t wgs = es == 4 && wgs_w > 2 * slots ? 2 * slots : std::max(slots / 2, slots - wgs_w);
   s.dx = dx_shape(cu, es, t, Bp, Dp, D, kp, wgs);
+  if (es == 2 && wgs_w <= 2 * slots) s.dx = dx_even(slots, t, Bp, Dp, kp, wgs_w, s.slabs_per, s.dx);
   return s;
 }
 
