@@ -69,7 +69,7 @@ int pfc_destroy(pfc_ctx* c) {
                   c->Xs, c->rnormX, c->Wn, c->rnormW, c->head, c->E, c->rowpart, c->rowmaxpart, c->rowmax,
                   c->rowref,
                   c->clabel, c->rowscale, c->dlabel, c->lossrow, c->dXpart, c->dlab, c->dWtmp,
-                  c->spare};
+                  c->spare, c->label_order, c->label_runs};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   if (c->host_pin) (void)hipHostFree(c->host_pin);
@@ -140,6 +140,10 @@ int pfc_create(pfc_ctx** out, int64_t N, int32_t D, int32_t B_max, double r_max,
         (nw >= 2 && nw <= kMaxLabelWindows && nw * (int64_t)kp <= ((int64_t)1 << 26)) ? (int32_t)nw : 0;
   }
   ALLOC(head, (size_t)(1 + c->label_windows) * kp * 4);
+  if (c->label_windows) {
+    ALLOC(label_order, (size_t)c->label_windows * kLabelWindow * 4);
+    ALLOC(label_runs, (size_t)c->label_windows * kWindowRuns * 4);
+  }
   ALLOC(E, Bp * kp * es);
   const size_t rowparts = (size_t)rowpart_floats(c->num_cu, B_max, c->kp_cap);
   const size_t parts = (size_t)part_floats(c->num_cu, D, B_max);

@@ -11,6 +11,8 @@ namespace pfc {
 
 constexpr int kLabelWindow = 1024;     // samples per window of the label part of dWn
 constexpr int kMaxLabelWindows = 64;   // one lane of a wavefront initialises one window's head
+// Classes of a window: their number, then where each begins in the window's ordered samples, and their end.
+constexpr int kWindowRuns = kLabelWindow + 2;
 
 // Kernel ids for the optional per-kernel timing.
 enum KernelId {
@@ -111,6 +113,8 @@ struct pfc_ctx {
                    // idx[j], else INT_MAX; then the same for every window of kLabelWindow samples
                    // (kp = k rounded up to 256 in the call at hand)
   int32_t label_windows;   // windows the head buffer has room for (0: none, batch in one piece)
+  int32_t* label_order;    // [label_windows x kLabelWindow] samples of each window, ordered by class
+  int32_t* label_runs;     // [label_windows x kWindowRuns]
   void* E;         // [Bp x kp]  exp(z), label column zeroed
   float* rowpart;  // [Bp x tiles_j] partial row sums of exp(z)
   float* rowmaxpart;  // [Bp x tiles_j] partial row maxima of the non-label cosines (options)

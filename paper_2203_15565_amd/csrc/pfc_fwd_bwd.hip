@@ -111,6 +111,78 @@ __device__ __forceinline__ void normalize_x_row(int i, const float* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------------
+// order_labels (in gather_normalize, batches of several label windows): the samples of window w ordered by class
+// and, inside a class, by number, and where each class begins; samples without a class of S are left out.  A bitonic
+// sort of (class, sample) in LDS, 55 passes for 1024 samples: about 10 us that the other workgroups of the launch cover.
+// ---------------------------------------------------------------------------------------------
+constexpr int kNormWaves = 4;   // wavefronts per workgroup
+struct OrderLds {
+  uint64_t key[kLabelWindow];
+  int runs[kNormWaves], samples;
+};
+__device__ __forceinline__ void order_labels(int w, OrderLds& lds, int B, const int32_t* __restrict__ yl,
+                                             int64_t k, int32_t* __restrict__ order,
+                                             int32_t* __restrict__ runs) {
+  constexpr int THREADS = kNormWaves * 64, PER = kLabelWindow / THREADS;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int i0 = w * kLabelWindow;
+  for (int e = t; e < kLabelWindow; e += THREADS) {
+    const int32_t y = i0 + e < B ? yl[i0 + e] : -1;
+    lds.key[e] = y >= 0 && (int64_t)y < k ? (uint64_t)(uint32_t)y << 32 | (uint32_t)(i0 + e) : ~0ull;
+  }
+  if (t == 0) lds.samples = 0;
+  __syncthreads();
+  for (int size = 2; size <= kLabelWindow; size *= 2)
+    for (int j = size / 2; j > 0; j /= 2) {
+#pragma unroll
+      for (int u = 0; u < PER / 2; ++u) {
+        const int q = u * THREADS + t, a = (q & ~(j - 1)) * 2 + (q & (j - 1)), b = a + j;
+        const uint64_t ka = lds.key[a], kb = lds.key[b];
+        if ((ka > kb) == ((a & size) == 0)) {
+          lds.key[a] = kb;
+          lds.key[b] = ka;
+        }
+      }
+      __syncthreads();
+    }
+  // thread t: PER neighbouring places
+  bool first[PER];
+  int n = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int at = t * PER + e;
+    const uint64_t key = lds.key[at];
+    const bool valid = key != ~0ull;
+    first[e] = valid && (at == 0 || (lds.key[at - 1] >> 32) != (key >> 32));
+    n += first[e];
+    if (valid) order[i0 + at] = (int32_t)(uint32_t)key;
+    if (valid && (at == kLabelWindow - 1 || lds.key[at + 1] == ~0ull)) lds.samples = at + 1;
+  }
+  int upto = n;   // classes that begin up to this thread's places, in its wavefront
+#pragma unroll
+  for (int o = 1; o < 64; o *= 2) {
+    const int v = __shfl_up(upto, o, 64);
+    if (lane >= o) upto += v;
+  }
+  if (lane == 63) lds.runs[wave] = upto;
+  __syncthreads();
+  int before = upto - n, total = 0;
+#pragma unroll
+  for (int v = 0; v < kNormWaves; ++v) {
+    if (v < wave) before += lds.runs[v];
+    total += lds.runs[v];
+  }
+  runs += (int64_t)w * kWindowRuns;
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (first[e]) runs[1 + before++] = t * PER + e;
+  if (t == 0) {
+    runs[0] = total;
+    runs[1 + total] = lds.samples;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // gather_normalize: the first x_blocks workgroups normalise the features (normalize_x_row), the others the
 // sampled centers: the two need nothing of each other, and a launch of its own for a few hundred
 // rows of features is 3-5 us that nothing runs beside (step, 128 x 1,000 x 512 fp32 62.2 -> 59.8 us, 512 x
@@ -119,22 +191,28 @@ __device__ __forceinline__ void normalize_x_row(int i, const float* __restrict__
 // (2 KB each at D = 512, ascending row ids) in flight before the first is reduced.
 // Rows k..kp-1 of Wn are written as zeros.
 // ---------------------------------------------------------------------------------------------
-constexpr int kNormWaves = 4;   // wavefronts per workgroup
+// (In front of either: one workgroup for every label window of a large batch, order_labels.)
 template <typename T, int NC>
 __global__ __launch_bounds__(kNormWaves * 64) void gather_normalize_kernel(
     int x_blocks, const float* __restrict__ X, int B, int Bp, const int32_t* __restrict__ yl,
     T* __restrict__ Xn, float* __restrict__ rnormX, float* __restrict__ clabel,
     const float* __restrict__ W, int64_t N, const int32_t* __restrict__ idx, int64_t k, int64_t kp,
     int D, int Dp, T* __restrict__ Wn, float* __restrict__ rnormW, int32_t* __restrict__ head,
-    int nwin, int32_t* __restrict__ err_flag) {
-  if ((int)blockIdx.x < x_blocks) {
-    const int i = blockIdx.x * kNormWaves + (threadIdx.x >> 6);
+    int nwin, int32_t* __restrict__ order, int32_t* __restrict__ runs, int32_t* __restrict__ err_flag) {
+  if ((int)blockIdx.x < nwin) {
+    __shared__ OrderLds lds;
+    order_labels(blockIdx.x, lds, B, yl, k, order, runs);
+    return;
+  }
+  const int block = (int)blockIdx.x - nwin;
+  if (block < x_blocks) {
+    const int i = block * kNormWaves + (threadIdx.x >> 6);
     if (i < Bp) normalize_x_row<T, NC>(i, X, B, D, Dp, yl, k, Xn, rnormX, clabel, err_flag);
     return;
   }
   constexpr int NB = 4;
   const int lane = threadIdx.x & 63;
-  const int64_t jb = ((int64_t)(blockIdx.x - x_blocks) * kNormWaves + (threadIdx.x >> 6)) * NB;
+  const int64_t jb = ((int64_t)(block - x_blocks) * kNormWaves + (threadIdx.x >> 6)) * NB;
   if (jb >= kp) return;
   float4 v[NB][NC];
   bool ok[NB];
@@ -828,16 +906,9 @@ __global__ void dweight_reduce_kernel(const float* __restrict__ part, int splits
 // so the result does not depend on timing.
 // LABEL_COMPACT (fused step): the sum is not added to dWn[y] but written to row i of a B x D side
 // buffer, i being that first sample; the fused GEMM picks it up through head[].
-// LABEL_WINDOW (batches of more than kLabelWindow samples; Sec. 3.3 enlarges the batch to 8K and
-// 16K): with long-tailed labels one class can own a fifth of the batch, and one workgroup cannot
-// read thousands of feature rows quickly (a compute unit draws a small share of the memory
-// bandwidth).  The batch is cut into windows of kLabelWindow samples; block i sums the samples of
-// its class inside its own window if it is the first of them there (`head` then points at that
-// window's heads), and writes the partial sum to row i of the side buffer; dweight_label_combine
-// adds a class's window sums in window order.
+// Batches of several windows of kLabelWindow samples: window_label_block, further down.
 constexpr int kLabelThreads = 1024;
-static_assert(kLabelWindow == kLabelThreads, "a window is scanned in one pass of the workgroup");
-enum LabelMode { LABEL_ADD, LABEL_COMPACT, LABEL_WINDOW };
+enum LabelMode { LABEL_ADD, LABEL_COMPACT };
 struct LabelLds {
   float4 part[kLabelThreads];
   int list[kLabelThreads];
@@ -847,7 +918,7 @@ struct LabelLds {
 template <LabelMode MODE>
 __device__ __forceinline__ void dweight_label_block(
     int i, LabelLds& lds, const float* __restrict__ X, int B, int D,
-    const int32_t* __restrict__ yl, int64_t k, const int32_t* __restrict__ head, int64_t kp,
+    const int32_t* __restrict__ yl, int64_t k, const int32_t* __restrict__ head,
     const float* __restrict__ rnormX, const float* __restrict__ dlabel, float* __restrict__ dW) {
   int* s_list = lds.list;
   float* s_coef = lds.coef;
@@ -857,21 +928,15 @@ __device__ __forceinline__ void dweight_label_block(
   const int lane = t & 63, wave = t >> 6;
   const int32_t y = yl[i];
   if (y < 0 || (int64_t)y >= k) return;
-  int p_end = B;
-  if constexpr (MODE == LABEL_WINDOW) {
-    const int w = i / kLabelWindow;
-    head += (int64_t)(1 + w) * kp;   // the heads of this window
-    p_end = min(B, (w + 1) * kLabelWindow);
-  }
   if (head[y] != i) return;   // an earlier sample carries this label and does the sum
   const int cols = D >> 2;                 // float4 columns: 16 .. 256
   const int G = kLabelThreads / cols;      // thread groups
   const int col = t % cols, g = t / cols;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   int ordinal0 = 0;                        // matches seen in earlier chunks
-  for (int p0 = i; p0 < p_end; p0 += kLabelThreads) {
+  for (int p0 = i; p0 < B; p0 += kLabelThreads) {
     const int p = p0 + t;
-    const bool hit = (p < p_end) && (yl[p] == y);
+    const bool hit = (p < B) && (yl[p] == y);
     const unsigned long long bal = __ballot(hit);
     const int before = __popcll(bal & ((1ull << lane) - 1ull));
     if (lane == 0) s_wcnt[wave] = __popcll(bal);
@@ -936,39 +1001,171 @@ __device__ __forceinline__ void dweight_label_block(
 template <LabelMode MODE>
 __global__ __launch_bounds__(kLabelThreads) void dweight_label_kernel(
     const float* __restrict__ X, int B, int D, const int32_t* __restrict__ yl, int64_t k,
-    const int32_t* __restrict__ head, int64_t kp, const float* __restrict__ rnormX,
+    const int32_t* __restrict__ head, const float* __restrict__ rnormX,
     const float* __restrict__ dlabel, float* __restrict__ dW) {
   __shared__ LabelLds lds;
-  dweight_label_block<MODE>(blockIdx.x, lds, X, B, D, yl, k, head, kp, rnormX, dlabel, dW);
+  dweight_label_block<MODE>(blockIdx.x, lds, X, B, D, yl, k, head, rnormX, dlabel, dW);
 }
 
-// dweight_label_combine (after dweight_label<LABEL_WINDOW>): block i, if sample i is the first of
-// its class in the whole batch, adds the class's window sums (rows of `part` named by the window
-// heads) in window order; the total goes to row i of `part` (COMPACT, fused step) or is added to
-// dWn[y].  One float4 column per thread.
-template <bool COMPACT>
-__global__ void dweight_label_combine_kernel(int B, int D, const int32_t* __restrict__ yl,
-                                             int64_t k, const int32_t* __restrict__ head,
-                                             int64_t kp, int nwin, float* __restrict__ part,
-                                             float* __restrict__ dW) {
-  const int i = blockIdx.x, col = threadIdx.x;
-  const int32_t y = yl[i];
-  if (y < 0 || (int64_t)y >= k) return;
-  if (head[y] != i || col >= (D >> 2)) return;
-  float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int w = i / kLabelWindow; w < nwin; ++w) {
-    const int32_t h = head[(int64_t)(1 + w) * kp + y];
-    if (h == 0x7fffffff) continue;
-    const float4 o = *reinterpret_cast<const float4*>(part + (int64_t)h * D + col * 4);
-    r.x += o.x; r.y += o.y; r.z += o.z; r.w += o.w;
+// window_label_block (in gradients_final, or window_label in a launch of its own): the label part of batches of
+// several windows (Sec. 3.3 enlarges the batch to 8K and 16K).  With long-tailed labels one class can own a fifth
+// of the batch, and one workgroup cannot read thousands of feature rows quickly (a compute unit draws a small share
+// of the memory bandwidth); most classes have a sample or two.  order_labels has put the samples of a window in order
+// of their class.  kWindowBlocks workgroups share a window's classes: one wavefront sums a class of up to
+// kWindowWave samples, the 16 of the workgroup share a larger one.  The sum goes to row i of `part`, i being the class's
+// first sample in the window; window_label_sum adds a class's sums in window order.
+// (A workgroup for every sample of the batch, which scanned the window if it was the first of its class, and
+// nothing to do for most of them: gradients_final at 16,384 samples x 3,592 classes x 512 89.5 us, now 46.7; step
+// 403 -> 359.)
+constexpr int kWindowBlocks = 32, kWindowWave = 16;
+template <int NC>
+struct WindowLds {
+  int begin[kLabelWindow / kWindowBlocks], end[kLabelWindow / kWindowBlocks];
+  float4 part[kLabelThreads / 64 - 1][NC][64];
+};
+// sum over this wavefront's entries e < cnt (<= 64) of coef_e * X[row_e], lane e holding entry e
+template <int NC>
+__device__ __forceinline__ void label_rows(float4 (&acc)[NC], int cnt, int row, float coef,
+                                           const float* __restrict__ X, int D) {
+  constexpr int UN = NC <= 2 ? 4 : 2;   // rows in flight
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int e = 0; e < cnt; e += UN) {
+    float4 x[UN][NC];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      if (e + u >= cnt) continue;
+      const float* src = X + (int64_t)__builtin_amdgcn_readlane(row, e + u) * D + lane * 4;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        if (c * 256 + lane * 4 < D) x[u][c] = *reinterpret_cast<const float4*>(src + c * 256);
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      if (e + u >= cnt) continue;
+      const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, coef), e + u));
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (c * 256 + lane * 4 >= D) continue;
+        acc[c].x += a * x[u][c].x; acc[c].y += a * x[u][c].y;
+        acc[c].z += a * x[u][c].z; acc[c].w += a * x[u][c].w;
+      }
+    }
   }
-  if constexpr (COMPACT) {
-    *reinterpret_cast<float4*>(part + (int64_t)i * D + col * 4) = r;
-  } else {
-    float4* dst = reinterpret_cast<float4*>(dW + (int64_t)y * D + col * 4);
-    float4 cur = *dst;
-    cur.x += r.x; cur.y += r.y; cur.z += r.z; cur.w += r.w;
-    *dst = cur;
+}
+template <int NC>
+__device__ __forceinline__ void window_label_block(int block, WindowLds<NC>& lds, const float* __restrict__ X,
+                                                   int D, const int32_t* __restrict__ order,
+                                                   const int32_t* __restrict__ runs,
+                                                   const float* __restrict__ rnormX,
+                                                   const float* __restrict__ dlabel,
+                                                   float* __restrict__ part) {
+  constexpr int WAVES = kLabelThreads / 64;
+  const int w = block / kWindowBlocks, b = block % kWindowBlocks;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  order += (int64_t)w * kLabelWindow;
+  runs += (int64_t)w * kWindowRuns;
+  // this workgroup's classes: b, b + kWindowBlocks, ..
+  const int total = runs[0], mine = (total - b + kWindowBlocks - 1) / kWindowBlocks;
+  if (mine <= 0) return;
+  if ((int)threadIdx.x < mine) {
+    const int r = b + (int)threadIdx.x * kWindowBlocks;
+    lds.begin[threadIdx.x] = runs[1 + r];
+    lds.end[threadIdx.x] = runs[2 + r];
+  }
+  __syncthreads();
+  float4 acc[NC];
+  // entries first, first + step, .. below `end`, at most 64 of them
+  auto sum = [&](int first, int step, int end) __attribute__((always_inline)) {
+    const int at = first + lane * step;
+    int row = 0;
+    float coef = 0.f;
+    if (at < end) {
+      row = order[at];
+      coef = dlabel[row] * rnormX[row];
+    }
+    label_rows<NC>(acc, first < end ? (end - first + step - 1) / step : 0, row, coef, X, D);
+  };
+  auto store = [&](int begin) __attribute__((always_inline)) {
+    float* dst = part + (int64_t)order[begin] * D;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c * 256 + lane * 4 < D) *reinterpret_cast<float4*>(dst + c * 256 + lane * 4) = acc[c];
+  };
+  for (int u = 0; u < mine; ++u) {
+    const int begin = __builtin_amdgcn_readfirstlane(lds.begin[u]), end = __builtin_amdgcn_readfirstlane(lds.end[u]);
+    if (end - begin <= kWindowWave) {
+      if (u % WAVES == wave) {
+        sum(begin, 1, end);
+        store(begin);
+      }
+      continue;
+    }
+    sum(begin + wave, WAVES, end);
+    if (wave > 0) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) lds.part[wave - 1][c][lane] = acc[c];
+    }
+    __syncthreads();
+    if (wave == 0) {
+      for (int v = 0; v < WAVES - 1; ++v)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const float4 o = lds.part[v][c][lane];
+          acc[c].x += o.x; acc[c].y += o.y; acc[c].z += o.z; acc[c].w += o.w;
+        }
+      store(begin);
+    }
+    __syncthreads();
+  }
+}
+template <int NC>
+__global__ __launch_bounds__(kLabelThreads) void window_label_kernel(
+    const float* __restrict__ X, int D, const int32_t* __restrict__ order, const int32_t* __restrict__ runs,
+    const float* __restrict__ rnormX, const float* __restrict__ dlabel, float* __restrict__ part) {
+  __shared__ WindowLds<NC> lds;
+  window_label_block<NC>(blockIdx.x, lds, X, D, order, runs, rnormX, dlabel, part);
+}
+
+// window_label_sum (after window_label_block): the wavefront of sample i, if that is the first of its class in the whole
+// batch, adds the class's window sums (rows of `part` named by the window heads) in window order; the total
+// goes to row i of `part` (COMPACT, fused step) or is added to dWn[y].
+template <bool COMPACT>
+__global__ void window_label_sum_kernel(int B, int D, const int32_t* __restrict__ yl, int64_t k,
+                                        const int32_t* __restrict__ head, int64_t kp, int nwin,
+                                        float* __restrict__ part, float* __restrict__ dW) {
+  const int lane = threadIdx.x & 63;
+  const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (i >= B) return;
+  const int32_t y = __builtin_amdgcn_readfirstlane(yl[i]);
+  if (y < 0 || (int64_t)y >= k) return;
+  if (head[y] != i) return;
+  const int32_t h = lane < nwin ? head[(int64_t)(1 + lane) * kp + y] : INT_MAX;
+  const unsigned long long in = __ballot(h != INT_MAX);   // the windows that have the class
+  for (int d = lane * 4; d < D; d += 256) {
+    float4* dst = reinterpret_cast<float4*>((COMPACT ? part + (int64_t)i * D : dW + (int64_t)y * D) + d);
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (unsigned long long m = in; m;) {
+      constexpr int UN = 4;   // rows in flight
+      float4 o[UN];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        o[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!m) continue;
+        o[u] = *reinterpret_cast<const float4*>(part + (int64_t)__builtin_amdgcn_readlane(h, __builtin_ctzll(m)) * D + d);
+        m &= m - 1;
+      }
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        r.x += o[u].x; r.y += o[u].y; r.z += o[u].z; r.w += o[u].w;
+      }
+    }
+    if constexpr (!COMPACT) {
+      const float4 cur = *dst;
+      r.x += cur.x; r.y += cur.y; r.z += cur.z; r.w += cur.w;
+    }
+    *dst = r;
   }
 }
 
@@ -1294,23 +1491,24 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
 // From kFinalWideSplits slices on a sample gets 16 wavefronts instead of 4: below, a third of the 16 and more
 // would have no slice to add.
 constexpr int kFinalWideSplits = 12;
-template <int NC, int WPS, LabelMode MODE>
+template <int NC, int WPS, bool WINDOWS>
 __global__ __launch_bounds__(kLabelThreads, 8) void gradients_final_kernel(
-    FinalArgs a, int label_blocks, const int32_t* __restrict__ head, int64_t kp,
-    float* __restrict__ label_out) {
+    FinalArgs a, int label_blocks, const int32_t* __restrict__ head, const int32_t* __restrict__ order,
+    const int32_t* __restrict__ runs, float* __restrict__ label_out) {
   __shared__ union Lds {
-    LabelLds label;
+    std::conditional_t<WINDOWS, WindowLds<NC>, LabelLds> label;
     FinalLds<NC, WPS> final;
     float sum[256];
   } lds;
   const int b = (int)blockIdx.x - 1;
   if (b < 0)
     mean_loss_block(lds.sum, a);
-  else if (b < label_blocks)
-    dweight_label_block<MODE>(b, lds.label, a.X, a.B, a.D, a.yl, a.k, head, kp, a.rnormX, a.dlabel,
-                              label_out);
-  else
+  else if (b >= label_blocks)
     dfeatures_final_block<NC, WPS>(b - label_blocks, lds.final, a);
+  else if constexpr (WINDOWS)
+    window_label_block<NC>(b, lds.label, a.X, a.D, order, runs, a.rnormX, a.dlabel, label_out);
+  else
+    dweight_label_block<LABEL_ADD>(b, lds.label, a.X, a.B, a.D, a.yl, a.k, head, a.rnormX, a.dlabel, label_out);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1382,9 +1580,9 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   auto norm_kernel = gather_normalize_kernel<T, NC>;
   const int x_blocks = (Bp + kNormWaves - 1) / kNormWaves;
   PFC_LAUNCH(c, KID_GATHER_W, norm_kernel,
-             dim3((unsigned)(x_blocks + (kp / 4 + kNormWaves - 1) / kNormWaves)),
+             dim3((unsigned)(nwin + x_blocks + (kp / 4 + kNormWaves - 1) / kNormWaves)),
              dim3(kNormWaves * 64), 0, x_blocks, X, B, Bp, yl, Xn, c->rnormX, c->clabel, W, c->N,
-             idx, k, kp, D, Dp, Wn, c->rnormW, c->head, nwin, c->err_flag);
+             idx, k, kp, D, Dp, Wn, c->rnormW, c->head, nwin, c->label_order, c->label_runs, c->err_flag);
 
   // raise the dynamic LDS limit of this context's kernels once (a context has one precision and
   // one D, hence one instantiation of run)
@@ -1435,17 +1633,21 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   }
   // window sums of the label part, added up: to dW_out, or (compact) in the side buffer
   auto launch_label_sum = [&](auto compact) -> int {
-    PFC_LAUNCH(c, KID_DW_LABEL_SUM, dweight_label_combine_kernel<compact.value>, dim3(B), dim3(256),
+    PFC_LAUNCH(c, KID_DW_LABEL_SUM, window_label_sum_kernel<compact.value>, dim3((B + 3) / 4), dim3(256),
                0, B, D, yl, k, c->head, kp, nwin, c->dlab, dW_out);
     return PFC_OK;
   };
   // label part of dWn in a launch of its own: added to dW_out, or (compact) left in the side buffer
   auto launch_label = [&](auto compact) -> int {
-    auto kernel = nwin ? dweight_label_kernel<LABEL_WINDOW>
-                       : dweight_label_kernel<compact.value ? LABEL_COMPACT : LABEL_ADD>;
-    PFC_LAUNCH(c, KID_DW_LABEL, kernel, dim3(B), dim3(kLabelThreads), 0, X, B, D, yl, k, c->head, kp,
-               c->rnormX, c->dlabel, nwin || compact.value ? c->dlab : dW_out);
-    return nwin ? launch_label_sum(compact) : PFC_OK;
+    if (nwin) {
+      PFC_LAUNCH(c, KID_DW_LABEL, window_label_kernel<NC>, dim3(nwin * kWindowBlocks), dim3(kLabelThreads), 0,
+                 X, D, c->label_order, c->label_runs, c->rnormX, c->dlabel, c->dlab);
+      return launch_label_sum(compact);
+    }
+    auto kernel = dweight_label_kernel<compact.value ? LABEL_COMPACT : LABEL_ADD>;
+    PFC_LAUNCH(c, KID_DW_LABEL, kernel, dim3(B), dim3(kLabelThreads), 0, X, B, D, yl, k, c->head,
+               c->rnormX, c->dlabel, compact.value ? c->dlab : dW_out);
+    return PFC_OK;
   };
   // The rest of both gradients; with_label: the label part of dWn is still to be added to dW_out.
   // (One thing keeps them apart: dX written over the features that the label part reads.)
@@ -1459,15 +1661,14 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     const FinalArgs fa{c->dXpart, dx.splits, B, Bp, D, Dp, X, W, c->N, idx, yl, k, c->rnormX,
                        c->rnormW, wlab, c->rowscale, c->dlabel, dX_out, c->lossrow, loss_out,
                        c->clabel, c->rowmax, stats_out};
-    const int label_blocks = with_label ? B : 0;
+    const int label_blocks = !with_label ? 0 : nwin ? nwin * kWindowBlocks : B;
     const bool wide = dx.splits >= kFinalWideSplits;
     const int spb = kLabelThreads / 64 / (wide ? 16 : 4);
-    auto kernel = nwin ? (wide ? gradients_final_kernel<NC, 16, LABEL_WINDOW>
-                               : gradients_final_kernel<NC, 4, LABEL_WINDOW>)
-                       : (wide ? gradients_final_kernel<NC, 16, LABEL_ADD>
-                               : gradients_final_kernel<NC, 4, LABEL_ADD>);
+    auto kernel = nwin ? (wide ? gradients_final_kernel<NC, 16, true> : gradients_final_kernel<NC, 4, true>)
+                       : (wide ? gradients_final_kernel<NC, 16, false> : gradients_final_kernel<NC, 4, false>);
     PFC_LAUNCH(c, KID_GRAD_FINAL, kernel, dim3((unsigned)(1 + label_blocks + (B + spb - 1) / spb)),
-               dim3(kLabelThreads), 0, fa, label_blocks, c->head, kp, nwin ? c->dlab : dW_out);
+               dim3(kLabelThreads), 0, fa, label_blocks, c->head, c->label_order, c->label_runs,
+               nwin ? c->dlab : dW_out);
     return with_label && nwin ? launch_label_sum(std::false_type{}) : PFC_OK;
   };
   const BackwardShape shape = backward_shape(c->num_cu, sizeof(T), size_b, Bp, Dp, D, kp);
