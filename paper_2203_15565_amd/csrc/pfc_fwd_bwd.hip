@@ -1012,20 +1012,20 @@ __global__ __launch_bounds__(kLabelThreads) void dweight_label_kernel(
 // of the batch, and one workgroup cannot read thousands of feature rows quickly (a compute unit draws a small share
 // of the memory bandwidth); most classes have a sample or two.  order_labels has put the samples of a window in order
 // of their class.  kWindowBlocks workgroups share a window's classes: one wavefront sums a class of up to
-// kWindowWave samples, the 16 of the workgroup share a larger one.  The sum goes to row i of `part`, i being the class's
-// first sample in the window; window_label_sum adds a class's sums in window order.
+// kWindowWave samples, the 16 of a workgroup share a larger one.  The sum goes to row i of `part`, i being the class's
+// first sample in the window; dweight_label_combine adds a class's sums in window order.
 // (A workgroup for every sample of the batch, which scanned the window if it was the first of its class, and
 // nothing to do for most of them: gradients_final at 16,384 samples x 3,592 classes x 512 89.5 us, now 46.7; step
 // 403 -> 359.)
-constexpr int kWindowBlocks = 32, kWindowWave = 16;
+constexpr int kWindowBlocks = 32, kWindowWave = 8;
 template <int NC>
 struct WindowLds {
   int begin[kLabelWindow / kWindowBlocks], end[kLabelWindow / kWindowBlocks];
   float4 part[kLabelThreads / 64 - 1][NC][64];
 };
-// sum over this wavefront's entries e < cnt (<= 64) of coef_e * X[row_e], lane e holding entry e
+// sum over this wavefront's entries e < cnt (<= 64) of dl_e * rn_e * X[row_e], lane e holding entry e
 template <int NC>
-__device__ __forceinline__ void label_rows(float4 (&acc)[NC], int cnt, int row, float coef,
+__device__ __forceinline__ void label_rows(float4 (&acc)[NC], int cnt, int row, float dl, float rn,
                                            const float* __restrict__ X, int D) {
   constexpr int UN = NC <= 2 ? 4 : 2;   // rows in flight
   const int lane = threadIdx.x & 63;
@@ -1044,7 +1044,7 @@ __device__ __forceinline__ void label_rows(float4 (&acc)[NC], int cnt, int row, 
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       if (e + u >= cnt) continue;
-      const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, coef), e + u));
+      const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dl * rn), e + u));
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         if (c * 256 + lane * 4 >= D) continue;
@@ -1068,8 +1068,7 @@ __device__ __forceinline__ void window_label_block(int block, WindowLds<NC>& lds
   runs += (int64_t)w * kWindowRuns;
   // this workgroup's classes: b, b + kWindowBlocks, ..
   const int total = runs[0], mine = (total - b + kWindowBlocks - 1) / kWindowBlocks;
-  if (mine <= 0) return;
-  if ((int)threadIdx.x < mine) {
+  if (threadIdx.x < kLabelWindow / kWindowBlocks) {   // (not waiting for their number: those behind it are not used)
     const int r = b + (int)threadIdx.x * kWindowBlocks;
     lds.begin[threadIdx.x] = runs[1 + r];
     lds.end[threadIdx.x] = runs[2 + r];
@@ -1080,12 +1079,13 @@ __device__ __forceinline__ void window_label_block(int block, WindowLds<NC>& lds
   auto sum = [&](int first, int step, int end) __attribute__((always_inline)) {
     const int at = first + lane * step;
     int row = 0;
-    float coef = 0.f;
+    float dl = 0.f, rn = 0.f;
     if (at < end) {
       row = order[at];
-      coef = dlabel[row] * rnormX[row];
+      dl = dlabel[row];
+      rn = rnormX[row];
     }
-    label_rows<NC>(acc, first < end ? (end - first + step - 1) / step : 0, row, coef, X, D);
+    label_rows<NC>(acc, first < end ? (end - first + step - 1) / step : 0, row, dl, rn, X, D);
   };
   auto store = [&](int begin) __attribute__((always_inline)) {
     float* dst = part + (int64_t)order[begin] * D;
@@ -1109,6 +1109,7 @@ __device__ __forceinline__ void window_label_block(int block, WindowLds<NC>& lds
     }
     __syncthreads();
     if (wave == 0) {
+#pragma unroll NC <= 2 ? 3 : 1
       for (int v = 0; v < WAVES - 1; ++v)
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -1128,11 +1129,11 @@ __global__ __launch_bounds__(kLabelThreads) void window_label_kernel(
   window_label_block<NC>(blockIdx.x, lds, X, D, order, runs, rnormX, dlabel, part);
 }
 
-// window_label_sum (after window_label_block): the wavefront of sample i, if that is the first of its class in the whole
+// dweight_label_combine (after window_label_block): the wavefront of sample i, if that is the first of its class in the whole
 // batch, adds the class's window sums (rows of `part` named by the window heads) in window order; the total
 // goes to row i of `part` (COMPACT, fused step) or is added to dWn[y].
 template <bool COMPACT>
-__global__ void window_label_sum_kernel(int B, int D, const int32_t* __restrict__ yl, int64_t k,
+__global__ void dweight_label_combine_kernel(int B, int D, const int32_t* __restrict__ yl, int64_t k,
                                         const int32_t* __restrict__ head, int64_t kp, int nwin,
                                         float* __restrict__ part, float* __restrict__ dW) {
   const int lane = threadIdx.x & 63;
@@ -1354,7 +1355,7 @@ __global__ __launch_bounds__(CfgB::THREADS) void gemm_backward_update_kernel(
 //   dx = (g - <g, xn_i> xn_i) / |x_i|
 template <int NC, int WPS>
 struct FinalLds {
-  float4 part[kLabelThreads / 64 / WPS][WPS - 1][NC][64];
+  float4 part[kLabelThreads / 64 / WPS][WPS > 1 ? WPS - 1 : 1][WPS > 1 ? NC : 1][64];
 };
 struct FinalArgs {
   const float* part;
@@ -1405,72 +1406,79 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
   // The wavefronts of a sample share the slices of S (wavefront w takes slices w, w + WPS, ...:
   // several independent loads in flight each); their partial rows are added in wavefront order by
   // wavefront 0, which then finishes the row: the same order on every run.
-  constexpr int nchunk = NC;
-  float4 sum[NC];
+  // What the last step needs is requested before the slices and in front of the barrier: the chain label -> class id
+  // -> row of W behind them was most of a small launch.
+  const bool ends = wave == 0 && i < a.B;
+  float rs = 0.f, rnx = 0.f, dl = 0.f, rnw = 0.f;
+  int32_t y = -1;
+  float4 x[NC], w[NC], sum[NC];
 #pragma unroll
-  for (int c = 0; c < nchunk; ++c) sum[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int c = 0; c < NC; ++c) x[c] = w[c] = sum[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (ends) {
+    y = a.yl[i];
+    rs = a.rowscale[i];
+    rnx = a.rnormX[i];
+    dl = a.dlabel[i];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c * 256 + lane * 4 < D) x[c] = *reinterpret_cast<const float4*>(a.X + (int64_t)i * D + c * 256 + lane * 4);
+  }
   for (int sp = wave; i < a.B && sp < a.splits; sp += WPS) {
 #pragma unroll
-    for (int c = 0; c < nchunk; ++c) {
+    for (int c = 0; c < NC; ++c) {
       if (c * 256 + lane * 4 >= D) continue;   // columns from D on are zero
       const float4 t = *reinterpret_cast<const float4*>(a.part + ((int64_t)sp * a.Bp + i) * a.Dp +
                                                         c * 256 + lane * 4);
       sum[c].x += t.x; sum[c].y += t.y; sum[c].z += t.z; sum[c].w += t.w;
     }
   }
-  if (wave > 0) {
+  if (ends && y >= 0 && (int64_t)y < a.k) {
+    const int64_t row = a.idx[y];
+    rnw = a.rnormW[y];
+    if (row >= 0 && row < a.N) {
+      // (a.wlab: W has been updated already, the label's row as it was)
+      const float* src = a.wlab ? a.wlab + (int64_t)i * D : a.W + row * D;
 #pragma unroll
-    for (int c = 0; c < nchunk; ++c) lds.part[grp][wave - 1][c][lane] = sum[c];
-  }
-  __syncthreads();
-  if (wave > 0 || i >= a.B) return;
-#pragma unroll
-  for (int c = 0; c < nchunk; ++c) {
-#pragma unroll
-    for (int w = 0; w < WPS - 1; ++w) {
-      if (w + 1 >= a.splits) break;   // those wavefronts had no slice
-      const float4 t = lds.part[grp][w][c][lane];
-      sum[c].x += t.x; sum[c].y += t.y; sum[c].z += t.z; sum[c].w += t.w;
+      for (int c = 0; c < NC; ++c)
+        if (c * 256 + lane * 4 < D) w[c] = *reinterpret_cast<const float4*>(src + c * 256 + lane * 4);
     }
   }
-  const float* W = a.W;
-  const float* X = a.X;
+  if constexpr (WPS > 1) {
+    if (wave > 0) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) lds.part[grp][wave - 1][c][lane] = sum[c];
+    }
+    __syncthreads();
+    if (!ends) return;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+#pragma unroll
+      for (int v = 0; v < WPS - 1; ++v) {
+        if (v + 1 >= a.splits) break;   // those wavefronts had no slice
+        const float4 t = lds.part[grp][v][c][lane];
+        sum[c].x += t.x; sum[c].y += t.y; sum[c].z += t.z; sum[c].w += t.w;
+      }
+    }
+  } else if (!ends) {
+    return;
+  }
   float* dX = a.dX;
-  const float rs = a.rowscale[i], rnx = a.rnormX[i], dl = a.dlabel[i];
-  const int32_t y = a.yl[i];
-  int64_t wrow = -1;
-  float rnw = 0.f;
-  if (y >= 0 && (int64_t)y < a.k) {
-    wrow = a.idx[y];
-    rnw = a.rnormW[y];
-    if (wrow < 0 || wrow >= a.N) wrow = -1;
-  }
-  if (a.wlab) {   // W has been updated already: the label's row as it was
-    W = a.wlab;
-    if (wrow >= 0) wrow = i;
-  }
   float4 g[NC], xn[NC];
   float u = 0.f;
 #pragma unroll
-  for (int c = 0; c < nchunk; ++c) {
-    const int d = c * 256 + lane * 4;
-    float4 t = sum[c];
+  for (int c = 0; c < NC; ++c) {   // (all are zero from column D on)
+    float4 t = sum[c], v = x[c];
+    const float f = dl * rnw;
     t.x *= rs; t.y *= rs; t.z *= rs; t.w *= rs;
-    if (wrow >= 0 && d < D) {
-      const float4 w = *reinterpret_cast<const float4*>(W + wrow * D + d);
-      const float f = dl * rnw;
-      t.x += f * w.x; t.y += f * w.y; t.z += f * w.z; t.w += f * w.w;
-    }
-    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);   // partial sums and x are zero from column D on
-    if (d < D) x = *reinterpret_cast<const float4*>(X + (int64_t)i * D + d);
-    x.x *= rnx; x.y *= rnx; x.z *= rnx; x.w *= rnx;
+    t.x += f * w[c].x; t.y += f * w[c].y; t.z += f * w[c].z; t.w += f * w[c].w;
+    v.x *= rnx; v.y *= rnx; v.z *= rnx; v.w *= rnx;
     g[c] = t;
-    xn[c] = x;
-    u += t.x * x.x + t.y * x.y + t.z * x.z + t.w * x.w;
+    xn[c] = v;
+    u += t.x * v.x + t.y * v.y + t.z * v.z + t.w * v.w;
   }
   u = wave_sum(u);
 #pragma unroll
-  for (int c = 0; c < nchunk; ++c) {
+  for (int c = 0; c < NC; ++c) {
     float4 o;
     o.x = (g[c].x - u * xn[c].x) * rnx;
     o.y = (g[c].y - u * xn[c].y) * rnx;
@@ -1490,7 +1498,8 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
 // 271, 16,384 samples x 3,592 476 -> 462.
 // From kFinalWideSplits slices on a sample gets 16 wavefronts instead of 4: below, a third of the 16 and more
 // would have no slice to add.
-constexpr int kFinalWideSplits = 12;
+// Up to kFinalOneSplits a sample gets one: three of four would have none.
+constexpr int kFinalWideSplits = 12, kFinalOneSplits = 2;
 template <int NC, int WPS, bool WINDOWS>
 __global__ __launch_bounds__(kLabelThreads, 8) void gradients_final_kernel(
     FinalArgs a, int label_blocks, const int32_t* __restrict__ head, const int32_t* __restrict__ order,
@@ -1633,7 +1642,7 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   }
   // window sums of the label part, added up: to dW_out, or (compact) in the side buffer
   auto launch_label_sum = [&](auto compact) -> int {
-    PFC_LAUNCH(c, KID_DW_LABEL_SUM, window_label_sum_kernel<compact.value>, dim3((B + 3) / 4), dim3(256),
+    PFC_LAUNCH(c, KID_DW_LABEL_SUM, dweight_label_combine_kernel<compact.value>, dim3((B + 3) / 4), dim3(256),
                0, B, D, yl, k, c->head, kp, nwin, c->dlab, dW_out);
     return PFC_OK;
   };
@@ -1662,10 +1671,14 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
                        c->rnormW, wlab, c->rowscale, c->dlabel, dX_out, c->lossrow, loss_out,
                        c->clabel, c->rowmax, stats_out};
     const int label_blocks = !with_label ? 0 : nwin ? nwin * kWindowBlocks : B;
-    const bool wide = dx.splits >= kFinalWideSplits;
-    const int spb = kLabelThreads / 64 / (wide ? 16 : 4);
-    auto kernel = nwin ? (wide ? gradients_final_kernel<NC, 16, true> : gradients_final_kernel<NC, 4, true>)
-                       : (wide ? gradients_final_kernel<NC, 16, false> : gradients_final_kernel<NC, 4, false>);
+    const bool wide = dx.splits >= kFinalWideSplits, one = dx.splits <= kFinalOneSplits;
+    const int spb = kLabelThreads / 64 / (wide ? 16 : one ? 1 : 4);
+    auto kernel = nwin ? (wide  ? gradients_final_kernel<NC, 16, true>
+                          : one ? gradients_final_kernel<NC, 1, true>
+                                : gradients_final_kernel<NC, 4, true>)
+                       : (wide  ? gradients_final_kernel<NC, 16, false>
+                          : one ? gradients_final_kernel<NC, 1, false>
+                                : gradients_final_kernel<NC, 4, false>);
     PFC_LAUNCH(c, KID_GRAD_FINAL, kernel, dim3((unsigned)(1 + label_blocks + (B + spb - 1) / spb)),
                dim3(kLabelThreads), 0, fa, label_blocks, c->head, c->label_order, c->label_runs,
                nwin ? c->dlab : dW_out);

@@ -1,5 +1,5 @@
 """The label part of batches of several windows, where the number of a class's samples in a window matters: one
-wavefront sums up to 16, all wavefronts of a workgroup more, up to a whole window of 1024."""
+wavefront sums up to 8, all wavefronts of a workgroup more, up to a whole window of 1024."""
 import numpy as np
 import pytest
 
@@ -10,7 +10,7 @@ from pfc_harness import ROW_GRAD_TOL, gpu_forward_backward, gpu_sample, rel_max,
 pytestmark = pytest.mark.gpu
 
 N = 3000
-COUNTS = [1, 2, 3, 4, 5, 15, 16, 17, 18, 31, 32, 33, 64, 65, 200]   # samples of one class in a window
+COUNTS = [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 18, 31, 32, 33, 64, 65, 200]   # samples of one class in a window
 
 
 def _labels(B, rng):
