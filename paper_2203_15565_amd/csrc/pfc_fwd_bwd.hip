@@ -1015,8 +1015,8 @@ __global__ __launch_bounds__(kLabelThreads) void dweight_label_kernel(
 // kWindowWave samples, the 16 of a workgroup share a larger one.  The sum goes to row i of `part`, i being the class's
 // first sample in the window; dweight_label_combine adds a class's sums in window order.
 // (A workgroup for every sample of the batch, which scanned the window if it was the first of its class, and
-// nothing to do for most of them: gradients_final at 16,384 samples x 3,592 classes x 512 89.5 us, now 46.7; step
-// 403 -> 359.)
+// nothing to do for most of them: gradients_final at 16,384 samples x 3,592 classes x 512 89.5 us, now 35.3; step
+// 392 -> 338.)
 constexpr int kWindowBlocks = 32, kWindowWave = 8;
 template <int NC>
 struct WindowLds {

@@ -63,7 +63,11 @@ struct TileCfg {
   // both operands k contiguous: the logits, products of unit vectors
   using Split = std::conditional_t<!AKM && !BKM, SplitUnit, SplitBf16>;
   static constexpr int PLANES = !AKM && !BKM ? 2 : 3;
-  static constexpr int LDS_BYTES = DMA ? (ABUF * BM + BBUF * BN) * SLAB : 2 * PLANES * 32 * (BM + BN);
+  // (fp32) groups of 16 reduction steps in a stage; two where the planes of two fit beside the other workgroups of
+  // a compute unit (three planes: 144 KB) and their fragments into the registers (256-tiles: 224 now)
+  static constexpr int STAGE_GROUPS = PLANES == 2 && BM < 256 ? 2 : 1;
+  static constexpr int LDS_BYTES =
+      DMA ? (ABUF * BM + BBUF * BN) * SLAB : 2 * STAGE_GROUPS * PLANES * 32 * (BM + BN);
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be whole 32x32 blocks");
 };
 
@@ -390,10 +394,13 @@ __device__ __forceinline__ SplitChunk split_chunk(int c, const float* base, int6
           L::BYTES};
 }
 
-// gemm_tile (below) for fp32 operands.  LDS holds two stages of 16 reduction steps, each the planes of both operands
-// (layout: DmaLds).  Every thread loads 8 neighbouring values of an operand, one slab or more ahead, splits them
-// between the MFMAs of the slab at hand and stores one 16-byte chunk to each plane of the other stage; the last product
-// of a slab is added up behind the barrier, under the first fragment reads of the next one.
+// gemm_tile (below) for fp32 operands.  LDS holds two stages of one or two groups of 16 reduction steps, each the planes
+// of both operands (layout: DmaLds).  Two groups (the logits in 128- and 64-tiles) are half the barriers and, with one
+// block a wavefront, two sums whose products need not wait for each other; step, us, one -> two: 128 x 1,000 x 512
+// 54.7 -> 53.5, 512 x 9,344 x 512 167.7 -> 165.5, 300 x 40,000 x 512 379 -> 371, 1024 x 36,024 x 512 with the update
+// 763 -> 749, 500 x 4,000 x 1024 137.4 -> 135.7.  Every thread loads 8 neighbouring values of an operand, one stage or more ahead, splits them
+// between the MFMAs of the stage at hand and stores one 16-byte chunk to each plane of the other; the last product
+// of a stage is added up behind the barrier, under the first fragment reads of the next one.
 // What it replaces: v_mfma_f32_32x32x2_f32, whose rate (157 TFLOP/s nominal) was the bound at any tile size; six bf16
 // products are 2.7 times that, three fp16 products 5.3 times.  Forward/backward, us, before -> now: 2048 x 30,000 x
 // 512 1588 -> 858, 1907 x 20,355 x 512 1134 -> 641, 512 x 9,344 x 512 163 -> 131, 1024 x 36,024 x 512 with the
@@ -410,12 +417,15 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
   typedef DmaLds<__bf16, Cfg::BM, Cfg::A_KMAJOR, 32> LA;   // a plane of 16 reduction steps
   typedef DmaLds<__bf16, Cfg::BN, Cfg::B_KMAJOR, 32> LB;
   typedef typename Cfg::Split S;
-  constexpr int NP = S::PLANES, NPR = S::PRODUCTS;
-  constexpr int STAGE = NP * (LA::BYTES + LB::BYTES), B0 = NP * LA::BYTES;
+  constexpr int NP = S::PLANES, NPR = S::PRODUCTS, G = Cfg::STAGE_GROUPS;
+  constexpr int GROUP = NP * (LA::BYTES + LB::BYTES), STAGE = G * GROUP, B0 = NP * LA::BYTES;
   constexpr int CA = LA::BYTES / 16, CB = LB::BYTES / 16, THREADS = Cfg::THREADS;
-  constexpr int NPT = (CA + CB + THREADS - 1) / THREADS;   // chunks of 8 values per thread and slab
+  constexpr int NPT = (CA + CB + THREADS - 1) / THREADS;   // chunks of 8 values per thread and group
   static_assert(CA % 64 == 0 && CB % 64 == 0, "a wavefront's chunks are of one operand");
+  static_assert(Cfg::BK / 16 % G == 0, "whole stages");
+  static_assert(G == 1 || CHAIN == 0, "sums in pieces: stages of one group");
   constexpr int MM = Cfg::TM * Cfg::TN;
+  constexpr int SETS = MM == 1 ? G : 1;   // one block a wavefront: a sum for every group, or its products wait in a row
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   FragAddr<LA, Cfg::A_KMAJOR, 1, Cfg::TM> ra;
@@ -432,73 +442,93 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
     if (first < CA) ch[p] = split_chunk<LA, Cfg::A_KMAJOR>(id, A, lda, 0);
     else ch[p] = split_chunk<LB, Cfg::B_KMAJOR>(has[p] ? id - CA : 0, B, ldb, B0);
   }
-  const int last = nslabs * (Cfg::BK / 16) - 1;
-  // values of the next DEPTH slabs, requested as soon as those before them are split
-  constexpr int DEPTH = THREADS == 256 ? 4 : 1;   // (128-tiles: the registers of a second workgroup)
-  f32x4 x[DEPTH][NPT][2];
+  const int last = nslabs * (Cfg::BK / 16 / G) - 1;
+  // values of the next DEPTH stages, requested as soon as those before them are split
+  constexpr int DEPTH = THREADS == 256 ? 4 / G : 1;   // (128-tiles: the registers of a second workgroup)
+  f32x4 x[DEPTH][G][NPT][2];
   auto load = [&](int s, int u) __attribute__((always_inline)) {
 #pragma unroll
-    for (int p = 0; p < NPT; ++p) {
-      if (NPT * THREADS > CA + CB && !has[p]) continue;
-      x[u][p][0] = *reinterpret_cast<const f32x4*>(ch[p].src + s * ch[p].step);
-      x[u][p][1] = *reinterpret_cast<const f32x4*>(ch[p].src + s * ch[p].step + 4);
-    }
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int p = 0; p < NPT; ++p) {
+        if (NPT * THREADS > CA + CB && !has[p]) continue;
+        const float* src = ch[p].src + (s * G + h) * ch[p].step;
+        x[u][h][p][0] = *reinterpret_cast<const f32x4*>(src);
+        x[u][h][p][1] = *reinterpret_cast<const f32x4*>(src + 4);
+      }
   };
   u32x4 w[NPT][NP];
   // pair i of this thread's chunks; the last of a chunk stores it to the stage
   auto split = [&](int i, int u, char* stage) __attribute__((always_inline)) {
-    const int p = i / 4, e = i % 4;
+    const int h = i / (4 * NPT), p = i / 4 % NPT, e = i % 4;
     uint32_t v[NP];
-    S::pair(x[u][p][e / 2][e % 2 * 2], x[u][p][e / 2][e % 2 * 2 + 1], v);
+    S::pair(x[u][h][p][e / 2][e % 2 * 2], x[u][h][p][e / 2][e % 2 * 2 + 1], v);
 #pragma unroll
     for (int q = 0; q < NP; ++q) w[p][q][e] = v[q];
     if (e == 3) {
       if (NPT * THREADS > CA + CB && !has[p]) return;
 #pragma unroll
-      for (int q = 0; q < NP; ++q) *reinterpret_cast<u32x4*>(stage + ch[p].dst + q * ch[p].plane) = w[p][q];
+      for (int q = 0; q < NP; ++q)
+        *reinterpret_cast<u32x4*>(stage + h * GROUP + ch[p].dst + q * ch[p].plane) = w[p][q];
     }
   };
-  u32x4 a[NP][Cfg::TM], b[NP][Cfg::TN];
-  auto read_a = [&](const char* stage, int q, u32x4 (&f)[Cfg::TM]) __attribute__((always_inline)) {
+  constexpr int PIECES = 4 * NPT * G;
+  u32x4 a[G][NP][Cfg::TM], b[G][NP][Cfg::TN];
+  auto read_a = [&](const char* group, int q, u32x4 (&f)[Cfg::TM]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < Cfg::TM; ++t) f[t] = ra.read(stage + q * LA::BYTES, t, 0);
+    for (int t = 0; t < Cfg::TM; ++t) f[t] = ra.read(group + q * LA::BYTES, t, 0);
   };
-  auto read_b = [&](const char* stage, int q, u32x4 (&f)[Cfg::TN]) __attribute__((always_inline)) {
+  auto read_b = [&](const char* group, int q, u32x4 (&f)[Cfg::TN]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < Cfg::TN; ++t) f[t] = rb.read(stage + B0 + q * LB::BYTES, t, 0);
+    for (int t = 0; t < Cfg::TN; ++t) f[t] = rb.read(group + B0 + q * LB::BYTES, t, 0);
   };
   load(0, 0);
 #pragma unroll
   for (int u = 1; u < DEPTH; ++u) load(u < last ? u : last, u);
 #pragma unroll
-  for (int i = 0; i < 4 * NPT; ++i) split(i, 0, smem);
+  for (int i = 0; i < PIECES; ++i) split(i, 0, smem);
   load(DEPTH < last ? DEPTH : last, 0);
   __syncthreads();
-  read_a(smem, 0, a[0]);
-  read_b(smem, 0, b[0]);
+  read_a(smem, 0, a[0][0]);
+  read_b(smem, 0, b[0][0]);
   f32x16 sums[Cfg::TM][Cfg::TN];
-  if constexpr (CHAIN > 0) zero_acc<Cfg>(sums);
+  if constexpr (CHAIN > 0 || SETS > 1) zero_acc<Cfg>(sums);
   for (int s0 = 0; s0 <= last; s0 += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      const int s = s0 + d, u = (d + 1) % DEPTH;   // set of slab s+1
+      const int s = s0 + d, u = (d + 1) % DEPTH;   // set of stage s+1
       if (s > last) break;
       char* cur = smem + (s & 1) * STAGE;
       char* nxt = smem + (~s & 1) * STAGE;
 #pragma unroll
-      for (int q = 1; q < NP; ++q) read_b(cur, q, b[q]);
+      for (int h = 1; h < G; ++h) {
+        read_a(cur + h * GROUP, 0, a[h][0]);
+        read_b(cur + h * GROUP, 0, b[h][0]);
+      }
 #pragma unroll
-      for (int q = 1; q < NP; ++q) read_a(cur, q, a[q]);
+      for (int q = 1; q < NP; ++q)
+#pragma unroll
+        for (int h = 0; h < G; ++h) read_b(cur + h * GROUP, q, b[h][q]);
+#pragma unroll
+      for (int q = 1; q < NP; ++q)
+#pragma unroll
+        for (int h = 0; h < G; ++h) read_a(cur + h * GROUP, q, a[h][q]);
       __builtin_amdgcn_sched_barrier(0);
-      // between the products of this slab the values of the next one are split, from the second product (the
+      // block t of product o of group h
+      auto product = [&](auto oc, auto hc, auto tc) __attribute__((always_inline)) {
+        constexpr int o = decltype(oc)::value, h = decltype(hc)::value, t = decltype(tc)::value;
+        auto& to = SETS > 1 && h > 0 ? sums : acc;
+        S::mfma(a[h][S::A[o]][t / Cfg::TN], b[h][S::B[o]][t % Cfg::TN], to[t / Cfg::TN][t % Cfg::TN]);
+      };
+      // between the products of this stage the values of the next one are split, from the second product (the
       // third of six) on
-      constexpr int Q = (NPR - 1) * MM, Q0 = NPR > 3 ? MM : 0, SPAN = NPR > 3 ? 3 * MM : Q;
+      constexpr int Q = (G * NPR - 1) * MM, Q0 = NPR > 3 ? MM : 0, SPAN = NPR > 3 ? 3 * MM : Q;
       static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
-        constexpr int q = decltype(qc)::value, t = q % MM, o = q / MM;
-        constexpr int from = pieces_before(q, Q0, SPAN, 4 * NPT), to = pieces_before(q + 1, Q0, SPAN, 4 * NPT);
+        constexpr int q = decltype(qc)::value, t = q % MM, h = q / MM % G, o = q / MM / G;
+        constexpr int from = pieces_before(q, Q0, SPAN, PIECES), to = pieces_before(q + 1, Q0, SPAN, PIECES);
         static_for<from, to>([&](auto i) __attribute__((always_inline)) { split(decltype(i)::value, u, nxt); });
         if constexpr (q == (NPR > 3 ? 4 * MM : Q - 1)) load(s + 1 + DEPTH < last ? s + 1 + DEPTH : last, u);
-        S::mfma(a[S::A[o]][t / Cfg::TN], b[S::B[o]][t % Cfg::TN], acc[t / Cfg::TN][t % Cfg::TN]);
+        product(std::integral_constant<int, o>{}, std::integral_constant<int, h>{}, std::integral_constant<int, t>{});
         __builtin_amdgcn_sched_barrier(0);
       });
       __syncthreads();
@@ -506,14 +536,14 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
       read_a(nxt, 0, an);
       read_b(nxt, 0, bn);
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int t = 0; t < MM; ++t)
-        S::mfma(a[S::A[NPR - 1]][t / Cfg::TN], b[S::B[NPR - 1]][t % Cfg::TN], acc[t / Cfg::TN][t % Cfg::TN]);
+      static_for<0, MM>([&](auto t) __attribute__((always_inline)) {
+        product(std::integral_constant<int, NPR - 1>{}, std::integral_constant<int, G - 1>{}, t);
+      });
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < Cfg::TM; ++t) a[0][t] = an[t];
+      for (int t = 0; t < Cfg::TM; ++t) a[0][0][t] = an[t];
 #pragma unroll
-      for (int t = 0; t < Cfg::TN; ++t) b[0][t] = bn[t];
+      for (int t = 0; t < Cfg::TN; ++t) b[0][0][t] = bn[t];
       if constexpr (CHAIN > 0) {
         if ((s + 1) % (CHAIN * Cfg::BK / 16) == 0 && s < last) {
           add_acc<Cfg>(sums, acc);
@@ -522,7 +552,7 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
       }
     }
   }
-  if constexpr (CHAIN > 0) add_acc<Cfg>(acc, sums);
+  if constexpr (CHAIN > 0 || SETS > 1) add_acc<Cfg>(acc, sums);
   if constexpr (S::UNSCALE != 1.f) {
 #pragma unroll
     for (int i = 0; i < Cfg::TM; ++i)
