@@ -223,6 +223,17 @@ __device__ __forceinline__ float wave_sum(float v) {
   return (r0 + r1) + (r2 + r3);
 }
 
+// Likewise over each group of 16 or 32 neighbouring lanes (the bits of wave_sum with zeros in the other lanes).
+template <int LANES>
+__device__ __forceinline__ float lane_group_sum(float v) {
+  static_assert(LANES == 16 || LANES == 32, "a row of 16 lanes or two");
+  v = dpp_xadd<0xB1>(v);
+  v = dpp_xadd<0x4E>(v);
+  v = dpp_xadd<0x141>(v);
+  v = dpp_xadd<0x140>(v);
+  return LANES == 32 ? v + __shfl_xor(v, 16, 64) : v;
+}
+
 template <typename T>
 __device__ __forceinline__ T from_float(float x);
 template <>
