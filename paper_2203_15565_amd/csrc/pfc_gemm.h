@@ -12,8 +12,9 @@
 //
 // A workgroup of WM x WN wavefronts (64 lanes each) owns a BM x BN tile of C.  K is walked in
 // slabs of BK = 64 (bf16) or 32 (fp32) reduction steps.  bf16 operands go from global memory to LDS
-// without registers (gemm_tile_dma).  fp32 operands are split into planes of 16 bits on the way
-// (gemm_tile_split): three bf16 planes and six products, or for the logits two fp16 planes and three.
+// without registers (gemm_tile_dma).  The fp32 operands of the backward products are split into planes of 16 bits on the
+// way (gemm_tile_split): three bf16 planes and six products; those of the logits are multiplied as they are
+// (gemm_tile_fp32).
 //
 // Fragment convention (the same for A and B, which is all a dot product needs): a group of 16 reduction
 // steps is split between the lane halves, lanes 0..31 taking the first half and lanes 32..63 the
@@ -30,13 +31,8 @@
 
 namespace pfc {
 
-struct SplitUnit;
-struct SplitBf16;
-
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -60,14 +56,10 @@ struct TileCfg {
   static constexpr int WTM = BM / WM, WTN = BN / WN;       // tile of one wavefront
   static constexpr int TM = WTM / 32, TN = WTN / 32;       // 32x32 blocks per wavefront
   static constexpr bool DMA = sizeof(T) == 2;
-  // both operands k contiguous: the logits, products of unit vectors
-  using Split = std::conditional_t<!AKM && !BKM, SplitUnit, SplitBf16>;
-  static constexpr int PLANES = !AKM && !BKM ? 2 : 3;
-  // (fp32) groups of 16 reduction steps in a stage; two where the planes of two fit beside the other workgroups of
-  // a compute unit (three planes: 144 KB) and their fragments into the registers (256-tiles: 224 now)
-  static constexpr int STAGE_GROUPS = PLANES == 2 && BM < 256 ? 2 : 1;
-  static constexpr int LDS_BYTES =
-      DMA ? (ABUF * BM + BBUF * BN) * SLAB : 2 * STAGE_GROUPS * PLANES * 32 * (BM + BN);
+  static constexpr bool SPLIT = !DMA && (AKM || BKM);   // fp32: all but the logits (both k contiguous)
+  static constexpr int LDS_BYTES = DMA     ? (ABUF * BM + BBUF * BN) * SLAB
+                                   : SPLIT ? 2 * 3 * 32 * (BM + BN)
+                                           : 2 * (SLAB + 16) * (BM + BN);
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be whole 32x32 blocks");
 };
 
@@ -326,7 +318,6 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
 struct SplitBf16 {
   static constexpr int PLANES = 3, PRODUCTS = 6;
   static constexpr int A[PRODUCTS] = {0, 0, 0, 1, 2, 1}, B[PRODUCTS] = {0, 1, 2, 0, 0, 1};
-  static constexpr float UNSCALE = 1.f;
   // words of one pair of neighbours in the planes; the remainders are exact, the dot instruction takes a plane
   // off without widening it first (x - 1 * h + 0 * h')
   static __device__ __forceinline__ void pair(float a, float b, uint32_t (&w)[PLANES]) {
@@ -345,25 +336,6 @@ struct SplitBf16 {
     }
   }
   static __device__ __forceinline__ void mfma(const u32x4& a, const u32x4& b, f32x16& c) { mfma_bf16(a, b, c); }
-};
-
-// Components of unit vectors: 2^12 x = h + l in fp16, to 2^-23 of the value (2^-37 of the vector's length for small
-// ones); l l, at most 2^-24 of a product, is left out.
-struct SplitUnit {
-  static constexpr int PLANES = 2, PRODUCTS = 3;
-  static constexpr int A[PRODUCTS] = {0, 0, 1}, B[PRODUCTS] = {0, 1, 0};
-  static constexpr float SCALE = 4096.f, UNSCALE = 1.f / (SCALE * SCALE);
-  static __device__ __forceinline__ void pair(float a, float b, uint32_t (&w)[PLANES]) {
-    const f16x2 h = __builtin_convertvector(f32x2{a * SCALE, b * SCALE}, f16x2);
-    const f16x2 l = __builtin_convertvector(
-        f32x2{__builtin_fmaf(a, SCALE, -(float)h[0]), __builtin_fmaf(b, SCALE, -(float)h[1])}, f16x2);
-    w[0] = __builtin_bit_cast(uint32_t, h);
-    w[1] = __builtin_bit_cast(uint32_t, l);
-  }
-  static __device__ __forceinline__ void mfma(const u32x4& a, const u32x4& b, f32x16& c) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
-                                               0, 0);
-  }
 };
 
 // f(0th), .., f(last) with the index as a type: the bodies are whole before any loop optimisation.
@@ -394,15 +366,12 @@ __device__ __forceinline__ SplitChunk split_chunk(int c, const float* base, int6
           L::BYTES};
 }
 
-// gemm_tile (below) for fp32 operands.  LDS holds two stages of one or two groups of 16 reduction steps, each the planes
-// of both operands (layout: DmaLds).  Two groups (the logits in 128- and 64-tiles) are half the barriers and, with one
-// block a wavefront, two sums whose products need not wait for each other; step, us, one -> two: 128 x 1,000 x 512
-// 54.7 -> 53.5, 512 x 9,344 x 512 167.7 -> 165.5, 300 x 40,000 x 512 379 -> 371, 1024 x 36,024 x 512 with the update
-// 763 -> 749, 500 x 4,000 x 1024 137.4 -> 135.7.  Every thread loads 8 neighbouring values of an operand, one stage or more ahead, splits them
-// between the MFMAs of the stage at hand and stores one 16-byte chunk to each plane of the other; the last product
-// of a stage is added up behind the barrier, under the first fragment reads of the next one.
+// gemm_tile (below) for the fp32 operands of the backward products.  LDS holds two stages of 16 reduction steps, each the planes of both operands
+// (layout: DmaLds).  Every thread loads 8 neighbouring values of an operand, one slab or more ahead, splits them
+// between the MFMAs of the slab at hand and stores one 16-byte chunk to each plane of the other stage; the last product
+// of a slab is added up behind the barrier, under the first fragment reads of the next one.
 // What it replaces: v_mfma_f32_32x32x2_f32, whose rate (157 TFLOP/s nominal) was the bound at any tile size; six bf16
-// products are 2.7 times that, three fp16 products 5.3 times.  Forward/backward, us, before -> now: 2048 x 30,000 x
+// products are 2.7 times that.  Forward/backward, us, before -> now: 2048 x 30,000 x
 // 512 1588 -> 858, 1907 x 20,355 x 512 1134 -> 641, 512 x 9,344 x 512 163 -> 131, 1024 x 36,024 x 512 with the
 // update 1183 -> 701, 300 x 40,000 x 512 642 -> 278, 128 x 1,000 x 512 35.4 -> 34.7 (latency).
 // Error against 64 bits (2-norm), fp32 products -> now: feature gradient 512 x 9,344 x 512 6.4e-7 -> 4.2e-7, 64 x
@@ -416,16 +385,13 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
                                                 f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
   typedef DmaLds<__bf16, Cfg::BM, Cfg::A_KMAJOR, 32> LA;   // a plane of 16 reduction steps
   typedef DmaLds<__bf16, Cfg::BN, Cfg::B_KMAJOR, 32> LB;
-  typedef typename Cfg::Split S;
-  constexpr int NP = S::PLANES, NPR = S::PRODUCTS, G = Cfg::STAGE_GROUPS;
-  constexpr int GROUP = NP * (LA::BYTES + LB::BYTES), STAGE = G * GROUP, B0 = NP * LA::BYTES;
+  typedef SplitBf16 S;
+  constexpr int NP = S::PLANES, NPR = S::PRODUCTS;
+  constexpr int STAGE = NP * (LA::BYTES + LB::BYTES), B0 = NP * LA::BYTES;
   constexpr int CA = LA::BYTES / 16, CB = LB::BYTES / 16, THREADS = Cfg::THREADS;
-  constexpr int NPT = (CA + CB + THREADS - 1) / THREADS;   // chunks of 8 values per thread and group
+  constexpr int NPT = (CA + CB + THREADS - 1) / THREADS;   // chunks of 8 values per thread and slab
   static_assert(CA % 64 == 0 && CB % 64 == 0, "a wavefront's chunks are of one operand");
-  static_assert(Cfg::BK / 16 % G == 0, "whole stages");
-  static_assert(G == 1 || CHAIN == 0, "sums in pieces: stages of one group");
   constexpr int MM = Cfg::TM * Cfg::TN;
-  constexpr int SETS = MM == 1 ? G : 1;   // one block a wavefront: a sum for every group, or its products wait in a row
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   FragAddr<LA, Cfg::A_KMAJOR, 1, Cfg::TM> ra;
@@ -442,93 +408,73 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
     if (first < CA) ch[p] = split_chunk<LA, Cfg::A_KMAJOR>(id, A, lda, 0);
     else ch[p] = split_chunk<LB, Cfg::B_KMAJOR>(has[p] ? id - CA : 0, B, ldb, B0);
   }
-  const int last = nslabs * (Cfg::BK / 16 / G) - 1;
-  // values of the next DEPTH stages, requested as soon as those before them are split
-  constexpr int DEPTH = THREADS == 256 ? 4 / G : 1;   // (128-tiles: the registers of a second workgroup)
-  f32x4 x[DEPTH][G][NPT][2];
+  const int last = nslabs * (Cfg::BK / 16) - 1;
+  // values of the next DEPTH slabs, requested as soon as those before them are split
+  constexpr int DEPTH = THREADS == 256 ? 4 : 1;   // (128-tiles: the registers of a second workgroup)
+  f32x4 x[DEPTH][NPT][2];
   auto load = [&](int s, int u) __attribute__((always_inline)) {
 #pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int p = 0; p < NPT; ++p) {
-        if (NPT * THREADS > CA + CB && !has[p]) continue;
-        const float* src = ch[p].src + (s * G + h) * ch[p].step;
-        x[u][h][p][0] = *reinterpret_cast<const f32x4*>(src);
-        x[u][h][p][1] = *reinterpret_cast<const f32x4*>(src + 4);
-      }
+    for (int p = 0; p < NPT; ++p) {
+      if (NPT * THREADS > CA + CB && !has[p]) continue;
+      x[u][p][0] = *reinterpret_cast<const f32x4*>(ch[p].src + s * ch[p].step);
+      x[u][p][1] = *reinterpret_cast<const f32x4*>(ch[p].src + s * ch[p].step + 4);
+    }
   };
   u32x4 w[NPT][NP];
   // pair i of this thread's chunks; the last of a chunk stores it to the stage
   auto split = [&](int i, int u, char* stage) __attribute__((always_inline)) {
-    const int h = i / (4 * NPT), p = i / 4 % NPT, e = i % 4;
+    const int p = i / 4, e = i % 4;
     uint32_t v[NP];
-    S::pair(x[u][h][p][e / 2][e % 2 * 2], x[u][h][p][e / 2][e % 2 * 2 + 1], v);
+    S::pair(x[u][p][e / 2][e % 2 * 2], x[u][p][e / 2][e % 2 * 2 + 1], v);
 #pragma unroll
     for (int q = 0; q < NP; ++q) w[p][q][e] = v[q];
     if (e == 3) {
       if (NPT * THREADS > CA + CB && !has[p]) return;
 #pragma unroll
-      for (int q = 0; q < NP; ++q)
-        *reinterpret_cast<u32x4*>(stage + h * GROUP + ch[p].dst + q * ch[p].plane) = w[p][q];
+      for (int q = 0; q < NP; ++q) *reinterpret_cast<u32x4*>(stage + ch[p].dst + q * ch[p].plane) = w[p][q];
     }
   };
-  constexpr int PIECES = 4 * NPT * G;
-  u32x4 a[G][NP][Cfg::TM], b[G][NP][Cfg::TN];
-  auto read_a = [&](const char* group, int q, u32x4 (&f)[Cfg::TM]) __attribute__((always_inline)) {
+  u32x4 a[NP][Cfg::TM], b[NP][Cfg::TN];
+  auto read_a = [&](const char* stage, int q, u32x4 (&f)[Cfg::TM]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < Cfg::TM; ++t) f[t] = ra.read(group + q * LA::BYTES, t, 0);
+    for (int t = 0; t < Cfg::TM; ++t) f[t] = ra.read(stage + q * LA::BYTES, t, 0);
   };
-  auto read_b = [&](const char* group, int q, u32x4 (&f)[Cfg::TN]) __attribute__((always_inline)) {
+  auto read_b = [&](const char* stage, int q, u32x4 (&f)[Cfg::TN]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < Cfg::TN; ++t) f[t] = rb.read(group + B0 + q * LB::BYTES, t, 0);
+    for (int t = 0; t < Cfg::TN; ++t) f[t] = rb.read(stage + B0 + q * LB::BYTES, t, 0);
   };
   load(0, 0);
 #pragma unroll
   for (int u = 1; u < DEPTH; ++u) load(u < last ? u : last, u);
 #pragma unroll
-  for (int i = 0; i < PIECES; ++i) split(i, 0, smem);
+  for (int i = 0; i < 4 * NPT; ++i) split(i, 0, smem);
   load(DEPTH < last ? DEPTH : last, 0);
   __syncthreads();
-  read_a(smem, 0, a[0][0]);
-  read_b(smem, 0, b[0][0]);
+  read_a(smem, 0, a[0]);
+  read_b(smem, 0, b[0]);
   f32x16 sums[Cfg::TM][Cfg::TN];
-  if constexpr (CHAIN > 0 || SETS > 1) zero_acc<Cfg>(sums);
+  if constexpr (CHAIN > 0) zero_acc<Cfg>(sums);
   for (int s0 = 0; s0 <= last; s0 += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      const int s = s0 + d, u = (d + 1) % DEPTH;   // set of stage s+1
+      const int s = s0 + d, u = (d + 1) % DEPTH;   // set of slab s+1
       if (s > last) break;
       char* cur = smem + (s & 1) * STAGE;
       char* nxt = smem + (~s & 1) * STAGE;
 #pragma unroll
-      for (int h = 1; h < G; ++h) {
-        read_a(cur + h * GROUP, 0, a[h][0]);
-        read_b(cur + h * GROUP, 0, b[h][0]);
-      }
+      for (int q = 1; q < NP; ++q) read_b(cur, q, b[q]);
 #pragma unroll
-      for (int q = 1; q < NP; ++q)
-#pragma unroll
-        for (int h = 0; h < G; ++h) read_b(cur + h * GROUP, q, b[h][q]);
-#pragma unroll
-      for (int q = 1; q < NP; ++q)
-#pragma unroll
-        for (int h = 0; h < G; ++h) read_a(cur + h * GROUP, q, a[h][q]);
+      for (int q = 1; q < NP; ++q) read_a(cur, q, a[q]);
       __builtin_amdgcn_sched_barrier(0);
-      // block t of product o of group h
-      auto product = [&](auto oc, auto hc, auto tc) __attribute__((always_inline)) {
-        constexpr int o = decltype(oc)::value, h = decltype(hc)::value, t = decltype(tc)::value;
-        auto& to = SETS > 1 && h > 0 ? sums : acc;
-        S::mfma(a[h][S::A[o]][t / Cfg::TN], b[h][S::B[o]][t % Cfg::TN], to[t / Cfg::TN][t % Cfg::TN]);
-      };
-      // between the products of this stage the values of the next one are split, from the second product (the
+      // between the products of this slab the values of the next one are split, from the second product (the
       // third of six) on
-      constexpr int Q = (G * NPR - 1) * MM, Q0 = NPR > 3 ? MM : 0, SPAN = NPR > 3 ? 3 * MM : Q;
+      constexpr int Q = (NPR - 1) * MM, Q0 = NPR > 3 ? MM : 0, SPAN = NPR > 3 ? 3 * MM : Q;
       static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
-        constexpr int q = decltype(qc)::value, t = q % MM, h = q / MM % G, o = q / MM / G;
-        constexpr int from = pieces_before(q, Q0, SPAN, PIECES), to = pieces_before(q + 1, Q0, SPAN, PIECES);
+        constexpr int q = decltype(qc)::value, t = q % MM, o = q / MM;
+        constexpr int from = pieces_before(q, Q0, SPAN, 4 * NPT), to = pieces_before(q + 1, Q0, SPAN, 4 * NPT);
         static_for<from, to>([&](auto i) __attribute__((always_inline)) { split(decltype(i)::value, u, nxt); });
         if constexpr (q == (NPR > 3 ? 4 * MM : Q - 1)) load(s + 1 + DEPTH < last ? s + 1 + DEPTH : last, u);
-        product(std::integral_constant<int, o>{}, std::integral_constant<int, h>{}, std::integral_constant<int, t>{});
+        S::mfma(a[S::A[o]][t / Cfg::TN], b[S::B[o]][t % Cfg::TN], acc[t / Cfg::TN][t % Cfg::TN]);
         __builtin_amdgcn_sched_barrier(0);
       });
       __syncthreads();
@@ -536,14 +482,14 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
       read_a(nxt, 0, an);
       read_b(nxt, 0, bn);
       __builtin_amdgcn_sched_barrier(0);
-      static_for<0, MM>([&](auto t) __attribute__((always_inline)) {
-        product(std::integral_constant<int, NPR - 1>{}, std::integral_constant<int, G - 1>{}, t);
-      });
+#pragma unroll
+      for (int t = 0; t < MM; ++t)
+        S::mfma(a[S::A[NPR - 1]][t / Cfg::TN], b[S::B[NPR - 1]][t % Cfg::TN], acc[t / Cfg::TN][t % Cfg::TN]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < Cfg::TM; ++t) a[0][0][t] = an[t];
+      for (int t = 0; t < Cfg::TM; ++t) a[0][t] = an[t];
 #pragma unroll
-      for (int t = 0; t < Cfg::TN; ++t) b[0][0][t] = bn[t];
+      for (int t = 0; t < Cfg::TN; ++t) b[0][t] = bn[t];
       if constexpr (CHAIN > 0) {
         if ((s + 1) % (CHAIN * Cfg::BK / 16) == 0 && s < last) {
           add_acc<Cfg>(sums, acc);
@@ -552,14 +498,155 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
       }
     }
   }
-  if constexpr (CHAIN > 0 || SETS > 1) add_acc<Cfg>(acc, sums);
-  if constexpr (S::UNSCALE != 1.f) {
+  if constexpr (CHAIN > 0) add_acc<Cfg>(acc, sums);
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------------------------
+// fp32 operands of the logits: both k contiguous, multiplied by v_mfma_f32_32x32x2_f32.
+// ---------------------------------------------------------------------------------------------
+// Operand slab in LDS: R rows of SLAB bytes, padded so that the fragment reads of 32 rows miss each other's banks.
+template <int R, int SLAB>
+struct PlainLds {
+  static constexpr int STRIDE = SLAB + 16, BYTES = R * STRIDE;
+  static constexpr int CPR = SLAB / 16, CHUNKS = R * CPR;
+};
+
+// Global -> register -> LDS staging of one slab.  Thread t owns chunk t % CPR of rows t / CPR + p * RPP, p = 0 .. NCH-1.
+// A wave-uniform base (tile, slab, pass) and one 32-bit offset per thread keep addresses out of the vector registers.
+template <class L, int THREADS, int SLAB>
+struct PlainStager {
+  static constexpr int RPP = THREADS / L::CPR, NCH = L::CHUNKS / THREADS;
+  static_assert(L::CHUNKS % THREADS == 0 && THREADS % L::CPR == 0, "whole rows in every pass");
+  const char* base;
+  uint32_t toff;
+  int64_t pass;
+  int lds;
+  // one vector value, so that they are registers whatever the control flow around the loads
+  typedef uint32_t Regs __attribute__((ext_vector_type(NCH * 4)));
+  __device__ __forceinline__ void init(const float* tile, int64_t ld) {
+    const int row = threadIdx.x / L::CPR, ch = threadIdx.x % L::CPR;
+    base = reinterpret_cast<const char*>(tile);
+    toff = (uint32_t)((int64_t)row * ld * 4 + ch * 16);
+    pass = (int64_t)RPP * ld * 4;
+    lds = row * L::STRIDE + ch * 16;
+  }
+  __device__ __forceinline__ void load(int s, int p, Regs& r) const {
+    const u32x4 t = *reinterpret_cast<const u32x4*>(base + (int64_t)s * SLAB + p * pass + toff);
 #pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i)
+    for (int e = 0; e < 4; ++e) r[4 * p + e] = t[e];
+  }
+  __device__ __forceinline__ void store(char* region, const Regs& r) const {
 #pragma unroll
-      for (int j = 0; j < Cfg::TN; ++j)
+    for (int p = 0; p < NCH; ++p) {
+      u32x4 t;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] *= S::UNSCALE;
+      for (int e = 0; e < 4; ++e) t[e] = r[4 * p + e];
+      *reinterpret_cast<u32x4*>(region + lds + p * RPP * L::STRIDE) = t;
+    }
+  }
+};
+
+// gemm_tile (below) for the fp32 operands of the logits: two stages in LDS, one set of registers, loads two slabs
+// ahead, issued one at a time between the MFMAs of the first groups; fragments are read a group ahead; the last group of
+// a slab is multiplied behind the barrier.  Slab numbers past the end are clamped: such loads and stores are redundant.
+// Why not in 16-bit planes, as the backward products: two fp16 planes and three products are as close to 64 bits (a
+// cosine 6e-8 off instead of 2e-7) and take 22 of 60 us less at 512 x 9,344 x 512, but what a confident sample
+// passes on is p - 1, the rounding of a sum and a quotient next to 1 multiplied by the scale: with other roundings of its
+// cosines the gradients of samples aligned to their centers move by 1e-5 .. 1e-4 of their 2-norm, as far as they are
+// off from 64 bits either way, and more than a change of the summation order may move them.
+template <class Cfg>
+__device__ __forceinline__ void gemm_tile_fp32(const float* __restrict__ A, int64_t lda, const float* __restrict__ B,
+                                               int64_t ldb, int nslabs, char* smem,
+                                               f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
+  constexpr int SLAB = Cfg::SLAB_BYTES;
+  typedef PlainLds<Cfg::BM, SLAB> LA;
+  typedef PlainLds<Cfg::BN, SLAB> LB;
+  typedef PlainStager<LA, Cfg::THREADS, SLAB> SA;
+  typedef PlainStager<LB, Cfg::THREADS, SLAB> SB;
+  constexpr int STAGE = LA::BYTES + LB::BYTES;
+  constexpr int NA = SA::NCH, NB = SB::NCH, NL = NA + NB, MM = Cfg::TM * Cfg::TN, HEAD = Cfg::GROUPS - 1;
+  // the loads of a slab are placed in front of the MFMAs of the first one or two groups (of all groups before the
+  // barrier if two do not have an MFMA for each load)
+  constexpr int SPAN = (NL <= 2 * MM ? (HEAD < 2 ? HEAD : 2) : HEAD) * MM;
+  static_assert(HEAD >= 1, "the last group is multiplied behind the barrier");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ra = ((wave / Cfg::WN) * Cfg::WTM + (lane & 31)) * LA::STRIDE + (lane >> 5) * 16;
+  const int rb = LA::BYTES + ((wave % Cfg::WN) * Cfg::WTN + (lane & 31)) * LB::STRIDE + (lane >> 5) * 16;
+  auto read = [&](const char* stage, int g, Frags<Cfg>& f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < Cfg::TM; ++b)
+      f.a[b] = *reinterpret_cast<const u32x4*>(stage + ra + b * 32 * LA::STRIDE + g * 32);
+#pragma unroll
+    for (int b = 0; b < Cfg::TN; ++b)
+      f.b[b] = *reinterpret_cast<const u32x4*>(stage + rb + b * 32 * LB::STRIDE + g * 32);
+  };
+  // 8 reduction steps: four instructions, the t-th of which pairs element t of every lane
+  auto multiply = [&](const Frags<Cfg>& f, int q) __attribute__((always_inline)) {
+    // whole-vector casts: a bit_cast applied to a single vector element reads element 0
+    const f32x4 a = __builtin_bit_cast(f32x4, f.a[q / Cfg::TN]), b = __builtin_bit_cast(f32x4, f.b[q % Cfg::TN]);
+    f32x16& c = acc[q / Cfg::TN][q % Cfg::TN];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b[t], c, 0, 0, 0);
+  };
+  SA sa;
+  SB sb;
+  sa.init(A, lda);
+  sb.init(B, ldb);
+  const int last = nslabs - 1;
+  typename SA::Regs a0 = {};
+  typename SB::Regs b0 = {};
+  {
+    typename SA::Regs af = {};
+    typename SB::Regs bf = {};
+    const int next = last < 1 ? last : 1;
+#pragma unroll
+    for (int p = 0; p < NA; ++p) sa.load(0, p, af);
+#pragma unroll
+    for (int p = 0; p < NB; ++p) sb.load(0, p, bf);
+#pragma unroll
+    for (int p = 0; p < NA; ++p) sa.load(next, p, a0);
+#pragma unroll
+    for (int p = 0; p < NB; ++p) sb.load(next, p, b0);
+    sa.store(smem, af);
+    sb.store(smem + LA::BYTES, bf);
+  }
+  __syncthreads();
+  Frags<Cfg> fc;
+  read(smem, 0, fc);
+  for (int s = 0; s < nslabs; ++s) {
+    char* cur = smem + (s & 1) * STAGE;
+    char* nxt = smem + (~s & 1) * STAGE;
+    const int s2 = s + 2 < last ? s + 2 : last;
+    sa.store(nxt, a0);
+    sb.store(nxt + LA::BYTES, b0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < HEAD; ++g) {
+      Frags<Cfg> fn;
+      read(cur, g + 1, fn);
+      __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs they do not feed
+#pragma unroll
+      for (int q = 0; q < MM; ++q) {
+#pragma unroll
+        for (int c = 0; c < NL; ++c)       // chunk c is requested in front of block c * SPAN / NL
+          if (c * SPAN / NL == g * MM + q) {
+            if (c < NA) sa.load(s2, c, a0);
+            else sb.load(s2, c - NA, b0);
+          }
+        multiply(fc, q);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      fc = fn;
+    }
+    __syncthreads();
+    Frags<Cfg> fn;
+    read(nxt, 0, fn);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < MM; ++q) multiply(fc, q);
+    __builtin_amdgcn_sched_barrier(0);
+    fc = fn;
   }
   __syncthreads();
 }
@@ -577,7 +664,8 @@ __device__ __forceinline__ void gemm_tile(const typename Cfg::elem* __restrict__
                                           f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
   static_assert(CHAIN == 0 || !Cfg::DMA, "bf16 operands: their rounding is what counts");
   if constexpr (Cfg::DMA) gemm_tile_dma<Cfg>(A, lda, B, ldb, nslabs, smem, acc);
-  else gemm_tile_split<Cfg, CHAIN>(A, lda, B, ldb, nslabs, smem, acc);
+  else if constexpr (Cfg::SPLIT) gemm_tile_split<Cfg, CHAIN>(A, lda, B, ldb, nslabs, smem, acc);
+  else gemm_tile_fp32<Cfg>(A, lda, B, ldb, nslabs, smem, acc);
 }
 
 // Row / column of accumulator register r of block (bm, bn) inside the workgroup tile.

@@ -157,31 +157,29 @@ inline bool long_batch(int cu, int es, int D, int Bp, int64_t kp) {
 //     more (128 x 200,000: 210 / 179 / 260) or the reduction is short and the tiles few
 //     (256 x 36,000: 42 / 39 / 57; 256 x 200,000: 221 / 260 / 368); 64-tiles for the smallest
 //     problems (128 x 1,000: 15 / 7.3 / 5.8).
-//   fp32: by estimate.  A compute unit full of tiles of one size takes fp32_slab_us for a slab of 32 steps of
+//   fp32 logits: the fp32 matrix instruction is the bound at any of the sizes, so what counts is how evenly the
+//     compute units are loaded: 64-tiles where a few 128-tiles per compute unit do not come out
+//     even (512 x 9,344: 135 / 77 / 57; 128 x 1,000: 129 / 37 / 15).  From one 256-tile per
+//     compute unit on the sizes are close (2048 x 60,000: 1144 / 1127 / 1207; 512 x 60,000: 299 /
+//     315 / 330) and the logits keep 256 and its order of the row sums.
+//   fp32 backward: by estimate.  A compute unit full of tiles of one size takes fp32_slab_us for a slab of 32 steps of
 //     one tile: a 256-tile reads the least from LDS and splits the fewest values for every product, smaller
-//     ones come out more even.  Forward/backward with the logits in 64 / 128 / 256 (backward 128): 1907 x 20,355
-//     835 / 783 / 781, 4096 x 8,000 711 / 645 / 622, 2048 x 30,000 1316 / 1183 / 1142, 512 x 9,344 148 / 152 /
-//     172, 230 x 3,000 61 / 69 / 111; with the backward launch in 64 / 128 / 256 (logits 128): 837 / 783 / 821,
-//     731 / 645 / 577, 1288 / 1183 / 1025, 147 / 152 / 140, 63 / 69 / 83.
+//     ones come out more even.  Forward/backward with the backward launch in 64 / 128 / 256: 1907 x 20,355 837 / 783 /
+//     821, 4096 x 8,000 731 / 645 / 577, 2048 x 30,000 1288 / 1183 / 1025, 512 x 9,344 147 / 152 / 140, 230 x 3,000
+//     63 / 69 / 83 (logits in planes then).
 enum TileSize { TILES_64 = 64, TILES_128 = 128, TILES_256 = 256 };
 
 // fp32: microseconds a compute unit takes for one slab of one tile, full of tiles of that size.
 inline double fp32_slab_us(TileSize t) { return t == TILES_256 ? 3.2 : t == TILES_128 ? 0.98 : 0.36; }
 
+inline bool even_rounds(int64_t tiles, int64_t cu) {   // at most 15 % of the rounds' room is idle
+  return tiles > 4 * cu || (tiles + cu - 1) / cu * cu * 100 <= tiles * 115;
+}
+
 inline TileSize logits_tiles(int64_t cu, int es, int B, int64_t kp, int D) {
   const int64_t mid = kp / 128 * ((B + 127) / 128);
   const int64_t big = kp / 256 * ((B + 255) / 256), rounds = (big + cu - 1) / cu;
-  if (es == 4) {
-    const int64_t small = kp / 64 * ((B + 63) / 64);
-    TileSize best = TILES_128;
-    auto us = [&](TileSize t, int64_t tiles) { return (double)((tiles + cu - 1) / cu) * fp32_slab_us(t); };
-    if (us(TILES_256, big) < us(TILES_128, mid)) best = TILES_256;
-    // (row sums of 64-tiles: what rowpart_floats has room for)
-    if (kp / 64 * round_up(B, kPadB) <= (int64_t)2048 * cu &&
-        us(TILES_64, small) < std::min(us(TILES_128, mid), us(TILES_256, big)))
-      best = TILES_64;
-    return best;
-  }
+  if (es == 4) return big >= cu ? TILES_256 : even_rounds(mid, cu) ? TILES_128 : TILES_64;
   if (D > 256 && rounds * cu * 4 * 100 <= mid * 109) return TILES_256;
   return 2 * mid > cu ? TILES_128 : TILES_64;
 }

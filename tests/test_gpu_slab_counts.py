@@ -31,9 +31,8 @@ def test_few_slabs_fused(precision, B):
     fused_equals_two_calls(36_000, B, 512, 1.0, precision, 36_000, False)
 
 
-# fp32 operands are split into 16-bit planes; the logits' into two of fp16, whose range ends at 2^-24 of a
-# row scaled by 2^12.  Rows of one component, of components 2^-40 .. 1 and of equal ones; tolerances: a cosine
-# is off by 2^-23 of its products and 512 2^-37 of small components, < 1.2e-7 + 4e-9, the logit by 64 of that.
+# The fp32 operands of the backward products are split into 16-bit planes.  Rows of one component, of components 2^-40
+# .. 1 and of equal ones; tolerances: a cosine is off by 2^-23 of its products, < 1.2e-7, the logit by 64 of that.
 @pytest.mark.parametrize("N,B", [(300, 70), (5_000, 300), (33_000, 512)])
 def test_fp32_components_of_any_size(N, B):
     import torch
