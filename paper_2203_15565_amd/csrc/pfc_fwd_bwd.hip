@@ -448,13 +448,17 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   const int64_t j0 = (int64_t)tj * Cfg::BM;
   const int i0 = ti * Cfg::BN;
 
-  // labels: requested in front of the reduction (behind it they were a wait of 2 us of their own)
+  // labels: requested in front of the reduction (behind it they were a wait of 2 us of their own; with fp32 operands
+  // they only delay the first slab)
   int32_t ylab[Cfg::TN];
+  auto request_labels = [&]() {
 #pragma unroll
-  for (int bn = 0; bn < Cfg::TN; ++bn) {
-    const int i = i0 + acc_col<Cfg>(bn);
-    ylab[bn] = i < B ? yl[i] : -1;
-  }
+    for (int bn = 0; bn < Cfg::TN; ++bn) {
+      const int i = i0 + acc_col<Cfg>(bn);
+      ylab[bn] = i < B ? yl[i] : -1;
+    }
+  };
+  if constexpr (Cfg::DMA) request_labels();
 
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
@@ -462,6 +466,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   // the reduction ends with column D (a multiple of every slab): the rest of the rows is zero
   gemm_tile<Cfg>(Wn + j0 * Dp, Dp, Xn + (int64_t)i0 * Dp, Dp, D / Cfg::BK, smem, acc);
   PFC_PHASE(1, 1);
+  if constexpr (!Cfg::DMA) request_labels();
   // Pull the Wn block of the class tile that the workgroups `ahead` ids later will multiply (same
   // XCD, about one round later) into this XCD's L2: the tiles_i workgroups of a class tile touch
   // a part of the rows each, one 4-byte load per 128-byte line.  The values are only kept alive
