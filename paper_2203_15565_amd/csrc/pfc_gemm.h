@@ -371,12 +371,12 @@ __device__ __forceinline__ SplitChunk split_chunk(int c, const float* base, int6
 // between the MFMAs of the slab at hand and stores one 16-byte chunk to each plane of the other stage; the last product
 // of a slab is added up behind the barrier, under the first fragment reads of the next one.
 // What it replaces: v_mfma_f32_32x32x2_f32, whose rate (157 TFLOP/s nominal) was the bound at any tile size; six bf16
-// products are 2.7 times that.  Forward/backward, us, before -> now: 2048 x 30,000 x
-// 512 1588 -> 858, 1907 x 20,355 x 512 1134 -> 641, 512 x 9,344 x 512 163 -> 131, 1024 x 36,024 x 512 with the
-// update 1183 -> 701, 300 x 40,000 x 512 642 -> 278, 128 x 1,000 x 512 35.4 -> 34.7 (latency).
-// Error against 64 bits (2-norm), fp32 products -> now: feature gradient 512 x 9,344 x 512 6.4e-7 -> 4.2e-7, 64 x
-// 8,000 x 64 9.2e-7 -> 6.8e-7, 4096 x 8,000 x 512 6.8e-7 -> 4.4e-7; center gradient off the labels 2.9e-6 -> 1.9e-6,
-// 1.6e-6 -> 1.2e-6, 2.8e-6 -> 1.8e-6: an accumulator takes 3 or 6 roundings for 16 products instead of 8.
+// products are 2.7 times that.  Step, us, before -> now: 512 x 9,344 x 512 199 -> 183, 300 x 40,000 x 512 736 -> 608,
+// 1024 x 36,024 x 512 with the update 1211 -> 1003, 500 x 4,000 x 1024 173 -> 154, 128 x 1,000 x 512 even (latency).
+// Error against 64 bits (2-norm, features | centers off the labels), fp32 products -> now, most of it the logits': 512 x
+// 9,344 x 512 6.37e-7 -> 6.37e-7 | 2.99e-6 -> 2.98e-6, 1500 x 20,000 x 512 5.59e-7 -> 5.58e-7 | 3.15e-6 -> 3.13e-6, 2048 x
+// 30,000 x 512 5.08e-7 -> 5.07e-7 | 3.21e-6 -> 3.20e-6, 700 x 20,000 x 256 8.79e-7 -> 8.77e-7 | 2.39e-6 -> 2.38e-6: an
+// accumulator takes 6 roundings for 16 products instead of 8.
 // What bounds it: large problems the clock that the power leaves (1.1 PFLOP/s of 16-bit products), small ones
 // the way from global memory through registers and LDS to the fragments in every slab.
 template <class Cfg, int CHAIN>

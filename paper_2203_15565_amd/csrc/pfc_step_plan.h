@@ -76,6 +76,11 @@ inline int64_t launch_slabs(int64_t cu, int64_t na, int64_t a, int64_t nb, int64
 // Partial tiles of either product that there is room for.
 inline int64_t slice_room(int cu, int Bp) { return (int64_t)(Bp > kLongBatch ? kLongRoom : 1) * cu; }
 
+// The longest fp32 sum without pieces.  Batches up to kLongBatch could take the smaller tiles, whose sums are in
+// pieces of 256 and 512: there 256-tiles may not add up more than 1024 (2048 x 30,000 x 512 in sums of 2048: gradients
+// 5.12e-7 and 3.23e-6 off 64 bits, with fp32 MFMAs in pieces 5.08e-7 and 3.21e-6).
+inline int max_plain_sum(int Bp) { return Bp > kLongBatch ? kMaxPlainSum : kMaxPlainSum / 4; }
+
 // Whether there is room for fp32 sums of at most `most` products.
 inline bool plain_sums_fit(int cu, int Bp, int Dp, int64_t kp, int most) {
   const int64_t w = (Bp + most - 1) / most, x = (kp + most - 1) / most;
@@ -110,7 +115,7 @@ inline LongSlices long_batch_slices(int cu, int es, int Bp, int Dp, int64_t kp) 
   const int slabs_w = Bp / bk, slabs_x = (int)(kp / bk);
   const int64_t tiles_w = kp / 256 * (Dp / 256), tiles_x = (int64_t)(Bp / 256) * (Dp / 256);
   const int64_t room = slice_room(cu, Bp), edge = es == 2 ? 10 : 4;
-  const int most = es == 2 ? INT_MAX : plain_sums_fit(cu, Bp, Dp, kp, kPlainSum) ? kPlainSum : kMaxPlainSum;
+  const int most = es == 2 ? INT_MAX : Bp > kLongBatch && plain_sums_fit(cu, Bp, Dp, kp, kPlainSum) ? kPlainSum : max_plain_sum(Bp);
   const double slab_us = es == 2 ? 1.45 : 3.2, dw_tile_us = 0.05, dx_tile_us = 0.06;
   const int64_t work = tiles_w * slabs_w + tiles_x * slabs_x;
   LongSlices best = {0, 0, false, false};
@@ -309,7 +314,7 @@ inline TileSize backward_tiles(int cu, int es, int B, int64_t kp, int D) {
     };
     if (!fits_one_kernel(cu, D, kp)) {
       take(TILES_64, fp32_backward_us(cu, TILES_64, (int)round_up(B, logits_tiles(cu, es, B, kp, D)), Dp, D, kp));
-      if (plain_sums_fit(cu, Bp256, Dp256, kp, kMaxPlainSum))
+      if (plain_sums_fit(cu, Bp256, Dp256, kp, max_plain_sum(Bp256)))
         take(TILES_256, fp32_backward_us(cu, TILES_256, Bp256, Dp256, D, kp));
     }
     return best;
