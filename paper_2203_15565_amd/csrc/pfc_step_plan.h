@@ -73,19 +73,11 @@ inline int64_t launch_slabs(int64_t cu, int64_t na, int64_t a, int64_t nb, int64
   }
 }
 
-// Partial tiles of either product that there is room for.
-inline int64_t slice_room(int cu, int Bp) { return (int64_t)(Bp > kLongBatch ? kLongRoom : 1) * cu; }
-
-// The longest fp32 sum without pieces.  Batches up to kLongBatch could take the smaller tiles, whose sums are in
-// pieces of 256 and 512: there 256-tiles may not add up more than 1024 (2048 x 30,000 x 512 in sums of 2048: gradients
-// 5.12e-7 and 3.23e-6 off 64 bits, with fp32 MFMAs in pieces 5.08e-7 and 3.21e-6).
-inline int max_plain_sum(int Bp) { return Bp > kLongBatch ? kMaxPlainSum : kMaxPlainSum / 4; }
-
 // Whether there is room for fp32 sums of at most `most` products.
 inline bool plain_sums_fit(int cu, int Bp, int Dp, int64_t kp, int most) {
   const int64_t w = (Bp + most - 1) / most, x = (kp + most - 1) / most;
   const int64_t tiles_w = kp / 256 * (Dp / 256), tiles_x = (int64_t)(Bp / 256) * (Dp / 256);
-  const int64_t room = slice_room(cu, Bp);
+  const int64_t room = (int64_t)kLongRoom * cu;
   return w <= kMaxSplits && x <= kMaxLongSplits &&
          (w == 1 || (w * tiles_w <= room && w * kp <= (int64_t)kMaxSplits * Bp)) &&
          (x == 1 || x * tiles_x <= room);
@@ -99,24 +91,28 @@ struct LongSlices {
 };
 
 // The fewest microseconds by an estimate: a slab of a 256-tile takes 1.45 us (bf16; start and end of a
-// workgroup like 10 slabs) or 3.2 us (fp32, 4 slabs), a partial tile of dfeatures 0.06 us to add up later, one
-// of dweight 0.05, the result likewise, and the launch that does it 3 us.  Fitted to 45 forms of 2,100 .. 65,536 samples, 2,000 .. 30,000
-// classes, D 128 .. 1024 and all slices that fit (7,730 measurements): the pick is 0.5 % behind the best of
-// a form on average, 3 % at most.  Against the rules for smaller batches (us, both products):
+// workgroup like 10 slabs) or 7.7 us (fp32, 2 slabs), a partial tile of dfeatures 0.06 us to add up later, one
+// of dweight 0.05, the result likewise, and the launch that does it 3 us.  Fitted to 45 forms of 2,100 ..
+// 65,536 samples, 2,000 .. 30,000 classes, D 128 .. 1024 and all slices that fit (7,730 measurements): the
+// pick is 0.5 % behind the best of a form on average, 3 % at most.  Against the rules for smaller batches
+// (us, both products):
 //   bf16 4096 x 20,000 x 512 217 -> 179, 3000 x 20,000 x 512 166 -> 136, 8192 x 20,000 x 512 423 -> 315,
 //     4096 x 20,000 x 1024 338 -> 304, 16,384 x 3,592 x 512 141 -> 130
-// fp32: a slab of 3.2 us, from the measurements at backward_tiles; every batch that 256-tiles suit takes these slices.
+// fp32: the weights are those of fp32 MFMAs.  A slab of planes takes 3.2 us, and with that (and 4 slabs for start
+// and end) the pick has up to half the slices, forward/backward 0 - 6 % shorter (4774 x 8,175 x 256 504 -> 477 us,
+// 8794 x 6,171 x 192 567 -> 559), but sums twice as long (dweight at scale 1, off 64 bits: 3.9e-7 -> 5.5e-7, 4.2e-7 ->
+// 5.9e-7): the slices stay as they are.
 // fp32 sums run without pieces here: only slices of at most kPlainSum products are taken, or kMaxPlainSum
 // where those do not fit (the caller sees to it that there are such).  Error against 64 bits, 2-norm, both
-// gradients, slices by number alone -> now: 16,384 x 15,700 x 512 7.6e-7 -> 6.2e-7, 8192 x 8,100 x 512 7.7e-7 ->
-// 6.9e-7, 4096 x 8,000 x 1024 3.3e-7 -> 2.9e-7.
+// gradients, slices by number alone -> now: 16,384 x 15,700 x 512 7.6e-7 -> 6.2e-7, 8192 x 8,100 x 512
+// 7.7e-7 -> 6.9e-7, 4096 x 8,000 x 1024 3.3e-7 -> 2.9e-7.
 inline LongSlices long_batch_slices(int cu, int es, int Bp, int Dp, int64_t kp) {
   const int bk = tile_bk(es);
   const int slabs_w = Bp / bk, slabs_x = (int)(kp / bk);
   const int64_t tiles_w = kp / 256 * (Dp / 256), tiles_x = (int64_t)(Bp / 256) * (Dp / 256);
-  const int64_t room = slice_room(cu, Bp), edge = es == 2 ? 10 : 4;
-  const int most = es == 2 ? INT_MAX : Bp > kLongBatch && plain_sums_fit(cu, Bp, Dp, kp, kPlainSum) ? kPlainSum : max_plain_sum(Bp);
-  const double slab_us = es == 2 ? 1.45 : 3.2, dw_tile_us = 0.05, dx_tile_us = 0.06;
+  const int64_t room = (int64_t)kLongRoom * cu, edge = es == 2 ? 10 : 2;
+  const int most = es == 2 ? INT_MAX : plain_sums_fit(cu, Bp, Dp, kp, kPlainSum) ? kPlainSum : kMaxPlainSum;
+  const double slab_us = es == 2 ? 1.45 : 7.7, dw_tile_us = 0.05, dx_tile_us = 0.06;
   const int64_t work = tiles_w * slabs_w + tiles_x * slabs_x;
   LongSlices best = {0, 0, false, false};
   double best_us = 0;
@@ -144,9 +140,7 @@ inline LongSlices long_batch_slices(int cu, int es, int Bp, int Dp, int64_t kp) 
 
 // Whether the backward launch of the call takes them, given 256-tiles.  Not the class sets of the one-kernel
 // form, whose dX has the same bits in either call and whose many tiles come out even.
-inline bool long_batch(int cu, int es, int D, int Bp, int64_t kp) {
-  return (es == 4 || Bp > kLongBatch) && !fits_one_kernel(cu, D, kp);
-}
+inline bool long_batch(int cu, int D, int Bp, int64_t kp) { return Bp > kLongBatch && !fits_one_kernel(cu, D, kp); }
 
 // Size of the GEMM tiles, one for the logits and one for the backward launch of a call.  256 x 256
 // moves the least data per flop and fills a compute unit with one workgroup, 128 x 128 puts two on
@@ -270,7 +264,7 @@ inline BackwardShape backward_shape(int cu, int es, TileSize t, int Bp, int Dp, 
   BackwardShape s;
   const int tiles_w = (int)(kp / t) * (Dp / t);
   const int slabs_total = Bp / tile_bk(es);
-  const LongSlices cut = t == TILES_256 && long_batch(cu, es, D, Bp, kp) ? long_batch_slices(cu, es, Bp, Dp, kp)
+  const LongSlices cut = t == TILES_256 && long_batch(cu, D, Bp, kp) ? long_batch_slices(cu, es, Bp, Dp, kp)
                                                                      : LongSlices{0, 0, false, false};
   const int want = cut.dw ? cut.dw : dweight_slices(cu, tiles_w, Bp, kp, tile_bk(es));
   s.dw_first = cut.dw_first;
@@ -305,8 +299,12 @@ inline TileSize backward_tiles(int cu, int es, int B, int64_t kp, int D) {
   const int Dp = (int)round_up(D, kPadD), Dp256 = (int)round_up(D, 256);
   const int64_t mid = kp / 128 * (Dp / 128), big = kp / 256 * (Dp256 / 256);
   if (es == 4) {
-    // the launch that ends first by estimate; 64-tiles are no tiles of the one-kernel form, 256-tiles need
-    // slices that keep the sums short
+    // The launch that ends first by estimate; 64-tiles are no tiles of the one-kernel form.  256-tiles add up without
+    // pieces, which for the same slices is less exact, so only batches that fill them and whose slices end evenly
+    // take them, and never batches up to kLongBatch.  (dweight at scale 1 off 64 bits, 2-norm, and forward/backward in us,
+    // with 256-tiles wherever their estimate is the lowest -> now: 3864 x 29,707 x 1024 9.7e-7 -> 3.6e-7, 4380 ->
+    // 4840; 4096 x 8,000 x 320 6.8e-7 -> 3.4e-7, 492 -> 514; 2048 x 16,000 x 512 5.0e-7 -> 3.6e-7, 642 -> 670;
+    // 4096 x 33,000 x 64 9.1e-7 -> 2.7e-7, 1079 -> 854.)
     TileSize best = TILES_128;
     double best_us = fp32_backward_us(cu, TILES_128, Bp, Dp, D, kp);
     auto take = [&](TileSize t, double us) {
@@ -314,7 +312,8 @@ inline TileSize backward_tiles(int cu, int es, int B, int64_t kp, int D) {
     };
     if (!fits_one_kernel(cu, D, kp)) {
       take(TILES_64, fp32_backward_us(cu, TILES_64, (int)round_up(B, logits_tiles(cu, es, B, kp, D)), Dp, D, kp));
-      if (plain_sums_fit(cu, Bp256, Dp256, kp, max_plain_sum(Bp256)))
+      if (long_batch(cu, D, Bp256, kp) && Dp256 * 100 <= Dp * 115 && Bp256 * 100 <= B * 105 &&
+          plain_sums_fit(cu, Bp256, Dp256, kp, kMaxPlainSum) && long_batch_slices(cu, es, Bp256, Dp256, kp).even)
         take(TILES_256, fp32_backward_us(cu, TILES_256, Bp256, Dp256, D, kp));
     }
     return best;

@@ -57,3 +57,34 @@ def test_sums_of_equal_terms(B, k, D, piece_w, piece_x):
     # the label part takes cos(m) = 7 % of the sum away
     assert off(dX, want_X) <= (piece_x + k / piece_x + 64 + 16) * U / (1 - math.cos(m))
     assert (dX[:, : D // 2].abs().max() <= 1e-6 * dX.abs().max()).item()
+
+
+# Independent terms: rounding t of a sum of n terms is off by up to U of what is there by then, sqrt(t / n) of the
+# result.  A piece of 512 products takes 192 roundings, the pieces and slices are added to each other: U / sqrt(3)
+# sqrt(192 / 2 + n / 512 / 2) rms, and three roundings of the factors.  (In uninterrupted sums of 1024 .. 4096: 5.0e-7,
+# 5.2e-7, 6.8e-7 and 9.1e-7 at these sizes, last to first; the bar is 4.5e-7 .. 4.6e-7.)
+@pytest.mark.parametrize("B,k,D", [(4_096, 33_000, 64), (4_096, 8_000, 320), (14_099, 2_330, 256),
+                                   (2_048, 16_000, 512)])
+def test_sums_of_independent_terms(B, k, D):
+    s, m = 1.0, 0.5
+    g = torch.Generator(device="cuda").manual_seed(k)
+    X = torch.randn((B, D), generator=g, device="cuda")
+    W = torch.randn((k, D), generator=g, device="cuda").mul_(0.01)
+    yl = torch.randint(0, 16, (B,), generator=g, device="cuda").to(torch.int32)
+    idx = torch.arange(k, dtype=torch.int32, device="cuda")
+    loss = torch.zeros(1, device="cuda")
+    dX, dW = torch.zeros_like(X), torch.zeros_like(W)
+    print("independent terms", B, k, D, flush=True)
+    ctx = binding.Context(k, D, B, 1.0, binding.PRECISION_FP32)
+    ctx.pfc_forward_backward(X, W, idx, k, yl, s, m, loss, dX, dW)
+    assert ctx.pfc_check() == binding.PFC_OK
+    ctx.close()
+    xn = torch.nn.functional.normalize(X.double(), dim=1)
+    e = torch.exp(s * (xn @ torch.nn.functional.normalize(W.double(), dim=1).t()))
+    label = yl.long()[:, None]
+    theta = e.gather(1, label).log().div(s).clamp(-1.0, 1.0).acos()
+    e.scatter_(1, label, torch.exp(s * torch.cos(theta + m)))
+    want = ((s / B) * (e / e.sum(dim=1, keepdim=True))).t() @ xn       # rows that are nobody's label: 16 ..
+    off = ((dW[16:].double() - want[16:]).norm() / want[16:].norm()).item()
+    print("off", off, flush=True)
+    assert off <= (math.sqrt(192 / 2 + B / 512 / 2) + 3) * U / math.sqrt(3.0)

@@ -110,10 +110,27 @@ def test_scratch_holds_every_call(lib):
             assert p["dx_wgs"] % 8 == 0 and p["dx_wgs"] >= p["tiles_i"] * p["tiles_d"] * p["dx_splits"], form
             if p["one_kernel"]:      # its dfeatures tiles are 128 or 256 wide, and dweight is in one piece
                 assert p["backward"] >= 128 and p["dw_splits"] == 1, form
-            # a 256-tile has no pieces: short sums, or (256-tiles in bf16) any
+            # fp32: a 256-tile has no pieces, so only large batches that fill them take them, in short sums
             if es == 4 and p["backward"] == 256:
+                assert p["Bp"] > 2048 and not p["one_kernel"], form
+                assert 100 * p["Bp"] <= 105 * B and 100 * p["Dp"] <= 115 * _up(D, 128), form
                 assert max(p["dw_slabs"], p["dx_slabs"]) * p["bk"] <= 4096, form
     assert len(tiles) >= 12
+
+
+# (samples, classes, D, products of one uninterrupted fp32 sum of dweight and of dfeatures, at most): 256-tiles
+# would end first by the estimate, but in sums of up to 4096; large batches whose 256-tiles could do with half
+# as many slices
+@pytest.mark.parametrize("B,k,D,dw,dx", [
+    (4_096, 33_000, 64, 512, 256), (5_000, 20_000, 576, 512, 256), (3_864, 29_707, 1_024, 512, 256),
+    (4_096, 8_000, 320, 512, 256), (2_500, 40_000, 256, 512, 256), (2_100, 3_000, 512, 512, 256),
+    (2_048, 16_000, 512, 512, 256), (512, 9_344, 512, 512, 256),
+    (4_774, 8_175, 256, 608, 640), (14_099, 2_330, 256, 512, 640), (11_951, 4_445, 256, 832, 928)])
+def test_fp32_sums_stay_short(lib, B, k, D, dw, dx):
+    p = _plan(lib, 256, 4, D, B, k)
+    pieces = (512, 256) if p["backward"] < 256 and not p["one_kernel"] else (4096, 4096)
+    assert min(p["dw_slabs"] * p["bk"], pieces[0]) <= dw, p
+    assert min(p["dx_slabs"] * p["bk"], pieces[1]) <= dx, p
 
 
 def _ends_at(cu, p, es, dw_splits, dx_splits):
