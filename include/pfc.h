@@ -32,7 +32,8 @@ extern "C" {
 #define PFC_EHIP    (-3)  /* a HIP runtime call failed; pfc_last_hip_error() has the text        */
 #define PFC_ENOMEM  (-4)  /* scratch allocation failed in pfc_create                              */
 
-#define PFC_PRECISION_FP32 0  /* GEMM operands fp32 (fp32 MFMA)                                   */
+#define PFC_PRECISION_FP32 0  /* GEMM operands fp32: logits by fp32 MFMA, backward products as six
+                                 products of bf16 planes that add up to the operands; fp32 sums   */
 #define PFC_PRECISION_BF16 1  /* GEMM operands rounded to bf16 (RNE), fp32 accumulate; W, v fp32 */
 
 typedef struct pfc_ctx pfc_ctx;

@@ -313,11 +313,17 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
 // ---------------------------------------------------------------------------------------------
 // fp32 operands, split into planes of 16 bits.
 // ---------------------------------------------------------------------------------------------
-// Any values: x = h + m + l in bf16, exactly, each rounded to nearest, so that a plane is at most 2^-9 of the one
-// above.  Of the nine products of two values six are added up; those left out (m l, l m, l l) are at most 2^-26.
+// x = h + m + l in bf16, each rounded to nearest, so that a plane is at most 2^-9 of the one above.  That is exact for
+// |x| from 2^-109 to the largest bf16; below, where l gets to the last place of bf16's subnormal numbers (which the
+// conversion, the dot and the matrix instruction keep), it is off by at most 2^-134.  The operands: normalised rows,
+// exp(z) <= e^64, and Xs = (s / (B l)) xn, whose components come to 2^-119 when all of 60,000 centers are next to all of 4096
+// samples (dWn then 2.7e-6 off 64 bits, 2.8e-6 with fp32 MFMAs).
+// Of the nine products of two values six are added up; those left out (m l, l m, l l) come to at most 2^-26.
 struct SplitBf16 {
   static constexpr int PLANES = 3, PRODUCTS = 6;
-  static constexpr int A[PRODUCTS] = {0, 0, 0, 1, 2, 1}, B[PRODUCTS] = {0, 1, 2, 0, 0, 1};
+  // h h last: where one product dominates a sum, the accumulator is as large for one rounding of six.  (A product
+  // alone off by, rms: 3.1e-8; h h first 5.2e-8; fp32 MFMA 2.5e-8.)
+  static constexpr int A[PRODUCTS] = {1, 1, 0, 2, 0, 0}, B[PRODUCTS] = {1, 0, 1, 0, 2, 0};
   // words of one pair of neighbours in the planes; the remainders are exact, the dot instruction takes a plane
   // off without widening it first (x - 1 * h + 0 * h')
   static __device__ __forceinline__ void pair(float a, float b, uint32_t (&w)[PLANES]) {
@@ -373,10 +379,11 @@ __device__ __forceinline__ SplitChunk split_chunk(int c, const float* base, int6
 // What it replaces: v_mfma_f32_32x32x2_f32, whose rate (157 TFLOP/s nominal) was the bound at any tile size; six bf16
 // products are 2.7 times that.  Step, us, before -> now: 512 x 9,344 x 512 199 -> 183, 300 x 40,000 x 512 736 -> 608,
 // 1024 x 36,024 x 512 with the update 1211 -> 1003, 500 x 4,000 x 1024 173 -> 154, 128 x 1,000 x 512 even (latency).
-// Error against 64 bits (2-norm, features | centers off the labels), fp32 products -> now, most of it the logits': 512 x
-// 9,344 x 512 6.37e-7 -> 6.37e-7 | 2.99e-6 -> 2.98e-6, 1500 x 20,000 x 512 5.59e-7 -> 5.58e-7 | 3.15e-6 -> 3.13e-6, 2048 x
-// 30,000 x 512 5.08e-7 -> 5.07e-7 | 3.21e-6 -> 3.20e-6, 700 x 20,000 x 256 8.79e-7 -> 8.77e-7 | 2.39e-6 -> 2.38e-6: an
-// accumulator takes 6 roundings for 16 products instead of 8.
+// Error against 64 bits (2-norm, features | centers off the labels), fp32 products -> now.  Scale 64, most of it the
+// logits': 512 x 9,344 x 512 6.43e-7 -> 6.41e-7 | 3.07e-6 -> 3.06e-6, 2048 x 16,000 x 512 5.76e-7 -> 5.75e-7 |
+// 3.05e-6 -> 3.04e-6, 4096 x 20,000 x 512 5.69e-7 -> 5.60e-7 | 3.01e-6 -> 2.98e-6.  Scale 1, centers, most of it the
+// sums': 4.2e-7 -> 3.4e-7, 4.2e-7 -> 3.5e-7, 5.9e-7 -> 5.0e-7: an accumulator takes 6 roundings for 16 products
+// instead of 8.
 // What bounds it: large problems the clock that the power leaves (1.1 PFLOP/s of 16-bit products), small ones
 // the way from global memory through registers and LDS to the fragments in every slab.
 template <class Cfg, int CHAIN>
@@ -450,8 +457,8 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
   for (int i = 0; i < 4 * NPT; ++i) split(i, 0, smem);
   load(DEPTH < last ? DEPTH : last, 0);
   __syncthreads();
-  read_a(smem, 0, a[0]);
-  read_b(smem, 0, b[0]);
+  read_a(smem, 1, a[1]);
+  read_b(smem, 1, b[1]);
   f32x16 sums[Cfg::TM][Cfg::TN];
   if constexpr (CHAIN > 0) zero_acc<Cfg>(sums);
   for (int s0 = 0; s0 <= last; s0 += DEPTH) {
@@ -461,10 +468,10 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
       if (s > last) break;
       char* cur = smem + (s & 1) * STAGE;
       char* nxt = smem + (~s & 1) * STAGE;
-#pragma unroll
-      for (int q = 1; q < NP; ++q) read_b(cur, q, b[q]);
-#pragma unroll
-      for (int q = 1; q < NP; ++q) read_a(cur, q, a[q]);
+      read_b(cur, 0, b[0]);   // in the order that the products need them
+      read_a(cur, 0, a[0]);
+      read_a(cur, 2, a[2]);
+      read_b(cur, 2, b[2]);
       __builtin_amdgcn_sched_barrier(0);
       // between the products of this slab the values of the next one are split, from the second product (the
       // third of six) on
@@ -479,17 +486,17 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
       });
       __syncthreads();
       u32x4 an[Cfg::TM], bn[Cfg::TN];
-      read_a(nxt, 0, an);
-      read_b(nxt, 0, bn);
+      read_a(nxt, 1, an);
+      read_b(nxt, 1, bn);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < MM; ++t)
         S::mfma(a[S::A[NPR - 1]][t / Cfg::TN], b[S::B[NPR - 1]][t % Cfg::TN], acc[t / Cfg::TN][t % Cfg::TN]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < Cfg::TM; ++t) a[0][t] = an[t];
+      for (int t = 0; t < Cfg::TM; ++t) a[1][t] = an[t];
 #pragma unroll
-      for (int t = 0; t < Cfg::TN; ++t) b[0][t] = bn[t];
+      for (int t = 0; t < Cfg::TN; ++t) b[1][t] = bn[t];
       if constexpr (CHAIN > 0) {
         if ((s + 1) % (CHAIN * Cfg::BK / 16) == 0 && s < last) {
           add_acc<Cfg>(sums, acc);
