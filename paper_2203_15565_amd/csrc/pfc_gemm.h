@@ -140,15 +140,18 @@ struct DmaStager {
   }
   // Load p of slab s into the LDS region at byte `lds` (this wavefront's first byte there).
   // Assembly, because the compiler makes every LDS read that follows the builtin wait for all loads in
-  // flight.  The load has no output register; who reads the region waits for it (dma_wait).  M0 needs a
-  // wait state before it is used.
+  // flight.  The load has no output register.  Its write to LDS is done when dma_wait_barrier is behind it: whoever
+  // reads the region waits there first.  The five wait states: the base may come straight from v_readfirstlane (a VALU
+  // write of an SGPR that a vector memory instruction reads), and the compiler, which sets M0 (one wait state), does
+  // not look into assembly for either.
   __device__ __forceinline__ void load(int s, int p, uint32_t lds) const {
     const uint64_t at = (uint64_t)(base + (int64_t)s * slab + p * pass);
     const uint64_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) |
                        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
-                 : "s"(__builtin_amdgcn_readfirstlane(lds + p * THREADS * 16)), "v"(toff), "s"(g));
+                 : "{m0}"(__builtin_amdgcn_readfirstlane(lds + p * THREADS * 16)), "v"(toff), "s"(g)
+                 : "memory");
   }
 };
 
