@@ -18,11 +18,24 @@ pytestmark = pytest.mark.gpu
 U = 2.0 ** -24   # half an ulp
 
 
-# 128-tiles with the batch in one slice, 64-tiles, 128-tiles with the batch cut into slices: in pieces.
-# 256-tiles: the classes in four slices, or the batch in many.
-@pytest.mark.parametrize("B,k,D,piece_w,piece_x", [
-    (2_048, 16_000, 512, 512, 256), (4_096, 33_000, 64, 512, 256), (16_384, 3_000, 128, 512, 256),
-    (16_384, 15_000, 256, 4_096, 4_096), (16_384, 3_000, 256, 4_096, 4_096)])
+# samples, classes, D, products of one sum of dweight and of dfeatures without a break; backward tile, slices of the
+# batch and of the classes that the call has on 256 compute units (tests/test_step_plan.py sees to it)
+EQUAL = [
+    (2_048, 16_000, 512, 512, 256, 128, 1, 4),          # in pieces
+    (5_000, 20_000, 576, 512, 256, 128, 1, 1),
+    (6_884, 21_623, 384, 512, 256, 64, 1, 1),
+    (14_912, 3_225, 640, 512, 256, 64, 1, 1),
+    (16_384, 3_000, 128, 512, 256, 128, 10, 2),
+    (16_384, 15_000, 256, 4_096, 4_096, 256, 13, 8),    # in slices
+    (16_384, 3_000, 256, 4_096, 4_096, 256, 10, 2),
+]
+INDEPENDENT = [
+    (4_096, 33_000, 64, 128, 1, 8), (4_096, 8_000, 320, 128, 1, 3), (2_048, 16_000, 512, 128, 1, 4),
+    (6_884, 21_623, 384, 64, 1, 1), (14_099, 2_330, 256, 256, 28, 4),
+]
+
+
+@pytest.mark.parametrize("B,k,D,piece_w,piece_x", [c[:5] for c in EQUAL])
 def test_sums_of_equal_terms(B, k, D, piece_w, piece_x):
     s, m = 64.0, 1.5
     rng = np.random.default_rng(B + k)
@@ -61,10 +74,9 @@ def test_sums_of_equal_terms(B, k, D, piece_w, piece_x):
 
 # Independent terms: rounding t of a sum of n terms is off by up to U of what is there by then, sqrt(t / n) of the
 # result.  A piece of 512 products takes 192 roundings, the pieces and slices are added to each other: U / sqrt(3)
-# sqrt(192 / 2 + n / 512 / 2) rms, and three roundings of the factors.  (In uninterrupted sums of 1024 .. 4096: 5.0e-7,
-# 5.2e-7, 6.8e-7 and 9.1e-7 at these sizes, last to first; the bar is 4.5e-7 .. 4.6e-7.)
-@pytest.mark.parametrize("B,k,D", [(4_096, 33_000, 64), (4_096, 8_000, 320), (14_099, 2_330, 256),
-                                   (2_048, 16_000, 512)])
+# sqrt(192 / 2 + n / 512 / 2) rms, and three roundings of the factors: a bar of 4.5e-7 .. 4.6e-7.  (Sums of 4096
+# products without a break 9.1e-7, the first form; of 2048 6.8e-7, the second; of 1024 5.0e-7, the third.)
+@pytest.mark.parametrize("B,k,D", [c[:3] for c in INDEPENDENT])
 def test_sums_of_independent_terms(B, k, D):
     s, m = 1.0, 0.5
     g = torch.Generator(device="cuda").manual_seed(k)

@@ -10,6 +10,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_sum_pieces import EQUAL, INDEPENDENT
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2203_15565_amd", "csrc")
 
@@ -131,6 +133,13 @@ def test_fp32_sums_stay_short(lib, B, k, D, dw, dx):
     pieces = (512, 256) if p["backward"] < 256 and not p["one_kernel"] else (4096, 4096)
     assert min(p["dw_slabs"] * p["bk"], pieces[0]) <= dw, p
     assert min(p["dx_slabs"] * p["bk"], pieces[1]) <= dx, p
+
+
+# (the GPU tests of these sums are about the tiles and slices that they name)
+@pytest.mark.parametrize("B,k,D,tile,dw,dx", [c[:3] + c[5:] for c in EQUAL] + INDEPENDENT)
+def test_sums_of_the_gpu_tests(lib, B, k, D, tile, dw, dx):
+    p = _plan(lib, 256, 4, D, B, k)
+    assert (p["backward"], p["dw_splits"], p["dx_splits"]) == (tile, dw, dx) and not p["one_kernel"]
 
 
 def _ends_at(cu, p, es, dw_splits, dx_splits):
