@@ -11,7 +11,8 @@ namespace pfc {
 
 constexpr int kLabelWindow = 1024;     // samples per window of the label part of dWn
 constexpr int kMaxLabelWindows = 64;   // one lane of a wavefront initialises one window's head
-// Classes of a window: their number, then where each begins in the window's ordered samples, and their end.
+// Classes of a window: their number, then where each begins in the window's ordered samples, and
+// their end.
 constexpr int kWindowRuns = kLabelWindow + 2;
 
 // Kernel ids for the optional per-kernel timing.
@@ -223,7 +224,8 @@ __device__ __forceinline__ float wave_sum(float v) {
   return (r0 + r1) + (r2 + r3);
 }
 
-// Likewise over each group of 16 or 32 neighbouring lanes (the bits of wave_sum with zeros in the other lanes).
+// Likewise over each group of 16 or 32 neighbouring lanes (the bits of wave_sum with zeros in the
+// other lanes).
 template <int LANES>
 __device__ __forceinline__ float lane_group_sum(float v) {
   static_assert(LANES == 16 || LANES == 32, "a row of 16 lanes or two");

@@ -111,9 +111,10 @@ __device__ __forceinline__ void normalize_x_row(int i, const float* __restrict__
 }
 
 // ---------------------------------------------------------------------------------------------
-// order_labels (in gather_normalize, batches of several label windows): the samples of window w ordered by class
-// and, inside a class, by number, and where each class begins; samples without a class of S are left out.  A bitonic
-// sort of (class, sample) in LDS, 55 passes for 1024 samples, beside the other workgroups of the launch.
+// order_labels (in gather_normalize, batches of several label windows): the samples of window w
+// ordered by class and, inside a class, by number, and where each class begins; samples without a
+// class of S are left out.  A bitonic sort of (class, sample) in LDS, 55 passes for 1024 samples,
+// beside the other workgroups of the launch.
 // ---------------------------------------------------------------------------------------------
 constexpr int kNormWaves = 4;   // wavefronts per workgroup
 struct OrderLds {
@@ -132,8 +133,8 @@ __device__ __forceinline__ void order_labels(int w, OrderLds& lds, int B, const 
   }
   if (t == 0) lds.samples = 0;
   __syncthreads();
-  // A wavefront's pairs lie in its own 256 places as long as partners are at most 128 apart: only the three wider
-  // passes need the workgroup to meet, before and behind them.
+  // A wavefront's pairs lie in its own 256 places as long as partners are at most 128 apart: only
+  // the three wider passes need the workgroup to meet, before and behind them.
   static_assert(PER == 4 && kNormWaves == 4, "128 pairs to a wavefront");
   for (int size = 2; size <= kLabelWindow; size *= 2)
     for (int j = size / 2; j > 0; j /= 2) {
@@ -192,17 +193,17 @@ __device__ __forceinline__ void order_labels(int w, OrderLds& lds, int B, const 
 }
 
 // ---------------------------------------------------------------------------------------------
-// gather_normalize: the first x_blocks workgroups normalise the features (normalize_x_row), the others the
-// sampled centers: the two need nothing of each other, and a launch of its own for a few hundred
-// rows of features is 3-5 us that nothing runs beside (step, 128 x 1,000 x 512 fp32 62.2 -> 59.8 us, 512 x
-// 9,344 x 512 104.4 -> 102.5).
-// Centers: one wavefront per group of NB consecutive sampled rows, all NB row reads
-// (2 KB each at D = 512, ascending row ids) in flight before the first is reduced.
-// Rows k..kp-1 of Wn are written as zeros.
+// gather_normalize: the first x_blocks workgroups normalise the features (normalize_x_row), the
+// others the sampled centers: the two need nothing of each other, and a launch of its own for a few
+// hundred rows of features is 3-5 us that nothing runs beside (step, 128 x 1,000 x 512 fp32 62.2 ->
+// 59.8 us, 512 x 9,344 x 512 104.4 -> 102.5).  Centers: one wavefront per group of NB consecutive
+// sampled rows, all NB row reads (2 KB each at D = 512, ascending row ids) in flight before the
+// first is reduced.  Rows k..kp-1 of Wn are written as zeros.
 // ---------------------------------------------------------------------------------------------
-// SHORT (rows of at most 128 floats): half a wavefront to a center, twice the centers in flight.  Step, us, before -> now:
-// 256 samples x 25,723 classes x 128 69.4 -> 67.9, 256 x 40,000 x 64 76.9 -> 73.7, 300 x 300,000 x 64 368 -> 348.
-// (In front of either: one workgroup for every label window of a large batch, order_labels.)
+// SHORT (rows of at most 128 floats): half a wavefront to a center, twice the centers in flight.
+// Step, us, before -> now: 256 samples x 25,723 classes x 128 69.4 -> 67.9, 256 x 40,000 x 64 76.9
+// -> 73.7, 300 x 300,000 x 64 368 -> 348.  (In front of either: one workgroup for every label
+// window of a large batch, order_labels.)
 template <typename T, int NC, bool SHORT>
 __global__ __launch_bounds__(kNormWaves * 64) void gather_normalize_kernel(
     int x_blocks, const float* __restrict__ X, int B, int Bp, const int32_t* __restrict__ yl,
@@ -357,9 +358,9 @@ __device__ __forceinline__ float label_logit(const LossParams& lp, float c) {
 }
 
 // The row sum of exp(z) enters the gradient through p - 1, which for a confident sample is nothing
-// but its rounding: its additions therefore keep one order whether a tile has 128 classes or 64.
-// A wavefront of a 128-tile chains the 32 values a lane holds of 64 classes; a 64-tile, whose wavefronts
-// hold 32 classes each, chains the two of them, and row_combine adds the tiles in pairs.
+// but its rounding: its additions therefore keep one order whether a tile has 128 classes or 64.  A
+// wavefront of a 128-tile chains the 32 values a lane holds of 64 classes; a 64-tile, whose
+// wavefronts hold 32 classes each, chains the two of them, and row_combine adds the tiles in pairs.
 template <class Cfg>
 constexpr bool logits_chained() { return Cfg::BM == 64; }
 
@@ -448,8 +449,8 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   const int64_t j0 = (int64_t)tj * Cfg::BM;
   const int i0 = ti * Cfg::BN;
 
-  // labels: requested in front of the reduction (behind it they were a wait of 2 us of their own; with fp32 operands
-  // they only delay the first slab)
+  // labels: requested in front of the reduction (behind it they were a wait of 2 us of their own;
+  // with fp32 operands they only delay the first slab)
   int32_t ylab[Cfg::TN];
   auto request_labels = [&]() {
 #pragma unroll
@@ -805,12 +806,13 @@ __global__ void row_combine_kernel(int head_blocks, const float* __restrict__ ro
 }
 
 // ---------------------------------------------------------------------------------------------
-// dfeatures_tile (in gemm_backward): slice `sp` of S: part[sp][i][d] = sum_{j in slice} E[i][j] * Wn[j][d]
-// (A = E with k contiguous, B = Wn k-major).
+// dfeatures_tile (in gemm_backward): slice `sp` of S: part[sp][i][d] = sum_{j in slice} E[i][j] *
+// Wn[j][d] (A = E with k contiguous, B = Wn k-major).
 // ---------------------------------------------------------------------------------------------
-// Products of one uninterrupted sum (gemm_tile's CHAIN) in the two backward products with fp32 operands.
-// Their 128- and 64-tiles need fewer slices than 256-tiles to fill the GPU, and a slice of many thousand
-// products adds up rounding errors.  The pieces cost 0 - 3 % of a step, as many slices as 256-tiles take up to 18 %.
+// Products of one uninterrupted sum (gemm_tile's CHAIN) in the two backward products with fp32
+// operands.  Their 128- and 64-tiles need fewer slices than 256-tiles to fill the GPU, and a slice
+// of many thousand products adds up rounding errors.  The pieces cost 0 - 3 % of a step, as many
+// slices as 256-tiles take up to 18 %.
 constexpr int kDxSumSteps = 256, kDwSumSteps = 512;
 template <class Cfg, int STEPS, bool PIECES>
 constexpr int sum_slabs() { return PIECES ? STEPS / Cfg::BK : 0; }
@@ -846,11 +848,12 @@ __device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
 }
 
 // ---------------------------------------------------------------------------------------------
-// dweight_tile (in gemm_backward): dWn[j][d] = sum_i E[i][j] * Xs[i][d] (both operands k-major); rows j < k are
-// written.  When k is small and the batch large (the regime without extra negatives, Sec. 3.3)
-// there are too few tiles to fill the GPU: SPLIT cuts the batch (the reduction) into slices that
-// write partial tiles, summed in fixed order by dweight_reduce.  Xs has rows of Dp elements; the
-// partial tiles too; dWn (the caller's) has rows of D floats, columns from D on are not stored.
+// dweight_tile (in gemm_backward): dWn[j][d] = sum_i E[i][j] * Xs[i][d] (both operands k-major);
+// rows j < k are written.  When k is small and the batch large (the regime without extra negatives,
+// Sec. 3.3) there are too few tiles to fill the GPU: SPLIT cuts the batch (the reduction) into
+// slices that write partial tiles, summed in fixed order by dweight_reduce.  Xs has rows of Dp
+// elements; the partial tiles too; dWn (the caller's) has rows of D floats, columns from D on are
+// not stored.
 // ---------------------------------------------------------------------------------------------
 template <class Cfg, bool SPLIT, bool PIECES>
 __device__ __forceinline__ void dweight_tile(
@@ -904,13 +907,14 @@ __device__ __forceinline__ void dweight_tile(
 }
 
 // gemm_backward: the two backward products need nothing of each other, so they share a launch: the
-// first dx.wgs workgroups (a multiple of 8, so that workgroup ids keep their XCD) work on dfeatures,
-// the others on dweight.  Alone, either leaves the GPU partly idle: small problems have too few
-// tiles and are bound by the latency of a tile (17 + 18 us one after the other, 24 together at 512
-// samples x 9,344 classes x 512), large ones lose the last round of dweight tiles and have all
-// compute units store their tiles at the same time (291 + 219 us, 495 together at 1024 x 205,991 x
-// 512).  The dfeatures workgroups are the longest and start first; dx_shape says how many there are.
-// (Large batches can have the longer reduction in dweight: its workgroups are then in front, w_first of them.)
+// first dx.wgs workgroups (a multiple of 8, so that workgroup ids keep their XCD) work on
+// dfeatures, the others on dweight.  Alone, either leaves the GPU partly idle: small problems have
+// too few tiles and are bound by the latency of a tile (17 + 18 us one after the other, 24 together
+// at 512 samples x 9,344 classes x 512), large ones lose the last round of dweight tiles and have
+// all compute units store their tiles at the same time (291 + 219 us, 495 together at 1024 x
+// 205,991 x 512).  The dfeatures workgroups are the longest and start first; dx_shape says how many
+// there are.  (Large batches can have the longer reduction in dweight: its workgroups are then in
+// front, w_first of them.)
 template <class CfgX, class CfgW, bool SPLIT, bool PIECES>
 __global__ __launch_bounds__(CfgX::THREADS, CfgX::MIN_WAVES) void gemm_backward_kernel(
     const typename CfgX::elem* __restrict__ E, const typename CfgX::elem* __restrict__ Wn,
@@ -946,15 +950,15 @@ __global__ void dweight_reduce_kernel(const float* __restrict__ part, int splits
   *reinterpret_cast<float4*>(dW + e4 * 4) = a;
 }
 
-// dweight_label_block (in gradients_final, or dweight_label in a launch of its own): dWn[y] += sum over samples i with label y of dlabel_i * xn_i.
-// Block i does the whole sum for its class if i is the first sample carrying that label
-// (head[y] == i, found with an integer atomicMin by row_combine).  The
-// matching samples are listed in ascending order; thread group g (one float4 column per thread)
-// sums the matches whose ordinal is congruent to g, and the groups are combined in fixed order,
-// so the result does not depend on timing.
-// LABEL_COMPACT (fused step): the sum is not added to dWn[y] but written to row i of a B x D side
-// buffer, i being that first sample; the fused GEMM picks it up through head[].
-// Batches of several windows of kLabelWindow samples: window_label_block, further down.
+// dweight_label_block (in gradients_final, or dweight_label in a launch of its own): dWn[y] += sum
+// over samples i with label y of dlabel_i * xn_i.  Block i does the whole sum for its class if i is
+// the first sample carrying that label (head[y] == i, found with an integer atomicMin by
+// row_combine).  The matching samples are listed in ascending order; thread group g (one float4
+// column per thread) sums the matches whose ordinal is congruent to g, and the groups are combined
+// in fixed order, so the result does not depend on timing.  LABEL_COMPACT (fused step): the sum is
+// not added to dWn[y] but written to row i of a B x D side buffer, i being that first sample; the
+// fused GEMM picks it up through head[].  Batches of several windows of kLabelWindow samples:
+// window_label_block, further down.
 constexpr int kLabelThreads = 1024;
 enum LabelMode { LABEL_ADD, LABEL_COMPACT };
 struct LabelLds {
@@ -1055,16 +1059,17 @@ __global__ __launch_bounds__(kLabelThreads) void dweight_label_kernel(
   dweight_label_block<MODE>(blockIdx.x, lds, X, B, D, yl, k, head, rnormX, dlabel, dW);
 }
 
-// window_label_block (in gradients_final, or window_label in a launch of its own): the label part of batches of
-// several windows (Sec. 3.3 enlarges the batch to 8K and 16K).  With long-tailed labels one class can own a fifth
-// of the batch, and one workgroup cannot read thousands of feature rows quickly (a compute unit draws a small share
-// of the memory bandwidth); most classes have a sample or two.  order_labels has put the samples of a window in order
-// of their class.  kWindowBlocks workgroups share a window's classes: one wavefront sums a class of up to
-// kWindowWave samples, the 16 of a workgroup share a larger one.  The sum goes to row i of `part`, i being the class's
-// first sample in the window; dweight_label_combine adds a class's sums in window order.
-// (A workgroup for every sample of the batch, which scanned the window if it was the first of its class, and
-// nothing to do for most of them: gradients_final at 16,384 samples x 3,592 classes x 512 89.5 us, now 35.3; step
-// 392 -> 338.)
+// window_label_block (in gradients_final, or window_label in a launch of its own): the label part
+// of batches of several windows (Sec. 3.3 enlarges the batch to 8K and 16K).  With long-tailed
+// labels one class can own a fifth of the batch, and one workgroup cannot read thousands of feature
+// rows quickly (a compute unit draws a small share of the memory bandwidth); most classes have a
+// sample or two.  order_labels has put the samples of a window in order of their class.
+// kWindowBlocks workgroups share a window's classes: one wavefront sums a class of up to
+// kWindowWave samples, the 16 of a workgroup share a larger one.  The sum goes to row i of `part`,
+// i being the class's first sample in the window; dweight_label_combine adds a class's sums in
+// window order.  (A workgroup for every sample of the batch, which scanned the window if it was the
+// first of its class, and nothing to do for most of them: gradients_final at 16,384 samples x 3,592
+// classes x 512 89.5 us, now 35.3; step 392 -> 338.)
 constexpr int kWindowBlocks = 32, kWindowWave = 8;
 template <int NC>
 struct WindowLds {
@@ -1177,9 +1182,10 @@ __global__ __launch_bounds__(kLabelThreads) void window_label_kernel(
   window_label_block<NC>(blockIdx.x, lds, X, D, order, runs, rnormX, dlabel, part);
 }
 
-// dweight_label_combine (after window_label_block): the wavefront of sample i, if that is the first of its class in the whole
-// batch, adds the class's window sums (rows of `part` named by the window heads) in window order; the total
-// goes to row i of `part` (COMPACT, fused step) or is added to dWn[y].
+// dweight_label_combine (after window_label_block): the wavefront of sample i, if that is the first
+// of its class in the whole batch, adds the class's window sums (rows of `part` named by the window
+// heads) in window order; the total goes to row i of `part` (COMPACT, fused step) or is added to
+// dWn[y].
 template <bool COMPACT>
 __global__ void dweight_label_combine_kernel(int B, int D, const int32_t* __restrict__ yl, int64_t k,
                                         const int32_t* __restrict__ head, int64_t kp, int nwin,
@@ -1252,12 +1258,13 @@ __device__ __forceinline__ void fused_update_tile(
                            // update 1099 us a step, 3 rows 1089, 5 rows 1083)
   static_assert(D % 256 == 0 && HR % WAVES == 0 && ROWS <= 64 && WIN <= ROWS, "fused update geometry");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // Two spare rows of D floats: the first holds zeros (never written) and is what a padding row of the last tile
-  // reads instead of W and v; the second takes the stores of the padding rows and is never read.
-  // Every row thus issues the same loads of W and v and the same stores in the same order with no branch in
-  // between, which is what lets the wait for row n's operands leave the younger requests of rows
-  // n+1 .. n+WIN in flight.  The few centers that are the label of a sample read their label part when
-  // they are at it: as part of the window it was a third of all loads, of a row of zeros for nearly every center.
+  // Two spare rows of D floats: the first holds zeros (never written) and is what a padding row of
+  // the last tile reads instead of W and v; the second takes the stores of the padding rows and is
+  // never read.  Every row thus issues the same loads of W and v and the same stores in the same
+  // order with no branch in between, which is what lets the wait for row n's operands leave the
+  // younger requests of rows n+1 .. n+WIN in flight.  The few centers that are the label of a
+  // sample read their label part when they are at it: as part of the window it was a third of all
+  // loads, of a row of zeros for nearly every center.
   const float* zero_row = spare;
   float* trash_row = spare + D;
 
@@ -1371,10 +1378,10 @@ __device__ __forceinline__ void fused_update_tile(
 
 // gemm_backward_update: as gemm_backward, the dfeatures product (MFMA bound) shares the launch with
 // the dweight product that ends in the update (HBM bound more than half of its time): 715 us one
-// after the other, 698 together at 1024 samples x 205,991 classes x 512, 162 -> 137 at 36,024 classes.
-// Behind the dfeatures workgroups, n_big workgroups take tiles of CfgB::BM rows; the rows left over when
-// those no longer fill a whole round of workgroups on the GPU go to the following workgroups in
-// tiles of CfgS::BM rows, so that the last, partly filled round is short.
+// after the other, 698 together at 1024 samples x 205,991 classes x 512, 162 -> 137 at 36,024
+// classes.  Behind the dfeatures workgroups, n_big workgroups take tiles of CfgB::BM rows; the rows
+// left over when those no longer fill a whole round of workgroups on the GPU go to the following
+// workgroups in tiles of CfgS::BM rows, so that the last, partly filled round is short.
 template <class CfgX, class CfgB, class CfgS>
 __global__ __launch_bounds__(CfgB::THREADS) void gemm_backward_update_kernel(
     const typename CfgB::elem* __restrict__ E, const typename CfgB::elem* __restrict__ Wn,
@@ -1453,8 +1460,8 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
   const int D = a.D;
   // The wavefronts of a sample share the slices of S (wavefront w takes slices w, w + WPS, ...:
   // several independent loads in flight each); their partial rows are added in wavefront order by
-  // wavefront 0, which then finishes the row: the same order on every run.
-  // What the last step needs is requested before the slices and in front of the barrier: the chain label -> class id
+  // wavefront 0, which then finishes the row: the same order on every run.  What the last step
+  // needs is requested before the slices and in front of the barrier: the chain label -> class id
   // -> row of W behind them was most of a small launch.
   const bool ends = wave == 0 && i < a.B;
   float rs = 0.f, rnx = 0.f, dl = 0.f, rnw = 0.f;
@@ -1538,15 +1545,14 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
 }
 
 // gradients_final: what is left after the backward products, in one launch: the label part of dWn
-// (`label_blocks` workgroups), the finished rows of dX and the mean loss (workgroup 0: the longest with a
-// large batch).  None needs anything of the others; one after the other they are two chains of
-// dependent loads that leave the GPU idle, and with a large batch the mean loss runs alone at the end.
-// 64 registers: two workgroups on a compute unit.  Step, two launches -> one: 128 x 1,000 x 512 fp32 59.9 ->
-// 56.1 us, 512 x 9,344 x 512 104.4 -> 101.0, 256 x 25,723 x 128 79.5 -> 74.1, 768 x 20,599 x 1024 277 ->
-// 271, 16,384 samples x 3,592 476 -> 462.
-// From kFinalWideSplits slices on a sample gets 16 wavefronts instead of 4: below, a third of the 16 and more
-// would have no slice to add.
-// Up to kFinalOneSplits a sample gets one: three of four would have none.
+// (`label_blocks` workgroups), the finished rows of dX and the mean loss (workgroup 0: the longest
+// with a large batch).  None needs anything of the others; one after the other they are two chains
+// of dependent loads that leave the GPU idle, and with a large batch the mean loss runs alone at
+// the end.  64 registers: two workgroups on a compute unit.  Step, two launches -> one: 128 x 1,000
+// x 512 fp32 59.9 -> 56.1 us, 512 x 9,344 x 512 104.4 -> 101.0, 256 x 25,723 x 128 79.5 -> 74.1,
+// 768 x 20,599 x 1024 277 -> 271, 16,384 samples x 3,592 476 -> 462.  From kFinalWideSplits slices
+// on a sample gets 16 wavefronts instead of 4: below, a third of the 16 and more would have no
+// slice to add.  Up to kFinalOneSplits a sample gets one: three of four would have none.
 constexpr int kFinalWideSplits = 12, kFinalOneSplits = 2;
 template <int NC, int WPS, bool WINDOWS>
 __global__ __launch_bounds__(kLabelThreads, 8) void gradients_final_kernel(

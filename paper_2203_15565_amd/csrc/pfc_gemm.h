@@ -10,11 +10,11 @@
 // copy of E, Wn or Xs is ever written.  Operands are padded with zeros to whole tiles by their
 // producers: the main loop has no bounds checks.
 //
-// A workgroup of WM x WN wavefronts (64 lanes each) owns a BM x BN tile of C.  K is walked in
-// slabs of BK = 64 (bf16) or 32 (fp32) reduction steps.  bf16 operands go from global memory to LDS
-// without registers (gemm_tile_dma).  The fp32 operands of the backward products are split into planes of 16 bits on the
-// way (gemm_tile_split): three bf16 planes and six products; those of the logits are multiplied as they are
-// (gemm_tile_fp32).
+// A workgroup of WM x WN wavefronts (64 lanes each) owns a BM x BN tile of C.  K is walked in slabs
+// of BK = 64 (bf16) or 32 (fp32) reduction steps.  bf16 operands go from global memory to LDS
+// without registers (gemm_tile_dma).  The fp32 operands of the backward products are split into
+// planes of 16 bits on the way (gemm_tile_split): three bf16 planes and six products; those of the
+// logits are multiplied as they are (gemm_tile_fp32).
 //
 // Fragment convention (the same for A and B, which is all a dot product needs): a group of 16 reduction
 // steps is split between the lane halves, lanes 0..31 taking the first half and lanes 32..63 the
@@ -99,13 +99,13 @@ __device__ __forceinline__ void add_acc(f32x16 (&to)[Cfg::TM][Cfg::TN],
 // ---------------------------------------------------------------------------------------------
 // bf16 operands: global memory -> LDS without registers (global_load_lds_dwordx4).
 // ---------------------------------------------------------------------------------------------
-// A wavefront's load fills 1 KB of consecutive LDS (16 bytes a lane), so rows cannot be padded; what keeps
-// the fragment reads off each other's banks is the order of the 16-byte chunks inside a row, chosen by the
-// lane's global address:
-//   k contiguous: chunk c of row r lies at position c ^ (r/2 % 8): a fragment read by 16 consecutive rows
-//                 touches every bank once.
-//   k-major:      likewise for units of 64 bytes, so that the four k-rows of one transpose read fall into
-//                 different banks.
+// A wavefront's load fills 1 KB of consecutive LDS (16 bytes a lane), so rows cannot be padded;
+// what keeps the fragment reads off each other's banks is the order of the 16-byte chunks inside a
+// row, chosen by the lane's global address:
+//   k contiguous: chunk c of row r lies at position c ^ (r/2 % 8): a fragment read by 16
+//                 consecutive rows touches every bank once.
+//   k-major:      likewise for units of 64 bytes, so that the four k-rows of one transpose read
+//                 fall into different banks.
 template <typename T, int R, bool KMAJOR, int SLAB>
 struct DmaLds {
   static constexpr int BK = SLAB / (int)sizeof(T);
@@ -139,11 +139,11 @@ struct DmaStager {
     slab = KMAJOR ? (int64_t)L::BK * ld * (int64_t)sizeof(T) : (int64_t)L::BK * (int64_t)sizeof(T);
   }
   // Load p of slab s into the LDS region at byte `lds` (this wavefront's first byte there).
-  // Assembly, because the compiler makes every LDS read that follows the builtin wait for all loads in
-  // flight.  The load has no output register.  Its write to LDS is done when dma_wait_barrier is behind it: whoever
-  // reads the region waits there first.  The five wait states: the base may come straight from v_readfirstlane (a VALU
-  // write of an SGPR that a vector memory instruction reads), and the compiler, which sets M0 (one wait state), does
-  // not look into assembly for either.
+  // Assembly, because the compiler makes every LDS read that follows the builtin wait for all loads
+  // in flight.  The load has no output register.  Its write to LDS is done when dma_wait_barrier is
+  // behind it: whoever reads the region waits there first.  The five wait states: the base may come
+  // straight from v_readfirstlane (a VALU write of an SGPR that a vector memory instruction reads),
+  // and the compiler, which sets M0 (one wait state), does not look into assembly for either.
   __device__ __forceinline__ void load(int s, int p, uint32_t lds) const {
     const uint64_t at = (uint64_t)(base + (int64_t)s * slab + p * pass);
     const uint64_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) |
@@ -155,8 +155,9 @@ struct DmaStager {
   }
 };
 
-// Waits until at most N of this wavefront's loads are in flight and its LDS reads are back, then meets the
-// workgroup: what all wavefronts have loaded before is in LDS, what they have read may be overwritten.
+// Waits until at most N of this wavefront's loads are in flight and its LDS reads are back, then
+// meets the workgroup: what all wavefronts have loaded before is in LDS, what they have read may be
+// overwritten.
 template <int N>
 __device__ __forceinline__ void dma_wait_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
@@ -206,19 +207,21 @@ struct FragAddr<L, true, GROUPS, NB> {
 };
 
 // gemm_tile (below) for bf16 operands.  LDS holds ABUF slabs of A and BBUF of B:
-//   * the barrier in front of the last group of slab s frees its buffers (all fragments are read by then)
-//     and publishes slab s+1; behind it B of slab s+BBUF and A of slab s+ABUF are requested, one load
-//     between two MFMAs, so a load has BBUF - 1 (A: ABUF - 1) whole slabs of MFMAs to arrive;
+//   * the barrier in front of the last group of slab s frees its buffers (all fragments are read by
+//     then) and publishes slab s+1; behind it B of slab s+BBUF and A of slab s+ABUF are requested,
+//     one load between two MFMAs, so a load has BBUF - 1 (A: ABUF - 1) whole slabs of MFMAs to
+//     arrive;
 //   * fragments are read one group ahead, the last group is multiplied behind the barrier.
-// Against staging through registers (two stages of 64 steps, 8 ds_write_b128 a wavefront and slab), both in
-// turn, us: logits 1024 x 205,991 x 512 296 -> 276, both backward products there 450 -> 401, 1024 x
-// 360,232 766 -> 690, 16,384 x 3,592 125 -> 113; products alone, 256 tiles of 256 x 256 over 6,400 steps,
-// 1.00 - 1.17 -> 1.28 - 1.36 PFLOP/s (both k contiguous), 1.03 -> 1.21 (both k-major), 0.97 -> 1.07 (dfeatures).
-// What bounds it now, by counters and variants of the loop: both k contiguous, the matrix cores are busy 82 %
-// of the cycles at 1.46 GHz, the clock that the power leaves; with operands from HBM (dfeatures: 57 % at
-// 1.76 GHz) the loads are: a compute unit's misses return in order, at about 33 GB/s whatever is
-// requested earlier (waits taken out: the same; requesting lines of later slabs by one of the workgroups that
-// share them: 17 % slower; rows of E stored in blocks of 64 classes: the same).
+// Against staging through registers (two stages of 64 steps, 8 ds_write_b128 a wavefront and slab),
+// both in turn, us: logits 1024 x 205,991 x 512 296 -> 276, both backward products there 450 ->
+// 401, 1024 x 360,232 766 -> 690, 16,384 x 3,592 125 -> 113; products alone, 256 tiles of 256 x 256
+// over 6,400 steps, 1.00 - 1.17 -> 1.28 - 1.36 PFLOP/s (both k contiguous), 1.03 -> 1.21 (both
+// k-major), 0.97 -> 1.07 (dfeatures).  What bounds it now, by counters and variants of the loop:
+// both k contiguous, the matrix cores are busy 82 % of the cycles at 1.46 GHz, the clock that the
+// power leaves; with operands from HBM (dfeatures: 57 % at 1.76 GHz) the loads are: a compute
+// unit's misses return in order, at about 33 GB/s whatever is requested earlier (waits taken out:
+// the same; requesting lines of later slabs by one of the workgroups that share them: 17 % slower;
+// rows of E stored in blocks of 64 classes: the same).
 template <class Cfg>
 __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restrict__ A, int64_t lda,
                                               const typename Cfg::elem* __restrict__ B, int64_t ldb, int nslabs,
@@ -231,7 +234,8 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
   typedef DmaStager<T, LA, Cfg::THREADS, Cfg::A_KMAJOR> SA;
   typedef DmaStager<T, LB, Cfg::THREADS, Cfg::B_KMAJOR> SB;
   constexpr int NA = SA::NCH, NB = SB::NCH, MM = Cfg::TM * Cfg::TN, HEAD = Cfg::GROUPS - 1;
-  // loads that may be in flight when slab s+1 (or slab 0) has to be there, nothing being left out at the end
+  // loads that may be in flight when slab s+1 (or slab 0) has to be there, nothing being left out
+  // at the end
   constexpr int FLY = ABUF == BBUF ? (BBUF - 2) * (NA + NB) : (BBUF - 1) * NA + (BBUF - 2) * NB;
   constexpr int FLY0 = (BBUF - 1) * (NA + NB) + (ABUF - BBUF) * NA;
   const int wave = threadIdx.x >> 6;
@@ -316,21 +320,23 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
 // ---------------------------------------------------------------------------------------------
 // fp32 operands, split into planes of 16 bits.
 // ---------------------------------------------------------------------------------------------
-// x = h + m + l in bf16, each rounded to nearest, so that a plane is at most 2^-9 of the one above.  That is exact for
-// |x| from 2^-109 to the largest bf16; below, where l gets to the last place of bf16's subnormal numbers (which the
-// conversion, the dot and the matrix instruction keep), it is off by at most 2^-134.  The operands: normalised rows,
-// exp(z) <= e^64, and Xs = (s / (B l)) xn, whose components come to 2^-119 when all of 60,000 centers are next to all of 4096
-// samples (dWn then 2.7e-6 off 64 bits, 2.8e-6 with fp32 MFMAs).
-// Of the nine products of two values six are added up; those left out (m l, l m, l l) come to at most 2^-26.
+// x = h + m + l in bf16, each rounded to nearest, so that a plane is at most 2^-9 of the one above.
+// That is exact for |x| from 2^-109 to the largest bf16; below, where l gets to the last place of
+// bf16's subnormal numbers (which the conversion, the dot and the matrix instruction keep), it is
+// off by at most 2^-134.  The operands: normalised rows, exp(z) <= e^64, and Xs = (s / (B l)) xn,
+// whose components come to 2^-119 when all of 60,000 centers are next to all of 4096 samples (dWn
+// then 2.7e-6 off 64 bits, 2.8e-6 with fp32 MFMAs).  Of the nine products of two values six are
+// added up; those left out (m l, l m, l l) come to at most 2^-26.
 struct SplitBf16 {
   static constexpr int PLANES = 3, PRODUCTS = 6;
-  // h h last: where one product dominates a sum, the accumulator is as large for one rounding of six.  (A product
-  // alone off by, rms: 3.1e-8; h h first 5.2e-8; fp32 MFMA 2.5e-8.)
+  // h h last: where one product dominates a sum, the accumulator is as large for one rounding of
+  // six.  (A product alone off by, rms: 3.1e-8; h h first 5.2e-8; fp32 MFMA 2.5e-8.)
   static constexpr int A[PRODUCTS] = {1, 1, 0, 2, 0, 0}, B[PRODUCTS] = {1, 0, 1, 0, 2, 0};
-  // words of one pair of neighbours in the planes; the remainders are exact, the dot instruction takes a plane
-  // off without widening it first (x - 1 * h + 0 * h')
+  // words of one pair of neighbours in the planes; the remainders are exact, the dot instruction
+  // takes a plane off without widening it first (x - 1 * h + 0 * h')
   static __device__ __forceinline__ void pair(float a, float b, uint32_t (&w)[PLANES]) {
-    // (the constants come from registers: as an inline constant of the instruction, (-1, 0) reads (0, -1))
+    // (the constants come from registers: as an inline constant of the instruction, (-1, 0) reads
+    // (0, -1))
     uint32_t c_lo = 0x0000bf80u, c_hi = 0xbf800000u;
     asm("" : "+s"(c_lo), "+s"(c_hi));
     const bf16x2 lo = __builtin_bit_cast(bf16x2, c_lo), hi = __builtin_bit_cast(bf16x2, c_hi);
@@ -375,20 +381,22 @@ __device__ __forceinline__ SplitChunk split_chunk(int c, const float* base, int6
           L::BYTES};
 }
 
-// gemm_tile (below) for the fp32 operands of the backward products.  LDS holds two stages of 16 reduction steps, each the planes of both operands
-// (layout: DmaLds).  Every thread loads 8 neighbouring values of an operand, one slab or more ahead, splits them
-// between the MFMAs of the slab at hand and stores one 16-byte chunk to each plane of the other stage; the last product
-// of a slab is added up behind the barrier, under the first fragment reads of the next one.
-// What it replaces: v_mfma_f32_32x32x2_f32, whose rate (157 TFLOP/s nominal) was the bound at any tile size; six bf16
-// products are 2.7 times that.  Step, us, before -> now: 512 x 9,344 x 512 199 -> 183, 300 x 40,000 x 512 736 -> 608,
-// 1024 x 36,024 x 512 with the update 1211 -> 1003, 500 x 4,000 x 1024 173 -> 154, 128 x 1,000 x 512 even (latency).
-// Error against 64 bits (2-norm, features | centers off the labels), fp32 products -> now.  Scale 64, most of it the
-// logits': 512 x 9,344 x 512 6.43e-7 -> 6.41e-7 | 3.07e-6 -> 3.06e-6, 2048 x 16,000 x 512 5.76e-7 -> 5.75e-7 |
-// 3.05e-6 -> 3.04e-6, 4096 x 20,000 x 512 5.69e-7 -> 5.60e-7 | 3.01e-6 -> 2.98e-6.  Scale 1, centers, most of it the
-// sums': 4.2e-7 -> 3.4e-7, 4.2e-7 -> 3.5e-7, 5.9e-7 -> 5.0e-7: an accumulator takes 6 roundings for 16 products
-// instead of 8.
-// What bounds it: large problems the clock that the power leaves (1.1 PFLOP/s of 16-bit products), small ones
-// the way from global memory through registers and LDS to the fragments in every slab.
+// gemm_tile (below) for the fp32 operands of the backward products.  LDS holds two stages of 16
+// reduction steps, each the planes of both operands (layout: DmaLds).  Every thread loads 8
+// neighbouring values of an operand, one slab or more ahead, splits them between the MFMAs of the
+// slab at hand and stores one 16-byte chunk to each plane of the other stage; the last product of a
+// slab is added up behind the barrier, under the first fragment reads of the next one.  What it
+// replaces: v_mfma_f32_32x32x2_f32, whose rate (157 TFLOP/s nominal) was the bound at any tile
+// size; six bf16 products are 2.7 times that.  Step, us, before -> now: 512 x 9,344 x 512 199 ->
+// 183, 300 x 40,000 x 512 736 -> 608, 1024 x 36,024 x 512 with the update 1211 -> 1003, 500 x 4,000
+// x 1024 173 -> 154, 128 x 1,000 x 512 even (latency).  Error against 64 bits (2-norm, features |
+// centers off the labels), fp32 products -> now.  Scale 64, most of it the logits': 512 x 9,344 x
+// 512 6.43e-7 -> 6.41e-7 | 3.07e-6 -> 3.06e-6, 2048 x 16,000 x 512 5.76e-7 -> 5.75e-7 | 3.05e-6 ->
+// 3.04e-6, 4096 x 20,000 x 512 5.69e-7 -> 5.60e-7 | 3.01e-6 -> 2.98e-6.  Scale 1, centers, most of
+// it the sums': 4.2e-7 -> 3.4e-7, 4.2e-7 -> 3.5e-7, 5.9e-7 -> 5.0e-7: an accumulator takes 6
+// roundings for 16 products instead of 8.  What bounds it: large problems the clock that the power
+// leaves (1.1 PFLOP/s of 16-bit products), small ones the way from global memory through registers
+// and LDS to the fragments in every slab.
 template <class Cfg, int CHAIN>
 __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int64_t lda,
                                                 const float* __restrict__ B, int64_t ldb, int nslabs, char* smem,
@@ -476,14 +484,13 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
       read_a(cur, 2, a[2]);
       read_b(cur, 2, b[2]);
       __builtin_amdgcn_sched_barrier(0);
-      // between the products of this slab the values of the next one are split, from the second product (the
-      // third of six) on
-      constexpr int Q = (NPR - 1) * MM, Q0 = NPR > 3 ? MM : 0, SPAN = NPR > 3 ? 3 * MM : Q;
+      // between the products of this slab the values of the next one are split, from the second on
+      constexpr int Q = (NPR - 1) * MM, Q0 = MM, SPAN = 3 * MM;
       static_for<0, Q>([&](auto qc) __attribute__((always_inline)) {
         constexpr int q = decltype(qc)::value, t = q % MM, o = q / MM;
         constexpr int from = pieces_before(q, Q0, SPAN, 4 * NPT), to = pieces_before(q + 1, Q0, SPAN, 4 * NPT);
         static_for<from, to>([&](auto i) __attribute__((always_inline)) { split(decltype(i)::value, u, nxt); });
-        if constexpr (q == (NPR > 3 ? 4 * MM : Q - 1)) load(s + 1 + DEPTH < last ? s + 1 + DEPTH : last, u);
+        if constexpr (q == Q0 + SPAN) load(s + 1 + DEPTH < last ? s + 1 + DEPTH : last, u);
         S::mfma(a[S::A[o]][t / Cfg::TN], b[S::B[o]][t % Cfg::TN], acc[t / Cfg::TN][t % Cfg::TN]);
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -515,15 +522,17 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
 // ---------------------------------------------------------------------------------------------
 // fp32 operands of the logits: both k contiguous, multiplied by v_mfma_f32_32x32x2_f32.
 // ---------------------------------------------------------------------------------------------
-// Operand slab in LDS: R rows of SLAB bytes, padded so that the fragment reads of 32 rows miss each other's banks.
+// Operand slab in LDS: R rows of SLAB bytes, padded so that the fragment reads of 32 rows miss each
+// other's banks.
 template <int R, int SLAB>
 struct PlainLds {
   static constexpr int STRIDE = SLAB + 16, BYTES = R * STRIDE;
   static constexpr int CPR = SLAB / 16, CHUNKS = R * CPR;
 };
 
-// Global -> register -> LDS staging of one slab.  Thread t owns chunk t % CPR of rows t / CPR + p * RPP, p = 0 .. NCH-1.
-// A wave-uniform base (tile, slab, pass) and one 32-bit offset per thread keep addresses out of the vector registers.
+// Global -> register -> LDS staging of one slab.  Thread t owns chunk t % CPR of rows t / CPR + p *
+// RPP, p = 0 .. NCH-1.  A wave-uniform base (tile, slab, pass) and one 32-bit offset per thread
+// keep addresses out of the vector registers.
 template <class L, int THREADS, int SLAB>
 struct PlainStager {
   static constexpr int RPP = THREADS / L::CPR, NCH = L::CHUNKS / THREADS;
@@ -557,14 +566,16 @@ struct PlainStager {
   }
 };
 
-// gemm_tile (below) for the fp32 operands of the logits: two stages in LDS, one set of registers, loads two slabs
-// ahead, issued one at a time between the MFMAs of the first groups; fragments are read a group ahead; the last group of
-// a slab is multiplied behind the barrier.  Slab numbers past the end are clamped: such loads and stores are redundant.
-// Why not in 16-bit planes, as the backward products: two fp16 planes and three products are as close to 64 bits (a
-// cosine 6e-8 off instead of 2e-7) and take 22 of 60 us less at 512 x 9,344 x 512, but what a confident sample
-// passes on is p - 1, the rounding of a sum and a quotient next to 1 multiplied by the scale: with other roundings of its
-// cosines the gradients of samples aligned to their centers move by 1e-5 .. 1e-4 of their 2-norm, as far as they are
-// off from 64 bits either way, and more than a change of the summation order may move them.
+// gemm_tile (below) for the fp32 operands of the logits: two stages in LDS, one set of registers,
+// loads two slabs ahead, issued one at a time between the MFMAs of the first groups; fragments are
+// read a group ahead; the last group of a slab is multiplied behind the barrier.  Slab numbers past
+// the end are clamped: such loads and stores are redundant.  Why not in 16-bit planes, as the
+// backward products: two fp16 planes and three products are as close to 64 bits (a cosine 6e-8 off
+// instead of 2e-7) and take 22 of 60 us less at 512 x 9,344 x 512, but what a confident sample
+// passes on is p - 1, the rounding of a sum and a quotient next to 1 multiplied by the scale: with
+// other roundings of its cosines the gradients of samples aligned to their centers move by 1e-5 ..
+// 1e-4 of their 2-norm, as far as they are off from 64 bits either way, and more than a change of
+// the summation order may move them.
 template <class Cfg>
 __device__ __forceinline__ void gemm_tile_fp32(const float* __restrict__ A, int64_t lda, const float* __restrict__ B,
                                                int64_t ldb, int nslabs, char* smem,
@@ -576,8 +587,8 @@ __device__ __forceinline__ void gemm_tile_fp32(const float* __restrict__ A, int6
   typedef PlainStager<LB, Cfg::THREADS, SLAB> SB;
   constexpr int STAGE = LA::BYTES + LB::BYTES;
   constexpr int NA = SA::NCH, NB = SB::NCH, NL = NA + NB, MM = Cfg::TM * Cfg::TN, HEAD = Cfg::GROUPS - 1;
-  // the loads of a slab are placed in front of the MFMAs of the first one or two groups (of all groups before the
-  // barrier if two do not have an MFMA for each load)
+  // the loads of a slab are placed in front of the MFMAs of the first one or two groups (of all
+  // groups before the barrier if two do not have an MFMA for each load)
   constexpr int SPAN = (NL <= 2 * MM ? (HEAD < 2 ? HEAD : 2) : HEAD) * MM;
   static_assert(HEAD >= 1, "the last group is multiplied behind the barrier");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

@@ -62,9 +62,10 @@ __global__ void update_kernel(float* __restrict__ W, float* __restrict__ V, int6
   }
 }
 
-// Rows of 64 and 128 floats: LPR = D / 4 lanes a row, 64 / LPR rows a wavefront; a row to a wavefront left three and two
-// of four lanes without a load.  Same sums in the same order.  Step, us, before -> now: 256 samples x 25,723 classes x
-// 128 71.2 -> 69.8, 256 x 40,000 x 64 82.4 -> 76.9, 300 x 300,000 x 64 400 -> 368, 1024 x 200,000 x 128 503 -> 500.
+// Rows of 64 and 128 floats: LPR = D / 4 lanes a row, 64 / LPR rows a wavefront; a row to a
+// wavefront left three and two of four lanes without a load.  Same sums in the same order.  Step,
+// us, before -> now: 256 samples x 25,723 classes x 128 71.2 -> 69.8, 256 x 40,000 x 64 82.4 ->
+// 76.9, 300 x 300,000 x 64 400 -> 368, 1024 x 200,000 x 128 503 -> 500.
 template <int LPR>
 __global__ void update_short_kernel(float* __restrict__ W, float* __restrict__ V, int64_t N,
                                     const int32_t* __restrict__ idx, int64_t k,
