@@ -392,7 +392,7 @@ __device__ __forceinline__ SplitChunk split_chunk(int c, const float* base, int6
 // slab is added up behind the barrier, under the first fragment reads of the next one.  What it
 // replaces: v_mfma_f32_32x32x2_f32, whose rate (157 TFLOP/s nominal) was the bound at any tile
 // size; six bf16 products are 2.7 times that.  Step, us, before -> now: 512 x 9,344 x 512 199 ->
-// 183, 300 x 40,000 x 512 736 -> 608, 1024 x 36,024 x 512 with the update 1211 -> 1003, 500 x 4,000
+// 181, 300 x 40,000 x 512 736 -> 608, 1024 x 36,024 x 512 with the update 1211 -> 1003, 500 x 4,000
 // x 1024 173 -> 154, 128 x 1,000 x 512 even (latency).  Error against 64 bits (2-norm, features |
 // centers off the labels), fp32 products -> now.  Scale 64, most of it the logits': 512 x 9,344 x
 // 512 6.43e-7 -> 6.41e-7 | 3.07e-6 -> 3.06e-6, 2048 x 16,000 x 512 5.76e-7 -> 5.75e-7 | 3.05e-6 ->
