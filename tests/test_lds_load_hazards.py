@@ -24,7 +24,8 @@ __global__ __launch_bounds__(Cfg::THREADS) void tile(const __bf16* A, const __bf
   gemm_tile<Cfg>(A + o * lda, lda, B + i * ldb, ldb, n, smem, acc);
   for (int a = 0; a < Cfg::TM; ++a)
     for (int b = 0; b < Cfg::TN; ++b)
-      for (int r = 0; r < 16; ++r) C[((blockIdx.x * Cfg::THREADS + threadIdx.x) * Cfg::TM * Cfg::TN + a * Cfg::TN + b) * 16 + r] = acc[a][b][r];
+      for (int r = 0; r < 16; ++r)
+        C[((blockIdx.x * Cfg::THREADS + threadIdx.x) * Cfg::TM * Cfg::TN + a * Cfg::TN + b) * 16 + r] = acc[a][b][r];
 }
 #define TILE(...) template __global__ void tile<TileCfg<__bf16, __VA_ARGS__>>(const __bf16*, const __bf16*, int64_t, \
                                                                               int64_t, int, int, float*);
