@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "pfc.h"
+#include "pfc_sample_plan.h"
 #include "pfc_step_plan.h"
 
 namespace pfc {
@@ -48,8 +49,8 @@ struct SampleHdr {
   uint32_t npos;        // and the ones inside it (entries of pos_list)
   uint32_t overflow;    // a workgroup had more classes in the window than it can list
   uint32_t nblk, nwords;   // workgroups and bitmap words of the call (what is to be cleared)
-  uint32_t listed;      // entries of list
-  uint32_t pad[9];
+  uint32_t pad[26];
+  uint32_t listed[kListParts][32];   // entries of the parts of list, each count on a line of its own
 };
 // State of the radix selection between its launches (pfc_sample_radix.hip).
 struct RadixState {

@@ -28,30 +28,63 @@ __device__ __forceinline__ void philox_block(uint32_t q, const PhiloxKey& key, u
   out[0] = c0 & key.mask; out[1] = c1 & key.mask; out[2] = c2 & key.mask; out[3] = c3 & key.mask;
 }
 
-// Sum over the NT threads of a block, to every thread; sm: NT / 64 words.
-template <int NT>
-__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* sm) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  uint32_t r = 0;
-#pragma unroll
-  for (int i = 0; i < NT / 64; ++i) r += sm[i];
-  __syncthreads();
-  return r;
+// Sum over the 64 lanes of a wavefront, to every lane: through the cross-lane modifiers of the vector
+// ALU (as wave_sum), where a shuffle a step is a round trip to LDS.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_uadd(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+__device__ __forceinline__ uint32_t wave_usum(uint32_t v) {
+  v = dpp_uadd<0xB1>(v);    // quad_perm [1,0,3,2]
+  v = dpp_uadd<0x4E>(v);    // quad_perm [2,3,0,1]
+  v = dpp_uadd<0x141>(v);   // row_half_mirror
+  v = dpp_uadd<0x140>(v);   // row_mirror
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 0) + (uint32_t)__builtin_amdgcn_readlane((int)v, 16) +
+         (uint32_t)__builtin_amdgcn_readlane((int)v, 32) + (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+}
+// Inclusive sums over the lanes.
+__device__ __forceinline__ uint32_t wave_uscan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);   // row_shr 1, 2, 4, 8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // last lane of rows 0 and 2 to the next
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // lane 31 to rows 2 and 3
+  return v;
 }
 
-// exclusive scan over the NT threads of a block; also returns the block total
-template <int NT>
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* sm, uint32_t& total) {
-  uint32_t inc = v;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// Sums of M values over the NT threads of a block, to every thread; sm: M * NT / 64 words, not in use
+// again before the block has met once more.
+template <int NT, int M>
+__device__ __forceinline__ void block_sums(uint32_t (&v)[M], uint32_t* sm) {
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t n = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += n;
+  for (int m = 0; m < M; ++m) {
+    v[m] = wave_usum(v[m]);
+    if ((threadIdx.x & 63) == 0) sm[m * (NT / 64) + (threadIdx.x >> 6)] = v[m];
   }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    v[m] = 0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) v[m] += sm[m * (NT / 64) + i];
+  }
+}
+// One value; sm may be used again at once.
+template <int NT>
+__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* sm) {
+  uint32_t one[1] = {v};
+  block_sums<NT, 1>(one, sm);
+  __syncthreads();
+  return one[0];
+}
+
+// exclusive scan over the NT threads of a block; also returns the block total.  sm: NT / 64 words, not
+// in use again before the block has met once more.
+template <int NT>
+__device__ __forceinline__ uint32_t block_excl_scan_once(uint32_t v, uint32_t* sm, uint32_t& total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t inc = wave_uscan(v);
   if (lane == 63) sm[w] = inc;
   __syncthreads();
   uint32_t base = 0;
@@ -62,8 +95,14 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* sm, ui
     if (i < w) base += x;
     total += x;
   }
-  __syncthreads();
   return base + inc - v;
+}
+// sm may be used again at once.
+template <int NT>
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* sm, uint32_t& total) {
+  const uint32_t r = block_excl_scan_once<NT>(v, sm, total);
+  __syncthreads();
+  return r;
 }
 
 // All NT threads: walk a histogram of NB bins from the largest bin downwards until `need`
@@ -85,7 +124,7 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t need, ui
     s_bin = 0u;
     s_need = 0u;
   }
-  const uint32_t exc = block_excl_scan<NT>(mine, sm, total);
+  const uint32_t exc = block_excl_scan_once<NT>(mine, sm, total);   // a barrier behind the lines above
   if (exc < need && need <= exc + mine) {   // exactly one thread
     uint32_t cum = exc;
 #pragma unroll
@@ -102,18 +141,65 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t need, ui
   need_inside = s_need;
 }
 
-// One lane per distinct label of the wavefront: with long-tailed labels a frequent class would otherwise
-// bring thousands of atomics onto one word.
-__device__ __forceinline__ bool first_of_label(int64_t y, bool valid) {
-  bool lead = false;
-  unsigned long long todo = __ballot(valid);
-  while (todo) {   // wave-uniform loop over the distinct labels
-    const int src = __ffsll(todo) - 1;
-    const int64_t y0 = __shfl(y, src, 64);
-    lead = lead || (int)(threadIdx.x & 63) == src;
-    todo &= ~__ballot(valid && y == y0);
+// Marks the classes of a workgroup's labels, PER of them to a thread, in pos_bits; first[c]: no label in
+// front has marked class y[c], in this workgroup or another.  An LDS hash table of the bitmap's 64-bit
+// words gathers their bits, then one atomic sets those of a word: with long-tailed labels a frequent
+// class would bring thousands of atomics onto one word, with ids in the order of frequency a few lines
+// of memory those of all frequent classes.  (Before, a loop over the distinct labels of a wavefront,
+// one after the other: 2.5 us where all 64 differ.)  alone: no other workgroup marks.  pos_bits: 8-byte
+// aligned, whole 64-bit words.
+constexpr int kMarkSlots = 2048;   // more than labels in a workgroup; a quarter full, few look twice
+struct MarkLds {
+  unsigned long long bits[kMarkSlots];
+  int32_t key[kMarkSlots];         // word
+};
+template <int NT, int PER>
+__device__ __forceinline__ void mark_labels(const int64_t (&y)[PER], const bool (&valid)[PER], bool (&first)[PER],
+                                            MarkLds& lds, uint32_t* pos_bits, bool alone) {
+  static_assert(kMarkSlots >= 2 * NT * PER && kMarkSlots % NT == 0, "room for every label");
+  constexpr int OWN = kMarkSlots / NT;
+  unsigned long long* words = reinterpret_cast<unsigned long long*>(pos_bits);
+#pragma unroll
+  for (int s = 0; s < OWN; ++s) {
+    lds.key[s * NT + threadIdx.x] = -1;
+    lds.bits[s * NT + threadIdx.x] = 0u;
   }
-  return lead;
+  __syncthreads();
+  unsigned at[PER];
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    first[c] = false;
+    at[c] = 0u;
+    if (!valid[c]) continue;
+    const int32_t w = (int32_t)(y[c] >> 6);   // classes: below 2^31
+    unsigned slot = ((unsigned)w * 2654435761u) >> 8;
+    for (;;) {   // ends: there are more slots than labels
+      slot %= kMarkSlots;
+      const int32_t seen = atomicCAS(&lds.key[slot], -1, w);
+      if (seen == -1 || seen == w) break;
+      ++slot;
+    }
+    at[c] = slot;
+    const unsigned long long bit = 1ull << (y[c] & 63);
+    first[c] = !(atomicOr(&lds.bits[slot], bit) & bit);
+  }
+  __syncthreads();
+  unsigned long long old[OWN];
+#pragma unroll
+  for (int s = 0; s < OWN; ++s) {
+    const int32_t w = lds.key[s * NT + threadIdx.x];
+    old[s] = 0u;
+    if (w < 0) continue;
+    const unsigned long long bits = lds.bits[s * NT + threadIdx.x];
+    if (alone) words[w] = bits;
+    else old[s] = atomicOr(&words[w], bits);
+  }
+  if (alone) return;
+#pragma unroll
+  for (int s = 0; s < OWN; ++s) lds.bits[s * NT + threadIdx.x] = old[s];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < PER; ++c) first[c] = first[c] && !((lds.bits[at[c]] >> (y[c] & 63)) & 1u);
 }
 
 // The radix selection (pfc_sample_radix.hip); k is left in sc.st->k.

@@ -11,13 +11,14 @@ namespace pfc {
 constexpr int kWindowBins = 1024;      // histogram of the window (LDS)
 constexpr int kLocalList = 4096;       // classes of one workgroup that may lie in the window
 constexpr int kBinList = 256;          // classes that may share the bin in which the selection ends
+constexpr int kListParts = 8;          // parts of the list of the window
 constexpr int kMinClsLog2 = 10, kMaxClsLog2 = 15;   // classes per workgroup: 2^10 .. 2^15
 constexpr int kMaxBlocks = 640;        // workgroups, as long as 2^15 classes each suffice for that
                                        // (up to 20,971,520 classes; beyond, one per 2^15 classes)
 constexpr int64_t kWindowBatch = 1 << 16;     // largest batch of the window selection
 constexpr int64_t kMissClasses = 10 * 1024;   // classes up to which a missed window costs little
 
-// Classes per workgroup (log2): few enough workgroups that the parts every one of them repeats
+// Classes per workgroup of sample_scan (log2): few enough workgroups that the parts every one of them repeats
 // (the list, the counts, the labels) stay small, enough of them to use the GPU (up to 2.5 per
 // compute unit).
 inline int sample_cls_log2(int64_t N) {
@@ -30,6 +31,18 @@ inline int64_t sample_blocks(int64_t N) {
   const int l = sample_cls_log2(N);
   return (N + ((int64_t)1 << l) - 1) >> l;
 }
+
+// Of sample_write: no more workgroups than the compute units hold at a time (two each), because each
+// goes through the whole list (10 million classes: 611 workgroups, which are two rounds, 35 us, 306 of
+// twice the classes 24; the scores, which are work, stay with 611: 20 us there).
+inline int sample_write_log2(int64_t N) {
+  const int l = sample_cls_log2(N);
+  return l < kMaxClsLog2 && sample_blocks(N) > 512 ? l + 1 : l;
+}
+
+// Parts of the list of the window, one count each: the workgroups of sample_scan queue up on a count
+// (503 on one count: 5 us of a launch of 11).  Few workgroups would fill the parts unevenly.
+inline int list_parts(int scan_blocks) { return scan_blocks >= 64 ? kListParts : 1; }
 
 // Half width of the window in classes at rank n q of N (two thirds of it are never used up).
 inline double window_margin(double n, double q) { return 6.5 * sqrt(n * q * (1.0 - q)) + 40.0; }

@@ -104,17 +104,17 @@ __global__ __launch_bounds__(kThreads) void sample_hist_kernel(
       const int64_t y = i < B ? labels[i] : 0;
       const bool valid = i < B && y >= 0 && y < N;
       if (i < B && !valid) atomicOr(err_flag, 1);
-      bool first = false;
-      if (first_of_label(y, valid)) {
-        const uint32_t bit = 1u << (y & 31);
-        first = !(atomicOr(&pos_bits[y >> 5], bit) & bit);
-        if (first) {   // first to mark class y
-          uint32_t u[4];
-          philox_block((uint32_t)(y >> 2), key, u);
-          atomicSub(&sc.hist[u[y & 3] >> kShift], 1u);
-        }
+      __shared__ MarkLds marks;
+      const int64_t ys[1] = {y};
+      const bool valids[1] = {valid};
+      bool first[1];
+      mark_labels<kThreads, 1>(ys, valids, first, marks, pos_bits, false);
+      if (first[0]) {   // first to mark class y
+        uint32_t u[4];
+        philox_block((uint32_t)(y >> 2), key, u);
+        atomicSub(&sc.hist[u[y & 3] >> kShift], 1u);
       }
-      const uint32_t nf = __popcll(__ballot(first));
+      const uint32_t nf = __popcll(__ballot(first[0]));
       if (nf && (threadIdx.x & 63) == 0) atomicAdd(&sc.st->radix.U, nf);
       return;
     }
