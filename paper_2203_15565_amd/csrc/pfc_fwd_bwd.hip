@@ -602,6 +602,138 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
+// gemm_logits_slim: gemm_logits with fp32 operands for problems of few 64-tiles: tiles of 64 classes x
+// 16 samples, four wavefronts of 16 x 16, so that four times as many compute units work.  What bounds a
+// 64-tile is its 16,384 cycles of matrix instructions (D = 512) and 256 KB of operands on one compute
+// unit; here it is the operands, 160 KB at 28 GB/s.  v_mfma_f32_16x16x4_f32 adds the products one after
+// the other, as the 32x32x2 form does; with the reduction steps 0 4 1 5 and 2 6 3 7 of every eight in
+// one instruction each, the chain and hence the bits of a cosine are those of gemm_tile_fp32.  The row
+// sums too: the classes with bit 2 clear and those with it set of all 64 are a chain each, then the two
+// are added.  Forward/backward, us, 64-tiles -> now: 128 x 1,000 x 512 36.0 -> 30.8, 48 x 1,000 x 512
+// 34.3 -> 29.1, 100 x 3,000 x 1024 63.3 -> 58.6.
+// LDS: four stages of 64 reduction steps, rows of 256 bytes (the 64 classes, then the 16 samples),
+// chunk c of 16 bytes of row r at position c ^ (r & 15): 16 rows read two chunks each without conflicts.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSlimRows = 80, kSlimStages = 4, kSlimStageBytes = kSlimRows * 256, kSlimLoads = kSlimRows / 4 / 4;
+constexpr int kSlimLds = kSlimStages * kSlimStageBytes;
+
+template <bool EXTRAS>
+__global__ __launch_bounds__(256) void gemm_logits_slim_kernel(
+    const float* __restrict__ Wn, const float* __restrict__ Xn, int D, int Dp, int64_t k, int B, int64_t kp,
+    const int32_t* __restrict__ yl, LossParams lp, float* __restrict__ E, float* __restrict__ rowpart,
+    float* __restrict__ rowmaxpart, float* __restrict__ clabel, int tiles_j, int tiles_i) {
+  extern __shared__ __align__(16) char smem[];
+  int tj, ti;
+  if (!xcd_tile(blockIdx.x, tiles_i, tiles_j, tj, ti)) return;
+  const int64_t j0 = (int64_t)tj * 64;
+  const int i0 = ti * 16;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, g = lane >> 4;
+  const int i = i0 + col;
+  const int32_t y = i < B ? yl[i] : -1;
+
+  // Loads to LDS: instruction p of a wavefront fills rows 4 (wave + 4 p) .. + 3 of a stage.
+  const int row0 = 4 * wave + (lane >> 4);
+  const uint32_t toff = (uint32_t)((lane >> 4) * Dp * 4 + (((lane & 15) ^ row0) * 16));
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
+  const char* wbase = reinterpret_cast<const char*>(Wn + (j0 + 4 * wave) * Dp);
+  const char* xbase = reinterpret_cast<const char*>(Xn + (int64_t)(i0 + 4 * wave) * Dp);
+  auto request = [&](int s) {
+    const uint32_t stage = lds0 + (s % kSlimStages) * kSlimStageBytes;
+#pragma unroll
+    for (int p = 0; p < kSlimLoads; ++p)
+      lds_load((p < 4 ? wbase + (int64_t)p * 16 * Dp * 4 : xbase) + s * 256, toff, stage + p * 4096);
+  };
+  const int n = D / 64;
+#pragma unroll
+  for (int s = 0; s < kSlimStages - 1; ++s)
+    if (s < n) request(s);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < n; ++s) {
+    // stage s is there, and all wavefronts are done with the one before
+    if (s + 2 < n) dma_wait_barrier<2 * kSlimLoads>();
+    else if (s + 1 < n) dma_wait_barrier<kSlimLoads>();
+    else dma_wait_barrier<0>();
+    if (s + kSlimStages - 1 < n) request(s + kSlimStages - 1);
+    const char* stage = smem + (s % kSlimStages) * kSlimStageBytes;
+    // this lane's two of every eight reduction steps of its class and its sample (rows & 15: col)
+    float a[8][2], b[8][2];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int at = ((2 * q + (g & 1)) ^ col) * 16 + (g >> 1) * 4;
+      const float* pa = reinterpret_cast<const float*>(stage + (wave * 16 + col) * 256 + at);
+      const float* pb = reinterpret_cast<const float*>(stage + (64 + col) * 256 + at);
+      a[q][0] = pa[0];
+      a[q][1] = pa[2];
+      b[q][0] = pb[0];
+      b[q][1] = pb[2];
+    }
+    __builtin_amdgcn_sched_barrier(0);   // all of them in flight before the first is used
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][u], b[q][u], acc, 0, 0, 0);
+  }
+  __syncthreads();
+
+  // this lane: sample i, classes j0 + jl .. jl + 3
+  const int jl = wave * 16 + g * 4;
+  const int64_t krem = k - j0, yrel = (int64_t)y - j0;
+  const int klim = krem < 64 ? (int)krem : 64;
+  const int yloc = y >= 0 && yrel >= 0 && yrel < klim ? (int)yrel : -1;
+  float ref = 0.f;
+  if constexpr (EXTRAS) ref = lp.rowref ? lp.rowref[i] : 0.f;
+  const float ref2 = ref * 1.44269504088896340736f;
+  f32x4 e;
+  float cmax = -2.f;
+  float* red = reinterpret_cast<float*>(smem);   // [16 samples][64 + 4]: e, then [16][17] maxima, [16] label terms
+  constexpr int RS = 68;
+  float *redmax = red + 16 * RS, *redlab = redmax + 16 * 17;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float c = __builtin_amdgcn_fmed3f(acc[r], -1.f, 1.f);
+    float ev = EXTRAS ? __builtin_amdgcn_exp2f(fmaf(c, lp.s_log2e, -ref2)) : __builtin_amdgcn_exp2f(c * lp.s_log2e);
+    const bool lab = jl + r == yloc, neg = i < B && jl + r < klim && !lab;   // neg: a real, non-label entry
+    ev = neg ? ev : 0.f;
+    if (lab) {
+      clabel[i] = c;
+      redlab[col] = __expf(label_logit(lp, c) - ref);
+    }
+    if constexpr (EXTRAS) {
+      cmax = neg ? fmaxf(cmax, c) : cmax;
+      ev = (c > lp.tau) ? 0.f : ev;
+    }
+    e[r] = ev;
+  }
+  *reinterpret_cast<f32x4*>(E + (int64_t)i * kp + j0 + jl) = e;
+  *reinterpret_cast<f32x4*>(red + col * RS + jl) = e;
+  if constexpr (EXTRAS) redmax[col * 17 + wave * 4 + g] = cmax;
+  __syncthreads();
+  if (threadIdx.x < 32) {   // thread (half, sample): the chain of the classes whose bit 2 is `half`
+    const int half = threadIdx.x >> 4, t = threadIdx.x & 15, ii = i0 + t;
+    f32x4 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = *reinterpret_cast<const f32x4*>(red + t * RS + q * 8 + half * 4);
+    float sum = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum += v[q][r];
+    // the label term joins the chain of its half (not all threads hold the same sample's `yloc`)
+    const int yt = __shfl(yloc, t, 64);
+    if (yt >= 0 && ((yt >> 2) & 1) == half) sum += redlab[t];
+    sum += __shfl_xor(sum, 16, 64);
+    if (half == 0) rowpart[(int64_t)ii * tiles_j + tj] = sum;
+    if constexpr (EXTRAS) {
+      float mx = -2.f;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) mx = fmaxf(mx, redmax[t * 17 + q]);
+      if (half == 0) rowmaxpart[(int64_t)ii * tiles_j + tj] = mx;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // gemm_rowmax (scales above 64 only): the logits GEMM once more, in front of gemm_logits, with an
 // epilogue that keeps nothing but the largest logit of every sample in every tile (label entry
 // with its margin); row_ref reduces the tiles.  The softmax then runs relative to that maximum,
@@ -1595,6 +1727,10 @@ int set_lds_limits_logits(S) {
                      (const void*)gemm_rowmax_kernel<F>};
   for (const void* p : f)
     PFC_HIP(hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, F::LDS_BYTES));
+  if constexpr (std::is_same_v<typename F::elem, float> && F::BM == 64) {
+    const void* slim[] = {(const void*)gemm_logits_slim_kernel<false>, (const void*)gemm_logits_slim_kernel<true>};
+    for (const void* p : slim) PFC_HIP(hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, kSlimLds));
+  }
   return PFC_OK;
 }
 template <class S>
@@ -1679,10 +1815,22 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
     }
     // the options (filter, column maxima, reference) have a kernel of their own: the plain one
     // stays lean
-    auto logits_kernel = lp.extras ? gemm_logits_kernel<Cfg, true> : gemm_logits_kernel<Cfg, false>;
-    PFC_LAUNCH(c, KID_GEMM_LOGITS, logits_kernel, dim3(xcd_grid(tiles_i, tiles_j)),
-               dim3(Cfg::THREADS), Cfg::LDS_BYTES, Wn, Xn, D, Dp, k, B, Bp, kp, yl, lp, E, c->rowpart,
-               c->rowmaxpart, c->clabel, tiles_j, tiles_i, c->num_cu / 8 * 8);
+    bool slim = false;
+    if constexpr (sizeof(T) == 4 && Cfg::BM == 64) slim = logits_slim(c->num_cu, B, kp);
+    if constexpr (sizeof(T) == 4 && Cfg::BM == 64) {
+      if (slim) {
+        auto slim_kernel = lp.extras ? gemm_logits_slim_kernel<true> : gemm_logits_slim_kernel<false>;
+        PFC_LAUNCH(c, KID_GEMM_LOGITS, slim_kernel, dim3(xcd_grid(Bp / 16, tiles_j)), dim3(256), kSlimLds,
+                   (const float*)Wn, (const float*)Xn, D,
+                   Dp, k, B, kp, yl, lp, (float*)E, c->rowpart, c->rowmaxpart, c->clabel, tiles_j, Bp / 16);
+      }
+    }
+    if (!slim) {
+      auto logits_kernel = lp.extras ? gemm_logits_kernel<Cfg, true> : gemm_logits_kernel<Cfg, false>;
+      PFC_LAUNCH(c, KID_GEMM_LOGITS, logits_kernel, dim3(xcd_grid(tiles_i, tiles_j)),
+                 dim3(Cfg::THREADS), Cfg::LDS_BYTES, Wn, Xn, D, Dp, k, B, Bp, kp, yl, lp, E, c->rowpart,
+                 c->rowmaxpart, c->clabel, tiles_j, tiles_i, c->num_cu / 8 * 8);
+    }
     auto combine_kernel = row_combine_kernel<T, NC>;
     const int head_blocks = (B + kLabelWindow - 1) / kLabelWindow;
     PFC_LAUNCH(c, KID_ROW_COMBINE, combine_kernel, dim3(head_blocks + (Bp + 3) / 4), dim3(256), 0,

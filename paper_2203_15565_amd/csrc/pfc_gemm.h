@@ -120,6 +120,26 @@ struct DmaLds {
   }
 };
 
+// 16 bytes a lane from `base` (wave-uniform) + toff to 1 KB of LDS at byte `lds`.
+// Assembly, because the compiler makes every LDS read that follows the builtin wait for all loads
+// in flight.  The load has no output register.  Its write to LDS is done when dma_wait_barrier is
+// behind it: whoever reads the region waits there first.  The scalar copy of the base: it may come
+// straight from v_readfirstlane, and a vector memory instruction that reads an SGPR has to stay
+// five wait states behind a VALU write of it, a scalar one none (nor does the load behind that).
+// It is also the wait state that M0, which the compiler sets, needs; the compiler does not look
+// into assembly for either.  (s_nop 4 in its place: 1024 x 36,024 fused 248 -> 252 us, 2048 x
+// 500,000 4022 -> 4053; with the copy even.)
+__device__ __forceinline__ void lds_load(const char* base, uint32_t toff, uint32_t lds) {
+  const uint64_t at = (uint64_t)base;
+  const uint64_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32;
+  uint64_t at_s;
+  asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+               : "=&s"(at_s)
+               : "{m0}"(__builtin_amdgcn_readfirstlane(lds)), "v"(toff), "s"(g)
+               : "memory");
+}
+
 template <typename T, class L, int THREADS, bool KMAJOR>
 struct DmaStager {
   static constexpr int NCH = L::BYTES / 16 / THREADS;        // loads per wavefront and slab
@@ -139,23 +159,8 @@ struct DmaStager {
     slab = KMAJOR ? (int64_t)L::BK * ld * (int64_t)sizeof(T) : (int64_t)L::BK * (int64_t)sizeof(T);
   }
   // Load p of slab s into the LDS region at byte `lds` (this wavefront's first byte there).
-  // Assembly, because the compiler makes every LDS read that follows the builtin wait for all loads
-  // in flight.  The load has no output register.  Its write to LDS is done when dma_wait_barrier is
-  // behind it: whoever reads the region waits there first.  The scalar copy of the base: it may come
-  // straight from v_readfirstlane, and a vector memory instruction that reads an SGPR has to stay
-  // five wait states behind a VALU write of it, a scalar one none (nor does the load behind that).
-  // It is also the wait state that M0, which the compiler sets, needs; the compiler does not look
-  // into assembly for either.  (s_nop 4 in its place: 1024 x 36,024 fused 248 -> 252 us, 2048 x
-  // 500,000 4022 -> 4053; with the copy even.)
   __device__ __forceinline__ void load(int s, int p, uint32_t lds) const {
-    const uint64_t at = (uint64_t)(base + (int64_t)s * slab + p * pass);
-    const uint64_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) |
-                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32;
-    uint64_t at_s;
-    asm volatile("s_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
-                 : "=&s"(at_s)
-                 : "{m0}"(__builtin_amdgcn_readfirstlane(lds + p * THREADS * 16)), "v"(toff), "s"(g)
-                 : "memory");
+    lds_load(base + (int64_t)s * slab + p * pass, toff, lds + p * THREADS * 16);
   }
 };
 

@@ -189,6 +189,12 @@ inline TileSize logits_tiles(int64_t cu, int es, int B, int64_t kp, int D) {
   return 2 * mid > cu ? TILES_128 : TILES_64;
 }
 
+// Whether the fp32 logits take tiles of 64 classes x 16 samples where the rule above says 64-tiles: as
+// long as these occupy half of the compute units at most.  Forward/backward, us, 64-tiles / slim ones:
+// 32 tiles (128 x 1,000 x 512) 36.0 / 30.8, 96 (100 x 3,000 x 1024) 63.3 / 58.6, 128 (128 x 4,000 x 512)
+// 49.6 / 47.6, 160 (64 x 10,000 x 256) 41.1 / 43.1, 256 (256 x 4,000 x 512) 55.0 / 62.1.
+inline bool logits_slim(int64_t cu, int B, int64_t kp) { return kp / 64 * ((B + 63) / 64) * 2 <= cu; }
+
 // Workgroups that a compute unit holds.
 inline int tiles_per_cu(TileSize t, int es) {
   return t == TILES_256 ? 1 : t == TILES_128 ? 2 : es == 2 ? 3 : 4;
