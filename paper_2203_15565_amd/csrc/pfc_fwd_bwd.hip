@@ -333,8 +333,8 @@ __global__ __launch_bounds__(kNormWaves * 64) void gather_normalize_kernel(
 // gemm_logits: tile of c[j][i] (rows = sampled classes, columns = samples), fused epilogue:
 // clamp, margin on the label entry, e = exp(s*c), per-tile column sums, and E[i][j] = e (label
 // entry and padding stored as zero).  A lane holds one sample i and runs of 4 consecutive
-// classes j, so the sums over j are in-lane; the bf16 tile is transposed through LDS so that E
-// is written in whole 512-byte rows.
+// classes j, so the sums over j are in-lane; in bf16 E lies in octets of classes (OctetLds), which
+// a wavefront writes straight from its registers, 512 bytes in one piece.
 //
 // The element-wise part exists in four versions.  GUARDED: the wavefront's part of the tile holds
 // a label entry or padding (few wavefronts do); the plain version costs 5 VALU instructions per
@@ -367,11 +367,11 @@ constexpr bool logits_chained() { return Cfg::BM == 64; }
 template <class Cfg, bool GUARDED, bool EXTRAS>
 __device__ __forceinline__ void logits_epilogue_columns(
     const f32x16 (&acc)[Cfg::TM][Cfg::TN], int64_t j0, int i0, int B, int klim, int64_t kp,
-    const int (&ylane)[Cfg::TN], const LossParams& lp, char* smem, int SX,
+    int Bp, const int (&ylane)[Cfg::TN], const LossParams& lp,
     typename Cfg::elem* __restrict__ E, float* __restrict__ clabel, float (&colsum)[Cfg::TN],
     float (&collab)[Cfg::TN], float (&colmax)[Cfg::TN]) {
   using T = typename Cfg::elem;
-  constexpr bool kStage = (sizeof(T) == 2), kChain = logits_chained<Cfg>();
+  constexpr bool kOctets = sizeof(T) == 2, kChain = logits_chained<Cfg>();
 #pragma unroll
   for (int bn = 0; bn < Cfg::TN; ++bn) {
     const int il = acc_col<Cfg>(bn);
@@ -384,6 +384,7 @@ __device__ __forceinline__ void logits_epilogue_columns(
     const float ref2 = ref * 1.44269504088896340736f;
 #pragma unroll
     for (int bm = 0; bm < Cfg::TM; ++bm) {
+      uint32_t w[4][2];
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         T pack[4];
@@ -410,14 +411,25 @@ __device__ __forceinline__ void logits_epilogue_columns(
           sum += ev;
           pack[e] = from_float<T>(ev);
         }
-        if constexpr (kStage) {
-          uint2 pk;
-          __builtin_memcpy(&pk, pack, 8);
-          *reinterpret_cast<uint2*>(smem + il * SX + jl * 2) = pk;
+        if constexpr (kOctets) {
+          __builtin_memcpy(w[g4], pack, 8);
         } else {
           uint4 pk;
           __builtin_memcpy(&pk, pack, 16);
           *reinterpret_cast<uint4*>(E + (int64_t)i * kp + j0 + jl) = pk;
+        }
+      }
+      if constexpr (kOctets) {
+        // The lane halves hold classes 0..3 and 4..7 of every eight: exchanged, a lane has an octet, the
+        // second half of the wavefront the next one.
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const auto lo = __builtin_amdgcn_permlane32_swap(w[2 * h][0], w[2 * h + 1][0], false, false);
+          const auto hi = __builtin_amdgcn_permlane32_swap(w[2 * h][1], w[2 * h + 1][1], false, false);
+          const int64_t octet = ((j0 + acc_row<Cfg>(bm, 0)) >> 3) + 2 * h + ((threadIdx.x >> 5) & 1);
+          // E is far larger than the L2 and next read by another kernel: store it nontemporally
+          __builtin_nontemporal_store(u32x4{lo[0], hi[0], lo[1], hi[1]},
+                                      reinterpret_cast<u32x4*>(E + (octet * Bp + i) * 8));
         }
       }
     }
@@ -487,10 +499,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  constexpr bool kStage = (sizeof(T) == 2);          // bf16: transpose the tile through LDS
-  constexpr int SX = Cfg::BM * 2 + 8;                // staging row (one sample) stride in bytes
-  constexpr int RED_OFF = kStage ? Cfg::BN * SX : 0; // cross-wave reduction scratch behind it
-  static_assert(RED_OFF + 2 * Cfg::WM * Cfg::BN * 4 <= Cfg::LDS_BYTES, "epilogue LDS");
+  static_assert(2 * Cfg::WM * Cfg::BN * 4 <= Cfg::LDS_BYTES, "epilogue LDS");
   static_assert(!logits_chained<Cfg>() || 2 * Cfg::BN * 2 <= 2 * Cfg::WM * Cfg::BN, "chain LDS");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t krem = k - j0;
@@ -515,16 +524,16 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   }
   const bool guarded = __any(any_label) || klim < Cfg::BM || i0 + Cfg::BN > B;   // wave-uniform
 
-  float* red = reinterpret_cast<float*>(smem + RED_OFF);   // [WM][BN] sums, then [WM][BN] maxima
+  float* red = reinterpret_cast<float*>(smem);   // [WM][BN] sums, then [WM][BN] maxima
   float colsum[Cfg::TN], collab[Cfg::TN], colmax[Cfg::TN];
 #pragma unroll
   for (int bn = 0; bn < Cfg::TN; ++bn) colmax[bn] = -2.f;
   auto epilogue = [&]() {
     if (guarded)
-      logits_epilogue_columns<Cfg, true, EXTRAS>(acc, j0, i0, B, klim, kp, ylane, lp, smem, SX, E,
+      logits_epilogue_columns<Cfg, true, EXTRAS>(acc, j0, i0, B, klim, kp, Bp, ylane, lp, E,
                                                  clabel, colsum, collab, colmax);
     else
-      logits_epilogue_columns<Cfg, false, EXTRAS>(acc, j0, i0, B, klim, kp, ylane, lp, smem, SX, E,
+      logits_epilogue_columns<Cfg, false, EXTRAS>(acc, j0, i0, B, klim, kp, Bp, ylane, lp, E,
                                                   clabel, colsum, collab, colmax);
   };
   if constexpr (logits_chained<Cfg>()) {
@@ -582,20 +591,6 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
     }
     rowpart[(int64_t)(i0 + t) * tiles_j + tj] = v;
     if constexpr (EXTRAS) rowmaxpart[(int64_t)(i0 + t) * tiles_j + tj] = mx;
-  }
-  if constexpr (kStage) {
-    // whole rows of the tile (BM * 2 bytes, 8 per lane) leave in one piece
-    constexpr int LPR = Cfg::BM / 4;        // lanes per tile row
-    constexpr int RPW = 64 / LPR;           // tile rows per wavefront instruction
-    static_assert(LPR <= 64 && 64 % LPR == 0, "row write-out: 4 classes per lane");
-    const int sub = lane / LPR, l = lane % LPR;
-    for (int row = wave * RPW + sub; row < Cfg::BN; row += (Cfg::THREADS / 64) * RPW) {
-      const uint2 v = *reinterpret_cast<const uint2*>(smem + row * SX + l * 8);
-      // E is far larger than the L2 and next read by another kernel: store it nontemporally
-      // (measured: 0.320 -> 0.302 ms for this kernel at the headline workload)
-      __builtin_nontemporal_store(__builtin_bit_cast(u32x2, v),
-                                  reinterpret_cast<u32x2*>(E + (int64_t)(i0 + row) * kp + j0 + l * 4));
-    }
   }
   PFC_PHASE(1, 3);
   asm volatile("" ::"v"(touched));
@@ -949,6 +944,15 @@ constexpr int kDxSumSteps = 256, kDwSumSteps = 512;
 template <class Cfg, int STEPS, bool PIECES>
 constexpr int sum_slabs() { return PIECES ? STEPS / Cfg::BK : 0; }
 
+// E from entry (sample i, class j) on, as an operand of a backward product: rows of kp, or octets.
+template <class Cfg>
+__device__ __forceinline__ const typename Cfg::elem* e_tile(const typename Cfg::elem* E, int64_t i, int64_t j, int Bp,
+                                                            int64_t kp) {
+  return Cfg::A_OCTETS ? E + j * Bp + i * 8 : E + i * kp + j;
+}
+template <class Cfg>
+__device__ __forceinline__ int64_t e_ld(int Bp, int64_t kp) { return Cfg::A_OCTETS ? Bp : kp; }
+
 template <class Cfg, bool PIECES>
 __device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
                                                const typename Cfg::elem* __restrict__ E,
@@ -965,7 +969,7 @@ __device__ __forceinline__ void dfeatures_tile(int wg, char* smem,
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
   const int64_t koff = (int64_t)slab0 * Cfg::BK;
-  gemm_tile<Cfg, sum_slabs<Cfg, kDxSumSteps, PIECES>()>(E + (int64_t)i0 * kp + koff, kp,
+  gemm_tile<Cfg, sum_slabs<Cfg, kDxSumSteps, PIECES>()>(e_tile<Cfg>(E, i0, koff, Bp, kp), e_ld<Cfg>(Bp, kp),
                                                         Wn + koff * D + d0, D, ns, smem, acc);
   float* out = part + (int64_t)sp * Bp * D;
 #pragma unroll
@@ -1009,8 +1013,8 @@ __device__ __forceinline__ void dweight_tile(
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
   PFC_PHASE(2, 0);
-  gemm_tile<Cfg, sum_slabs<Cfg, kDwSumSteps, PIECES>()>(E + i0 * kp + j0, kp, Xs + i0 * Dp + d0, Dp, ns,
-                                                        smem, acc);
+  gemm_tile<Cfg, sum_slabs<Cfg, kDwSumSteps, PIECES>()>(e_tile<Cfg>(E, i0, j0, Bp, kp), e_ld<Cfg>(Bp, kp),
+                                                        Xs + i0 * Dp + d0, Dp, ns, smem, acc);
   PFC_PHASE(2, 1);
   float* dst = SPLIT ? out + (int64_t)sp * kp * Dp : out;
   const int ld = SPLIT ? Dp : D;
@@ -1419,7 +1423,7 @@ __device__ __forceinline__ void fused_update_tile(
   f32x16 acc[Cfg::TM][Cfg::TN];
   zero_acc<Cfg>(acc);
   PFC_PHASE(3, 0);
-  gemm_tile<Cfg>(E + j0, kp, Xs, D, Bp / Cfg::BK, smem, acc);
+  gemm_tile<Cfg>(e_tile<Cfg>(E, 0, j0, Bp, kp), e_ld<Cfg>(Bp, kp), Xs, D, Bp / Cfg::BK, smem, acc);
   PFC_PHASE(3, 1);
 
   // A window of WIN rows of W and v is kept in flight: the loads of row n+WIN

@@ -56,6 +56,7 @@ struct TileCfg {
   static constexpr int WTM = BM / WM, WTN = BN / WN;       // tile of one wavefront
   static constexpr int TM = WTM / 32, TN = WTN / 32;       // 32x32 blocks per wavefront
   static constexpr bool DMA = sizeof(T) == 2;
+  static constexpr bool A_OCTETS = DMA && BKM;   // A is E in both backward products
   static constexpr bool SPLIT = !DMA && (AKM || BKM);   // fp32: all but the logits (both k contiguous)
   static constexpr int LDS_BYTES = DMA     ? (ABUF * BM + BBUF * BN) * SLAB
                                    : SPLIT ? 2 * 3 * 32 * (BM + BN)
@@ -140,23 +141,55 @@ __device__ __forceinline__ void lds_load(const char* base, uint32_t toff, uint32
                : "memory");
 }
 
-template <typename T, class L, int THREADS, bool KMAJOR>
+// E (bf16) lies in octets of classes: entry (sample i, class j) at (j / 8 * Bp + i) * 8 + j % 8, Bp
+// samples to a panel.  What a wavefront of the logits holds is 8 classes of 32 samples each, 512 bytes
+// that go out in one piece without a way through LDS (gemm_logits).  An operand slab of it is cut
+// into panels likewise, each a run of 16-byte entries (fragment reads and loads touch whole lines):
+//   k contiguous (dfeatures): the BK / 8 octets of the slab, each R samples;
+//   k-major (dweight): the octets of the slab's R classes, each BK samples; sample k of panel o lies at
+//                      position k ^ (o % 4 * 4), so that a transpose read finds the four panels and the
+//                      four samples of every 32 lanes in different banks.
+// Against rows of classes, written through LDS (us): logits 1024 x 205,991 x 512 280 -> 260, 1024 x
+// 360,232 494 -> 463, 1024 x 36,024 55.8 -> 50.8, 16,384 x 3,592 104 -> 95; both backward products
+// 413 -> 409, 715 -> 684, fused 1024 x 36,024 133.9 -> 131.2, 16,384 x 3,592 115 -> 117.  (Reading
+// dfeatures' slabs into LDS rows of 8 octets, a line for 8 samples from each of 8 panels in one
+// load: both products of 512 x 9,344 20.4 -> 22.9.)
+template <typename T, int R, bool KMAJOR, int SLAB>
+struct OctetLds {
+  static constexpr int BK = SLAB / (int)sizeof(T), SAMPLES = KMAJOR ? BK : R, PANEL = SAMPLES * 16;
+  static constexpr int BYTES = (KMAJOR ? R : BK) / 8 * PANEL;
+  static_assert(BK % 16 == 0 && R % 32 == 0, "order of the samples");
+  static __device__ __forceinline__ int turn(int o) { return KMAJOR ? (o & 3) * 4 : 0; }
+};
+
+template <typename T, class L, int THREADS, bool KMAJOR, bool OCTETS>
 struct DmaStager {
   static constexpr int NCH = L::BYTES / 16 / THREADS;        // loads per wavefront and slab
-  static constexpr int RPP = THREADS * 16 / L::ROW_BYTES;    // LDS rows that one load of every wavefront fills
   static_assert(NCH >= 1 && L::BYTES % (THREADS * 16) == 0, "slab must divide evenly");
-  static_assert(RPP % (KMAJOR ? 4 : 16) == 0, "one order of the chunks for all loads of a lane");
   const char* base;   // wave-uniform: first byte of the operand tile at the first k of the range
   uint32_t toff;      // this lane's byte offset from there
   int64_t pass, slab; // global byte steps between a lane's loads of one slab / between slabs (uniform)
 
+  // ld: elements from row to row; OCTETS: samples to a panel
   __device__ __forceinline__ void init(const T* tile, int64_t ld) {
     const int t = threadIdx.x;
-    const int row = t / L::CPR, ch = (t % L::CPR) ^ L::turn(row);
     base = reinterpret_cast<const char*>(tile);
-    toff = (uint32_t)((int64_t)row * ld * (int64_t)sizeof(T) + ch * 16);
-    pass = (int64_t)RPP * ld * (int64_t)sizeof(T);
-    slab = KMAJOR ? (int64_t)L::BK * ld * (int64_t)sizeof(T) : (int64_t)L::BK * (int64_t)sizeof(T);
+    if constexpr (OCTETS) {
+      constexpr int PPP = THREADS / L::SAMPLES;   // panels that one load of every wavefront fills
+      static_assert(PPP >= 1 && THREADS % L::SAMPLES == 0 && (!KMAJOR || PPP % 4 == 0),
+                    "one order of the samples for all loads of a lane");
+      const int o = t / L::SAMPLES, k = (t % L::SAMPLES) ^ L::turn(o);
+      toff = (uint32_t)(((int64_t)o * ld + k) * 16);
+      pass = PPP * ld * 16;
+      slab = KMAJOR ? (int64_t)L::BK * 16 : L::BK / 8 * ld * 16;
+    } else {
+      constexpr int RPP = THREADS * 16 / L::ROW_BYTES;    // LDS rows that one load of every wavefront fills
+      static_assert(RPP % (KMAJOR ? 4 : 16) == 0, "one order of the chunks for all loads of a lane");
+      const int row = t / L::CPR, ch = (t % L::CPR) ^ L::turn(row);
+      toff = (uint32_t)((int64_t)row * ld * (int64_t)sizeof(T) + ch * 16);
+      pass = (int64_t)RPP * ld * (int64_t)sizeof(T);
+      slab = KMAJOR ? (int64_t)L::BK * ld * (int64_t)sizeof(T) : (int64_t)L::BK * (int64_t)sizeof(T);
+    }
   }
   // Load p of slab s into the LDS region at byte `lds` (this wavefront's first byte there).
   __device__ __forceinline__ void load(int s, int p, uint32_t lds) const {
@@ -173,10 +206,10 @@ __device__ __forceinline__ void dma_wait_barrier() {
 }
 
 // Byte offsets of this lane's fragment reads in an operand slab.
-template <class L, bool KMAJOR, int GROUPS, int NB>
+template <class L, bool KMAJOR, bool OCTETS, int GROUPS, int NB>
 struct FragAddr;
 template <class L, int GROUPS, int NB>
-struct FragAddr<L, false, GROUPS, NB> {
+struct FragAddr<L, false, false, GROUPS, NB> {
   uint32_t a[GROUPS];   // of each reduction group; blocks of 32 rows follow at constant distances
   __device__ __forceinline__ void init(int r0) {
     const int lane = threadIdx.x & 63, row = r0 + (lane & 31);
@@ -188,7 +221,7 @@ struct FragAddr<L, false, GROUPS, NB> {
   }
 };
 template <class L, int GROUPS, int NB>
-struct FragAddr<L, true, GROUPS, NB> {
+struct FragAddr<L, true, false, GROUPS, NB> {
   uint32_t a[NB];       // of each block of 32 rows; groups follow at constant distances
   __device__ __forceinline__ void init(int r0) {
     // ds_read_b64_tr_b16: inside each group of 16 lanes, lane s addresses the 4 consecutive tile
@@ -208,6 +241,39 @@ struct FragAddr<L, true, GROUPS, NB> {
     // (four k-rows further the order of the chunks is the same)
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * L::ROW_BYTES));
+    const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+    u32x4 r;
+    r[0] = l2[0]; r[1] = l2[1]; r[2] = h2[0]; r[3] = h2[1];
+    return r;
+  }
+};
+
+template <class L, int GROUPS, int NB>
+struct FragAddr<L, false, true, GROUPS, NB> {
+  uint32_t a;   // groups and blocks of 32 rows follow at constant distances
+  __device__ __forceinline__ void init(int r0) {
+    const int lane = threadIdx.x & 63;
+    a = (lane >> 5) * L::PANEL + (r0 + (lane & 31)) * 16;
+  }
+  __device__ __forceinline__ u32x4 read(const char* region, int b, int g) const {
+    return *reinterpret_cast<const u32x4*>(region + a + g * 2 * L::PANEL + b * 512);
+  }
+};
+template <class L, int GROUPS, int NB>
+struct FragAddr<L, true, true, GROUPS, NB> {
+  uint32_t a[2];   // of the four steps of either read; groups and blocks of 32 rows follow at constant distances
+  __device__ __forceinline__ void init(int r0) {
+    // lanes as above
+    const int lane = threadIdx.x & 63, grp = lane >> 4, s = lane & 15;
+    const int k0 = (grp >> 1) * 8 + (s >> 2), r = r0 + (grp & 1) * 16 + (s & 3) * 4, o = r >> 3;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) a[u] = o * L::PANEL + ((k0 + 4 * u) ^ L::turn(o)) * 16 + (r & 4) * 2;
+  }
+  __device__ __forceinline__ u32x4 read(const char* region, int b, int g) const {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const char* p = region + b * 4 * L::PANEL + g * 256;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + a[0]));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + a[1]));
     const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
     u32x4 r;
     r[0] = l2[0]; r[1] = l2[1]; r[2] = h2[0]; r[3] = h2[1];
@@ -236,12 +302,13 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
                                               const typename Cfg::elem* __restrict__ B, int64_t ldb, int nslabs,
                                               char* smem, f32x16 (&acc)[Cfg::TM][Cfg::TN]) {
   using T = typename Cfg::elem;
-  typedef DmaLds<T, Cfg::BM, Cfg::A_KMAJOR, Cfg::SLAB_BYTES> LA;
+  typedef std::conditional_t<Cfg::A_OCTETS, OctetLds<T, Cfg::BM, Cfg::A_KMAJOR, Cfg::SLAB_BYTES>,
+                             DmaLds<T, Cfg::BM, Cfg::A_KMAJOR, Cfg::SLAB_BYTES>> LA;
   typedef DmaLds<T, Cfg::BN, Cfg::B_KMAJOR, Cfg::SLAB_BYTES> LB;
   constexpr int ABUF = Cfg::ABUF, BBUF = Cfg::BBUF;
   static_assert(ABUF == BBUF || ABUF == BBUF + 1, "the counts of loads in flight");
-  typedef DmaStager<T, LA, Cfg::THREADS, Cfg::A_KMAJOR> SA;
-  typedef DmaStager<T, LB, Cfg::THREADS, Cfg::B_KMAJOR> SB;
+  typedef DmaStager<T, LA, Cfg::THREADS, Cfg::A_KMAJOR, Cfg::A_OCTETS> SA;
+  typedef DmaStager<T, LB, Cfg::THREADS, Cfg::B_KMAJOR, false> SB;
   constexpr int NA = SA::NCH, NB = SB::NCH, MM = Cfg::TM * Cfg::TN, HEAD = Cfg::GROUPS - 1;
   // loads that may be in flight when slab s+1 (or slab 0) has to be there, nothing being left out
   // at the end
@@ -253,8 +320,8 @@ __device__ __forceinline__ void gemm_tile_dma(const typename Cfg::elem* __restri
   SB sb;
   sa.init(A, lda);
   sb.init(B, ldb);
-  FragAddr<LA, Cfg::A_KMAJOR, Cfg::GROUPS, Cfg::TM> ra;
-  FragAddr<LB, Cfg::B_KMAJOR, Cfg::GROUPS, Cfg::TN> rb;
+  FragAddr<LA, Cfg::A_KMAJOR, Cfg::A_OCTETS, Cfg::GROUPS, Cfg::TM> ra;
+  FragAddr<LB, Cfg::B_KMAJOR, false, Cfg::GROUPS, Cfg::TN> rb;
   ra.init(wm * Cfg::WTM);
   rb.init(wn * Cfg::WTN);
   constexpr uint32_t B0 = ABUF * LA::BYTES;   // the B buffers lie behind those of A
@@ -421,8 +488,8 @@ __device__ __forceinline__ void gemm_tile_split(const float* __restrict__ A, int
   constexpr int MM = Cfg::TM * Cfg::TN;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
-  FragAddr<LA, Cfg::A_KMAJOR, 1, Cfg::TM> ra;
-  FragAddr<LB, Cfg::B_KMAJOR, 1, Cfg::TN> rb;
+  FragAddr<LA, Cfg::A_KMAJOR, false, 1, Cfg::TM> ra;
+  FragAddr<LB, Cfg::B_KMAJOR, false, 1, Cfg::TN> rb;
   ra.init(wm * Cfg::WTM);
   rb.init(wn * Cfg::WTN);
   // this thread's chunks: those of A first
@@ -683,7 +750,7 @@ __device__ __forceinline__ void gemm_tile_fp32(const float* __restrict__ A, int6
 
 // Accumulate acc += A_tile * B_tile^T over `nslabs` slabs of K.
 //   A: element (first of this workgroup's BM tile rows, first reduction step of its range)
-//   B: likewise for its BN tile rows;  lda / ldb in elements.
+//   B: likewise for its BN tile rows;  lda / ldb in elements (A in octets: lda samples to a panel).
 //   smem: Cfg::LDS_BYTES bytes, 16-byte aligned.  Ends with a barrier (smem may be reused).
 // CHAIN > 0 (fp32): every CHAIN slabs the accumulators are added to a second set and start again from
 // zero, so that no sum is a chain of more than CHAIN * BK products.
