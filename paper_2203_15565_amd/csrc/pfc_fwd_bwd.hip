@@ -204,7 +204,15 @@ __device__ __forceinline__ void order_labels(int w, OrderLds& lds, int B, const 
 // Step, us, before -> now: 256 samples x 25,723 classes x 128 69.4 -> 67.9, 256 x 40,000 x 64 76.9
 // -> 73.7, 300 x 300,000 x 64 368 -> 348.  (In front of either: one workgroup for every label
 // window of a large batch, order_labels.)
-template <typename T, int NC, bool SHORT>
+// PLAIN: the rows of W are to stay in the memory-side cache (row_policy); otherwise they are loaded
+// nontemporally, which keeps them from displacing what the GEMMs that follow want (0.145 -> 0.121 ms
+// at the headline workload).
+template <bool PLAIN>
+__device__ __forceinline__ f32x4 load_w(const float* p) {
+  if constexpr (PLAIN) return *reinterpret_cast<const f32x4*>(p);
+  else return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+}
+template <typename T, int NC, bool SHORT, bool PLAIN>
 __global__ __launch_bounds__(kNormWaves * 64) void gather_normalize_kernel(
     int x_blocks, const float* __restrict__ X, int B, int Bp, const int32_t* __restrict__ yl,
     T* __restrict__ Xn, float* __restrict__ rnormX, float* __restrict__ clabel,
@@ -236,7 +244,7 @@ __global__ __launch_bounds__(kNormWaves * 64) void gather_normalize_kernel(
       ok[u] = row >= 0 && row < N;
       if (j < k && !ok[u] && l == 0) atomicOr(err_flag, 4);
       v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (ok[u] && d < D) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(W + row * D + d));
+      if (ok[u] && d < D) v[u] = load_w<PLAIN>(W + row * D + d);
     }
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
@@ -271,13 +279,10 @@ __global__ __launch_bounds__(kNormWaves * 64) void gather_normalize_kernel(
       if (ok[u]) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          // streamed once: a nontemporal load keeps these rows from displacing what the GEMMs
-          // that follow want in the L2 (measured: 0.145 -> 0.121 ms at the headline workload)
           const int d = c * 256 + lane * 4;
           v[u][c] = make_float4(0.f, 0.f, 0.f, 0.f);
           if (d < D) {
-            const f32x4 t =
-                __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(W + row * D + d));
+            const f32x4 t = load_w<PLAIN>(W + row * D + d);
             v[u][c] = make_float4(t[0], t[1], t[2], t[3]);
           }
         }
@@ -458,6 +463,10 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
   extern __shared__ __align__(16) char smem[];
   int tj, ti;
   if (!xcd_tile(blockIdx.x, tiles_i, tiles_j, tj, ti)) return;
+  // From the last class down: Wn's last rows and then E's first are the ones that the memory-side
+  // cache still holds when they are next read (us a step: 1024 x 360,232 2059 -> 2021, 2048 x 500,000
+  // 3980 -> 3923, 1024 x 205,991 1239 -> 1233, others even).
+  tj = tiles_j - 1 - tj;
   const int64_t j0 = (int64_t)tj * Cfg::BM;
   const int i0 = ti * Cfg::BN;
 
@@ -490,6 +499,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_logits_kernel(
     const int nb = (int)blockIdx.x + ahead;
     if (nb < (int)gridDim.x && (int)(threadIdx.x >> 1) < Cfg::BM &&
         xcd_tile(nb, tiles_i, tiles_j, ntj, nti)) {
+      ntj = tiles_j - 1 - ntj;
       const int row_bytes = Dp * (int)sizeof(T);
       const int off = ((nti * 256) % row_bytes) + (threadIdx.x & 1) * 128;
       const char* p = reinterpret_cast<const char*>(Wn + (int64_t)ntj * Cfg::BM * Dp) +
@@ -1436,8 +1446,11 @@ __device__ __forceinline__ void fused_update_tile(
     const float* vsrc = row >= 0 ? V + row * D : zero_row;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      w[n % WIN][c] = *reinterpret_cast<const f32x4*>(wsrc + c * 256 + lane * 4);
-      v[n % WIN][c] = *reinterpret_cast<const f32x4*>(vsrc + c * 256 + lane * 4);
+      // nontemporal: rows loaded plainly would be written back to the memory-side cache and leave it
+      // while the next kernels run (us a step: 1024 x 36,024 249 -> 242, 1024 x 70,000 406 -> 386, 1024 x
+      // 205,991 1023 -> 1004, 2048 x 500,000 3980 -> 3927)
+      w[n % WIN][c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(wsrc + c * 256 + lane * 4));
+      v[n % WIN][c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(vsrc + c * 256 + lane * 4));
     }
   };
 #pragma unroll
@@ -1781,9 +1794,11 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
   const bool plain_sums = fits_one_kernel(c->num_cu, D, kp), one_kernel = upd && plain_sums;
 
   const bool short_rows = Dp == 128;
-  auto norm_kernel = gather_normalize_kernel<T, NC, false>;
+  const bool plain = !one_kernel && row_policy(c->esize, c->N, D, c->B_max, k).gather_plain;
+  auto norm_kernel = plain ? gather_normalize_kernel<T, NC, false, true> : gather_normalize_kernel<T, NC, false, false>;
   if constexpr (NC == 1)
-    if (short_rows) norm_kernel = gather_normalize_kernel<T, NC, true>;
+    if (short_rows)
+      norm_kernel = plain ? gather_normalize_kernel<T, NC, true, true> : gather_normalize_kernel<T, NC, true, false>;
   const int64_t rows_per_block = (short_rows ? 8 : 4) * kNormWaves;   // (a divisor of kPadK)
   const int x_blocks = (Bp + kNormWaves - 1) / kNormWaves;
   PFC_LAUNCH(c, KID_GATHER_W, norm_kernel,

@@ -14,8 +14,14 @@ namespace {
 
 // The gradient is read once and the new rows are not read again before the next step, so both go
 // through nontemporal accesses (measured at the headline workload: 0.403 -> 0.384 ms; more rows
-// per wavefront or other block sizes change nothing).
-template <int NC>
+// per wavefront or other block sizes change nothing).  LOADS: see row_policy.
+template <bool PLAIN>
+__device__ __forceinline__ f32x4 load_row(const float* p) {
+  if constexpr (PLAIN) return *reinterpret_cast<const f32x4*>(p);
+  else return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+}
+
+template <int NC, RowLoads LOADS>
 __global__ void update_kernel(float* __restrict__ W, float* __restrict__ V, int64_t N,
                               const int32_t* __restrict__ idx, int64_t k,
                               const float* __restrict__ dWn, int D, float lr, float mu,
@@ -35,9 +41,9 @@ __global__ void update_kernel(float* __restrict__ W, float* __restrict__ V, int6
     const int d = c * 256 + lane * 4;
     w[c] = g[c] = v[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (d < D) {
-      w[c] = *reinterpret_cast<const f32x4*>(W + row * D + d);
+      w[c] = load_row<LOADS == ROWS_RESIDENT>(W + row * D + d);
       g[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(dWn + j * D + d));
-      v[c] = *reinterpret_cast<const f32x4*>(V + row * D + d);
+      v[c] = load_row<LOADS != ROWS_REUSED>(V + row * D + d);
     }
     ww += w[c][0] * w[c][0] + w[c][1] * w[c][1] + w[c][2] * w[c][2] + w[c][3] * w[c][3];
     gw += g[c][0] * w[c][0] + g[c][1] * w[c][1] + g[c][2] * w[c][2] + g[c][3] * w[c][3];
@@ -66,7 +72,7 @@ __global__ void update_kernel(float* __restrict__ W, float* __restrict__ V, int6
 // wavefront left three and two of four lanes without a load.  Same sums in the same order.  Step,
 // us, before -> now: 256 samples x 25,723 classes x 128 71.2 -> 69.8, 256 x 40,000 x 64 82.4 ->
 // 76.9, 300 x 300,000 x 64 400 -> 368, 1024 x 200,000 x 128 503 -> 500.
-template <int LPR>
+template <int LPR, RowLoads LOADS>
 __global__ void update_short_kernel(float* __restrict__ W, float* __restrict__ V, int64_t N,
                                     const int32_t* __restrict__ idx, int64_t k,
                                     const float* __restrict__ dWn, float lr, float mu,
@@ -81,9 +87,9 @@ __global__ void update_short_kernel(float* __restrict__ W, float* __restrict__ V
     if (d == 0) atomicOr(err_flag, 8);
     return;
   }
-  const f32x4 w = *reinterpret_cast<const f32x4*>(W + row * D + d);
+  const f32x4 w = load_row<LOADS == ROWS_RESIDENT>(W + row * D + d);
   const f32x4 g = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(dWn + j * D + d));
-  const f32x4 v = *reinterpret_cast<const f32x4*>(V + row * D + d);
+  const f32x4 v = load_row<LOADS != ROWS_REUSED>(V + row * D + d);
   float ww = w[0] * w[0] + w[1] * w[1] + w[2] * w[2] + w[3] * w[3];
   float gw = g[0] * w[0] + g[1] * w[1] + g[2] * w[2] + g[3] * w[3];
   ww = lane_group_sum<LPR>(ww);
@@ -106,8 +112,12 @@ int update_impl(pfc_ctx* c, float* W, float* v, const int32_t* idx, int64_t k, c
                 float lr, float mu) {
   const int rows_per_block = 4;   // one wavefront per row
   const unsigned grid = (unsigned)((k + rows_per_block - 1) / rows_per_block);
+  const RowLoads loads = row_policy(c->esize, c->N, c->D, c->B_max, k).loads;
+#define PFC_BY_LOADS(KERNEL, A)                                     \
+  (loads == ROWS_RESIDENT ? KERNEL<A, ROWS_RESIDENT>                \
+   : loads == ROWS_REUSED ? KERNEL<A, ROWS_REUSED> : KERNEL<A, ROWS_STREAMED>)
   if (c->D <= 128) {   // 64 or 128
-    auto kernel = c->D == 64 ? update_short_kernel<16> : update_short_kernel<32>;
+    auto kernel = c->D == 64 ? PFC_BY_LOADS(update_short_kernel, 16) : PFC_BY_LOADS(update_short_kernel, 32);
     PFC_LAUNCH(c, KID_UPDATE, kernel, dim3((unsigned)((k * (c->D / 4) + 255) / 256)), dim3(256), 0, W, v, c->N, idx,
                k, dW, lr, mu, c->err_flag);
     return PFC_OK;
@@ -115,7 +125,8 @@ int update_impl(pfc_ctx* c, float* W, float* v, const int32_t* idx, int64_t k, c
   switch ((c->D + 255) / 256) {
 #define PFC_UPD(NC)                                                                              \
   case NC: {                                                                                     \
-    PFC_LAUNCH(c, KID_UPDATE, update_kernel<NC>, dim3(grid), dim3(rows_per_block * 64), 0, W, v, \
+    auto kernel = PFC_BY_LOADS(update_kernel, NC);                                               \
+    PFC_LAUNCH(c, KID_UPDATE, kernel, dim3(grid), dim3(rows_per_block * 64), 0, W, v,            \
                c->N, idx, k, dW, c->D, lr, mu, c->err_flag);                                     \
     return PFC_OK;                                                                               \
   }
@@ -124,6 +135,7 @@ int update_impl(pfc_ctx* c, float* W, float* v, const int32_t* idx, int64_t k, c
     PFC_UPD(3)
     PFC_UPD(4)
 #undef PFC_UPD
+#undef PFC_BY_LOADS
   }
   return PFC_EINVAL;
 }
