@@ -63,8 +63,7 @@ struct RadixState {
 };
 struct SampleState {
   uint32_t next, cur;   // set of the next window selection / of the one at hand
-  uint32_t k;           // |S| = max(U, ceil(r*N))
-  uint32_t spare[13];
+  uint32_t spare[14];
   SampleHdr hdr[2];
   RadixState radix;
 };
@@ -81,6 +80,10 @@ struct SampleScratch {
   uint32_t list_cap, pos_cap;
   uint32_t* hist;          // kRadixHistWords
   uint32_t* radix_cnt;     // per kRadixClasses classes: taken for sure, equal to the threshold
+  // Pinned host word that takes |S| = max(U, ceil(r*N)), null where the host knows it.  Stored by the
+  // kernel that finds it: a copy of 4 bytes behind it is a launch more (step, batch classes alone x
+  // 512: 16,384 samples 335.1 -> 333.0 us, 4,000 samples 111.9 -> 108.8).
+  uint32_t* k_host;
 };
 
 }  // namespace pfc

@@ -537,7 +537,7 @@ __global__ __launch_bounds__(kWriteThreads, 4) void sample_write_kernel(
     old->pos_above = 0u;
     old->npos = 0u;
     old->overflow = 0u;
-    sc.st->k = k;
+    if (sc.k_host) store_to_host(sc.k_host, k);
     sc.st->next = par ^ 1u;
   }
 }
@@ -587,6 +587,7 @@ int sample_impl(pfc_ctx* c, const int64_t* labels, int32_t B, double r, uint64_t
   key.mask = score_mask;
 
   const SelectWindow sw = select_window(N, crn, B);
+  c->samp.k_host = crn < (int64_t)B ? c->host_pin : nullptr;   // (otherwise U <= B <= ceil(r*N))
   const SampleScratch& sc = c->samp;
   // the timing hooks report the launches of this call, not those of an earlier one on the other way
   for (int id = KID_SAMPLE_SCAN; id <= KID_SAMPLE_REMAP; ++id) c->ev_used[id] = 0;
@@ -615,13 +616,11 @@ int sample_impl(pfc_ctx* c, const int64_t* labels, int32_t B, double r, uint64_t
     if (rc != PFC_OK) return rc;
   }
 
-  if (crn >= (int64_t)B) {
-    // U <= B <= ceil(r*N): k is known without the labels.
+  if (!sc.k_host) {
     *k_out = crn;
   } else {
-    PFC_HIP(hipMemcpyAsync(c->host_pin, &sc.st->k, 4, hipMemcpyDeviceToHost, c->stream));
     PFC_HIP(hipStreamSynchronize(c->stream));
-    *k_out = (int64_t)c->host_pin[0];
+    *k_out = (int64_t)*(volatile const uint32_t*)sc.k_host;
   }
   return PFC_OK;
 }

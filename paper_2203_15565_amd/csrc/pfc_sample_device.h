@@ -11,6 +11,11 @@ struct PhiloxKey {
   uint32_t mask;     // ANDed onto every score
 };
 
+// To pinned host memory, for a host that waits for the stream before it reads.
+__device__ __forceinline__ void store_to_host(uint32_t* p, uint32_t x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Scores of classes 4q .. 4q+3.
 __device__ __forceinline__ void philox_block(uint32_t q, const PhiloxKey& key, uint32_t out[4]) {
   uint32_t c0 = q, c1 = 0u, c2 = key.c2, c3 = key.c3;   // class ids are < 2^31, so hi32(j/4) = 0
@@ -202,7 +207,7 @@ __device__ __forceinline__ void mark_labels(const int64_t (&y)[PER], const bool 
   for (int c = 0; c < PER; ++c) first[c] = first[c] && !((lds.bits[at[c]] >> (y[c] & 63)) & 1u);
 }
 
-// The radix selection (pfc_sample_radix.hip); k is left in sc.st->k.
+// The radix selection (pfc_sample_radix.hip).
 int sample_radix(pfc_ctx* ctx, const int64_t* labels, int32_t B, uint32_t ceil_rN, int64_t cap,
                  const PhiloxKey& key, int32_t* idx_out, int32_t* yl_out);
 

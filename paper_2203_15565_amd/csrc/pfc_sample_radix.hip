@@ -59,7 +59,7 @@ __device__ __forceinline__ void select_state(const SampleScratch& sc, uint32_t c
     need_in = k - U;
     prefix_in = 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-      sc.st->k = k;
+      if (sc.k_host) store_to_host(sc.k_host, k);
       sel->none = none;
     }
   } else {
