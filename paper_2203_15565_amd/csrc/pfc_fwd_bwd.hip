@@ -1642,13 +1642,26 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
     for (int c = 0; c < NC; ++c)
       if (c * 256 + lane * 4 < D) x[c] = *reinterpret_cast<const float4*>(a.X + (int64_t)i * D + c * 256 + lane * 4);
   }
-  for (int sp = wave; i < a.B && sp < a.splits; sp += WPS) {
+  if (i < a.B) {
+    // U slices requested before the first is added (longer rows have no registers for it)
+    constexpr int U = NC <= 2 ? 2 : 1;
+    for (int sp = wave; sp < a.splits; sp += U * WPS) {
+      float4 t[U][NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      if (c * 256 + lane * 4 >= D) continue;   // columns from D on are zero
-      const float4 t = *reinterpret_cast<const float4*>(a.part + ((int64_t)sp * a.Bp + i) * a.Dp +
-                                                        c * 256 + lane * 4);
-      sum[c].x += t.x; sum[c].y += t.y; sum[c].z += t.z; sum[c].w += t.w;
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          t[u][c] = make_float4(0.f, 0.f, 0.f, 0.f);   // columns from D on are zero
+          if (sp + u * WPS < a.splits && c * 256 + lane * 4 < D)
+            t[u][c] = *reinterpret_cast<const float4*>(a.part + ((int64_t)(sp + u * WPS) * a.Bp + i) * a.Dp + c * 256 +
+                                                       lane * 4);
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          sum[c].x += t[u][c].x; sum[c].y += t[u][c].y; sum[c].z += t[u][c].z; sum[c].w += t[u][c].w;
+        }
     }
   }
   if (ends && y >= 0 && (int64_t)y < a.k) {
@@ -1714,9 +1727,12 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
 // of dependent loads that leave the GPU idle, and with a large batch the mean loss runs alone at
 // the end.  64 registers: two workgroups on a compute unit.  Step, two launches -> one: 128 x 1,000
 // x 512 fp32 59.9 -> 56.1 us, 512 x 9,344 x 512 104.4 -> 101.0, 256 x 25,723 x 128 79.5 -> 74.1,
-// 768 x 20,599 x 1024 277 -> 271, 16,384 samples x 3,592 476 -> 462.  From kFinalWideSplits slices
-// on a sample gets 16 wavefronts instead of 4: below, a third of the 16 and more would have no
-// slice to add.  Up to kFinalOneSplits a sample gets one: three of four would have none.
+// 768 x 20,599 x 1024 277 -> 271, 16,384 samples x 3,592 476 -> 462.  A sample gets four wavefronts; up
+// to kFinalOneSplits slices one: three of four would have none; from kFinalWideSplits on 16, below
+// which a third of them would have none, if there is a compute unit for every sample.  (This launch,
+// us, 16 wavefronts / 4: 1024 x 205,991 x 512 20.8 / 17.7, fused 16.9 / 12.6, fused 1024 x 36,024 13.8 /
+// 10.0, 1024 x 40,000 x 256 14.8 / 12.2, 400 x 40,000 x 1024 14.7 / 12.3; 200 x 60,000 x 768 11.2 /
+// 12.8, 64 x 200,000 x 512 in fp32 12.3 / 16.0.)
 constexpr int kFinalWideSplits = 12, kFinalOneSplits = 2;
 template <int NC, int WPS, bool WINDOWS>
 __global__ __launch_bounds__(kLabelThreads, 8) void gradients_final_kernel(
@@ -1911,14 +1927,13 @@ int run(pfc_ctx* c, const float* X, const float* W, const int32_t* idx, int64_t 
                        c->rnormW, wlab, c->rowscale, c->dlabel, dX_out, c->lossrow, loss_out,
                        c->clabel, c->rowmax, stats_out};
     const int label_blocks = !with_label ? 0 : nwin ? nwin * kWindowBlocks : B;
-    const bool wide = dx.splits >= kFinalWideSplits, one = dx.splits <= kFinalOneSplits;
+    const bool wide = dx.splits >= kFinalWideSplits && B <= c->num_cu && !nwin, one = dx.splits <= kFinalOneSplits;
     const int spb = kLabelThreads / 64 / (wide ? 16 : one ? 1 : 4);
-    auto kernel = nwin ? (wide  ? gradients_final_kernel<NC, 16, true>
-                          : one ? gradients_final_kernel<NC, 1, true>
-                                : gradients_final_kernel<NC, 4, true>)
-                       : (wide  ? gradients_final_kernel<NC, 16, false>
-                          : one ? gradients_final_kernel<NC, 1, false>
-                                : gradients_final_kernel<NC, 4, false>);
+    // (windows: batches above one window, many samples)
+    auto kernel = nwin   ? (one ? gradients_final_kernel<NC, 1, true> : gradients_final_kernel<NC, 4, true>)
+                  : wide ? gradients_final_kernel<NC, 16, false>
+                  : one  ? gradients_final_kernel<NC, 1, false>
+                         : gradients_final_kernel<NC, 4, false>;
     PFC_LAUNCH(c, KID_GRAD_FINAL, kernel, dim3((unsigned)(1 + label_blocks + (B + spb - 1) / spb)),
                dim3(kLabelThreads), 0, fa, label_blocks, c->head, c->label_order, c->label_runs,
                nwin ? c->dlab : dW_out);
