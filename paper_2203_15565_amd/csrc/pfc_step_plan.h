@@ -157,13 +157,15 @@ inline bool long_batch(int cu, int D, int Bp, int64_t kp) { return Bp > kLongBat
 //   128 x 6,000 of 30,000 x 512 55.5 / 56.3 / 56.5 / 53.1, 256 x 25,723 of 85,742 x 128 60.6 / 62.3 / 63.0
 //   / 59.8, 333 x 15,601 of 120,007 x 192 67.3 / 67.3 / 68.0 / 66.1; 512 x 40,000 of 40,000 (8 N D is 164
 //   MB, all 336) 189.9 / 192.1 / 191.6 / 193.2; 512 x 18,000 of 60,000 (246, 327) 115.8 / 113.7 / 114.0 /
-//   115.7; from many classes: 768 x 20,599 x 1024 (all of the step: 268 MB) 257 / 250 / 243, 512 x
-//   40,000 (254) 224 / 218 / 214, 128 x 45,000 192 / 182 / 177, 1024 x 36,024 (276) 269 / 266 / 260, 1024 x
+//   115.7; from many classes: 512 x 30,000 (all of the step: 192 MB) 175 / 169 / 165, 128 x 45,000 (222)
+//   192 / 182 / 177, 768 x 20,599 x 1024 (268) 257 / 250 / 243, 1024 x 36,024 (276) 269 / 266 / 260, 1024 x
 //   45,000 (339) 306 / 304 / 306, 2725 x 16,917 x 1024 (354) 441 / 439 / 444, 2048 x 40,000 (403) 424 / 422 /
-//   426, 4096 x 30,000 (466) 513 / 509 / 517,
-//   1024 x 70,000 455 / 451 / 464, 1024 x 205,991 1239 / 1215 / 1232, 1024 x 360,232 2059 / 1985 / 1996.
+//   426, 1024 x 70,000 455 / 451 / 464, 1024 x 205,991 1239 / 1215 / 1232, 1024 x 360,232 2059 / 1985 / 1996.
+// Where other data went through the cache between two steps, reused is 2 - 5 % ahead of streamed up to 205
+// MB (512 x 30,000 174.7 / 171.5, 128 x 80,000 x 256 176.7 / 168.5), 0 - 1 % from 220 to 270; a first step
+// on rows that have just been written takes 2 - 6 % more with it.  Hence the line at 215 MB.
 enum RowLoads { ROWS_RESIDENT, ROWS_REUSED, ROWS_STREAMED };
-constexpr int64_t kResidentBytes = 200000000, kStepBytes = 290000000;
+constexpr int64_t kResidentBytes = 200000000, kStepBytes = 290000000, kReusedBytes = 215000000;
 struct RowPolicy {
   RowLoads loads;
   bool gather_plain;
@@ -172,7 +174,7 @@ inline RowPolicy row_policy(int es, int64_t N, int D, int B_max, int64_t k) {
   // dWn, Wn, E; features, their gradient and its partial sums, about eight rows of floats a sample
   const int64_t all = 8 * N * D, rest = k * (4ll * D + es * (round_up(D, kPadD) + B_max)) + 32ll * B_max * D;
   if (all <= kResidentBytes) return {ROWS_RESIDENT, all + rest <= kStepBytes};
-  if (4 * k * D + rest <= kStepBytes) return {ROWS_REUSED, true};
+  if (4 * k * D + rest <= kReusedBytes) return {ROWS_REUSED, true};
   return {ROWS_STREAMED, false};
 }
 

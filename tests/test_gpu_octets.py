@@ -14,8 +14,9 @@ BF16 = binding.PRECISION_BF16
 # one more and one less than an octet, a slab and a tile
 @pytest.mark.parametrize("N,B,D", [(263, 100, 64),          # 64 and 64
                                    (511, 97, 128),          # 64 and 64, either end of the padding
-                                   (1025, 160, 192),        # 64 and 128
-                                   (9_001, 129, 256),       # 128 and 128
+                                   (1025, 160, 192),        # 64 and 64
+                                   (4_001, 500, 512),       # 64 and 128
+                                   (9_001, 129, 256),       # 128 and 64
                                    (16_383, 513, 320),      # 128 and 128, samples one past a tile
                                    (20_479, 700, 512),      # 256 and 256
                                    (16_897, 1025, 512),     # 128 and 256: 128-tiles write 1280 samples
