@@ -31,19 +31,19 @@ PEAK_FP32_MFMA_TFLOPS = 157.3  # fp32 MFMA
 # no counter run has been recorded.
 MEASURED_TRAFFIC_BYTES: dict = {
     ("headline", 0.1, "update"): 2116000000,
-    ("headline", 0.1, "gather_normalize_w"): 639800000,
-    ("headline", 0.1, "gemm_logits"): 730100000,
-    ("headline", 0.1, "gemm_backward"): 1727100000,
-    ("headline", 0.1, "gemm_backward_update"): 2916400000,
+    ("headline", 0.1, "gather_normalize_w"): 639700000,
+    ("headline", 0.1, "gemm_logits"): 712800000,
+    ("headline", 0.1, "gemm_backward"): 1826600000,
+    ("headline", 0.1, "gemm_backward_update"): 2932200000,
 }
 
 # Fraction of a GEMM kernel's own cycles in which an MFMA pipe was busy, from the rocprofv3 --pmc
 # run summarised in profiles/headline_step_mfma_lds_counters.md (SQ_VALU_MFMA_BUSY_CYCLES over
 # the kernel's SQ_BUSY_CYCLES: independent of the clock the kernel ran at).
 MEASURED_MFMA_BUSY: dict = {
-    ("headline", 0.1, "gemm_logits"): 0.383,
-    ("headline", 0.1, "gemm_backward"): 0.543,
-    ("headline", 0.1, "gemm_backward_update"): 0.325,
+    ("headline", 0.1, "gemm_logits"): 0.433,
+    ("headline", 0.1, "gemm_backward"): 0.562,
+    ("headline", 0.1, "gemm_backward_update"): 0.345,
 }
 
 
