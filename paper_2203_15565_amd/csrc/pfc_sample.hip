@@ -592,7 +592,7 @@ int sample_impl(pfc_ctx* c, const int64_t* labels, int32_t B, double r, uint64_t
   // the timing hooks report the launches of this call, not those of an earlier one on the other way
   for (int id = KID_SAMPLE_SCAN; id <= KID_SAMPLE_REMAP; ++id) c->ev_used[id] = 0;
   if (window_select(N, crn, B, score_mask, sw)) {
-    const int cls_log2 = sample_write_log2(N), nblk = (int)((N + ((int64_t)1 << cls_log2) - 1) >> cls_log2);
+    const int cls_log2 = sample_write_log2(N), nblk = (int)sample_write_blocks(N);
     const int split = cls_log2 - sample_cls_log2(N), nscan = nblk << split;
     const uint32_t part_mask = list_parts(nscan) - 1;
     const Window win{sw.lo, sw.width, sw.shift};

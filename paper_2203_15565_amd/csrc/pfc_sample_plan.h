@@ -40,6 +40,11 @@ inline int sample_write_log2(int64_t N) {
   return l < kMaxClsLog2 && sample_blocks(N) > 512 ? l + 1 : l;
 }
 
+inline int64_t sample_write_blocks(int64_t N) {
+  const int l = sample_write_log2(N);
+  return (N + ((int64_t)1 << l) - 1) >> l;
+}
+
 // Parts of the list of the window, one count each: the workgroups of sample_scan queue up on a count
 // (503 on one count: 5 us of a launch of 11).  Few workgroups would fill the parts unevenly.
 inline int list_parts(int scan_blocks) { return scan_blocks >= 64 ? kListParts : 1; }
@@ -113,15 +118,21 @@ inline double window_bin_classes(int64_t N, const SelectWindow& w) {
 // from the window makes every workgroup select for itself.  The end bin has to hold the classes that
 // fall into it (8 standard deviations kept).
 //
-// The line between them is an estimate of both in us, fitted to 306 forms of 8 thousand .. 16.7 million classes
-// and batches of 2,048 .. 65,536 on 256 compute units (beyond, up to 200 million classes and batches from
-// 4,096); the way it picks is 0.1 % behind the other on average, 13 % at most (65,536 samples of 8,000
-// classes).  Measured, window / radix:
-//   N = 93,431, r = 0.1:      B = 8,192 25.8 / 42.0;  no negatives: 32,768 44 / 57, 65,536 64 / 74
-//   N = 2,059,906, r = 0.1:   B = 16,384 51 / 60, 32,768 89 / 68, 65,536 165 / 84, 262,144 3,869 / 187
-//   N = 2,059,906, no negatives: B = 16,384 37 / 60, 65,536 67 / 85
-//   N = 6,000,000, r = 0.1:   B = 16,384 62 / 86, 32,768 93 / 95
-//   N = 16,700,000, r = 0.5:  B = 49,152 169 / 184, 65,536 204 / 194
+// The line between them is an estimate of both in us, fitted to 369 forms of 8 thousand .. 200 million
+// classes and batches of 2,048 .. 65,536 on 256 compute units; over these the way it picks is 0.3 %
+// behind the other on average and 5 % at most, but for batches whose distinct labels leave no negative
+// to look for, which the rule cannot know (40,000 classes, r = 0.5, 32,768 samples: 40.6 / 52.1, and it
+// picks the second).  The workgroups that count are those of sample_write.  (With those of sample_scan,
+// and weights of kernels that marked label by label, grids that sample_write halves took the radix
+// passes too early: 1,187,840 classes, r = 0.1, 8,192 samples 46.9 us instead of 28.0; 8,437,760 and
+// 16,384 97.7 instead of 61.2.)  Measured, window / radix, calls back to back (without negatives the
+// wait for k is in it; the masked ones were measured on kernels that marked label by label):
+//   N = 527,360, r = 0.1:     B = 8,192 26.3 / 39.7, 16,384 38 / 43, 24,576 53 / 47
+//   N = 2,109,440, r = 0.1:   B = 16,384 44 / 58, 24,576 57 / 63, 32,768 72 / 67, 65,536 130 / 83
+//   N = 2,059,906, no negatives: B = 16,384 34 / 57, 65,536 55 / 82
+//   N = 6,553,600, r = 0.1:   B = 16,384 55 / 85, 32,768 82 / 94, 65,536 139 / 110
+//   N = 10,469,376, r = 0.1:  B = 32,768 93 / 118, 49,152 120 / 126, 65,536 147 / 134
+//   N = 20,000,000, r = 0.01: B = 32,768 136 / 166, 49,152 183 / 175;  60,000,000: 65,536 490 / 501
 //   N = 2,059,906, mask 0x3FF: 8,168 / 69; N = 10,000 41 / 42; N = 15,000 51 / 44
 inline bool window_select(int64_t N, int64_t ceil_rN, int64_t B, uint32_t mask, const SelectWindow& w) {
   if (B > kWindowBatch) return false;
@@ -132,16 +143,16 @@ inline bool window_select(int64_t N, int64_t ceil_rN, int64_t B, uint32_t mask, 
   const double n = (double)N, classes = n * 1e-6, b = (double)B * 1e-3;
   const double list = ceil_rN > 1 ? w.expected * 1e-3 : 0.0;   // no negatives: nothing to look for
   const double distinct = n * (1.0 - exp(-(double)B / n)) * 1e-3;
-  const double blocks = (double)sample_blocks(N);
+  const double blocks = (double)sample_write_blocks(N);
   // more workgroups than the compute units hold at a time (two each) repeat the common part later
   const double rounds = 1.0 + 0.75 * floor((blocks - 1.0) / 512.0);
   // every workgroup: its classes, the list, all labels; and atomics on the counts of a workgroup and
   // on the list of the batch classes inside the window
-  const double window_us = 7.0 + 1.4 * classes + rounds * (1.1 * list + b) + 2.5 * distinct / blocks +
-                           1.05 * distinct * fmin(1.0, w.expected / n);
+  const double window_us = 10.0 + 1.3 * classes + rounds * (list + 0.6 * b) + distinct / blocks +
+                           0.5 * distinct * fmin(1.0, w.expected / n);
   // the passes over the classes, the counts in front of each workgroup (their square), the labels
   const double far = fmax(0.0, classes - 20.0);
-  const double radix_us = 31.0 + 6.9 * classes + 0.035 * far * far + 0.68 * b;
+  const double radix_us = 32.0 + 6.9 * classes + 0.035 * far * far + 0.55 * b;
   return window_us <= radix_us;
 }
 

@@ -180,3 +180,22 @@ def test_both_selections_replay_from_a_graph():
         for (lab, r, idx, yl), (oidx, oyl, ok) in zip(calls, want):
             assert np.array_equal(idx.cpu().numpy()[:ok], oidx)
             assert np.array_equal(yl.cpu().numpy(), oyl)
+
+
+# Larger batches than before on the window: grids that sample_write halves, and others; labels spread out and
+# in the order of frequency
+@pytest.mark.parametrize("N,B,r", [(527_360, 8_192, 0.1), (1_187_841, 8_191, 0.1), (2_390_744, 7_615, 0.5),
+                                   (4_751_361, 16_385, 0.1), (9_502_720, 24_576, 0.03), (12_000, 32_768, 0.5)])
+def test_window_of_larger_batches(N, B, r):
+    ctx = binding.Context(N, 64, B, r, binding.PRECISION_BF16)
+    ctx.pfc_set_timing(True)
+    rng = np.random.default_rng(N + B)
+    for step, power in enumerate((1, 3)):
+        labels = (rng.random(B) ** power * N).astype(np.int64)
+        _say("window of larger batches", N, B, step)
+        idx, yl, k = gpu_sample(ctx, labels, r, 17, step)
+        assert {n for n in ctx.pfc_get_timing() if n.startswith("sample_")} == WINDOW
+        oidx, oyl, ok = O.sample(labels, N, r, 17, step)
+        assert k == ok and np.array_equal(idx[:k], oidx) and np.array_equal(yl, oyl)
+    assert ctx.pfc_check() == binding.PFC_OK
+    ctx.close()

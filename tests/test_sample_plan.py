@@ -100,3 +100,15 @@ def test_large_batches_and_moved_scores_take_the_radix_passes(plan):
     assert plan(655_361, 6554, 300, 0xFFFFF000)[0]              # ties, but where the window is
     assert not plan(655_361, 6554, 300, 0xFFFF0000)[0]          # ten classes to a score: not any more
     assert plan(2_059_906, 1, 16_384)[0]                        # the classes of the batch alone
+
+
+# (classes, ratio, samples): 512 .. 640 workgroups of sample_scan, half as many of sample_write, where the window took 60 to
+# 80 % of the time of the radix passes; either side of the line, where the two were 10 % or more apart
+@pytest.mark.parametrize("N,r,B,window", [
+    (527_360, 0.1, 8_192, True), (1_187_840, 0.1, 8_192, True), (1_143_244, 0.5, 8_064, True), (2_390_744, 0.5, 7_615, True),
+    (4_751_360, 0.1, 16_384, True), (8_437_760, 0.1, 16_384, True), (9_502_720, 0.1, 24_576, True),
+    (93_431, 0.1, 8_192, True), (2_059_906, 1e-9, 65_536, True), (6_553_600, 0.1, 32_768, True),
+    (527_360, 0.1, 24_576, False), (1_187_840, 0.1, 32_768, False), (2_109_440, 0.1, 49_152, False),
+    (9_502_720, 0.1, 65_536, False), (90_000, 1.0, 32_768, False), (17_000_000, 0.01, 49_152, False)])
+def test_the_way_that_was_measured_faster(plan, N, r, B, window):
+    assert plan(N, max(1, math.ceil(r * N)), B)[0] is window
