@@ -146,36 +146,46 @@ inline bool long_batch(int cu, int D, int Bp, int64_t kp) { return Bp > kLongBat
 // How the rows of W and v are loaded, for what the memory-side cache (256 MB) still holds when they are
 // next read; their stores are always nontemporal.  A row that is loaded plainly goes to that cache, is
 // stored back to it, and leaves it for memory while the next kernels run.
-//   resident: W and v as a whole stay there from step to step: the update loads plainly, and the gather
-//             where the rest of a step fits beside them.
-//   reused:   the sampled rows of W stay from the gather (plain) to the update, which loads
-//             nontemporally: their last use in the step.
-//   streamed: nothing fits: nontemporal, but for v in the update.
+//   gather_plain: the sampled rows of W stay from the gather to the update.
+//   resident: W and v as a whole may stay from step to step: the update loads both plainly.
+//   reused:   after a plain gather the update loads nontemporally: the rows' last use in the step.
+//   streamed: nontemporal, but for v in the update.
 // The batch is the context's largest, so that gather and update, which are calls of their own, decide
-// alike.  The one-kernel form loads nontemporally in either place.  Step, us, gather nontemporal and update
-// plain (as it was) / streamed / reused / resident:
-//   128 x 6,000 of 30,000 x 512 55.5 / 56.3 / 56.5 / 53.1, 256 x 25,723 of 85,742 x 128 60.6 / 62.3 / 63.0
-//   / 59.8, 333 x 15,601 of 120,007 x 192 67.3 / 67.3 / 68.0 / 66.1; 512 x 40,000 of 40,000 (8 N D is 164
-//   MB, all 336) 189.9 / 192.1 / 191.6 / 193.2; 512 x 18,000 of 60,000 (246, 327) 115.8 / 113.7 / 114.0 /
-//   115.7; from many classes: 512 x 30,000 (all of the step: 192 MB) 175 / 169 / 165, 128 x 45,000 (222)
-//   192 / 182 / 177, 768 x 20,599 x 1024 (268) 257 / 250 / 243, 1024 x 36,024 (276) 269 / 266 / 260, 1024 x
-//   45,000 (339) 306 / 304 / 306, 2725 x 16,917 x 1024 (354) 441 / 439 / 444, 2048 x 40,000 (403) 424 / 422 /
-//   426, 1024 x 70,000 455 / 451 / 464, 1024 x 205,991 1239 / 1215 / 1232, 1024 x 360,232 2059 / 1985 / 1996.
-// Where other data went through the cache between two steps, reused is 2 - 5 % ahead of streamed up to 205
-// MB (512 x 30,000 174.7 / 171.5, 128 x 80,000 x 256 176.7 / 168.5), 0 - 1 % from 220 to 270; a first step
-// on rows that have just been written takes 2 - 6 % more with it.  Hence the line at 215 MB.
+// alike.  The one-kernel form loads nontemporally in either place.
+// Between two steps a program runs its backbone, which leaves the cache full of other, partly dirty
+// data: what a plain gather brings in has to push that out first.  Step, us, in the order gather
+// nontemporal and update plain / streamed / reused / resident with a plain gather, (a) steps one right
+// after the other, (b) behind an in-place pass over 512 MB, (c) behind a copy of as much, (d) behind eight
+// bf16 products of 2048 x 4096 x 4096 (bytes of the step as counted below):
+//   256 x 25,724 of 85,742 x 128 (47 MB)   (a) 59.8 / 60.1 / 60.5 / 58.2   (b) 71.4 / 70.8 / 70.7 / 70.8
+//                                          (c) 68.6 / 68.2 / 68.0 / 67.4   (d) 67.4 / 67.0 / 67.7 / 67.2
+//   512 x 9,344 of 93,431 x 512 (66)       (a) 81.9 / 81.3 / 81.5 / 81.9   (b) 90.9 / 90.9 / 91.3 / 91.4
+//   700 x 8,000 of 40,000 x 512 (64)       (a) 84.6 / 85.4 / 85.6 / 83.6   (b) 94.9 / 94.3 / 93.5 / 93.7
+//   1024 x 18,000 of 90,000 x 256 (91)     (a) 109.9 / 109.0 / 108.4 / 107.5   (b) 119.4 / 118.9 / 118.4 / 118.7
+//                                          (c) 116.9 / 117.4 / 113.8 / 113.9   (d) 116.7 / 116.7 / 116.0 / 115.9
+//   512 x 16,000 of 40,000 x 512 (107)     (a) 107.5 / 108.8 / 108.8 / 106.9   (b) 118.3 / 117.5 / 121.3 / 121.2
+//                                          (c) 113.9 / 114.1 / 115.9 / 116.3   (d) 116.0 / 115.6 / 115.4 / 116.8
+//   512 x 18,000 of 300,000 x 512 (119)    (a) 126.3 / 123.5 / 121.9   (b) 136.1 / 135.8 / 139.5
+//                                          (c) 130.3 / 131.5 / 133.9   (d) 129.7 / 129.7 / 134.1
+//   512 x 30,000 of 300,000 x 512 (193)    (a) 177 / 169 / 167   (b) 190 / 190 / 198   (c) 177 / 179 / 183
+//                                          (d) 177 / 177 / 182
+//   768 x 20,599 of 205,990 x 1024 (268)   (a) 254 / 247 / 238   (b) 260 / 263 / 279   (c) 248 / 250 / 257
+//   1024 x 205,991 of 2,059,906 x 512      (a) 1204 / 1195 / 1202   (b) 1204 / 1192 / 1242   (c) 1178 / 1173 / 1222
+// From 107 MB on a plain gather is 2 - 6 % behind there (a state's first step 5 - 7 %: 512 x 30,000 203 / 214),
+// whatever it gains where steps follow each other; up to 91 MB it is even or ahead.  Hence the line at 95 MB
+// between them.  (Streamed is up to 2 % behind the first order in (b) and (c) from 200 to 270 MB, 2 - 5 % ahead in
+// (a), and ahead everywhere in larger steps.)
 enum RowLoads { ROWS_RESIDENT, ROWS_REUSED, ROWS_STREAMED };
-constexpr int64_t kResidentBytes = 200000000, kStepBytes = 290000000, kReusedBytes = 215000000;
+constexpr int64_t kResidentBytes = 200000000, kGatherPlainBytes = 95000000;
 struct RowPolicy {
   RowLoads loads;
   bool gather_plain;
 };
 inline RowPolicy row_policy(int es, int64_t N, int D, int B_max, int64_t k) {
-  // dWn, Wn, E; features, their gradient and its partial sums, about eight rows of floats a sample
-  const int64_t all = 8 * N * D, rest = k * (4ll * D + es * (round_up(D, kPadD) + B_max)) + 32ll * B_max * D;
-  if (all <= kResidentBytes) return {ROWS_RESIDENT, all + rest <= kStepBytes};
-  if (4 * k * D + rest <= kReusedBytes) return {ROWS_REUSED, true};
-  return {ROWS_STREAMED, false};
+  // W's rows, dWn, Wn, E; features, their gradient and its partial sums, about eight rows of floats a sample
+  const int64_t step = k * (8ll * D + es * (round_up(D, kPadD) + B_max)) + 32ll * B_max * D;
+  const bool plain = step <= kGatherPlainBytes;
+  return {8 * N * D <= kResidentBytes ? ROWS_RESIDENT : plain ? ROWS_REUSED : ROWS_STREAMED, plain};
 }
 
 // Size of the GEMM tiles, one for the logits and one for the backward launch of a call.  256 x 256
