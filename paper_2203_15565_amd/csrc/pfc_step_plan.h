@@ -405,15 +405,22 @@ inline TileSize backward_tiles(int cu, int es, int B, int64_t kp, int D) {
   const TileSize usual = fill ? TILES_256 : B > 128 || 2 * mid > cu ? TILES_128 : TILES_64;
   // Another size where an estimate of the launch is 6 % lower: a launch of one to three rounds ends
   // with its last workgroup, which the number of tiles alone does not tell.  Step, us, by number / now:
-  // 1106 x 5,673 x 1024 163 / 139 (128), 1359 x 7,578 x 512 134 / 118 (128), 651 x 10,642 x 768 128 / 117
-  // (256), 450 x 15,139 x 512 109 / 102 (256), 913 x 4,403 x 384 72 / 65 (64), 1018 x 12,161 x 128 73 / 66
-  // (64), 153 x 4,761 x 64 42 / 39 (64).  Over 140 forms drawn from 50 .. 4000 samples, 1,000 .. 40,000
-  // classes and all D the step is 1.7 % shorter on average and 3.5 % longer at most.
+  // 1106 x 5,673 x 1024 163 / 139 (128), 1359 x 7,578 x 512 134 / 118 (128), 1891 x 15,915 x 448 217 / 204
+  // (128), 913 x 4,403 x 384 72 / 65 (64), 1018 x 12,161 x 128 73 / 66 (64), 153 x 4,761 x 64 42 / 39 (64),
+  // 484 x 24,076 x 768 203 / 191 (256).  In 88 forms drawn from 50 .. 2048 samples, 1,000 .. 60,000 classes
+  // and all D that change to a smaller size the step is 3.9 % shorter on average; 128 -> 64 costs up to 3.7 %
+  // (790 x 2,932 x 448 58.2 / 60.4) around 800 samples of 3,000 classes, where it is 2.7 % shorter on average.
+  // 256-tiles that the number does not suggest only where D is whole tiles of columns: 21 forms, 0.4 %
+  // shorter on average, 3.7 % longer at most (570 x 25,793 x 1024 290 / 301).  24 forms with other D were 3.8 %
+  // longer on average, up to 8 %, whatever the estimate (187 x 29,073 x 576 152 / 164, 474 x 18,827 x 896
+  // 183 / 196, 531 x 51,903 x 448 275 / 289): beyond 512 their rows get longer, which the launches around pay
+  // for as well.
   // (Where 256-tiles of dweight alone are half a round or more, they stay: 1756 x 27,321 x 512 286 / 297.)
   if (B > kLongBatch || fits_one_kernel(cu, D, kp) || (usual == TILES_256 && big * 2 > cu)) return usual;
   TileSize best = usual;
   double best_us = 0.94 * bf16_backward_us(cu, usual, B, kp, D);
   for (TileSize t : {TILES_256, TILES_128, TILES_64}) {
+    if (t == TILES_256 && D % 256 != 0) continue;
     const double us = t == usual ? best_us : bf16_backward_us(cu, t, B, kp, D);
     if (us < best_us) best = t, best_us = us;
   }
