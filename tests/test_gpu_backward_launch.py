@@ -15,23 +15,23 @@ pytestmark = pytest.mark.gpu
 
 # (N, B, D, r)
 CASES = [
-    (32_512, 64, 256, 1.0),     # 127 big tiles: small ones are taken
-    (32_513, 64, 256, 1.0),     # 128 big tiles: big ones, last tile with one class
-    (1_000, 64, 512, 0.256),    # one tile of 256 classes, one slice of dfeatures
-    (1_000, 64, 512, 0.257),    # two of them, the second with one class
-    (6_000, 1_024, 64, 0.5),    # batch of a whole number of tiles, D narrower than a tile
+    (32_512, 64, 256, 1.0),     # a whole number of tiles of 256 classes
+    (32_513, 64, 256, 1.0),     # the last of them with one class
+    (1_000, 64, 512, 0.256),    # one tile of 256 classes, one slice of dfeatures (fp32: two)
+    (1_000, 64, 512, 0.257),    # two of them, twice the slices, the second tile with one class
+    (6_000, 1_024, 64, 0.5),    # batch of a whole number of tiles, cut into slices; fp32: D narrower than a tile
     (50_000, 2_049, 320, 1e-9),  # classes of the batch alone: batch cut into slices
     (50_000, 4_096, 256, 1e-9),  # likewise, whole tiles
     (300, 65, 64, 1.0),         # 64-tiles, second tile of the batch with one sample, half a column tile
     (16_384, 128, 128, 1.0),    # bf16: 128 tiles of 128 classes: 64-tiles for logits and backward
-    (16_385, 129, 128, 1.0),    # one more of each: 128-tiles
-    (3_300, 512, 384, 1.0),     # three column tiles of 128
+    (16_385, 129, 128, 1.0),    # one more of each: bf16: 128-tiles for the logits
+    (3_300, 512, 384, 1.0),     # six column tiles of 64
     (16_000, 1_024, 320, 1.0),  # 256-tiles for the logits alone (0.98 of a round), rows of 384
-    (16_000, 1_000, 512, 1.0),  # 256-tiles everywhere, batch ends inside a tile
+    (16_000, 1_000, 512, 1.0),  # the same, batch ends inside a tile
     (9_000, 300, 640, 1.0),     # fp32: 64-tiles, bf16: 128-tiles; five column tiles
     (8_192, 256, 512, 1.0),     # fp32: exactly one 128-tile per compute unit
     # batches above 2048, 256-tiles in both precisions:
-    (3_000, 8_100, 512, 1.0),   # batch and classes cut, dweight in front, last slices shorter
+    (3_000, 8_100, 512, 1.0),   # batch and classes cut, dweight in front, last slices shorter, batch ends inside a tile
     (16_100, 4_000, 512, 1.0),  # batch in one piece, dweight in front
     (2_000, 4_096, 768, 1.0),   # dfeatures in front; three column tiles
     (5_000, 2_250, 1_024, 1.0),  # bf16: batch in one piece
@@ -44,15 +44,39 @@ def test_backward_launch_edges(precision, N, B, D, r):
     _fb_parity(precision, N, B, D, r, 64.0, 0.5, seed=5)
 
 
+# bf16 forms at sizes where a kernel can go wrong: (N, B, D, tiles of the logits and of the backward launch, slices of
+# the batch and of the classes); tests/test_step_plan.py holds the rules to them.  (256-tiles with the batch cut
+# are for batches above 2048 alone: 3,000 x 8,100 and 2,000 x 4,096 above.)
+BF16_FORMS = [
+    (20_000, 137, 64, 128, 128, 1, 32),     # 128-tiles, half a column tile, shortest reductions
+    (19_000, 137, 128, 128, 128, 1, 30),    # one column tile
+    (16_385, 129, 192, 128, 128, 1, 26),    # a tile and one sample, a tile and one class
+    (233, 1_430, 384, 64, 128, 3, 1),       # three column tiles of 128, batch cut, one slice of dfeatures
+    (9_345, 300, 384, 128, 128, 1, 14),     # three column tiles, classes cut
+    (701, 1_186, 64, 64, 64, 2, 2),         # 64-tiles, batch and classes cut
+    (21_487, 652, 448, 256, 256, 1, 14),    # 256-tiles everywhere, batch and columns end inside a tile
+    (20_225, 726, 512, 256, 256, 1, 16),    # likewise, the last tile with one class
+    (31_791, 910, 384, 256, 128, 1, 9),     # 256-tiles for the logits alone
+]
+
+
+@pytest.mark.parametrize("N,B,D,logits,backward,dw,dx", BF16_FORMS)
+def test_bf16_forms(N, B, D, logits, backward, dw, dx):
+    _fb_parity(binding.PRECISION_BF16, N, B, D, 1.0, 64.0 if B > 200 else 20.0, 0.5, seed=N + B)
+
+
 # (N, B, D, r): the last launch (label parts, rows of dfeatures, loss) takes four samples to a
-# workgroup, or one where the classes were cut into at least 12 slices.  Scale 16: with a few samples
-# a peaked softmax leaves most rows of the center gradient below the floor of the row-wise bar.
+# workgroup, or one where the classes were cut into at least 12 slices and there is a compute unit
+# for every sample.  Scale 16: with a few samples a peaked softmax leaves most
+# rows of the center gradient below the floor of the row-wise bar.
 FINAL_CASES = [
     (5_000, 1, 64, 0.01),       # one sample
     (5_000, 5, 1_024, 0.01),    # one sample in the second workgroup, few slices
     (40_000, 7, 1_024, 1.0),    # one sample to a workgroup
     (40_000, 1_023, 192, 0.5),  # last workgroup with three samples
     (40_000, 1_025, 192, 0.5),  # window sums of the label part, the second of one sample
+    (20_000, 256, 192, 1.0),    # 12 slices and more: one sample to a workgroup (256 compute units) ..
+    (20_000, 257, 192, 1.0),    # .. and four
 ]
 
 

@@ -11,15 +11,20 @@ BF16 = binding.PRECISION_BF16
 
 
 # samples: either side of a half wavefront, of a tile and of the padding that the other product asks for; classes:
-# one more and one less than an octet, a slab and a tile
-@pytest.mark.parametrize("N,B,D", [(263, 100, 64),          # 64 and 64
-                                   (511, 97, 128),          # 64 and 64, either end of the padding
-                                   (1025, 160, 192),        # 64 and 64
-                                   (4_001, 500, 512),       # 64 and 128
-                                   (9_001, 129, 256),       # 128 and 64
-                                   (16_383, 513, 320),      # 128 and 128, samples one past a tile
-                                   (20_479, 700, 512),      # 256 and 256
-                                   (16_897, 1025, 512),     # 128 and 256: 128-tiles write 1280 samples
-                                   (33_000, 1000, 448)])        # 128 and 256
-def test_parity(N, B, D):
+# one more and one less than an octet, a slab and a tile; tiles of the logits and of the backward launch
+# (tests/test_step_plan.py holds the rules to them)
+FORMS = [(263, 100, 64, 64, 64),
+         (511, 97, 128, 64, 64),          # either end of the padding
+         (1025, 160, 192, 64, 64),
+         (4_001, 500, 512, 64, 128),
+         (9_001, 129, 256, 128, 64),
+         (16_383, 513, 320, 128, 128),    # samples one past a tile
+         (20_479, 700, 512, 256, 256),
+         (16_897, 1025, 512, 128, 256),   # 128-tiles write 1280 samples
+         (33_000, 1000, 448, 128, 256),
+         (30_215, 403, 320, 256, 128)]    # 256-tiles write 512 samples
+
+
+@pytest.mark.parametrize("N,B,D,logits,backward", FORMS)
+def test_parity(N, B, D, logits, backward):
     _fb_parity(BF16, N, B, D, 1.0, 64.0 if B > 200 else 20.0, 0.5, N + B + D)

@@ -16,11 +16,19 @@ BF16, FP32 = binding.PRECISION_BF16, binding.PRECISION_FP32
 
 
 # logits: D / 64 slabs; dweight: as many as 64 samples go into the padded batch; dfeatures: slices of at least 4
-@pytest.mark.parametrize("N,B,D", [(1_000, 100, D) for D in (64, 128, 192, 256, 320, 384)] +          # 64-tiles
-                         [(10_000, 300, D) for D in (64, 128, 192, 256, 320, 384)] +                  # 128-tiles
-                         [(16_384, 1_024, 320), (51_200, 256, 512), (20_000, 512, 448)])              # 256-tiles
+# (classes, samples, D, tiles of the logits and of the backward launch in bf16 and in fp32;
+# tests/test_step_plan.py holds the rules to them; 128-tiles of the backward launch in bf16 at D = 64 and 128:
+# BF16_FORMS of test_gpu_backward_launch.py)
+FORMS = ([(1_000, 100, D, (64, 64), (64, 64)) for D in (64, 128, 192, 256, 320, 384)] +
+         [(10_000, 300, D, (128, 64), (128, 64)) for D in (64, 128)] +
+         [(10_000, 300, D, (128, 128), (128, 128)) for D in (192, 256, 320, 384)] +
+         [(16_384, 1_024, 320, (256, 128), (256, 128)), (51_200, 256, 512, (128, 256), (64, 128)),
+          (20_000, 512, 448, (128, 256), (64, 128))])
+
+
+@pytest.mark.parametrize("N,B,D,bf16,fp32", FORMS)
 @pytest.mark.parametrize("precision", [BF16, FP32])
-def test_few_slabs(precision, N, B, D):
+def test_few_slabs(precision, N, B, D, bf16, fp32):
     _fb_parity(precision, N, B, D, 1.0, 64.0, 0.5, N + B + D)
 
 

@@ -10,6 +10,10 @@ import subprocess
 
 import pytest
 
+import test_gpu_backward_launch as backward_launch
+import test_gpu_logits_slim as logits_slim
+import test_gpu_octets as octets
+import test_gpu_slab_counts as slab_counts
 from test_gpu_sum_pieces import EQUAL, INDEPENDENT
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -27,6 +31,7 @@ extern "C" void plan(int cu, int es, int D, int B, int64_t k, double* out) {
   out[5] = s.splits; out[6] = s.slabs_per; out[7] = s.dx.splits; out[8] = s.dx.slabs_per;
   out[9] = s.dx.wgs; out[10] = s.dx.tiles_i; out[11] = s.dx.tiles_d; out[12] = s.dx.slabs_total;
   out[13] = fits_one_kernel(cu, D, kp); out[14] = tile_bk(es); out[15] = s.dw_first;
+  out[16] = es == 4 && f == TILES_64 && logits_slim(cu, B, kp);
 }
 extern "C" int64_t slabs(int64_t cu, int64_t na, int64_t a, int64_t nb, int64_t b) {
   return launch_slabs(cu, na, a, nb, b);
@@ -37,7 +42,7 @@ extern "C" void scratch(int cu, int D, int B_max, int64_t k_cap, double* out) {
 }
 """
 _KEYS = ("logits", "backward", "Bp", "Dp", "kp", "dw_splits", "dw_slabs", "dx_splits", "dx_slabs", "dx_wgs",
-         "tiles_i", "tiles_d", "dx_total", "one_kernel", "bk", "dw_first")
+         "tiles_i", "tiles_d", "dx_total", "one_kernel", "bk", "dw_first", "slim")
 
 
 @pytest.fixture(scope="module")
@@ -140,6 +145,37 @@ def test_fp32_sums_stay_short(lib, B, k, D, dw, dx):
 def test_sums_of_the_gpu_tests(lib, B, k, D, tile, dw, dx):
     p = _plan(lib, 256, 4, D, B, k)
     assert (p["backward"], p["dw_splits"], p["dx_splits"]) == (tile, dw, dx) and not p["one_kernel"]
+
+
+def _bf16(lib, N, B, D, *keys):
+    p = _plan(lib, 256, 2, D, B, N)
+    return tuple(p[n] for n in keys)
+
+
+# (likewise the forms that the GPU tests name: a rule that moves them leaves a kernel without its test)
+def test_forms_of_the_gpu_tests(lib):
+    for N, B, D, *form in backward_launch.BF16_FORMS:
+        assert _bf16(lib, N, B, D, "logits", "backward", "dw_splits", "dx_splits") == tuple(form), (N, B, D)
+    for N, B, D, logits, backward in octets.FORMS:
+        assert _bf16(lib, N, B, D, "logits", "backward") == (logits, backward), (N, B, D)
+    pairs = {f[3:5] for f in octets.FORMS}
+    assert pairs == {(64, 64), (64, 128), (128, 64), (128, 128), (128, 256), (256, 128), (256, 256)}
+    rng = random.Random(4)
+    for _ in range(20_000):      # .. and no other pair is reached
+        B, k, D = _log(rng, 2**16), _log(rng, 2**20), 64 * rng.randint(1, 16)
+        assert _bf16(lib, k, B, D, "logits", "backward") in pairs, (B, k, D)
+    for N, B, D, bf16, fp32 in slab_counts.FORMS:
+        for es, form in ((2, bf16), (4, fp32)):
+            p = _plan(lib, 256, es, D, B, N)
+            assert (p["logits"], p["backward"]) == form, (es, N, B, D)
+    # the last launch of one sample to a workgroup, and of four because of the batch
+    for es in (2, 4):
+        assert all(_plan(lib, 256, es, 192, B, 20_000)["dx_splits"] >= 12 for B in (256, 257))
+        assert _plan(lib, 256, es, 1_024, 7, 40_000)["dx_splits"] >= 12
+    assert all(_plan(lib, 256, 4, D, B, N)["slim"] for N, B, D in logits_slim.SLIM)
+    for D in (64, 512, 832):     # the bits of slim tiles against those of 64-tiles
+        assert [(_plan(lib, 256, 4, D, B, 8_192)["logits"], _plan(lib, 256, 4, D, B, 8_192)["slim"])
+                for B in (64, 128)] == [(64, 1), (64, 0)]
 
 
 def _ends_at(cu, p, es, dw_splits, dx_splits):
