@@ -552,8 +552,7 @@ size_t sample_layout(int64_t N, int64_t B, char* base, SampleScratch* out) {
     return p;
   };
   const size_t words = (size_t)(N + 31) / 32;
-  const int64_t nb = sample_blocks(N);
-  const size_t blk = (size_t)(nb > kMaxBlocks ? nb : kMaxBlocks);   // smaller N may have more blocks
+  const size_t blk = (size_t)sample_count_cap(N);
   const size_t list = (size_t)window_list_cap(N, B), pos = (size_t)window_pos_cap(B);
   out->st = (SampleState*)take(sizeof(SampleState));
   for (int i = 0; i < 2; ++i) {

@@ -153,7 +153,7 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t need, ui
 // of memory those of all frequent classes.  (Before, a loop over the distinct labels of a wavefront,
 // one after the other: 2.5 us where all 64 differ.)  alone: no other workgroup marks.  pos_bits: 8-byte
 // aligned, whole 64-bit words.
-constexpr int kMarkSlots = 2048;   // more than labels in a workgroup; a quarter full, few look twice
+constexpr int kMarkSlots = 2048;   // at least twice the labels of a workgroup (512 or 1024; radix passes 256)
 struct MarkLds {
   unsigned long long bits[kMarkSlots];
   int32_t key[kMarkSlots];         // word

@@ -45,6 +45,13 @@ inline int64_t sample_write_blocks(int64_t N) {
   return (N + ((int64_t)1 << l) - 1) >> l;
 }
 
+// Counts that the scratch has room for: of sample_write's workgroups, and of sample_scan's, which are whole
+// ones of those.  (Smaller N may have more of either.)
+inline int64_t sample_count_cap(int64_t N) {
+  const int64_t n = sample_blocks(N);
+  return n > kMaxBlocks ? n : kMaxBlocks;
+}
+
 // Parts of the list of the window, one count each: the workgroups of sample_scan queue up on a count
 // (503 on one count: 5 us of a launch of 11).  Few workgroups would fill the parts unevenly.
 inline int list_parts(int scan_blocks) { return scan_blocks >= 64 ? kListParts : 1; }

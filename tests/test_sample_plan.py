@@ -23,6 +23,9 @@ extern "C" int plan(int64_t N, int64_t crn, int64_t B, uint32_t mask, double* ou
   out[6] = pfc::sample_cls_log2(N); out[7] = pfc::sample_blocks(N);
   out[8] = pfc::kBinList; out[9] = pfc::kLocalList; out[10] = pfc::kWindowBatch;
   out[11] = pfc::kWindowBins; out[12] = pfc::kMissClasses; out[13] = pfc::window_pos_cap(B);
+  out[14] = pfc::sample_write_blocks(N); out[15] = pfc::sample_write_log2(N); out[16] = pfc::sample_count_cap(N);
+  const int64_t scan = pfc::sample_write_blocks(N) << (pfc::sample_write_log2(N) - pfc::sample_cls_log2(N));
+  out[17] = scan; out[18] = pfc::list_parts((int)scan); out[19] = pfc::kMaxClsLog2;
   return pfc::window_select(N, crn, B, mask, w) ? 1 : 0;
 }
 """
@@ -42,7 +45,8 @@ def plan(tmp_path_factory):
     f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_uint32,
                   ctypes.POINTER(ctypes.c_double)]
     keys = ("lo", "width", "shift", "expected", "bin", "list_cap", "cls_log2", "blocks", "bin_list",
-            "local_list", "window_batch", "bins", "miss_classes", "pos_cap")
+            "local_list", "window_batch", "bins", "miss_classes", "pos_cap", "write_blocks", "write_log2", "count_cap",
+            "scan", "parts", "max_log2")
 
     def call(N, crn, B, mask=FULL):
         out = (ctypes.c_double * len(keys))()
@@ -89,6 +93,30 @@ def test_window_lists_hold_what_falls_into_them(plan):
             else:
                 assert got <= max(0.0, rank - 6 * sigma) + 1e-3, (N, crn, B)
     assert taken > 5_000
+
+
+def test_parts_of_the_list_and_counts_hold_what_is_written(plan):
+    """sample_scan leaves a count for each of its workgroups, whole ones of sample_write, and appends to one
+    part of the list; a part that overflows costs a selection of every workgroup for itself."""
+    sizes = [(N, max(1, N // d), B) for e in range(10, 15) for n in (63, 64, 65, 71, 512, 513, 639, 640)
+             for N in ((n << e) - 1, n << e, (n << e) + 1) for d in (1, 2, 10) for B in (1, 64, 1_000, 65_536)]
+    uneven = 0
+    for N, crn, B in list(_forms(20_000)) + sizes:
+        window, p = plan(N, crn, B)
+        scan, parts, write = int(p["scan"]), int(p["parts"]), int(p["write_blocks"])
+        assert p["cls_log2"] <= p["write_log2"] <= min(p["cls_log2"] + 1, p["max_log2"])
+        # every class in a workgroup of either launch; counts within what the scratch has room for
+        assert scan << int(p["cls_log2"]) >= N and write << int(p["write_log2"]) >= N, N
+        assert p["blocks"] <= scan <= p["count_cap"] and write <= p["count_cap"], N
+        assert write <= 512 or p["write_log2"] == p["max_log2"], N
+        # a context whose largest call is this one, or any larger; parts of whole workgroups
+        for B_max in (B, 2 * B, 2**20):
+            cap = int(plan(N, crn, B_max)[1]["list_cap"]) // parts
+            most = min(-(-scan // parts) * 2.0 ** p["cls_log2"], N) * p["expected"] / N
+            if window:
+                assert most + 8 * math.sqrt(most) <= cap, (N, crn, B, B_max)
+        uneven += window and scan % parts != 0
+    assert uneven > 1_000
 
 
 def test_large_batches_and_moved_scores_take_the_radix_passes(plan):
