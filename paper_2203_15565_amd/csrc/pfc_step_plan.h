@@ -171,12 +171,20 @@ inline bool long_batch(int cu, int D, int Bp, int64_t kp) { return Bp > kLongBat
 //                                          (d) 177 / 177 / 182
 //   768 x 20,599 of 205,990 x 1024 (268)   (a) 254 / 247 / 238   (b) 260 / 263 / 279   (c) 248 / 250 / 257
 //   1024 x 205,991 of 2,059,906 x 512      (a) 1204 / 1195 / 1202   (b) 1204 / 1192 / 1242   (c) 1178 / 1173 / 1222
-// From 107 MB on a plain gather is 2 - 6 % behind there (a state's first step 5 - 7 %: 512 x 30,000 203 / 214),
+// From 107 MB on a plain gather is up to 6 % behind there (a state's first step 5 - 7 %: 512 x 30,000 203 / 214),
 // whatever it gains where steps follow each other; up to 91 MB it is even or ahead.  Hence the line at 95 MB
 // between them.  (Streamed is up to 2 % behind the first order in (b) and (c) from 200 to 270 MB, 2 - 5 % ahead in
-// (a), and ahead everywhere in larger steps.)
+// (a), and ahead everywhere in larger steps.)  The shorter the rows, the less a plain gather loses behind other
+// data and the more it gains in a row; at D = 64, rows of two cache lines, it is ahead in nearly all (streamed / reused):
+//   67 x 78,698 of 430,107 x 128 (112 MB)  (a) 108.4 / 105.3   (b) 120.1 / 124.1   (c) 116.5 / 117.3   (d) 115.6 / 115.8
+//   128 x 120,000 of 1,200,000 x 128 (185) (a) 146.6 / 142.2   (b) 163.0 / 167.4   (c) 151.9 / 154.8   (d) 153.3 / 157.3
+//   100 x 150,000 of 1,500,000 x 64 (145)  (a) 134.6 / 130.5   (b) 163.6 / 159.4   (c) 144.0 / 143.3   (d) 146.3 / 149.3
+//   64 x 200,000 of 2,000,000 x 64 (179)   (a) 167.5 / 162.6   (b) 207.3 / 202.2   (c) 175.5 / 174.4   (d) 177.4 / 170.6
+//   100 x 200,000 of 200,000 x 64 (194)    (a) 150.2 / 149.8   (b) 190.4 / 177.0   (c) 167.2 / 165.8   (d) 163.0 / 162.6
+//   900 x 80,000 of 800,000 x 64 (207)     (a) 170.5 / 168.4   (b) 196.8 / 197.0   (c) 179.9 / 178.8   (d) 178.3 / 178.9
+// There the line is at 215 MB.
 enum RowLoads { ROWS_RESIDENT, ROWS_REUSED, ROWS_STREAMED };
-constexpr int64_t kResidentBytes = 200000000, kGatherPlainBytes = 95000000;
+constexpr int64_t kResidentBytes = 200000000, kGatherPlainBytes = 95000000, kGatherPlainBytes64 = 215000000;
 struct RowPolicy {
   RowLoads loads;
   bool gather_plain;
@@ -184,7 +192,7 @@ struct RowPolicy {
 inline RowPolicy row_policy(int es, int64_t N, int D, int B_max, int64_t k) {
   // W's rows, dWn, Wn, E; features, their gradient and its partial sums, about eight rows of floats a sample
   const int64_t step = k * (8ll * D + es * (round_up(D, kPadD) + B_max)) + 32ll * B_max * D;
-  const bool plain = step <= kGatherPlainBytes;
+  const bool plain = step <= (D == 64 ? kGatherPlainBytes64 : kGatherPlainBytes);
   return {8 * N * D <= kResidentBytes ? ROWS_RESIDENT : plain ? ROWS_REUSED : ROWS_STREAMED, plain};
 }
 

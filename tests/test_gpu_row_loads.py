@@ -30,11 +30,14 @@ def test_the_rule(tmp_path):
     # reused means that the gather keeps the rows
     assert all(rule(es, N, 512, B, N // 10) in (0, 1, 3, 4) for es in (2, 4) for N in (10_000, 90_000, 400_000, 9_000_000)
                for B in (1, 512, 16_384))
-    # behind other data a plain gather was 2 - 6 % slower in steps of 107 MB and more, no slower up to 91
+    # behind other data a plain gather was up to 6 % slower in steps of 107 MB and more, no slower up to 91
     assert rule(2, 40_000, 512, 512, 16_000) == 0 and rule(2, 45_000, 512, 256, 20_000) == 0
     assert rule(2, 300_000, 512, 512, 18_000) == 4 and rule(2, 700_000, 256, 128, 70_000) == 4
     assert rule(2, 350_000, 512, 256, 35_000) == 4 and rule(4, 300_000, 512, 512, 18_000) == 4
     assert rule(2, 90_000, 256, 1024, 18_000) == 1 and rule(2, 85_742, 128, 256, 25_724) == 1
+    # .. but for rows of 64, where it was faster or even up to 207
+    assert rule(2, 1_500_000, 64, 100, 150_000) == 3 and rule(2, 2_000_000, 64, 64, 200_000) == 3
+    assert rule(2, 800_000, 64, 900, 80_000) == 3 and rule(2, 200_000, 64, 100, 200_000) == 1
     assert rule(2, 93_431, 512, 512, 9_344) == 3 and rule(4, 93_431, 512, 512, 9_344) == 3
 
 
