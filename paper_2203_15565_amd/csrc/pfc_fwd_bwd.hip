@@ -1732,7 +1732,8 @@ __device__ __forceinline__ void dfeatures_final_block(int block, FinalLds<NC, WP
 // which a third of them would have none, if there is a compute unit for every sample.  (This launch,
 // us, 16 wavefronts / 4: 1024 x 205,991 x 512 20.8 / 17.7, fused 16.9 / 12.6, fused 1024 x 36,024 13.8 /
 // 10.0, 1024 x 40,000 x 256 14.8 / 12.2, 400 x 40,000 x 1024 14.7 / 12.3; 200 x 60,000 x 768 11.2 /
-// 12.8, 64 x 200,000 x 512 in fp32 12.3 / 16.0.)
+// 12.8, 64 x 200,000 x 512 in fp32 12.3 / 16.0.  Behind the line: 260 x 60,000 x 512 9.1 / 9.9, in fp32 10.8 /
+// 12.3, 260 x 40,000 x 1024 12.0 / 11.9, 320 x 60,000 x 512 10.8 / 9.9, 400 12.6 / 10.3.)
 constexpr int kFinalWideSplits = 12, kFinalOneSplits = 2;
 template <int NC, int WPS, bool WINDOWS>
 __global__ __launch_bounds__(kLabelThreads, 8) void gradients_final_kernel(

@@ -151,9 +151,10 @@ __device__ __forceinline__ void lds_load(const char* base, uint32_t toff, uint32
 //                      four samples of every 32 lanes in different banks.
 // Against rows of classes, written through LDS (us): logits 1024 x 205,991 x 512 280 -> 260, 1024 x
 // 360,232 494 -> 463, 1024 x 36,024 55.8 -> 50.8, 16,384 x 3,592 104 -> 95; both backward products
-// 413 -> 409, 715 -> 684, fused 1024 x 36,024 133.9 -> 131.2, 16,384 x 3,592 115 -> 117.  (Reading
-// dfeatures' slabs into LDS rows of 8 octets, a line for 8 samples from each of 8 panels in one
-// load: both products of 512 x 9,344 20.4 -> 22.9.)
+// 413 -> 409, 715 -> 684, fused 1024 x 36,024 133.9 -> 131.2, 16,384 x 3,592 115 -> 117: they read more
+// (1024 x 205,991 1,272 -> 1,371 MB), which is not for the panels' beginning at the same place of every
+// cache (with Bp + 16 samples to a panel 1,361).  (Reading dfeatures' slabs into LDS rows of 8 octets, a
+// line for 8 samples from each of 8 panels in one load: both products of 512 x 9,344 20.4 -> 22.9.)
 template <typename T, int R, bool KMAJOR, int SLAB>
 struct OctetLds {
   static constexpr int BK = SLAB / (int)sizeof(T), SAMPLES = KMAJOR ? BK : R, PANEL = SAMPLES * 16;
