@@ -171,9 +171,10 @@ inline bool long_batch(int cu, int D, int Bp, int64_t kp) { return Bp > kLongBat
 //                                          (d) 177 / 177 / 182
 //   768 x 20,599 of 205,990 x 1024 (268)   (a) 254 / 247 / 238   (b) 260 / 263 / 279   (c) 248 / 250 / 257
 //   1024 x 205,991 of 2,059,906 x 512      (a) 1204 / 1195 / 1202   (b) 1204 / 1192 / 1242   (c) 1178 / 1173 / 1222
-// From 107 MB on a plain gather is up to 6 % behind there (a state's first step 5 - 7 %: 512 x 30,000 203 / 214),
-// whatever it gains where steps follow each other; up to 91 MB it is even or ahead.  Hence the line at 95 MB
-// between them.  (Streamed is up to 2 % behind the first order in (b) and (c) from 200 to 270 MB, 2 - 5 % ahead in
+// From 107 MB on a plain gather is up to 9 % behind there (64 x 20,000 x 1024 behind layers with weights of their
+// own 163 / 178; a state's first step 5 - 7 %: 512 x 30,000 203 / 214, 109 x 17,766 x 768 154 / 163), whatever it
+// gains where steps follow each other (1 - 6 %: the last form 123 / 118); up to 91 MB it is even or ahead.  Hence
+// the line at 95 MB between them.  (Streamed is up to 2 % behind the first order in (b) and (c) from 200 to 270 MB, 2 - 5 % ahead in
 // (a), and ahead everywhere in larger steps.)  The shorter the rows, the less a plain gather loses behind other
 // data and the more it gains in a row; at D = 64, rows of two cache lines, it is ahead in nearly all (streamed / reused):
 //   67 x 78,698 of 430,107 x 128 (112 MB)  (a) 108.4 / 105.3   (b) 120.1 / 124.1   (c) 116.5 / 117.3   (d) 115.6 / 115.8

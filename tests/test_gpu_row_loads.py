@@ -30,7 +30,7 @@ def test_the_rule(tmp_path):
     # reused means that the gather keeps the rows
     assert all(rule(es, N, 512, B, N // 10) in (0, 1, 3, 4) for es in (2, 4) for N in (10_000, 90_000, 400_000, 9_000_000)
                for B in (1, 512, 16_384))
-    # behind other data a plain gather was up to 6 % slower in steps of 107 MB and more, no slower up to 91
+    # behind other data a plain gather was up to 9 % slower in steps of 107 MB and more, no slower up to 91
     assert rule(2, 40_000, 512, 512, 16_000) == 0 and rule(2, 45_000, 512, 256, 20_000) == 0
     assert rule(2, 300_000, 512, 512, 18_000) == 4 and rule(2, 700_000, 256, 128, 70_000) == 4
     assert rule(2, 350_000, 512, 256, 35_000) == 4 and rule(4, 300_000, 512, 512, 18_000) == 4
